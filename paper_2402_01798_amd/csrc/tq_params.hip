@@ -13,24 +13,43 @@
 //                   s p1^(1/3) k / (p2^(1/3) (1-k) + p1^(1/3) k) uniform cells on [-k alpha, k alpha],
 //                   the other s - s_beta on the rest of [-alpha, alpha]
 //
-// The density p on [-alpha, alpha] is the histogram's (constant inside a bin).  With the
-// prefix sums cum[i] = #{|g| below bin i} and H[i] = int_0^{lo_i} p^(1/3), both Q_U(alpha)
-// and the integral of p^(1/3) up to alpha cost O(1) per evaluation.  The per-bin cube roots
-// and logarithms and the two prefix sums are computed by all lanes (4 bins per lane, a
-// wavefront scan, a 4-entry carry through LDS); only the fixed-point iteration itself, a
-// chain of dependent scalar steps, runs on lane 0.  For the BiScaled family every step of that
-// chain holds a minimum over up to 898 candidate k: there all lanes walk the chain together
-// (each computing the same scalars) and share the search, 4 candidates per lane.
+// The density p on [-alpha, alpha] is the histogram's (constant inside a bin).  With the counts
+// below each bin and H[i] = int_0^{lo_i} p^(1/3), both Q_U(alpha) and the integral of p^(1/3)
+// up to alpha cost O(1) per evaluation.
+//
+// What bounds it: latency.  A record is 3.6 KB of input and a chain of dependent scalar steps; one
+// tensor's record occupies one compute unit, and even 2736 records of small buckets are only two or
+// three workgroups' worth of time each.  So everything here shortens the chain:
+//   - per-bin work on all lanes, bin = 256 k + lane, with wavefronts whose bins are empty skipping
+//     it; scans by cross-lane moves (DPP); the cube root of an integer count
+//     from the hardware's fp32 exp2/log2 and two fp64 Newton steps (the bins' widths are powers of
+//     two, so nothing else needs a root), the binned tail's logarithms from a 16-entry table;
+//   - the fixed point is first approached in fp32 (one iteration about 250 cycles instead of 1600),
+//     by the boxed map itself and, once that provably contracts, by Newton steps on it, and
+//     then polished by fp64 Newton steps on the logarithmic residual.  When the map does not
+//     contract safely (see kCertifiedSlope), the plain fp64 iteration of the definition runs,
+//     because there the result is where that iteration stops, not a fixed point;
+//   - a lane per level for the codebook and its reciprocal widths;
+//   - one kernel per codebook family: what a family does not need costs it no LDS and no
+//     instruction fetch.
+// Measured on MI355X, us for one launch, against all-fp64 iteration on lane 0 of one kernel for
+// all families: uniform, 4 records 11.2 -> 4.7, 952 records 30.3 -> 7.0; non-uniform, 1 record
+// 18.7 -> 7.4, 768 records 34.3 -> 9.7, 2736 records 78 -> 24.5; BiScaled, 391 records 128 -> 19.0.
+// 512 or 1024 threads per record instead of 256 gain 0.4 us on a single non-uniform record and lose
+// 6 and 18 us on 2736 of them.
 #include "tq_device.h"
 
 namespace tq {
 
 constexpr int kNB = TQ_NBINS;
-constexpr int kBinsPerLane = 4;                           // 256 lanes x 4 >= 898 bins
+constexpr int kParamsBlock = 256;                         // threads per workgroup
+constexpr int kParamsWaves = kParamsBlock / 64;
+constexpr int kBinsPerLane = 1024 / kParamsBlock;         // 1024 >= 898 bins
 constexpr double kGammaFloor = 2.02;
 constexpr double kAlphaFloor = 5.421010862427522e-20;     // 2^-64
 constexpr int kMaxIter = 100;
 constexpr double kRelTol = 1e-10;
+constexpr double kLn2 = 0.69314718055994530942;
 
 __device__ __forceinline__ double bin_lo(int i)
 {
@@ -40,240 +59,499 @@ __device__ __forceinline__ double bin_lo(int i)
     return ldexp(1.0 + (double)(j & 15) * 0.0625, (j >> 4) - 40);
 }
 
-__device__ __forceinline__ double bin_hi(int i, double absmax)
+__device__ __forceinline__ double last_bin_width(double absmax)
 {
-    if (i >= kNB - 1) return absmax > 131072.0 ? absmax : 131072.0;
-    return bin_lo(i + 1);
+    return (absmax > 131072.0 ? absmax : 131072.0) - 65536.0;
 }
 
-// Bin whose [lo, hi) holds x >= 0 (the last bin is closed above).
+// Bin whose [lo, hi) holds x >= 0 (the last bin is closed above): biased exponent and top four
+// mantissa bits, as the statistics kernel bins them.
 __device__ __forceinline__ int bin_of(double x)
 {
-    if (x < 9.094947017729282e-13) return 0;              // 2^-40
-    if (x >= 65536.0) return kNB - 1;
-    const int ex = ilogb(x);
-    const double m = ldexp(x, -ex);                        // in [1, 2), exact
-    return (ex + 40) * 16 + (int)((m - 1.0) * 16.0) + 1;
+    const int i = (__double2hiint(x) >> 16) - (((1023 - 40) << 4) - 1);
+    return i < 0 ? 0 : (i > kNB - 1 ? kNB - 1 : i);
 }
 
-struct ParamsLds {
-    double hist[kNB];
-    double cum[kNB + 1];   // cum[i] = sum of hist below bin i
-    double p13[kNB];       // cube root of the two-sided density on the bin
-    double H[kNB + 1];     // H[i] = int_0^{lo_i} p^(1/3)
-    double carry[4];       // per-wavefront totals of the scan in flight
-    double total;
-    int tail_bin;
-    double best_q[4];      // per-wavefront minimum of the BiScaled search and the bin it belongs to
-    int best_j[4];
+// 1 / x to about an ulp: hardware seed, two Newton steps.
+__device__ __forceinline__ double recip(double x)
+{
+    double r = __builtin_amdgcn_rcp(x);
+    r = __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
+    return __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
+}
+
+// ln x for finite x > 0: x = 2^e m with m in [sqrt(1/2), sqrt(2)), ln m = 2 artanh((m - 1) / (m + 1)), whose
+// series in z = ((m - 1) / (m + 1))^2 <= 0.0295 is cut after z^10 (below 1e-17).  Evaluated in pairs
+// of terms: a third of the dependent steps of the library's ln, in a third of its code.
+__device__ __forceinline__ double ln(double x)
+{
+    double m = __builtin_amdgcn_frexp_mant(x);             // [1/2, 1)
+    int e = __builtin_amdgcn_frexp_exp(x);
+    const bool low = m < 0.70710678118654752440;
+    m = low ? m + m : m;
+    e = low ? e - 1 : e;
+    const double den = m + 1.0;
+    const double r = recip(den);
+    double t = (m - 1.0) * r;
+    t = __builtin_fma(__builtin_fma(-den, t, m - 1.0), r, t);
+    const double z = t * t, z2 = z * z, z4 = z2 * z2;
+    const double p01 = __builtin_fma(z, 2.0 / 5.0, 2.0 / 3.0), p23 = __builtin_fma(z, 2.0 / 9.0, 2.0 / 7.0);
+    const double p45 = __builtin_fma(z, 2.0 / 13.0, 2.0 / 11.0), p67 = __builtin_fma(z, 2.0 / 17.0, 2.0 / 15.0);
+    const double p89 = __builtin_fma(z, 2.0 / 21.0, 2.0 / 19.0);
+    const double p03 = __builtin_fma(z2, p23, p01), p47 = __builtin_fma(z2, p67, p45);
+    const double p = __builtin_fma(z4, __builtin_fma(z4, p89, p47), p03);
+    return __builtin_fma((double)e, kLn2, __builtin_fma(t * z, p, t + t));
+}
+
+// log2, exp2 and the reciprocal as the hardware computes them (about 1 ulp of binary32).
+__device__ __forceinline__ float log2_hw(float x) { return __builtin_amdgcn_logf(x); }
+__device__ __forceinline__ float exp2_hw(float x) { return __builtin_amdgcn_exp2f(x); }
+__device__ __forceinline__ float rcp_hw(float x) { return __builtin_amdgcn_rcpf(x); }
+
+// Cube root of x >= 0: fp32 seed, two Newton steps in fp64 (the reciprocal of the derivative is
+// needed to the seed's precision only); below the range of binary32 the library's.
+__device__ __forceinline__ double cube_root(double x)
+{
+    const float xf = (float)x;
+    if (xf < 1.0e-37f && x > 0.0) return cbrt(x);
+    const float y0 = exp2_hw(log2_hw(xf) * (1.0f / 3.0f));
+    const double r = (double)rcp_hw(3.0f * y0 * y0);
+    double y = (double)y0;
+    y += (x - y * y * y) * r;
+    y += (x - y * y * y) * r;
+    return x > 0.0 ? y : 0.0;
+}
+
+// ln((1 + m/16)(1 + (m+1)/16)) / 2: the logarithm of a bin's geometric centre within its octave,
+// and ln(1 + m/16): that of its lower edge.
+struct OctaveLogs { double centre[16], edge[16]; };
+__constant__ OctaveLogs kOctaveLogs = {
+    {0.03031231090821742, 0.089203828736409141, 0.14481664629152136, 0.1974969041204345,
+     0.24753863339892576, 0.29519372330108817, 0.3406796124039515, 0.38418530089876646,
+     0.42587610536829196, 0.46589745920506015, 0.50437797977312426, 0.54143196584998532,
+     0.57716144784105772, 0.61165788358453343, 0.6450035708338695, 0.67727283140265515},
+    {0.0, 0.06062462181643484, 0.11778303565638346, 0.17185025692665923,
+     0.22314355131420976, 0.27193371548364176, 0.31845373111853459, 0.36290549368936847,
+     0.40546510810816438, 0.44628710262841953, 0.48550781578170077, 0.52324814376454787,
+     0.55961578793542266, 0.59470710774669278, 0.62860865942237409, 0.66139848224536502}
 };
 
-// Exclusive prefix sum over the 1024 (lane, slot) values v[0..3] of all 256 lanes, in bin
-// order; returns each lane's offset and leaves the grand total in L.total.
-__device__ __forceinline__ double block_exclusive_scan(double local, ParamsLds& L)
+template <bool ROOTS>
+struct ParamsLds {
+    uint2 hc[kNB];                         // count of bin i, and of all bins below it (exact: n < 2^32)
+    double H[ROOTS ? kNB + 1 : 1];         // H[i] = int_0^{lo_i} p^(1/3), times (2n)^(1/3)
+    uint32_t chunk_count[16];              // per 64 consecutive bins
+    double chunk_h[16];
+    double wave_tail[kParamsWaves];
+    double tail_edge_log;                  // ln(1 + m/16) of the tail's first bin
+    int tail_bin;
+    float search_q[2][kParamsWaves], search_slope[2][kParamsWaves];   // BiScaled search in fp32, double-buffered; in fp64
+    double best_q[kParamsWaves];
+    int best_j[kParamsWaves];
+};
+
+// Inclusive prefix sums over a wavefront by cross-lane moves: inside rows of 16 lanes, then the
+// rows' totals handed on (lane 15 of a row to the next row, lane 31 to the upper half).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    double incl = local;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const double o = __shfl_up(incl, off, 64);
-        if (lane >= off) incl += o;
-    }
-    __syncthreads();                                       // previous use of carry is over
-    if (lane == 63) L.carry[wave] = incl;
-    __syncthreads();
-    double base = 0.0;
-    for (int w = 0; w < wave; ++w) base += L.carry[w];
-    if (threadIdx.x == kBlock - 1) L.total = base + incl;
-    return base + incl - local;
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_or_zero(double v)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+template <typename T>
+__device__ __forceinline__ T row_scan(T v)
+{
+    v += dpp_or_zero<0x111, 0xf>(v);
+    v += dpp_or_zero<0x112, 0xf>(v);
+    v += dpp_or_zero<0x114, 0xf>(v);
+    v += dpp_or_zero<0x118, 0xf>(v);
+    return v;
+}
+template <typename T>
+__device__ __forceinline__ T wave_scan(T v)
+{
+    v = row_scan(v);
+    v += dpp_or_zero<0x142, 0xa>(v);
+    v += dpp_or_zero<0x143, 0xc>(v);
+    return v;
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float min_with_dpp(float v)
+{
+    return fminf(v, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), CTRL, ROWS, 0xf, false)));
+}
+__device__ __forceinline__ float wave_min(float v)
+{
+    v = min_with_dpp<0x111, 0xf>(v);
+    v = min_with_dpp<0x112, 0xf>(v);
+    v = min_with_dpp<0x114, 0xf>(v);
+    v = min_with_dpp<0x118, 0xf>(v);
+    v = min_with_dpp<0x142, 0xa>(v);
+    v = min_with_dpp<0x143, 0xc>(v);
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+__device__ __forceinline__ uint32_t lane_value(uint32_t v, int lane) { return (uint32_t)__builtin_amdgcn_readlane((int)v, lane); }
+__device__ __forceinline__ double lane_value(double v, int lane)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane), __builtin_amdgcn_readlane(__double2loint(v), lane));
 }
 
+// Exclusive prefix sums over the bins: lane values v[k] of bins kParamsBlock k + tid.  On return v[k] is
+// the sum over all bins below; the grand total is returned.  `chunk` is 16 entries of LDS that
+// nobody else uses; one barrier.
+template <typename T>
+__device__ __forceinline__ T bin_scan(T (&v)[kBinsPerLane], T* chunk)
+{
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    T incl[kBinsPerLane];
+#pragma unroll
+    for (int k = 0; k < kBinsPerLane; ++k) {
+        incl[k] = wave_scan(v[k]);
+        if (lane == 63) chunk[kParamsWaves * k + wave] = incl[k];
+    }
+    __syncthreads();
+    const T upto = row_scan(chunk[lane & 15]);
+#pragma unroll
+    for (int k = 0; k < kBinsPerLane; ++k) {
+        const int c = kParamsWaves * k + wave;
+        const T below = c > 0 ? lane_value(upto, c > 0 ? c - 1 : 0) : T(0);
+        v[k] = below + (incl[k] - v[k]);
+    }
+    return lane_value(upto, 15);
+}
+
+// The density's integrals up to x, in fp64.
+template <bool ROOTS>
 struct DensityView {
-    const ParamsLds& L;
-    double n, inv_n, absmax;
-    // Part of bin j below x, as a fraction of the bin (frac) and as a length (len).  The bins
-    // between 2^-40 and 2^16 are 2^(octave-44) wide, so their reciprocal width is exact.
-    __device__ void covered(int j, double x, double& frac, double& len) const
+    const ParamsLds<ROOTS>& L;
+    double inv_n, absmax;
+    // part of bin j below x, as a fraction of the bin; rw = 1 / its width
+    __device__ __forceinline__ void covered(int j, double x, double& frac, double& rw) const
     {
         const double lo = bin_lo(j);
-        double w, rw;
-        if (j >= 1 && j < kNB - 1) {
-            const int e = ((j - 1) >> 4) - 44;
+        double w;
+        if (j < kNB - 1) {
+            const int e = j > 0 ? ((j - 1) >> 4) - 44 : -40;
             w = ldexp(1.0, e);
             rw = ldexp(1.0, -e);
         } else {
-            w = bin_hi(j, absmax) - lo;
+            w = last_bin_width(absmax);
             rw = 1.0 / w;
         }
         double c = x - lo;
         c = c < 0.0 ? 0.0 : (c > w ? w : c);
-        len = c;
         frac = c * rw;
     }
-    __device__ double Q_U(double a) const
+    // Q_U(a) and, in `elasticity`, dlnQ/dlna
+    __device__ __forceinline__ double Q_U(double a, double& elasticity) const
     {
         const int j = bin_of(a);
-        double frac, len;
-        covered(j, a, frac, len);
-        return (L.cum[j] + L.hist[j] * frac) * inv_n;
+        double frac, rw;
+        covered(j, a, frac, rw);
+        const double h = (double)L.hc[j].x, mass = (double)L.hc[j].y + h * frac;
+        elasticity = h * rw * a * recip(mass);
+        return mass * inv_n;
     }
-    __device__ double half_int(double x) const            // int_0^x p^(1/3)
+    // int_0^x p^(1/3) and, in `density`, p^(1/3) at x, both times (2n)^(1/3)
+    __device__ __forceinline__ double half_int(double x, double& density) const
     {
         const int j = bin_of(x);
-        double frac, len;
-        covered(j, x, frac, len);
-        return L.H[j] + L.p13[j] * len;
+        double frac, rw;
+        covered(j, x, frac, rw);
+        const double below = L.H[j], mine = L.H[j + 1] - below;
+        density = mine * rw;
+        return below + mine * frac;
     }
-    __device__ double Q_N(double a) const
+    // Q_N(a) = (2 int_0^a p^(1/3))^3 / (4 a^2)
+    __device__ __forceinline__ double Q_N(double a, double& elasticity) const
     {
-        const double t = 2.0 * half_int(a);
-        return t * t * t / (4.0 * a * a);
+        double density;
+        const double half = half_int(a, density);
+        elasticity = 3.0 * a * density * recip(half) - 2.0;
+        const double u = half * recip(a);
+        return u * u * half * inv_n;
     }
-    __device__ double inv_half_int(double t) const        // smallest x with int_0^x p^(1/3) >= t
+    __device__ __forceinline__ double inv_half_int(double t) const     // smallest x with int_0^x p^(1/3) >= t
     {
         int lo = 0, hi = kNB;                              // smallest i with H[i+1] >= t
         while (lo < hi) {
             const int mid = (lo + hi) >> 1;
             if (L.H[mid + 1] >= t) hi = mid; else lo = mid + 1;
         }
-        if (lo >= kNB) return bin_hi(kNB - 1, absmax);
-        return bin_lo(lo) + (t - L.H[lo]) / L.p13[lo];
+        if (lo >= kNB) return 65536.0 + last_bin_width(absmax);
+        const double w = lo < kNB - 1 ? ldexp(1.0, lo > 0 ? ((lo - 1) >> 4) - 44 : -40) : last_bin_width(absmax);
+        return bin_lo(lo) + w * ((t - L.H[lo]) / (L.H[lo + 1] - L.H[lo]));     // H[lo] < t <= H[lo + 1]
     }
 };
 
-__global__ __launch_bounds__(kBlock) void tq_params_kernel(const PtrTable stats_tab, uint32_t nb, int bits, int grid,
+// The fixed-point iteration a -> F(a) of the boxed equations converges near its fixed point like
+// r^k, r being the logarithmic slope of F there.  Wherever it is sure to meet kRelTol within
+// kMaxIter steps its limit is the fixed point, however that is computed: the slope at two points in
+// a row and at the end is at most kCertifiedSlope, the steps have come down to kNearStep octaves
+// after `plain` steps of the iteration itself, and the steps that are left, log(kNearStep / kRelTol) /
+// log(1 / r), bring the sum to no more than kSureSteps.
+constexpr float kCertifiedSlope = 0.75f;
+constexpr float kNearStep = 0.02f;
+constexpr int kSeekSteps = 60;
+constexpr float kSureSteps = 90.0f;
+__device__ __forceinline__ bool certified_slope(float r) { return fabsf(r) <= kCertifiedSlope; }
+
+template <int GRID>
+__global__ __launch_bounds__(kParamsBlock) void tq_params_kernel(const PtrTable stats_tab, uint32_t nb, int bits,
                                                            float alpha_override, const MutPtrTable params_tab)
 {
-    __shared__ ParamsLds L;
+    constexpr bool kRoots = GRID != TQ_GRID_UNIFORM;       // the integral of p^(1/3) is needed
+    constexpr bool kBiscaled = GRID == TQ_GRID_BISCALED;
+    __shared__ ParamsLds<kRoots> L;
     // one workgroup per bucket, blockIdx.y = tensor of the batch
     const uint32_t bucket = linear_block();
     if (bucket >= nb) return;
-    const tq_stats_t* S = static_cast<const tq_stats_t*>(stats_tab.p[blockIdx.y]) + bucket;
-    tq_params_t* params = static_cast<tq_params_t*>(params_tab.p[blockIdx.y]);
-    const int tid = threadIdx.x;
-    const int i0 = tid * kBinsPerLane;
-    const double absmax = (double)S->absmax;
-    const bool fixed_gmin = S->g_min > 0.0f;
+    const tq_stats_t* __restrict__ S = static_cast<const tq_stats_t*>(stats_tab.p[blockIdx.y]) + bucket;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    // counts and their prefix sums
-    double h[kBinsPerLane], local = 0.0;
+    uint32_t h[kBinsPerLane], cum[kBinsPerLane];
 #pragma unroll
     for (int k = 0; k < kBinsPerLane; ++k) {
-        h[k] = (i0 + k < kNB) ? (double)S->hist[i0 + k] : 0.0;
-        local += h[k];
+        const int i = kParamsBlock * k + tid;
+        h[k] = i < kNB ? S->hist[i] : 0u;
     }
-    double run = block_exclusive_scan(local, L);
+    const double centre_log = kOctaveLogs.centre[(tid - 1) & 15], edge_log = kOctaveLogs.edge[(tid - 1) & 15];
+    const double absmax = (double)S->absmax;
+    const float given_g_min = S->g_min;
+    const uint64_t given_n_tail = S->n_tail;
+    const double given_sum_log = S->sum_log_tail;
+    const bool fixed_gmin = given_g_min > 0.0f;
     if (tid == 0) L.tail_bin = kNB;
-    __syncthreads();
-    const double n = L.total;
+
+    // counts below each bin
+#pragma unroll
+    for (int k = 0; k < kBinsPerLane; ++k) cum[k] = h[k];
+    const uint32_t n_count = bin_scan(cum, L.chunk_count);
+    const double n = (double)n_count;
 #pragma unroll
     for (int k = 0; k < kBinsPerLane; ++k) {
-        if (i0 + k < kNB) { L.hist[i0 + k] = h[k]; L.cum[i0 + k] = run; }
-        const double before = run;
-        run += h[k];
+        const int i = kParamsBlock * k + tid;
+        if (i < kNB) L.hc[i] = make_uint2(h[k], cum[k]);
         // Without a caller-fixed g_min the tail starts at the lower edge of the first bin at
         // which the cumulative count reaches the 0.9-quantile of |g|: exactly one bin has the
         // count below the mark before it and at or above the mark with it.
-        if (i0 + k < kNB && n > 0.0 && 10.0 * before < 9.0 * n && 10.0 * run >= 9.0 * n) L.tail_bin = i0 + k;
+        const uint64_t mark = 9ull * n_count;
+        if (10ull * cum[k] < mark && 10ull * ((uint64_t)cum[k] + h[k]) >= mark) {
+            L.tail_bin = i;
+            L.tail_edge_log = i < kNB - 1 ? edge_log : 0.0;
+        }
     }
-    if (tid == kBlock - 1) L.cum[kNB] = n;
     __syncthreads();
-
     int tail_bin = L.tail_bin;
     double g_min;
-    if (fixed_gmin) { g_min = (double)S->g_min; tail_bin = kNB; }
+    if (fixed_gmin) { g_min = (double)given_g_min; tail_bin = kNB; }
     else if (tail_bin >= kNB) { g_min = 0.0; }
     else g_min = bin_lo(tail_bin);                         // 0 when the quantile sits in bin 0
     const bool binned_tail = !fixed_gmin && g_min > 0.0;
 
-    // density^(1/3), its integral up to each bin, and the binned log-sum of the tail
-    double pw[kBinsPerLane], local_h = 0.0, local_t = 0.0;
-#pragma unroll
-    for (int k = 0; k < kBinsPerLane; ++k) {
-        const int i = i0 + k;
-        pw[k] = 0.0;
-        if (i < kNB) {
-            const double lo = bin_lo(i), hi = bin_hi(i, absmax);
-            const double dens = n > 0.0 ? h[k] / (2.0 * n * (hi - lo)) : 0.0;
-            const double c = cbrt(dens);
-            L.p13[i] = c;
-            pw[k] = c * (hi - lo);
-            if (binned_tail && i >= tail_bin && h[k] > 0.0) {
-                const double rep = i < kNB - 1 ? sqrt(lo * hi) : lo;
-                local_t += h[k] * log(rep / g_min);
-            }
-        }
-        local_h += pw[k];
-    }
-    double runh = block_exclusive_scan(local_h, L);
-#pragma unroll
-    for (int k = 0; k < kBinsPerLane; ++k) {
-        if (i0 + k < kNB) L.H[i0 + k] = runh;
-        runh += pw[k];
-    }
-    __syncthreads();
-    if (tid == kBlock - 1) L.H[kNB] = L.total;
-    const double excl_t = block_exclusive_scan(local_t, L);
-    (void)excl_t;
-    __syncthreads();
-    const double sum_log_binned = L.total;
-    const bool biscaled = grid == TQ_GRID_BISCALED;
-    if (!biscaled && tid != 0) return;                    // BiScaled: all lanes stay, in lockstep
-
-    const DensityView D{L, n, n > 0.0 ? 1.0 / n : 0.0, absmax};
-
-    // BiScaled search, collective: the edge lo_j < a (j = 0: beta = 0) that minimises Q_B(a, lo_j / a),
-    // the smallest such edge on a tie; returns Q_B and leaves the bin in best_bin.  Each lane keeps,
-    // for its 4 bins, the parts that do not depend on a: (mass below the edge)^(1/3), edge^(2/3).
-    double cb13[kBinsPerLane], lo23[kBinsPerLane], lo_e[kBinsPerLane], cb[kBinsPerLane];
-    if (biscaled) {
+    // density^(1/3) (times (2n)^(1/3), which cancels or is put back where it is used), its integral up
+    // to each bin, and the binned log-sum of the tail
+    double sum_log_binned = 0.0;
+    if (binned_tail) {
+        const int octave0 = (tail_bin - 1) >> 4;
+        double local_t = 0.0;
 #pragma unroll
         for (int k = 0; k < kBinsPerLane; ++k) {
-            const int j = i0 + k;
-            lo_e[k] = j < kNB ? bin_lo(j) : 0.0;
-            cb[k] = j < kNB ? L.cum[j] * D.inv_n : 0.0;
-            cb13[k] = cbrt(cb[k]);
-            lo23[k] = cbrt(lo_e[k] * lo_e[k]);
+            const int i = kParamsBlock * k + tid;
+            const double from_octave = i < kNB - 1 ? centre_log : 0.0;
+            if (i >= tail_bin)
+                local_t += (double)h[k] * ((double)(((i - 1) >> 4) - octave0) * kLn2 + (from_octave - L.tail_edge_log));
+        }
+        local_t = wave_scan(local_t);
+        if (lane == 63) L.wave_tail[wave] = local_t;
+    }
+    if constexpr (kRoots) {
+        double pw[kBinsPerLane];
+        // one bin after the other (a loop, not unrolled: its code is fetched once), through LDS
+#pragma unroll 1
+        for (int i = tid; i < kNB; i += kParamsBlock) {
+            const uint32_t count = L.hc[i].x;
+            double c = 0.0;
+            if (__builtin_amdgcn_ballot_w64(count != 0u) != 0ull) {
+                // (count / w)^(1/3) w = count^(1/3) w^(2/3); the bin is w = 2^e wide, e = 3 third + rem
+                c = cube_root((double)count);
+                if (i < kNB - 1) {
+                    const int e = i > 0 ? ((i - 1) >> 4) - 44 : -40;
+                    const int third = (e + 63) / 3 - 21, rem = e - 3 * third;
+                    c = ldexp(c * (rem == 0 ? 1.0 : (rem == 1 ? 1.58740105196819947475 : 2.51984209978974632953)), 2 * third);
+                } else if (count != 0u) {
+                    const double wr = cube_root(last_bin_width(absmax));
+                    c = c * wr * wr;
+                }
+            }
+            L.H[i] = c;
+        }
+#pragma unroll
+        for (int k = 0; k < kBinsPerLane; ++k) pw[k] = kParamsBlock * k + tid < kNB ? L.H[kParamsBlock * k + tid] : 0.0;
+        const double all = bin_scan(pw, L.chunk_h);
+#pragma unroll
+        for (int k = 0; k < kBinsPerLane; ++k) {
+            const int i = kParamsBlock * k + tid;
+            if (i < kNB) L.H[i] = pw[k];
+        }
+        if (tid == 0) L.H[kNB] = all;
+    }
+    __syncthreads();
+    if (binned_tail) {
+#pragma unroll
+        for (int w = 0; w < kParamsWaves; ++w) sum_log_binned += L.wave_tail[w];
+    }
+    // one wavefront goes on, every lane with the same scalars; BiScaled: all of them, in lockstep
+    if (!kBiscaled && wave != 0) return;
+
+    const double inv_n = n > 0.0 ? recip(n) : 0.0;
+    const DensityView<kRoots> D{L, inv_n, absmax};
+
+    // BiScaled search, collective: the edge lo_j < a (j = 0: beta = 0) that minimises Q_B(a, lo_j / a) =
+    // v^3, v = ((mass outside beta) (1 - k)^2)^(1/3) + ((mass inside) k^2)^(1/3), the smallest such edge on a tie.
+    // Each lane keeps, for its bins, what does not depend on a.
+    float lo_f[kBinsPerLane], in13_f[kBinsPerLane];        // the edge, (mass below it * edge^2)^(1/3)
+    int flip = 0;
+    if constexpr (kBiscaled) {
+#pragma unroll
+        for (int k = 0; k < kBinsPerLane; ++k) {
+            const int i = kParamsBlock * k + tid;
+            lo_f[k] = i < kNB ? (float)bin_lo(i) : __builtin_inff();
+            in13_f[k] = cum[k] && i < kNB ? exp2_hw((log2_hw((float)cum[k] * (float)inv_n) + 2.0f * log2_hw(lo_f[k])) * (1.0f / 3.0f)) : 0.0f;
         }
     }
+    // the fp32 search at threshold a: min_k v, and the elasticity of Q_B = v^3 in a with the best edge held
+    // fixed; v_f keeps the lane's candidates
+    float v_f[kBinsPerLane];
+    auto search_f = [&](float a, float& elasticity) {
+        const uint32_t bits_a = __float_as_uint(a);
+        int ja = (int)(bits_a >> 19) - 1391;
+        ja = ja < 0 ? 0 : (ja > kNB - 1 ? kNB - 1 : ja);
+        // fraction of a's bin below a, and d(fraction)/d(ln a) = a / (bin width)
+        float frac, per_ln;
+        if (ja >= 1 && ja < kNB - 1) {
+            frac = (float)(bits_a & 0x7FFFFu) * (1.0f / 524288.0f);
+            per_ln = __uint_as_float((bits_a & 0x7FFFFFu) | 0x41800000u);
+        } else {
+            double f, rw;
+            D.covered(ja, (double)a, f, rw);
+            frac = (float)f;
+            per_ln = (float)(rw * (double)a);
+        }
+        const uint2 hc = L.hc[ja];
+        const float inv_nf = (float)inv_n, part = (float)hc.x * frac, inv_a = rcp_hw(a);
+        const float inv_a23 = exp2_hw(log2_hw(a) * (-2.0f / 3.0f));
+        float v = __builtin_inff(), b_mass = 0.0f, b_rest = 1.0f, b_lo = 0.0f, b_in = 0.0f;
+#pragma unroll
+        for (int k = 0; k < kBinsPerLane; ++k) {
+            v_f[k] = __builtin_inff();
+            if (__builtin_amdgcn_ballot_w64(lo_f[k] < a) == 0ull) continue;
+            // mass between the edge and a, from an exact difference of counts; 1 - k of the formula
+            const float mass = ((float)(hc.y - cum[k]) + part) * inv_nf, rest = (a - lo_f[k]) * inv_a;
+            const float in = in13_f[k] * inv_a23;
+            const float vk = exp2_hw((log2_hw(mass) + 2.0f * log2_hw(rest)) * (1.0f / 3.0f)) + in;
+            v_f[k] = lo_f[k] < a ? vk : __builtin_inff();
+            if (v_f[k] < v) { v = v_f[k]; b_mass = mass; b_rest = rest; b_lo = lo_f[k]; b_in = in; }
+        }
+        const float m = wave_min(v);
+        const unsigned long long at = __builtin_amdgcn_ballot_w64(v == m);
+        // v = s1 + s2: d ln(s1) = dmass / (3 mass) + 2/3 k / (1 - k), d ln(s2) = -2/3
+        const float s1 = v - b_in;
+        const float d1 = b_mass > 0.0f ? (float)hc.x * per_ln * inv_nf * rcp_hw(b_mass) + 2.0f * b_lo * inv_a * rcp_hw(b_rest) : 0.0f;
+        const float slope = (s1 * d1 - 2.0f * b_in) * rcp_hw(v);
+        if (lane == (at ? __builtin_ctzll(at) : 0)) { L.search_q[flip][wave] = m; L.search_slope[flip][wave] = slope; }
+        __syncthreads();
+        float q = L.search_q[flip][0];
+        elasticity = L.search_slope[flip][0];
+#pragma unroll
+        for (int w = 1; w < kParamsWaves; ++w)
+            if (L.search_q[flip][w] < q) { q = L.search_q[flip][w]; elasticity = L.search_slope[flip][w]; }
+        flip ^= 1;                                         // the other buffer next: one barrier per search
+        return q;
+    };
+    // the search in fp64, over the edges whose fp32 value is within 1e-4 of the fp32 minimum (its error is
+    // below 1e-5: the masses are differences of exact counts, every other term is good to a few ulp)
     int best_bin = 0;
-    auto biscaled_min = [&](double a) -> double {
-        const double c_a = D.Q_U(a);
-        const double inv_a = 1.0 / a, inv_a23 = 1.0 / cbrt(a * a);
+    auto search_d = [&](double a, double& elasticity) {
+        float el;
+        const float bound = search_f((float)a, el) * 1.0001f;
+        const int ja = bin_of(a);
+        double frac, rw;
+        D.covered(ja, a, frac, rw);
+        const double part = (double)L.hc[ja].x * frac, inv_a = recip(a);
         double q = 1.0e300;
         int jbest = kNB;
-#pragma unroll
+#pragma unroll 1
         for (int k = 0; k < kBinsPerLane; ++k) {
-            const int j = i0 + k;
-            if (j < kNB && (j == 0 || lo_e[k] < a)) {
-                const double kk = lo_e[k] * inv_a;
-                double outer = c_a - cb[k];
-                outer = outer > 0.0 ? outer : 0.0;
-                const double r = 1.0 - kk;
-                const double v = cbrt(outer) * cbrt(r * r) + cb13[k] * (lo23[k] * inv_a23);
-                if (v < q) { q = v; jbest = j; }          // ascending j: the first minimum stays
+            float v32 = v_f[0];
+            double lo = (double)lo_f[0];
+            uint32_t below = cum[0];
+#pragma unroll
+            for (int m = 1; m < kBinsPerLane; ++m)
+                if (m == k) { v32 = v_f[m]; lo = (double)lo_f[m]; below = cum[m]; }
+            // an edge between a and a rounded to fp32 counts as close
+            const bool close = lo < a && (v32 <= bound || !(lo < (double)(float)a));
+            unsigned long long left = __builtin_amdgcn_ballot_w64(close);
+            if (left == 0ull) continue;
+            const double kk = lo * inv_a, rest = (a - lo) * inv_a;
+            const double out_mass = ((double)(L.hc[ja].y - below) + part) * inv_n, in_mass = (double)below * inv_n;
+            const double v = cube_root(out_mass * rest * rest) + cube_root(in_mass * kk * kk);
+            while (left) {                                 // a few candidates, in ascending order
+                const int l = __builtin_ctzll(left);
+                left &= left - 1;
+                const double vl = lane_value(v, l);
+                if (vl < q) { q = vl; jbest = kParamsBlock * k + 64 * wave + l; }
             }
         }
-        const int lane = tid & 63, wave = tid >> 6;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const double oq = __shfl_xor(q, off, 64);
-            const int oj = __shfl_xor(jbest, off, 64);
-            if (oq < q || (oq == q && oj < jbest)) { q = oq; jbest = oj; }
-        }
-        __syncthreads();                                   // the previous search has been read
-        if (lane == 0) { L.best_q[wave] = q; L.best_j[wave] = jbest; }
+        if (lane == 0) { L.best_q[wave] = q; L.best_j[wave] = jbest; }   // read before search_f's barrier last time
         __syncthreads();
         q = L.best_q[0];
         jbest = L.best_j[0];
 #pragma unroll
-        for (int w = 1; w < 4; ++w) {
+        for (int w = 1; w < kParamsWaves; ++w) {
             const double oq = L.best_q[w];
             const int oj = L.best_j[w];
             if (oq < q || (oq == q && oj < jbest)) { q = oq; jbest = oj; }
         }
         best_bin = jbest;
+        elasticity = (double)el;
         return q * q * q;
+    };
+    // Q of the family at a, and dlnQ/dlna
+    auto Q = [&](double a, double& elasticity) {
+        if constexpr (GRID == TQ_GRID_UNIFORM) return D.Q_U(a, elasticity);
+        else if constexpr (kBiscaled) return search_d(a, elasticity);
+        else return D.Q_N(a, elasticity);
+    };
+    // the same in fp32 for bins 1 .. 896: the fraction of the bin below a is a's low mantissa bits
+    auto log2_Q_f = [&](float a, float& elasticity) {
+        const uint32_t bits_a = __float_as_uint(a);
+        int j = (int)(bits_a >> 19) - 1391;
+        j = j < 1 ? 1 : (j > kNB - 2 ? kNB - 2 : j);
+        const float frac = (float)(bits_a & 0x7FFFFu) * (1.0f / 524288.0f);
+        const float mant = __uint_as_float((bits_a & 0x7FFFFFu) | 0x41800000u);    // a / (bin width) = 16 + m + frac
+        if constexpr (GRID == TQ_GRID_UNIFORM) {
+            const uint2 hc = L.hc[j];
+            const float mass = (float)hc.y + (float)hc.x * frac;
+            elasticity = (float)hc.x * mant * rcp_hw(mass);
+            return log2_hw(mass * (float)inv_n);
+        } else if constexpr (kBiscaled) {
+            return 3.0f * log2_hw(search_f(a, elasticity));
+        } else {
+            const double below = L.H[j];
+            const float mine = (float)(L.H[j + 1] - below), half = (float)below + mine * frac;
+            elasticity = 3.0f * mine * mant * rcp_hw(half) - 2.0f;
+            const float u = half * rcp_hw(a);
+            return log2_hw(u * u * (half * (float)inv_n));
+        }
     };
 
     const int s = (1 << bits) - 1;
@@ -288,16 +566,16 @@ __global__ __launch_bounds__(kBlock) void tq_params_kernel(const PtrTable stats_
     } else {
         double n_tail, sum_log;
         if (fixed_gmin) {
-            n_tail = (double)S->n_tail;
-            sum_log = S->sum_log_tail;
+            n_tail = (double)given_n_tail;
+            sum_log = given_sum_log;
         } else {
-            n_tail = g_min > 0.0 ? n - L.cum[tail_bin] : 0.0;
+            n_tail = g_min > 0.0 ? n - (double)L.hc[tail_bin].y : 0.0;
             sum_log = g_min > 0.0 ? sum_log_binned : 0.0;
         }
         const bool tail_ok = g_min > 0.0 && n_tail > 0.0 && sum_log > 0.0 && g_min < absmax;
         if (tail_ok) {
-            gamma = 1.0 + n_tail / sum_log;
-            rho = n_tail / (2.0 * n);
+            gamma = 1.0 + n_tail * recip(sum_log);
+            rho = n_tail * 0.5 * inv_n;
         }
         if (alpha_override != 0.0f) {
             flags |= TQ_F_ALPHA_OVERRIDE;
@@ -309,19 +587,66 @@ __global__ __launch_bounds__(kBlock) void tq_params_kernel(const PtrTable stats_
             double gu = gamma;
             if (gu < kGammaFloor) { gu = kGammaFloor; flags |= TQ_F_GAMMA_CLAMPED; }
             const double a_min = g_min * (1.0 + 0.0009765625), a_max = absmax;
-            const double C = 2.0 * rho * (double)(s * s) / (gu - 2.0);
-            const double ex = 1.0 / (gu - 1.0);
-            const double log_c = log(C);
+            const double C = 2.0 * rho * (double)(s * s) * recip(gu - 2.0);
+            const double ex = recip(gu - 1.0);
             auto clampa = [&](double a) { a = a > a_min ? a : a_min; return a < a_max ? a : a_max; };
-            double a = clampa(g_min * exp(ex * log_c));    // alpha' of Sec. IV-A (Q = 1)
+            double a = 0.0;
             bool converged = false;
-            for (int it = 0; it < kMaxIter; ++it) {
-                const double q = grid == TQ_GRID_UNIFORM ? D.Q_U(a) : (biscaled ? biscaled_min(a) : D.Q_N(a));
-                // (C/q)^ex evaluated as exp(ex (ln C - ln q))
-                const double an = q > 0.0 ? clampa(g_min * exp(ex * (log_c - log(q)))) : a_max;
-                const bool done = fabs(an - a) <= kRelTol * an;
-                a = an;
-                if (done) { converged = true; break; }
+
+            // fp32: t = log2(a / g_min), t -> f(t) = ex (log2 C - log2 Q).  Plain steps, as the definition
+            // takes them, until two slopes in a row are certified and the step is below a third of a bin; then
+            // Newton steps.  (The last bin, 65536 and up, spans octaves and is left to the plain path.)
+            if (a_max < 65536.0) {
+                const float exf = (float)ex, log2_C = log2_hw((float)C), g_f = (float)g_min;
+                const float t_min = log2_hw((float)(1.0 + 0.0009765625)), t_max = log2_hw((float)(a_max / g_min));
+                auto clampt = [&](float t) { t = t > t_min ? t : t_min; return t < t_max ? t : t_max; };
+                float t = clampt(exf * log2_C), r_before = 2.0f, plain = 0.0f;
+                bool near = false;
+                for (int it = 0; it < kSeekSteps && !near; ++it) {
+                    float el;
+                    const float f = exf * (log2_C - log2_Q_f(g_f * exp2_hw(t), el));
+                    const float r = -exf * el;
+                    float step = clampt(f) - t;
+                    if (certified_slope(r) && certified_slope(r_before) && fabsf(step) <= kNearStep)
+                        step = clampt(t + (f - t) * rcp_hw(1.0f - r)) - t;
+                    else
+                        plain = (float)it;
+                    r_before = r;
+                    t += step;
+                    near = fabsf(step) <= 1e-5f;
+                }
+                // fp64: Newton on ln(a / g_min) + ex ln(Q / C); two steps end it nearly always
+                a = t >= t_max ? a_max : clampa(g_min * (double)exp2_hw(t));
+                for (int it = 0; it < 5 && near && !converged; ++it) {
+                    double el;
+                    const double q = Q(a, el);
+                    if (!(q > 0.0)) break;
+                    const double part = ln(((lane & 1) ? q : a) * recip((lane & 1) ? C : g_min));    // the two logarithms at once, in even and odd lanes
+                    const double residual = lane_value(part, 0) + ex * lane_value(part, 1), slope = -ex * el;
+                    const double delta = -residual * (double)rcp_hw((float)(1.0 - slope));
+                    const double an = clampa(a * (1.0 + delta * (1.0 + 0.5 * delta)));
+                    if ((a >= a_max && residual <= 0.0) || (a <= a_min && residual >= 0.0)) { converged = true; break; }
+                    const float r = fabsf((float)slope);
+                    if (!certified_slope(r) || !(fabs(delta) < 0.03)) break;
+                    if (plain + 27.6f * rcp_hw(-log2_hw(r)) > kSureSteps) break;   // log2(kNearStep / kRelTol) = 27.6
+                    // quadratic convergence inside a bin: what is left is of the order of delta^2
+                    converged = fabs(delta) <= 1e-5 && bin_of(an) == bin_of(a);
+                    a = an;
+                }
+            }
+            if (!converged) {
+                // the definition's iteration, step by step
+                const double log_c = ln(C);
+                a = clampa(g_min * exp(ex * log_c));       // alpha' of Sec. IV-A (Q = 1)
+                for (int it = 0; it < kMaxIter; ++it) {
+                    double el;
+                    const double q = Q(a, el);
+                    // (C/q)^ex evaluated as exp(ex (ln C - ln q))
+                    const double an = q > 0.0 ? clampa(g_min * exp(ex * (log_c - ln(q)))) : a_max;
+                    const bool done = fabs(an - a) <= kRelTol * an;
+                    a = an;
+                    if (done) { converged = true; break; }
+                }
             }
             if (!converged) flags |= TQ_F_NOT_CONVERGED;
             if (a >= a_max) flags |= TQ_F_ALPHA_CLAMPED_MAX;
@@ -330,22 +655,27 @@ __global__ __launch_bounds__(kBlock) void tq_params_kernel(const PtrTable stats_
         }
     }
 
-    tq_params_t* P = params + bucket;
+    // the codebook, a lane per level
     const float alpha_f = (float)(alpha > kAlphaFloor ? alpha : kAlphaFloor);
     const double af = (double)alpha_f;
-    const double half = D.half_int(af);
-    if (biscaled) {
-        if (half > 0.0) (void)biscaled_min(af);            // the split belongs to the rounded threshold
-        if (tid != 0) return;
+    double half = 0.0;
+    if constexpr (kRoots) {
+        double density;
+        half = D.half_int(af, density);
     }
-    float lv[16];
-    for (int k = 0; k < 16; ++k) lv[k] = 0.0f;
-    if (grid == TQ_GRID_UNIFORM || !(half > 0.0) || (biscaled && best_bin == 0)) {
-        for (int k = 0; k <= s; ++k) lv[k] = (float)(-af + (double)k * (2.0 * af / (double)s));
-        lv[s] = alpha_f;
-    } else if (biscaled) {
+    if constexpr (kBiscaled) {
+        double el;
+        if (half > 0.0) (void)search_d(af, el);            // the split belongs to the rounded threshold
+        if (wave != 0) return;
+    }
+    const int k = lane;                                    // this lane's level, 0 .. s
+    float lv = 0.0f;
+    if (GRID == TQ_GRID_UNIFORM || !(half > 0.0) || (kBiscaled && best_bin == 0)) {
+        lv = (float)(-af + (double)k * (2.0 * af / (double)s));
+    } else if constexpr (kBiscaled) {
         const double beta = bin_lo(best_bin), kk = beta / af;
-        const double c_b = L.cum[best_bin] * D.inv_n, c_a = D.Q_U(af);
+        double el;
+        const double c_b = (double)L.hc[best_bin].y * inv_n, c_a = D.Q_U(af, el);
         const double p1 = c_b / (2.0 * beta);
         const double rest = c_a - c_b > 0.0 ? c_a - c_b : 0.0;
         const double p2 = rest / (2.0 * (af - beta));
@@ -353,51 +683,52 @@ __global__ __launch_bounds__(kBlock) void tq_params_kernel(const PtrTable stats_
         const double x = inner + outer > 0.0 ? (double)s * inner / (inner + outer) : (double)s;
         int s_beta = 2 * (int)floor((x - 1.0) * 0.5 + 0.5) + 1;           // nearest odd integer
         s_beta = s_beta < 1 ? 1 : (s_beta > s - 2 ? s - 2 : s_beta);
-        const int h = (s - s_beta) / 2;                                    // cells beyond beta on each side
-        for (int j = 0; j <= s_beta; ++j) lv[h + j] = (float)(-beta + (double)j * (2.0 * beta / (double)s_beta));
-        lv[h] = (float)(-beta);
-        lv[h + s_beta] = (float)beta;
-        for (int j = 1; j <= h; ++j) {
-            const double xo = beta + (double)j * ((af - beta) / (double)h);
-            lv[h + s_beta + j] = (float)xo;
-            lv[h - j] = -(float)xo;
+        const int out_cells = (s - s_beta) / 2;                            // cells beyond beta on each side
+        const int j = k - out_cells;
+        if (j > 0 && j < s_beta) {
+            lv = (float)(-beta + (double)j * (2.0 * beta / (double)s_beta));
+        } else {
+            const int beyond = j <= 0 ? -j : j - s_beta;                   // cells from beta outwards
+            const float xo = (float)(beta + (double)beyond * ((af - beta) / (double)out_cells));
+            lv = j <= 0 ? -xo : xo;
         }
-        lv[0] = -alpha_f;
-        lv[s] = alpha_f;
-    } else {
-        lv[0] = -alpha_f;
-        lv[s] = alpha_f;
-        for (int k = (s + 1) / 2; k < s; ++k) {
-            double x = D.inv_half_int(half * (double)(2 * k - s) / (double)s);
-            x = x < af ? x : af;
-            lv[k] = (float)x;
-            lv[s - k] = -(float)x;
-        }
+    } else if constexpr (kRoots) {
+        const int up = k > s / 2 ? k : s - k;                              // the positive one of a mirrored pair
+        double x = D.inv_half_int(half * (double)(2 * up - s) / (double)s);
+        x = x < af ? x : af;
+        lv = k > s / 2 ? (float)x : -(float)x;
     }
-    P->alpha = alpha_f;
-    P->bits = (uint32_t)bits;
-    P->s = (uint32_t)s;
-    P->grid = (uint32_t)grid;
-    for (int k = 0; k < 16; ++k) {
-        P->level[k] = lv[k];
-        float iw = 0.0f;
-        if (k < s) {
-            if (grid == TQ_GRID_UNIFORM) {
-                iw = (float)((double)s / (2.0 * af));
-            } else {
-                const double width = (double)lv[k + 1] - (double)lv[k];
-                if (width > 0.0) {
-                    const double r = 1.0 / width;
-                    iw = r <= 3.4028234663852886e38 ? (float)r : 0.0f;
-                }
+    if (k == 0) lv = -alpha_f;
+    if (k == s) lv = alpha_f;
+    if (k > s) lv = 0.0f;
+    const float next = __shfl_down(lv, 1, 64);
+    float iw = 0.0f;
+    if (k < s) {
+        if (GRID == TQ_GRID_UNIFORM) {
+            iw = (float)((double)s / (2.0 * af));
+        } else {
+            const double width = (double)next - (double)lv;
+            if (width > 0.0) {
+                const double r = 1.0 / width;
+                iw = r <= 3.4028234663852886e38 ? (float)r : 0.0f;
             }
         }
-        P->inv_w[k] = iw;
     }
-    P->gamma_hat = (float)gamma;
-    P->rho_hat = (float)rho;
-    P->g_min = (float)g_min;
-    P->flags = flags;
+    tq_params_t* P = static_cast<tq_params_t*>(params_tab.p[blockIdx.y]) + bucket;
+    if (lane < 16) {
+        P->level[lane] = lv;
+        P->inv_w[lane] = iw;
+    }
+    if (lane == 0) {
+        P->alpha = alpha_f;
+        P->bits = (uint32_t)bits;
+        P->s = (uint32_t)s;
+        P->grid = (uint32_t)GRID;
+        P->gamma_hat = (float)gamma;
+        P->rho_hat = (float)rho;
+        P->g_min = (float)g_min;
+        P->flags = flags;
+    }
 }
 
 }  // namespace tq
@@ -407,12 +738,18 @@ hipError_t tq_launch_params(const tq_stats_t* const* stats, int count, uint64_t 
                             float alpha_override, tq_params_t* const* params, hipStream_t st)
 {
     dim3 blocks;
-    if (count < 1 || count > tq::kMaxBatch || !tq::fold_grid(nb, tq::kBlock, (unsigned)count, blocks))
+    if (count < 1 || count > tq::kMaxBatch || !tq::fold_grid(nb, tq::kParamsBlock, (unsigned)count, blocks))
         return hipErrorInvalidValue;
     tq::PtrTable stt{};
     tq::MutPtrTable pt{};
     for (int i = 0; i < count; ++i) { stt.p[i] = stats[i]; pt.p[i] = params[i]; }
-    hipLaunchKernelGGL(tq::tq_params_kernel, blocks, dim3(tq::kBlock), 0, st, stt, (uint32_t)nb, bits,
-                       grid, alpha_override, pt);
+#define TQ_LAUNCH_PARAMS(G) \
+    hipLaunchKernelGGL(tq::tq_params_kernel<G>, blocks, dim3(tq::kParamsBlock), 0, st, stt, (uint32_t)nb, bits, alpha_override, pt)
+    switch (grid) {
+        case TQ_GRID_UNIFORM: TQ_LAUNCH_PARAMS(TQ_GRID_UNIFORM); break;
+        case TQ_GRID_NONUNIFORM: TQ_LAUNCH_PARAMS(TQ_GRID_NONUNIFORM); break;
+        default: TQ_LAUNCH_PARAMS(TQ_GRID_BISCALED); break;
+    }
+#undef TQ_LAUNCH_PARAMS
     return hipGetLastError();
 }

@@ -1,0 +1,71 @@
+"""tq_params where its ways of finding the threshold part: fixed points that the fp32 approach and the
+Newton steps may take, those it must leave to the plain iteration, and thresholds at the ends of their range."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import binding as O
+from oracle import params as OP
+from paper_2402_01798_amd import binding as B
+from test_gpu_stats_params import assert_params_close
+
+pytestmark = pytest.mark.gpu
+
+
+def edge(i):
+    return 2.0 ** ((i - 1) // 16 - 40) * (1 + ((i - 1) % 16) / 16)
+
+
+def record(hist, absmax):
+    r = np.zeros(1, dtype=B.STATS_DTYPE)
+    r["hist"][0, :len(hist)] = hist
+    r["absmax"] = absmax
+    r["n"] = int(np.sum(hist))
+    return r
+
+
+def power_law(gamma, lo, width, n=2_000_000):
+    x = np.arange(width)
+    h = np.zeros(898, dtype=np.int64)
+    h[lo:lo + width] = np.round(n * 2.0 ** (-(gamma - 1) * x / 16))
+    return record(h, edge(lo + int(np.nonzero(h[lo:])[0].max())) * 1.01)
+
+
+def records():
+    out = []
+    for gamma in (2.05, 2.5, 3.0, 4.0, 6.0, 9.0):            # slopes from nearly 0 to beyond what is certified
+        for lo in (1, 300, 640):
+            out.append(power_law(gamma, lo, 250))
+    one = np.zeros(898, dtype=np.int64)
+    one[500] = 1
+    out.append(record(one, edge(500)))                        # one element
+    two = np.zeros(898, dtype=np.int64)
+    two[[1, 896]] = [1_000_000, 70_000]                       # first and last regular bin
+    out.append(record(two, 65535.0))
+    top = np.zeros(898, dtype=np.int64)
+    top[880:898] = 1000                                       # into the last bin: the plain iteration
+    out.append(record(top, 3.0e5))
+    full = np.zeros(898, dtype=np.int64)
+    full[300:400] = 40_000_000                                # counts whose sum is near 2^32
+    full[400:440] = 5_000_000
+    out.append(record(full, edge(440)))
+    return np.concatenate(out)
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("grid", [B.GRID_UNIFORM, B.GRID_NONUNIFORM, B.GRID_BISCALED])
+def test_designed_histograms(bits, grid):
+    st = records()
+    dev = torch.from_numpy(st.view(np.uint8).reshape(-1).copy()).cuda()
+    pr = torch.full((st.size * B.PARAMS_BYTES,), 0x77, dtype=torch.uint8, device="cuda")
+    B.tq_params(dev, pr, bits, grid)
+    torch.cuda.synchronize()
+    got = B.params_to_numpy(pr)
+    want = OP.tq_params(st.view(O.STATS_DTYPE), bits, grid)
+    # An iteration that does not converge has no limit to compare, and whether one that ends up jumping
+    # between two equally good splits (BiScaled, steep tails) does is decided by the last bits of Q_B: records
+    # the oracle gives up on are left out (none of the uniform ones, at most 8 of 22 of the others).
+    steady = (want["flags"] & 4) == 0
+    assert steady.sum() >= (st.size if grid == B.GRID_UNIFORM else st.size - 8)
+    assert (got["flags"][steady] == want["flags"][steady]).all()
+    assert_params_close(got[steady], want[steady])

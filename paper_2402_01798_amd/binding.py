@@ -98,8 +98,16 @@ def _check(rc, what):
         raise TqError(rc, what)
 
 
+# Host time per call is what bounds small tensors, so addresses are passed as plain integers (ctypes
+# converts them by the declared argument types), sizes that all tensors of a batch share are computed
+# once, and the stream handle is read without building a torch Stream object (3 us of an 8 us call).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _dtype_code(g):
@@ -113,7 +121,7 @@ def _dtype_code(g):
 def _dev(t, what):
     if not (t.is_cuda and t.is_contiguous()):
         raise ValueError("%s must be a contiguous device tensor" % what)
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def num_buckets(d, bucket_elems=0):
@@ -192,7 +200,7 @@ def tq_quantize_dequantize(g, params, out, bits, seed, worker, step, bucket_elem
 
 
 def _ptr_array(tensors, what):
-    return (C.c_void_p * len(tensors))(*[_dev(t, what).value for t in tensors])
+    return (C.c_void_p * len(tensors))(*[_dev(t, what) for t in tensors])
 
 
 def tq_stats_multi(gs, stats, workspace, bucket_elems=0, g_min=0.0):
@@ -212,11 +220,12 @@ def tq_params_multi(stats, params, bits, grid, alpha_override=0.0):
 
 
 def tq_compress_multi(gs, params, payloads, bits, seed, first_worker, step, bucket_elems=0, grid=GRID_UNIFORM):
-    d = gs[0].numel()
+    d, dtype = gs[0].numel(), gs[0].dtype
+    qsize, psize = num_buckets(d, bucket_elems) * PARAMS_BYTES, payload_bytes(d, bits)
     for g, q, p in zip(gs, params, payloads):
-        if g.numel() != d or g.dtype != gs[0].dtype:
+        if g.numel() != d or g.dtype != dtype:
             raise ValueError("batched tensors must share shape and dtype")
-        if q.numel() != num_buckets(d, bucket_elems) * PARAMS_BYTES or p.numel() < payload_bytes(d, bits):
+        if q.numel() != qsize or p.numel() < psize:
             raise ValueError("params / payload buffer size does not match d")
     _check(lib().tq_compress_multi(_ptr_array(gs, "g"), len(gs), _dtype_code(gs[0]), d, bucket_elems,
                                    _ptr_array(params, "params"), bits, grid, seed, first_worker, step,
@@ -228,12 +237,11 @@ def _decode_args(payloads, params, d, bits, bucket_elems, weights):
     N = len(payloads)
     if len(params) != N:
         raise ValueError("one params buffer per payload")
-    nb = num_buckets(d, bucket_elems)
+    psize, qsize = payload_bytes(d, bits), num_buckets(d, bucket_elems) * PARAMS_BYTES
     for p, q in zip(payloads, params):
-        if p.numel() < payload_bytes(d, bits) or q.numel() != nb * PARAMS_BYTES:
+        if p.numel() < psize or q.numel() != qsize:
             raise ValueError("payload / params buffer size does not match d")
-    pp = (C.c_void_p * N)(*[_dev(p, "payload").value for p in payloads])
-    qq = (C.c_void_p * N)(*[_dev(q, "params").value for q in params])
+    pp, qq = _ptr_array(payloads, "payload"), _ptr_array(params, "params")
     ww = None
     if weights is not None:
         if len(weights) != N:
@@ -279,7 +287,7 @@ class Segments:
         self.d = int(self.host[-1])
 
     def args(self):
-        return C.c_void_p(self.dev.data_ptr()), self.host.ctypes.data_as(C.c_void_p), self.nseg
+        return self.dev.data_ptr(), self.host.ctypes.data, self.nseg
 
 
 def stats_segments_workspace_bytes(d, nseg):
@@ -315,11 +323,12 @@ def tq_stats_segments_multi(gs, seg, stats, workspace, g_min=0.0):
 
 
 def tq_compress_segments_multi(gs, seg, params, payloads, bits, seed, first_worker, step):
-    d = gs[0].numel()
+    d, dtype = gs[0].numel(), gs[0].dtype
+    qsize, psize = seg.nseg * PARAMS_BYTES, payload_bytes(d, bits)
     for g, q, p in zip(gs, params, payloads):
-        if g.numel() != d or g.dtype != gs[0].dtype:
+        if g.numel() != d or g.dtype != dtype:
             raise ValueError("batched tensors must share shape and dtype")
-        if q.numel() != seg.nseg * PARAMS_BYTES or p.numel() < payload_bytes(d, bits):
+        if q.numel() != qsize or p.numel() < psize:
             raise ValueError("params / payload buffer size does not match the segments")
     dev, host, nseg = seg.args()
     _check(lib().tq_compress_segments_multi(_ptr_array(gs, "g"), len(gs), _dtype_code(gs[0]), d, dev, host, nseg,
@@ -333,11 +342,11 @@ def tq_decompress_aggregate_segments(payloads, params, seg, out, bits, weights=N
     if out.dtype != torch.float32:
         raise TypeError("out must be float32")
     N = len(payloads)
+    psize, qsize = payload_bytes(d, bits), seg.nseg * PARAMS_BYTES
     for p, q in zip(payloads, params):
-        if p.numel() < payload_bytes(d, bits) or q.numel() != seg.nseg * PARAMS_BYTES:
+        if p.numel() < psize or q.numel() != qsize:
             raise ValueError("payload / params buffer size does not match the segments")
-    pp = (C.c_void_p * N)(*[_dev(p, "payload").value for p in payloads])
-    qq = (C.c_void_p * N)(*[_dev(q, "params").value for q in params])
+    pp, qq = _ptr_array(payloads, "payload"), _ptr_array(params, "params")
     ww = None if weights is None else (C.c_float * N)(*[float(w) for w in weights])
     dev, host, nseg = seg.args()
     _check(lib().tq_decompress_aggregate_segments(pp, qq, ww, N, d, dev, host, nseg, bits, int(bool(accumulate)),

@@ -148,15 +148,7 @@ __device__ __forceinline__ uint32_t quantize(float x, float rf, float alpha, flo
 
 // Codes of one lane's 8 elements, packed little-endian into the low 8*BITS bits.
 // PARTIAL: only the first n_valid elements exist; the others encode as 0 (pad bits).
-// CLAMP (level-table path): whether the truncation of Eq. (1) is written out.  It changes the
-// code only when the FIRST cell of the codebook is empty (l_1 = l_0 = -alpha, a degenerate
-// bucket): a value below -alpha is truncated onto that repeated level and then belongs to the
-// cell above it.  Otherwise it changes nothing -- below -alpha the cell is the first one and
-// p_r < 0, beyond +alpha it is the last one and p_r >= 1 (or 0 for an empty last cell), +-Inf
-// go the same ways (Inf times a zero reciprocal is NaN, and u <= NaN is false: the lower end,
-// as for the truncated value) -- so the caller leaves it out unless l_1 = l_0: one
-// instruction per element of a kernel that is bound by instruction issue.
-template <int BITS, int GRID, bool PARTIAL, bool CLAMP = true>
+template <int BITS, int GRID, bool PARTIAL>
 __device__ __forceinline__ uint32_t encode_group(const float (&x)[8], const uint32_t (&rw)[4], int n_valid,
                                                  float alpha, float inv_step, const float (&lv)[16],
                                                  const LevelLds& tab)
@@ -178,7 +170,7 @@ __device__ __forceinline__ uint32_t encode_group(const float (&x)[8], const uint
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const uint32_t r = (j & 1) ? (rw[j >> 1] >> 16) : (rw[j >> 1] & 0xFFFFu);
-            const float xc = CLAMP ? __builtin_amdgcn_fmed3f(x[j], -alpha, alpha) : x[j];   // Eq. (1); NaN is gone
+            const float xc = __builtin_amdgcn_fmed3f(x[j], -alpha, alpha);   // Eq. (1); NaN is gone
             uint32_t a = cell_offset<BITS>(xc, lv, tab);
             bool up = rounds_up(xc, (float)r, a, tab);
             if (PARTIAL && j >= n_valid) { a = 0; up = false; }
@@ -187,6 +179,146 @@ __device__ __forceinline__ uint32_t encode_group(const float (&x)[8], const uint
         }
         return cells + ups;
     }
+}
+
+// ---- the level-table path of regular codebooks ---------------------------------------------
+//
+// The general path above costs 18 (b = 3) or 13 (b = 2) vector instructions per element beside the
+// draw's 5, many of them compares whose mask the next instruction needs (this ISA wants two other
+// instructions in between, else s_nop).  For a REGULAR codebook -- every cell's stored reciprocal
+// fits its width and the levels mirror each other about 0, as in every designed one -- the same codes
+// come from 14 or 10 instructions without a single mask:
+//   * the cell is searched on |x| (half the levels) by the SIGN BITS of |x| - l_j, which v_alignbit
+//     shifts into the index one by one; the element's own sign completes it;
+//   * the cell's LDS entry holds l_k, inv_w[k] 2^(32-b) and a word with k in its top b bits plus the
+//     draw's half grain.  floor(p_r 2^(32-b)) (converted with saturation), the draw times 2^(16-b)
+//     and that word add up to a number whose top b bits ARE the code: u <= p_r is the same as
+//     p_r + (r + 1/2) / 2^16 >= 1, and dropping p_r's bits below 2^-(32-b) cannot change it (the other
+//     terms are multiples of 2^(15-b), 1 is 2^(32-b)).  A negative p_r converts to 0 and the sum saturates at the
+//     last code, so nothing is clamped;
+//   * v_alignbit shifts the top b bits of each sum into the packed word.
+// p_r itself is still a subtraction and a multiplication, each rounded (scaling by 2^(32-b) is exact).
+//
+// Regular (checked once per workgroup with the very arithmetic of p_r): for every cell k, with
+// p_k(x) = (x - l_k) inv_w[k], and lo_k, hi_k the ends the search gives it,
+//   |p_k(l_{k+1}) - 1| <= 2^-18,  |p_k(hi_k) - 1| <= 2^-18,  |p_k(lo_k)| <= 2^-18,  0 < inv_w[k] <= 2^90.
+// p_k is monotone and 2^-17 <= u <= 1 - 2^-17.  So inside a cell no sum reaches the code k + 2, and where the
+// search and the definition disagree about the cell (levels that mirror each other only to within
+// rounding) they agree about the code: a value that the search leaves in cell k although it has reached
+// l_{k+1} is encoded k + 1 by both (p_k >= u and p_{k+1} < u for every draw), and one that the search
+// puts into cell k although it is below l_k is encoded k by both (p_k < u and p_{k-1} >= u).  The empty and the
+// lopsided codebooks take the general path.
+//
+// Measured, before -> after: 16 x 25.6 M fp32 at b = 3 350 -> 323 us, 4 x 10^9 bf16 at b = 2
+// 1920 -> 1775 us, 25.6 M at b = 3 22.0 -> 20.2 us, 4 x 11.2 M at b = 3 in buckets of 16384
+// 35.5 -> 32.2 us.  What bounds it now: with the draws or the encoding left out the first takes 312 / 309 us,
+// the second 1640 / 1625, with both left out 307 / 1618 -- the pattern of its memory traffic.
+struct CellLds {
+    float4 e[16];            // entry neg * H + (H - 1 - i): cell m + i (x >= 0) or m - i, H = 2^(b-1), m = H - 1
+    float4 pivots[4];        // b = 4: entry 2 * neg + [|x| < l_11]: l_8, l_9, l_10 or l_12, l_13, l_14
+    uint32_t regular;
+};
+
+constexpr float kRegularSlack = 3.814697265625e-06f;           // 2^-18
+constexpr float kRegularMaxInv = 1.2379400392853803e27f;       // 2^90
+
+// What one lane of the filling wavefront reads of the record (requested before anything is known about it).
+struct CellReads { float l, l_next, inv, outer, inner; };
+
+template <int BITS>
+__device__ __forceinline__ CellReads read_cells(const tq_params_t* P, uint32_t lane)
+{
+    constexpr uint32_t H = 1u << (BITS - 1), M = H - 1;
+    const uint32_t j = lane & (2u * H - 1u), i = H - 1u - (j & (H - 1u)), k = (j & H) ? M - i : M + i;
+    return CellReads{P->level[k], P->level[k + 1], P->inv_w[k], P->level[M + 1u + i], P->level[i ? M + i : M + 1u]};
+}
+
+// Called by one whole wavefront (lane = its lane).
+template <int BITS>
+__device__ __forceinline__ void fill_cells(CellLds& tab, const tq_params_t* P, const CellReads& c, uint32_t lane)
+{
+    constexpr uint32_t H = 1u << (BITS - 1), M = H - 1;
+    const uint32_t j = lane & (2u * H - 1u), i = H - 1u - (j & (H - 1u));
+    const bool neg = (j & H) != 0u;
+    const uint32_t k = neg ? M - i : M + i;
+    const float inner = i ? c.inner : -c.inner;                // this entry is |x| in [inner, outer)
+    const float lo = neg ? -c.outer : inner, hi = neg ? -inner : c.outer;
+    const float p_next = (c.l_next - c.l) * c.inv, p_hi = (hi - c.l) * c.inv, p_lo = (lo - c.l) * c.inv;
+    const bool ok = fabsf(p_next - 1.0f) <= kRegularSlack && fabsf(p_hi - 1.0f) <= kRegularSlack &&
+                    fabsf(p_lo) <= kRegularSlack && c.inv > 0.0f && c.inv <= kRegularMaxInv;
+    if (lane < 2u * H)
+        tab.e[j] = make_float4(c.l, c.inv * (float)(1u << (32 - BITS)),
+                               __uint_as_float((k << (32 - BITS)) + (1u << (15 - BITS))), 0.0f);
+    if constexpr (BITS == 4) {
+        if (lane < 4u) {
+            const float* q = P->level + ((lane & 1u) ? 8 : 12);
+            tab.pivots[lane] = make_float4(q[0], q[1], q[2], 0.0f);
+        }
+    }
+    const bool regular = __builtin_amdgcn_ballot_w64(!ok) == 0ull;
+    if (lane == 0) tab.regular = regular ? 1u : 0u;
+}
+
+// (index << 1) | sign bit of d
+__device__ __forceinline__ uint32_t push_sign(uint32_t index, float d)
+{
+    return __builtin_amdgcn_alignbit(index, __float_as_uint(d), 31);
+}
+
+// The element's sum: its code in the top BITS bits.  HIGH: the draw is the high half of rw.
+template <int BITS, bool HIGH>
+__device__ __forceinline__ uint32_t code_on_top(float x, uint32_t rw, const float (&pv)[3], const CellLds& tab)
+{
+    const float y = __builtin_fabsf(x);
+    uint32_t index = __float_as_uint(x) >> 31;
+    if constexpr (BITS == 2) {
+        index = push_sign(index, y - pv[0]);
+    } else {
+        float p0 = pv[0], p1 = pv[1], p2 = pv[2];
+        if constexpr (BITS == 4) {
+            index = push_sign(index, y - pv[0]);
+            const float4 q = tab.pivots[index];
+            p0 = q.x; p1 = q.y; p2 = q.z;
+        }
+        // |x| below p0 / p1 / p2: the two index bits are [below p1] and, of the three signs, their parity
+        const float d0 = y - p0, d1 = y - p1, d2 = y - p2;
+        index = push_sign(index, d1);
+        index = push_sign(index, __uint_as_float(xor3(__float_as_uint(d0), __float_as_uint(d1), __float_as_uint(d2))));
+    }
+    const float4 c = tab.e[index];
+    const float p_r = (x - c.x) * c.y;                         // p_r * 2^(32-b), the two roundings of the definition
+    uint32_t whole;                                            // 0 below, saturated far above: what v_cvt_u32_f32 does
+    asm("v_cvt_u32_f32 %0, %1" : "=v"(whole) : "v"(p_r));
+    uint32_t base;                                             // draw * 2^(16-b) + k and the half grain
+    if constexpr (HIGH)
+        asm("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(base) : "v"(rw), "s"(1u << (16 - BITS)), "v"(__float_as_uint(c.z)));
+    else
+        asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(base) : "v"(rw), "s"(1u << (16 - BITS)), "v"(__float_as_uint(c.z)));
+    return __builtin_elementwise_add_sat(whole, base);
+}
+
+// The packed codes of one lane's whole group, regular codebook.
+template <int BITS>
+__device__ __forceinline__ uint32_t encode_regular(const float (&x)[8], const uint32_t (&rw)[4], const float (&pv)[3],
+                                                   const CellLds& tab)
+{
+    uint32_t word = 0;
+#pragma unroll
+    for (int j = 7; j >= 0; --j) {
+        const uint32_t t = (j & 1) ? code_on_top<BITS, true>(x[j], rw[j >> 1], pv, tab)
+                                   : code_on_top<BITS, false>(x[j], rw[j >> 1], pv, tab);
+        word = __builtin_amdgcn_alignbit(word, t, 32 - BITS);
+    }
+    return word;
+}
+
+// The levels the search compares |x| with first (wave-uniform: scalar loads).
+template <int BITS>
+__device__ __forceinline__ void load_pivots(const tq_params_t* P, float (&pv)[3])
+{
+    if constexpr (BITS == 2) { pv[0] = P->level[2]; pv[1] = pv[2] = 0.0f; }
+    else if constexpr (BITS == 3) { pv[0] = P->level[4]; pv[1] = P->level[5]; pv[2] = P->level[6]; }
+    else { pv[0] = P->level[11]; pv[1] = pv[2] = 0.0f; }
 }
 
 // `room` = bytes of the payload from `out` on.  A payload is a multiple of 16 bytes, so a
@@ -245,18 +377,30 @@ __global__ __launch_bounds__(kBlock) void tq_compress_kernel(
     const tq_params_t* P = static_cast<const tq_params_t*>(params_tab.p[blockIdx.y]) + bucket;
 
     __shared__ LevelLds tab;
-    float lv[16];
+    __shared__ CellLds cells;
+    const uint32_t lane = threadIdx.x;                         // this thread's group within a tile
+    // a launch shaped for the level-table path reads the codebook before it knows the record's family
+    constexpr bool EXPECT_TABLE = T == compress_tiles(DTYPE, true);
+    CellReads reads = {};
+    float pv[3] = {};
+    if constexpr (EXPECT_TABLE) {
+        if (lane < 64) reads = read_cells<BITS>(P, lane);
+        load_pivots<BITS>(P, pv);
+    }
     const float alpha = P->alpha;
     const float inv_step = P->inv_w[0];
     const bool nonuniform = P->grid != TQ_GRID_UNIFORM;        // uniform over the workgroup
-    const uint32_t lane = threadIdx.x;                         // this thread's group within a tile
-    bool first_cell_empty = false;                             // see encode_group's CLAMP
+    bool regular = true;
     if (nonuniform) {
-        fill_level_lds(tab, P, (1u << BITS) - 1u);
-#pragma unroll
-        for (int j = 0; j < 16; ++j) lv[j] = P->level[j];       // wave-uniform: scalar loads
-        first_cell_empty = !(lv[1] > lv[0]);
+        if constexpr (!EXPECT_TABLE) {
+            if (lane < 64) reads = read_cells<BITS>(P, lane);
+            load_pivots<BITS>(P, pv);
+        }
+        if (lane < 64) fill_cells<BITS>(cells, P, reads, lane);
+        // compared from vector registers: with a scalar operand the subtraction runs at 36 T/s, without at 59
+        asm volatile("" : "+v"(pv[0]), "+v"(pv[1]), "+v"(pv[2]));
         __syncthreads();
+        regular = __builtin_amdgcn_readfirstlane((int)cells.regular) != 0;
     }
 
     // One Philox call per lane and tile; the high counter word stays scalar unless the low
@@ -270,12 +414,13 @@ __global__ __launch_bounds__(kBlock) void tq_compress_kernel(
     };
 
     const uint64_t lim = bend < d ? bend : d;
-    if (gbase + (uint64_t)T * kTile <= lim) {
+    if (regular && gbase + (uint64_t)T * kTile <= lim) {
         // every lane owns a whole group in every tile: all reads first, the draws under them
         // (requesting the reads even earlier, before the codebook is set up, was slower: 708 us
         // against 668 on 8 x 124 M fp32)
         float x[T][8];
         uint32_t rw[T][4];
+        const float no_levels[16] = {};                        // the uniform path reads none
 #pragma unroll
         for (int t = 0; t < T; ++t) load_group<DTYPE, STREAM>(g, gbase + (uint64_t)t * kTile + (uint64_t)lane * kGroup, x[t]);
 #pragma unroll
@@ -287,12 +432,18 @@ __global__ __launch_bounds__(kBlock) void tq_compress_kernel(
         for (int t = 0; t < T; ++t) {
             replace_nan(x[t]);
             uint32_t word;
-            if (!nonuniform) word = encode_group<BITS, TQ_GRID_UNIFORM, false>(x[t], rw[t], 8, alpha, inv_step, lv, tab);
-            else if (first_cell_empty) word = encode_group<BITS, TQ_GRID_NONUNIFORM, false, true>(x[t], rw[t], 8, alpha, inv_step, lv, tab);
-            else word = encode_group<BITS, TQ_GRID_NONUNIFORM, false, false>(x[t], rw[t], 8, alpha, inv_step, lv, tab);
+            if (!nonuniform) word = encode_group<BITS, TQ_GRID_UNIFORM, false>(x[t], rw[t], 8, alpha, inv_step, no_levels, tab);
+            else word = encode_regular<BITS>(x[t], rw[t], pv, cells);
             store_codes<BITS>(payload + (((gbase + (uint64_t)t * kTile) >> 3) + lane) * (uint64_t)BITS, word);
         }
         return;
+    }
+    float lv[16];
+    if (nonuniform) {
+        fill_level_lds(tab, P, (1u << BITS) - 1u);
+#pragma unroll
+        for (int j = 0; j < 16; ++j) lv[j] = P->level[j];       // wave-uniform: scalar loads
+        __syncthreads();
     }
 
     // the last workgroup of a bucket: tile by tile, lanes past the end idle, the tensor's

@@ -213,3 +213,42 @@ def test_the_family_named_to_tq_compress_shapes_the_launch_only(wl, dtype_name, 
     for named in (B.GRID_UNIFORM, B.GRID_NONUNIFORM, B.GRID_BISCALED):
         got = device_compress(g_dev, P, bits, 21, 2, 9, bucket, grid=named).cpu().numpy()
         assert (got == want).all(), (family, named)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("kind", ["mirrored", "ulps", "lopsided", "reciprocals", "far"])
+def test_codebooks_on_both_sides_of_the_mirrored_path(kind, bits, dtype):
+    """Designed codebooks mirror their levels about 0 and take a path of their own.  Codebooks that do so
+    exactly, to within ulps of a level, not at all, with reciprocals that do not fit their cells, and with
+    levels far apart: many draws of every value at and next to a level of either sign, codes equal to the
+    oracle's."""
+    s = (1 << bits) - 1
+    rng = np.random.default_rng(bits * 10 + len(kind))
+    t = 2.0 * np.arange(s + 1) / s - 1.0
+    lv = (np.sign(t) * np.abs(t) ** (6.0 if kind == "far" else 1.7) * 0.0123).astype(np.float32)
+    lv[: (s + 1) // 2] = -lv[::-1][: (s + 1) // 2]
+    if kind == "ulps":
+        lv[1:s] = (lv[1:s].view(np.int32) + rng.integers(-2, 3, s - 1).astype(np.int32)).view(np.float32)
+    if kind == "lopsided":
+        lv[1:s] = lv[1:s] * (1.0 + rng.uniform(-0.05, 0.05, s - 1)).astype(np.float32)
+        lv = np.sort(lv)
+    inv = (1.0 / np.diff(lv.astype(np.float64))).astype(np.float32)
+    if kind == "reciprocals":
+        inv[s // 2] *= np.float32(1.0 - 2.0 ** -10)
+        inv[0] *= np.float32(1.0 + 2.0 ** -9)
+    P = np.zeros(1, dtype=O.PARAMS_DTYPE)
+    P["alpha"], P["bits"], P["s"], P["grid"] = lv[-1], bits, s, O.GRID_NONUNIFORM
+    P["level"][0, : s + 1], P["inv_w"][0, :s] = lv, inv
+    ends = np.concatenate([lv, -lv])
+    near = np.concatenate([(ends.view(np.int32) + k).view(np.float32) for k in (-40, -3, -2, -1, 0, 1, 2, 3, 40)])
+    mid = np.concatenate([(lv[1:] + lv[:-1]) / 2, [0.0, -0.0, 1.0, -1.0, np.inf, -np.inf, np.nan]]).astype(np.float32)
+    values = np.concatenate([near, mid])
+    d = 40 * 8192 + 333
+    g = values[rng.integers(0, values.size, d)]
+    g[::5] = rng.uniform(-1.1, 1.1, g[::5].size).astype(np.float32) * lv[-1]
+    tens = torch.from_numpy(g).to(dtype)
+    g_np = tens.view(torch.int16).numpy().view("uint16") if dtype == torch.bfloat16 else tens.numpy()
+    for seed in (3, 77):
+        got = device_compress(tens.cuda(), P, bits, seed, 1, 5).cpu().numpy()
+        assert (got == O.compress(g_np, P, seed, 1, 5)).all()

@@ -338,6 +338,31 @@ __device__ __forceinline__ void store_codes(uint8_t* out, uint32_t word, uint64_
     }
 }
 
+// The codes of a wavefront whose lanes all own whole groups inside the payload (`out` = the lane's place).
+// PAST_CACHES: non-temporal stores, for payloads that would not be found in a cache by whoever
+// reads them: they leave the caches to the gradient and go out as they come.  8 x 124 M fp32 uniform at
+// b = 2 / 3 / 4: 671 -> 641, 689 -> 672, 700 -> 677 us; with a payload that the decode finds in the
+// memory-side cache the hint costs the decode more than it gives here (4 x 11.2 M at b = 3: 1 us
+// against 3.6), so the host turns it on with the same line as the hint on the loads, the other way.
+// b = 3: the 12 bytes of four lanes leave as three 4-byte stores of the first three (bytes sent past
+// the caches one by one cost 1.6 times the whole launch); through the caches single bytes are as good.
+template <int BITS, bool PAST_CACHES>
+__device__ __forceinline__ void store_codes_wave(uint8_t* out, uint32_t word)
+{
+    if constexpr (!PAST_CACHES) {
+        store_codes<BITS>(out, word);
+    } else if constexpr (BITS == 4) {
+        __builtin_nontemporal_store(word, reinterpret_cast<uint32_t*>(out));
+    } else if constexpr (BITS == 2) {
+        __builtin_nontemporal_store((uint16_t)word, reinterpret_cast<uint16_t*>(out));
+    } else {
+        const uint32_t r = threadIdx.x & 3u;                   // the lane's 3 bytes start at byte 3 r of the quad's 12
+        const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)word, 0xF9, 0xf, 0xf, false);   // from lane r + 1
+        const uint32_t dword = (word >> (8u * r)) | (next << (24u - 8u * r));
+        if (r < 3u) __builtin_nontemporal_store(dword, reinterpret_cast<uint32_t*>(out + r));
+    }
+}
+
 // Tiles per workgroup (256 threads, every thread one group in every tile, all reads requested
 // first).  The two codebook families want different numbers, measured on MI355X:
 //   * the uniform path costs few instructions per element and runs at the speed of its memory
@@ -434,7 +459,7 @@ __global__ __launch_bounds__(kBlock) void tq_compress_kernel(
             uint32_t word;
             if (!nonuniform) word = encode_group<BITS, TQ_GRID_UNIFORM, false>(x[t], rw[t], 8, alpha, inv_step, no_levels, tab);
             else word = encode_regular<BITS>(x[t], rw[t], pv, cells);
-            store_codes<BITS>(payload + (((gbase + (uint64_t)t * kTile) >> 3) + lane) * (uint64_t)BITS, word);
+            store_codes_wave<BITS, !STREAM>(payload + (((gbase + (uint64_t)t * kTile) >> 3) + lane) * (uint64_t)BITS, word);
         }
         return;
     }

@@ -252,3 +252,27 @@ def test_codebooks_on_both_sides_of_the_mirrored_path(kind, bits, dtype):
     for seed in (3, 77):
         got = device_compress(tens.cuda(), P, bits, seed, 1, 5).cpu().numpy()
         assert (got == O.compress(g_np, P, seed, 1, 5)).all()
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("grid", [B.GRID_UNIFORM, B.GRID_NONUNIFORM])
+def test_batches_too_large_for_the_caches_write_the_same_bytes(bits, grid):
+    """A batch of more than 512 MiB of gradient is stored past the caches, its tensors taken one by one
+    are not: the payloads are the same bytes, and nothing behind them is touched."""
+    d = 70_000_000 + 8 * 1021 + 3
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(bits)
+    gs = [torch.randn(d, generator=gen, device="cuda") for _ in range(2)]
+    stats, ws = B.alloc_stats(d), B.alloc_stats_workspace(d)
+    params = [B.alloc_params(d) for _ in gs]
+    nbytes = B.payload_bytes(d, bits)
+    bufs = [torch.full((nbytes + 256 + (-nbytes) % 16,), 0xA5, dtype=torch.uint8, device="cuda") for _ in range(4)]
+    for g, p in zip(gs, params):
+        B.tq_stats(g, stats, ws)
+        B.tq_params(stats, p, bits, grid)
+    B.tq_compress_multi(gs, params, [b[:nbytes] for b in bufs[:2]], bits, 12, 0, 3, 0, grid)
+    for i in range(2):
+        B.tq_compress(gs[i], params[i], bufs[2 + i][:nbytes], bits, 12, i, 3, 0, grid)
+    for i in range(2):
+        assert torch.equal(bufs[i], bufs[2 + i])
+        assert bool((bufs[i][nbytes:] == 0xA5).all())

@@ -381,6 +381,76 @@ constexpr int compress_tiles(int dtype, bool table_path)
     return dtype == TQ_F32 ? (table_path ? 2 : 1) : (table_path ? 4 : 2);
 }
 
+// The same for segments, whose family the caller does not name: the level table's numbers.  One step of
+// 8 x 124 M with 68 layers, one (two at bf16) / two (four) / three / four (six) tiles: fp32 b = 2 tables 1605 / 1555 /
+// 1566 / 1577 us and 1679 before the mirrored path, b = 3 1866 / 1688 / 1671 / 1663 (1941), bf16 b = 2 1088 / 1013 /
+// 1035 / 1003 (1342); fp32 b = 2 uniform 1497 / 1529 / 1600 / 1586 (1593).
+constexpr int segment_tiles(int dtype) { return dtype == TQ_F32 ? 2 : 4; }
+
+// What a workgroup knows of its record.
+struct Codebook {
+    float alpha, inv_step;
+    bool nonuniform, regular;                                  // the same in the whole workgroup
+    float pv[3];
+};
+
+// Reads the record and, for a level table, fills `cells` (one barrier).  EXPECT_TABLE: a launch shaped for
+// the level-table path reads the codebook before it knows the record's family.
+template <int BITS, bool EXPECT_TABLE>
+__device__ __forceinline__ Codebook set_up_codebook(const tq_params_t* P, CellLds& cells, uint32_t lane)
+{
+    Codebook cb;
+    CellReads reads = {};
+    cb.pv[0] = cb.pv[1] = cb.pv[2] = 0.0f;
+    if constexpr (EXPECT_TABLE) {
+        if (lane < 64) reads = read_cells<BITS>(P, lane);
+        load_pivots<BITS>(P, cb.pv);
+    }
+    cb.alpha = P->alpha;
+    cb.inv_step = P->inv_w[0];
+    cb.nonuniform = P->grid != TQ_GRID_UNIFORM;
+    cb.regular = true;
+    if (cb.nonuniform) {
+        if constexpr (!EXPECT_TABLE) {
+            if (lane < 64) reads = read_cells<BITS>(P, lane);
+            load_pivots<BITS>(P, cb.pv);
+        }
+        if (lane < 64) fill_cells<BITS>(cells, P, reads, lane);
+        // compared from vector registers: with a scalar operand the subtraction runs at 36 T/s, without at 59
+        asm volatile("" : "+v"(cb.pv[0]), "+v"(cb.pv[1]), "+v"(cb.pv[2]));
+        __syncthreads();
+        cb.regular = __builtin_amdgcn_readfirstlane((int)cells.regular) != 0;
+    }
+    return cb;
+}
+
+// The draws of one tile whose first element is ebase: one Philox call per lane; the high counter word
+// stays scalar unless the low word wraps inside the tile.
+__device__ __forceinline__ void draw_tile(uint64_t ebase, uint32_t lane, uint32_t worker, uint32_t step,
+                                          uint32_t seed_lo, uint32_t seed_hi, uint32_t (&rw)[4])
+{
+    const uint64_t qb = ebase >> 3;                            // first group of the tile (uniform)
+    const uint32_t qb_lo = (uint32_t)qb, qb_hi = (uint32_t)(qb >> 32);
+    const uint32_t q_lo = qb_lo + lane;
+    if (qb_lo <= 0xFFFFFFFFu - kBlock) philox4x32_10(q_lo, qb_hi, worker, step, seed_lo, seed_hi, rw);
+    else philox4x32_10(q_lo, qb_hi + (q_lo < qb_lo ? 1u : 0u), worker, step, seed_lo, seed_hi, rw);
+}
+
+// The packed codes of a lane's whole group, uniform or regular codebook.
+template <int BITS>
+__device__ __forceinline__ uint32_t encode_whole(const float (&x)[8], const uint32_t (&rw)[4], const Codebook& cb,
+                                                 const CellLds& cells)
+{
+    if (cb.nonuniform) return encode_regular<BITS>(x, rw, cb.pv, cells);
+    uint32_t word = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const uint32_t r = (j & 1) ? (rw[j >> 1] >> 16) : (rw[j >> 1] & 0xFFFFu);
+        word |= quantize_uniform<BITS>(x[j], (float)r, cb.alpha, cb.inv_step) << (j * BITS);
+    }
+    return word;
+}
+
 template <int DTYPE, int BITS, bool STREAM, int T>
 __global__ __launch_bounds__(kBlock) void tq_compress_kernel(
     const PtrTable g_tab, uint64_t d, uint64_t d_pad, uint64_t bucket_elems,
@@ -404,48 +474,18 @@ __global__ __launch_bounds__(kBlock) void tq_compress_kernel(
     __shared__ LevelLds tab;
     __shared__ CellLds cells;
     const uint32_t lane = threadIdx.x;                         // this thread's group within a tile
-    // a launch shaped for the level-table path reads the codebook before it knows the record's family
-    constexpr bool EXPECT_TABLE = T == compress_tiles(DTYPE, true);
-    CellReads reads = {};
-    float pv[3] = {};
-    if constexpr (EXPECT_TABLE) {
-        if (lane < 64) reads = read_cells<BITS>(P, lane);
-        load_pivots<BITS>(P, pv);
-    }
-    const float alpha = P->alpha;
-    const float inv_step = P->inv_w[0];
-    const bool nonuniform = P->grid != TQ_GRID_UNIFORM;        // uniform over the workgroup
-    bool regular = true;
-    if (nonuniform) {
-        if constexpr (!EXPECT_TABLE) {
-            if (lane < 64) reads = read_cells<BITS>(P, lane);
-            load_pivots<BITS>(P, pv);
-        }
-        if (lane < 64) fill_cells<BITS>(cells, P, reads, lane);
-        // compared from vector registers: with a scalar operand the subtraction runs at 36 T/s, without at 59
-        asm volatile("" : "+v"(pv[0]), "+v"(pv[1]), "+v"(pv[2]));
-        __syncthreads();
-        regular = __builtin_amdgcn_readfirstlane((int)cells.regular) != 0;
-    }
-
-    // One Philox call per lane and tile; the high counter word stays scalar unless the low
-    // word wraps inside the tile.
-    auto draw = [&](uint64_t ebase, uint32_t (&rw)[4]) {
-        const uint64_t qb = ebase >> 3;                        // first group of the tile (uniform)
-        const uint32_t qb_lo = (uint32_t)qb, qb_hi = (uint32_t)(qb >> 32);
-        const uint32_t q_lo = qb_lo + lane;
-        if (qb_lo <= 0xFFFFFFFFu - kBlock) philox4x32_10(q_lo, qb_hi, worker, step, seed_lo, seed_hi, rw);
-        else philox4x32_10(q_lo, qb_hi + (q_lo < qb_lo ? 1u : 0u), worker, step, seed_lo, seed_hi, rw);
-    };
+    const Codebook cb = set_up_codebook<BITS, T == compress_tiles(DTYPE, true)>(P, cells, lane);
+    const float alpha = cb.alpha, inv_step = cb.inv_step;
+    const bool nonuniform = cb.nonuniform;
+    auto draw = [&](uint64_t ebase, uint32_t (&rw)[4]) { draw_tile(ebase, lane, worker, step, seed_lo, seed_hi, rw); };
 
     const uint64_t lim = bend < d ? bend : d;
-    if (regular && gbase + (uint64_t)T * kTile <= lim) {
+    if (cb.regular && gbase + (uint64_t)T * kTile <= lim) {
         // every lane owns a whole group in every tile: all reads first, the draws under them
         // (requesting the reads even earlier, before the codebook is set up, was slower: 708 us
         // against 668 on 8 x 124 M fp32)
         float x[T][8];
         uint32_t rw[T][4];
-        const float no_levels[16] = {};                        // the uniform path reads none
 #pragma unroll
         for (int t = 0; t < T; ++t) load_group<DTYPE, STREAM>(g, gbase + (uint64_t)t * kTile + (uint64_t)lane * kGroup, x[t]);
 #pragma unroll
@@ -456,9 +496,7 @@ __global__ __launch_bounds__(kBlock) void tq_compress_kernel(
 #pragma unroll
         for (int t = 0; t < T; ++t) {
             replace_nan(x[t]);
-            uint32_t word;
-            if (!nonuniform) word = encode_group<BITS, TQ_GRID_UNIFORM, false>(x[t], rw[t], 8, alpha, inv_step, no_levels, tab);
-            else word = encode_regular<BITS>(x[t], rw[t], pv, cells);
+            const uint32_t word = encode_whole<BITS>(x[t], rw[t], cb, cells);
             store_codes_wave<BITS, !STREAM>(payload + (((gbase + (uint64_t)t * kTile) >> 3) + lane) * (uint64_t)BITS, word);
         }
         return;
@@ -504,116 +542,112 @@ __global__ __launch_bounds__(kBlock) void tq_compress_kernel(
 
 // tq_compress_segments: the same client step with one (alpha, codebook) per variable-size
 // segment of the flat gradient (Sec. V: the layers of a network are quantized independently).
-// One tile of 2048 elements per workgroup, wherever the segments fall: the workgroup finds the
-// segment its tile starts in and takes the segments that overlap the tile one after the other
-// (a lane's group of 8 lies in exactly one, the offsets being multiples of 128); large layers
-// are the rule, so almost every workgroup makes one pass.  The last segment also owns the
+// T tiles per workgroup wherever the segments fall.  Large layers are the rule: nearly every workgroup's
+// range lies inside one segment and is encoded like a bucket's.  The others take their tiles one by
+// one, and the segments that overlap a tile one after the other (a lane's group of 8 lies in exactly
+// one, the offsets being multiples of 128).  The last segment also owns the
 // padding up to a multiple of 128 elements.  No access depends on the table being well-formed:
 // the segment index stays inside [0, nseg) and every element access is bounded by d.
-template <int DTYPE, int BITS>
+template <int DTYPE, int BITS, bool STREAM, int T>
 __global__ __launch_bounds__(kBlock) void tq_compress_segments_kernel(
     const PtrTable g_tab, uint64_t d, uint64_t d_pad, const uint64_t* __restrict__ seg_off, uint32_t nseg,
     const SegHints hints, const PtrTable params_tab, uint32_t seed_lo, uint32_t seed_hi, uint32_t first_worker, uint32_t step,
     const MutPtrTable payload_tab, uint64_t payload_bytes)
 {
-    const uint64_t ebase = (uint64_t)linear_block() * kTile;
-    if (ebase >= d_pad) return;                                // padding of a folded grid
+    const uint64_t gbase = (uint64_t)linear_block() * T * kTile;
+    if (gbase >= d_pad) return;                                // padding of a folded grid
     // blockIdx.y = tensor of the batch; its worker id keys the random draws
     const void* __restrict__ g = g_tab.p[blockIdx.y];
     const tq_params_t* __restrict__ params = static_cast<const tq_params_t*>(params_tab.p[blockIdx.y]);
     uint8_t* __restrict__ payload = static_cast<uint8_t*>(payload_tab.p[blockIdx.y]);
     const uint32_t worker = first_worker + blockIdx.y;
-    // positions inside the tile are 32-bit offsets from its first element (which is the same for
-    // the whole workgroup): the tensor's end, the payload's end and the segments' ends as such
     const uint32_t lane = threadIdx.x;
-    const uint32_t rel = lane * kGroup;                                              // this lane's group
-    const uint32_t tile_len = (uint32_t)(ebase + kTile < d_pad ? kTile : d_pad - ebase);   // multiple of 128
-    const uint32_t d_rel = ebase < d ? (uint32_t)(d - ebase < (uint64_t)kTile ? d - ebase : kTile) : 0u;
-    const uint64_t tile_byte = (ebase >> 3) * (uint64_t)BITS;                         // payload offset of the tile
-    const uint32_t pay_rel =                                                          // payload bytes from there on, capped
-        tile_byte < payload_bytes ? (uint32_t)(payload_bytes - tile_byte < (uint64_t)kTile ? payload_bytes - tile_byte : kTile) : 0u;
-    const uint32_t byte_rel = lane * (uint32_t)BITS;
     __shared__ LevelLds tab;
+    __shared__ CellLds cells;
 
-    // The lane's group and its draws depend on its position alone: the values are requested and
-    // the draws computed before the segment is looked up (a chain of dependent scalar loads).
-    const int n_valid = rel >= d_rel ? 0 : (d_rel - rel >= (uint32_t)kGroup ? kGroup : (int)(d_rel - rel));
-    float x[8];
-    if (n_valid == kGroup) {
-        load_group<DTYPE, false>(g, ebase + rel, x);
-    } else {
+    const uint32_t s0 = find_segment(seg_off, nseg, gbase < d ? gbase : d - 1, hints);
+    {
+        // The test uses the very segment ends the loop below would use, so both ways write the same bytes.
+        const uint64_t seg_lo = seg_off[s0];
+        const uint64_t seg_hi = s0 + 1 < nseg ? seg_off[s0 + 1] : d_pad;
+        const uint64_t gend = gbase + (uint64_t)T * kTile;
+        if (seg_lo <= gbase && seg_hi >= gend && gend <= d) {  // whole groups, and their codes lie inside the payload
+            const Codebook cb = set_up_codebook<BITS, true>(params + s0, cells, lane);
+            if (cb.regular) {
+                float x[T][8];
+                uint32_t rw[T][4];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) x[j] = (j < n_valid) ? load_one<DTYPE>(g, ebase + rel + j) : 0.0f;
+                for (int t = 0; t < T; ++t) load_group<DTYPE, STREAM>(g, gbase + (uint64_t)t * kTile + (uint64_t)lane * kGroup, x[t]);
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    draw_tile(gbase + (uint64_t)t * kTile, lane, worker, step, seed_lo, seed_hi, rw[t]);
+                    asm volatile("" : "+v"(rw[t][0]));         // computed here, under the loads
+                }
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    replace_nan(x[t]);
+                    const uint32_t word = encode_whole<BITS>(x[t], rw[t], cb, cells);
+                    store_codes_wave<BITS, !STREAM>(payload + (((gbase + (uint64_t)t * kTile) >> 3) + lane) * (uint64_t)BITS, word);
+                }
+                return;
+            }
+        }
     }
-    uint32_t rw[4];
-    {
-        // one Philox call per lane; the high counter word stays scalar unless the low word wraps inside the tile
-        const uint64_t qb = ebase >> 3;
-        const uint32_t qb_lo = (uint32_t)qb, qb_hi = (uint32_t)(qb >> 32);
-        const uint32_t q_lo = qb_lo + lane;
-        if (qb_lo <= 0xFFFFFFFFu - kBlock) philox4x32_10(q_lo, qb_hi, worker, step, seed_lo, seed_hi, rw);
-        else philox4x32_10(q_lo, qb_hi + (q_lo < qb_lo ? 1u : 0u), worker, step, seed_lo, seed_hi, rw);
-        asm volatile("" : "+v"(rw[0]));                        // computed here, under the loads
-    }
-
-    uint32_t s = find_segment(seg_off, nseg, ebase < d ? ebase : d - 1, hints);
-    replace_nan(x);
-    {
-        // Nearly every tile lies inside one segment, with all its groups whole and its codes inside
-        // the payload: straight-line code, as for a bucket.  The test uses the very segment ends
-        // the loop below would use, so both ways write the same bytes.
-        const uint64_t seg_lo = seg_off[s];
-        const uint64_t seg_hi = s + 1 < nseg ? seg_off[s + 1] : d_pad;
-        if (seg_lo <= ebase && seg_hi >= ebase + kTile && d_rel == (uint32_t)kTile &&
-            pay_rel >= (uint32_t)kBlock * (uint32_t)BITS) {
+    for (int t = 0; t < T; ++t) {
+        const uint64_t ebase = gbase + (uint64_t)t * kTile;
+        if (ebase >= d_pad) break;
+        // positions inside the tile are 32-bit offsets from its first element (which is the same for
+        // the whole workgroup): the tensor's end, the payload's end and the segments' ends as such
+        const uint32_t rel = lane * kGroup;                                              // this lane's group
+        const uint32_t tile_len = (uint32_t)(ebase + kTile < d_pad ? kTile : d_pad - ebase);   // multiple of 128
+        const uint32_t d_rel = ebase < d ? (uint32_t)(d - ebase < (uint64_t)kTile ? d - ebase : kTile) : 0u;
+        const uint64_t tile_byte = (ebase >> 3) * (uint64_t)BITS;                         // payload offset of the tile
+        const uint32_t pay_rel =                                                          // payload bytes from there on, capped
+            tile_byte < payload_bytes ? (uint32_t)(payload_bytes - tile_byte < (uint64_t)kTile ? payload_bytes - tile_byte : kTile) : 0u;
+        const uint32_t byte_rel = lane * (uint32_t)BITS;
+        const int n_valid = rel >= d_rel ? 0 : (d_rel - rel >= (uint32_t)kGroup ? kGroup : (int)(d_rel - rel));
+        float x[8];
+        if (n_valid == kGroup) {
+            load_group<DTYPE, false>(g, ebase + rel, x);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x[j] = (j < n_valid) ? load_one<DTYPE>(g, ebase + rel + j) : 0.0f;
+        }
+        uint32_t rw[4];
+        draw_tile(ebase, lane, worker, step, seed_lo, seed_hi, rw);
+        uint32_t s = t == 0 ? s0 : find_segment(seg_off, nseg, ebase < d ? ebase : d - 1, hints);
+        replace_nan(x);
+        for (;;) {
+            const uint64_t seg_lo = seg_off[s];
+            const uint64_t seg_hi = s + 1 < nseg ? seg_off[s + 1] : d_pad;
+            // the part of the tile that belongs to this segment, as offsets from the tile's start
+            const uint32_t lo_rel = (uint32_t)(seg_lo > ebase ? (seg_lo - ebase < (uint64_t)tile_len ? seg_lo - ebase : tile_len) : 0);
+            const uint32_t hi_rel = (uint32_t)(seg_hi > ebase ? (seg_hi - ebase < (uint64_t)tile_len ? seg_hi - ebase : tile_len) : 0);
             const tq_params_t* P = params + s;
+            float lv[16];
             const float alpha = P->alpha;
             const float inv_step = P->inv_w[0];
-            float lv[16];
-            uint32_t word;
-            if (P->grid != TQ_GRID_UNIFORM) {                  // uniform over the workgroup
+            const bool nonuniform = P->grid != TQ_GRID_UNIFORM;    // uniform over the workgroup
+            if (nonuniform) {
+                __syncthreads();                               // the table of the segment before is done with
                 fill_level_lds(tab, P, (1u << BITS) - 1u);
-#pragma unroll
-                for (int j = 0; j < 16; ++j) lv[j] = P->level[j];
+    #pragma unroll
+                for (int j = 0; j < 16; ++j) lv[j] = P->level[j];   // wave-uniform: scalar loads
                 __syncthreads();
-                word = encode_group<BITS, TQ_GRID_NONUNIFORM, false>(x, rw, 8, alpha, inv_step, lv, tab);
-            } else {
-                word = encode_group<BITS, TQ_GRID_UNIFORM, false>(x, rw, 8, alpha, inv_step, lv, tab);
             }
-            store_codes<BITS>(payload + tile_byte + byte_rel, word);
-            return;
+            if (rel >= lo_rel && rel < hi_rel && byte_rel < pay_rel) {
+                uint32_t word = 0;                                 // a group wholly in the padding encodes as 0
+                if (n_valid == kGroup)
+                    word = nonuniform ? encode_group<BITS, TQ_GRID_NONUNIFORM, false>(x, rw, 8, alpha, inv_step, lv, tab)
+                                      : encode_group<BITS, TQ_GRID_UNIFORM, false>(x, rw, 8, alpha, inv_step, lv, tab);
+                else if (n_valid > 0)
+                    word = nonuniform ? encode_group<BITS, TQ_GRID_NONUNIFORM, true>(x, rw, n_valid, alpha, inv_step, lv, tab)
+                                      : encode_group<BITS, TQ_GRID_UNIFORM, true>(x, rw, n_valid, alpha, inv_step, lv, tab);
+                store_codes<BITS>(payload + tile_byte + byte_rel, word, (uint64_t)(pay_rel - byte_rel));
+            }
+            if (hi_rel >= tile_len || s + 1 >= nseg) break;
+            ++s;
         }
-    }
-    for (;;) {
-        const uint64_t seg_lo = seg_off[s];
-        const uint64_t seg_hi = s + 1 < nseg ? seg_off[s + 1] : d_pad;
-        // the part of the tile that belongs to this segment, as offsets from the tile's start
-        const uint32_t lo_rel = (uint32_t)(seg_lo > ebase ? (seg_lo - ebase < (uint64_t)tile_len ? seg_lo - ebase : tile_len) : 0);
-        const uint32_t hi_rel = (uint32_t)(seg_hi > ebase ? (seg_hi - ebase < (uint64_t)tile_len ? seg_hi - ebase : tile_len) : 0);
-        const tq_params_t* P = params + s;
-        float lv[16];
-        const float alpha = P->alpha;
-        const float inv_step = P->inv_w[0];
-        const bool nonuniform = P->grid != TQ_GRID_UNIFORM;    // uniform over the workgroup
-        if (nonuniform) {
-            fill_level_lds(tab, P, (1u << BITS) - 1u);
-#pragma unroll
-            for (int j = 0; j < 16; ++j) lv[j] = P->level[j];   // wave-uniform: scalar loads
-            __syncthreads();
-        }
-        if (rel >= lo_rel && rel < hi_rel && byte_rel < pay_rel) {
-            uint32_t word = 0;                                 // a group wholly in the padding encodes as 0
-            if (n_valid == kGroup)
-                word = nonuniform ? encode_group<BITS, TQ_GRID_NONUNIFORM, false>(x, rw, 8, alpha, inv_step, lv, tab)
-                                  : encode_group<BITS, TQ_GRID_UNIFORM, false>(x, rw, 8, alpha, inv_step, lv, tab);
-            else if (n_valid > 0)
-                word = nonuniform ? encode_group<BITS, TQ_GRID_NONUNIFORM, true>(x, rw, n_valid, alpha, inv_step, lv, tab)
-                                  : encode_group<BITS, TQ_GRID_UNIFORM, true>(x, rw, n_valid, alpha, inv_step, lv, tab);
-            store_codes<BITS>(payload + tile_byte + byte_rel, word, (uint64_t)(pay_rel - byte_rel));
-        }
-        if (hi_rel >= tile_len || s + 1 >= nseg) break;
-        ++s;
-        __syncthreads();                                       // before the next segment's table replaces this one
     }
 }
 
@@ -690,6 +724,13 @@ __global__ __launch_bounds__(kBlock) void tq_simulate_kernel(
 
 namespace {
 
+// Non-temporal loads while the batch can still be (partly) cached from the statistics pass: up to twice the
+// 256 MiB of the memory-side cache.  Above that, non-temporal stores (see store_codes_wave).
+bool compress_streams(int count, uint64_t d, int dtype)
+{
+    return (uint64_t)count * d * (dtype == TQ_F32 ? 4u : 2u) <= (512ull << 20);
+}
+
 template <int DTYPE, bool STREAM, int T>
 hipError_t launch(int bits, dim3 blocks, hipStream_t st, const tq::PtrTable& g, uint64_t d, uint64_t d_pad,
                   uint64_t be, uint32_t tpb, const tq::PtrTable& params, uint64_t seed, uint32_t first_worker,
@@ -737,9 +778,7 @@ hipError_t tq_launch_compress(const void* const* g, int count, int dtype, uint64
     tq::PtrTable gt{}, pt{};
     tq::MutPtrTable yt{};
     for (int i = 0; i < count; ++i) { gt.p[i] = g[i]; pt.p[i] = params[i]; yt.p[i] = payload[i]; }
-    // non-temporal loads while the batch can still be (partly) cached from the statistics pass:
-    // up to twice the 256 MiB of the memory-side cache
-    const bool stream = (uint64_t)count * d * (dtype == TQ_F32 ? 4u : 2u) <= (512ull << 20);
+    const bool stream = compress_streams(count, d, dtype);
 #define TQ_LAUNCH_COMPRESS(DT, ST, TP) \
     launch<DT, ST, tq::compress_tiles(DT, TP)>(bits, blocks, st, gt, d, d_pad, be, (uint32_t)tpb, pt, seed, \
                                                first_worker, step, yt, pbytes)
@@ -792,7 +831,8 @@ hipError_t tq_launch_compress_segments(const void* const* g, int count, int dtyp
                                        uint32_t first_worker, uint32_t step, void* const* payload, hipStream_t st)
 {
     const uint64_t d_pad = (d + 127) / 128 * 128;
-    const uint64_t nblocks = (d_pad + tq::kTile - 1) / tq::kTile;
+    const uint64_t range = (uint64_t)tq::segment_tiles(dtype) * tq::kTile;        // elements per workgroup
+    const uint64_t nblocks = (d_pad + range - 1) / range;
     dim3 blocks;
     if (count < 1 || count > tq::kMaxBatch || nseg > 0xFFFFFFFFull ||
         !tq::fold_grid(nblocks, tq::kBlock, (unsigned)count, blocks))
@@ -804,17 +844,20 @@ hipError_t tq_launch_compress_segments(const void* const* g, int count, int dtyp
     const uint64_t pbytes = tq_payload_bytes(d, bits);
     const dim3 threads(tq::kBlock);
     const tq::SegHints hints = tq::make_seg_hints(seg_host, nseg, d);
-#define TQ_LAUNCH_CSEG(DT, B)                                                                                   \
-    hipLaunchKernelGGL((tq::tq_compress_segments_kernel<DT, B>), blocks, threads, 0, st, gt, d, d_pad, seg_off, \
-                       (uint32_t)nseg, hints, pt, slo, shi, first_worker, step, yt, pbytes)
-#define TQ_LAUNCH_CSEG_B(DT)                      \
-    switch (bits) {                               \
-        case 2: TQ_LAUNCH_CSEG(DT, 2); break;     \
-        case 3: TQ_LAUNCH_CSEG(DT, 3); break;     \
-        default: TQ_LAUNCH_CSEG(DT, 4); break;    \
+    const bool stream = compress_streams(count, d, dtype);
+#define TQ_LAUNCH_CSEG(DT, B, ST)                                                                               \
+    hipLaunchKernelGGL((tq::tq_compress_segments_kernel<DT, B, ST, tq::segment_tiles(DT)>), blocks, threads, 0, st, gt, d, \
+                       d_pad, seg_off, (uint32_t)nseg, hints, pt, slo, shi, first_worker, step, yt, pbytes)
+#define TQ_LAUNCH_CSEG_ST(DT, B) if (stream) TQ_LAUNCH_CSEG(DT, B, true); else TQ_LAUNCH_CSEG(DT, B, false)
+#define TQ_LAUNCH_CSEG_B(DT)                         \
+    switch (bits) {                                  \
+        case 2: TQ_LAUNCH_CSEG_ST(DT, 2); break;     \
+        case 3: TQ_LAUNCH_CSEG_ST(DT, 3); break;     \
+        default: TQ_LAUNCH_CSEG_ST(DT, 4); break;    \
     }
     if (dtype == TQ_F32) { TQ_LAUNCH_CSEG_B(TQ_F32) } else { TQ_LAUNCH_CSEG_B(TQ_BF16) }
 #undef TQ_LAUNCH_CSEG_B
+#undef TQ_LAUNCH_CSEG_ST
 #undef TQ_LAUNCH_CSEG
     return hipGetLastError();
 }

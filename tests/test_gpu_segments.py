@@ -162,3 +162,36 @@ def test_more_workers_than_the_fast_decode_takes():
     gs = [small_gradient("cfg3", i, seg.d) for i in range(N)]
     device = run_segments_batched([g[0] for g in gs], seg, bits, B.GRID_NONUNIFORM, 1e-5, seed=11, step=4)
     check_against_oracle([g[1] for g in gs], seg, bits, B.GRID_NONUNIFORM, 1e-5, device, 11, 4)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("bits", [2, 3, 4])
+def test_segment_ends_next_to_workgroup_ranges_and_mixed_codebooks(bits, dtype):
+    """Compression takes ranges of 4096 (fp32) or 8192 (bf16) elements: segments that end on a range's
+    end, 128 elements before and behind it and on a tile inside it, of uniform codebooks, mirrored tables
+    and tables that do not mirror, side by side; the payload equal to the oracle's."""
+    ends = [128, 2048, 4096, 8192 - 128, 16384, 16384 + 128, 24576, 24576 + 2048, 32768 + 128, 49152, 57344 + 40]
+    seg = B.Segments(np.array([0] + ends, dtype=np.uint64))
+    s, d = (1 << bits) - 1, ends[-1]
+    rng = np.random.default_rng(bits)
+    P = np.zeros(seg.nseg, dtype=O.PARAMS_DTYPE)
+    for k in range(seg.nseg):
+        alpha = np.float32(0.5 + k)
+        t = 2.0 * np.arange(s + 1) / s - 1.0
+        kind = k % 3
+        lv = (alpha * (t if kind == 0 else np.sign(t) * np.abs(t) ** 1.6)).astype(np.float32)
+        if kind == 2:
+            lv[1:s] += np.float32(0.07) * alpha / s
+        lv[0], lv[s] = -alpha, alpha
+        P["alpha"][k], P["bits"][k], P["s"][k] = alpha, bits, s
+        P["grid"][k] = O.GRID_UNIFORM if kind == 0 else O.GRID_NONUNIFORM
+        P["level"][k, : s + 1] = lv
+        if kind == 0:
+            P["inv_w"][k] = np.float32(s / (2.0 * float(alpha)))
+        else:
+            P["inv_w"][k, :s] = (1.0 / np.diff(lv.astype(np.float64))).astype(np.float32)
+    g = torch.from_numpy((rng.standard_normal(d) * 3.0).astype(np.float32)).to(dtype)
+    g_np = g.view(torch.int16).numpy().view("uint16") if dtype == torch.bfloat16 else g.numpy()
+    pay = B.alloc_payload(d, bits).fill_(0xA5)
+    B.tq_compress_segments(g.cuda(), seg, B.params_from_numpy(P), pay, bits, 9, 2, 4)
+    assert (pay.cpu().numpy() == O.compress_segments(g_np, seg.host, P, 9, 2, 4)).all()

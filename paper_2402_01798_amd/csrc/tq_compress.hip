@@ -653,69 +653,100 @@ __global__ __launch_bounds__(kBlock) void tq_compress_segments_kernel(
 
 // tq_quantize_dequantize: out[e] = Q[T_alpha(g[e])] as the server would reconstruct it from
 // this worker's message (the level of the code tq_compress_kernel would have written: same
-// draws, same arithmetic), without the round trip through a payload.  One tile per workgroup.
-template <int DTYPE, int BITS, bool ACC>
+// draws, same arithmetic), without the round trip through a payload.  T tiles per workgroup, the
+// encoding of the compress kernel, and the decode kernel's whole-line stores, past the caches if the
+// output is large (PAST_CACHES; never when accumulating).  Bound by its memory traffic and, at 25 M elements, by
+// filling and draining the chip.  One / two / four tiles at bf16, 25.6 M elements at b = 3: 30.6 / 30.0 / 32.1 us
+// (32.2 with half-line stores, compares and one tile); fp32 one / two / three 37.2 / 38.5 / 39.9 (38.2);
+// 124 M bf16 136.5 -> 121.
+constexpr int simulate_tiles(int dtype) { return dtype == TQ_F32 ? 1 : 2; }
+
+template <int DTYPE, int BITS, bool ACC, bool PAST_CACHES, int T>
 __global__ __launch_bounds__(kBlock) void tq_simulate_kernel(
-    const void* __restrict__ g, uint64_t d, uint64_t d_pad, uint64_t bucket_elems, uint32_t tiles_per_bucket,
+    const void* __restrict__ g, uint64_t d, uint64_t d_pad, uint64_t bucket_elems, uint32_t groups_per_bucket,
     const tq_params_t* __restrict__ params, uint32_t seed_lo, uint32_t seed_hi, uint32_t worker, uint32_t step,
     float* __restrict__ out)
 {
     constexpr uint32_t S = (1u << BITS) - 1u;
-    const TileGeom t = tile_geom(linear_block(), d_pad, bucket_elems, tiles_per_bucket);
-    const uint64_t bend = t.eend < d ? t.eend : d;
-    if (t.ebase >= bend) return;
-    const tq_params_t* P = params + t.bucket;
+    const uint32_t blk = linear_block();
+    const uint32_t bucket = blk / groups_per_bucket;
+    const uint32_t grp = blk - bucket * groups_per_bucket;
+    const uint64_t bstart = (uint64_t)bucket * bucket_elems;
+    uint64_t bend = bstart + bucket_elems < d_pad ? bstart + bucket_elems : d_pad;
+    bend = bend < d ? bend : d;
+    const uint64_t gbase = bstart + (uint64_t)grp * T * kTile;
+    if (gbase >= bend) return;
+    const tq_params_t* P = params + bucket;
 
-    __shared__ LevelLds tab;                                   // levels for the look-up of both families
-    float lv[16];
-    const float alpha = P->alpha;
-    const float inv_step = P->inv_w[0];
-    const bool nonuniform = P->grid != TQ_GRID_UNIFORM;        // uniform over the workgroup
-    fill_level_lds(tab, P, S);
-#pragma unroll
-    for (int j = 0; j < 16; ++j) lv[j] = P->level[j];           // wave-uniform: scalar loads
-    __syncthreads();
+    __shared__ LevelLds tab;                                   // the general path's table
+    __shared__ CellLds cells;
+    __shared__ float levels[16];                               // what a code stands for
+    __shared__ float4 xbuf[kBlock / 64][128];                  // store8_wave's exchange buffers
+    const uint32_t lane = threadIdx.x;
+    if (lane >= 64 && lane < 80) levels[lane - 64] = P->level[lane - 64];
+    const Codebook cb = set_up_codebook<BITS, true>(P, cells, lane);
+    if (!cb.nonuniform) __syncthreads();                       // a level table has had its barrier
 
-    const uint64_t e0 = t.ebase + (uint64_t)threadIdx.x * kGroup;
-    if (e0 >= bend) return;
-    const int n_valid = bend - e0 >= (uint64_t)kGroup ? kGroup : (int)(bend - e0);
-    float x[8];
-    if (n_valid == kGroup) {
-        load_group<DTYPE, false>(g, e0, x);
-    } else {
+    if (cb.regular && gbase + (uint64_t)T * kTile <= bend) {   // whole groups in every tile
+        float x[T][8];
+        uint32_t rw[T][4];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) x[j] = (j < n_valid) ? load_one<DTYPE>(g, e0 + j) : 0.0f;
-    }
-    const uint64_t q = e0 >> 3;
-    uint32_t rw[4];
-    philox4x32_10((uint32_t)q, (uint32_t)(q >> 32), worker, step, seed_lo, seed_hi, rw);
-    replace_nan(x);
-    float y[8];
+        for (int t = 0; t < T; ++t) load_group<DTYPE, false>(g, gbase + (uint64_t)t * kTile + (uint64_t)lane * kGroup, x[t]);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const uint32_t r = (j & 1) ? (rw[j >> 1] >> 16) : (rw[j >> 1] & 0xFFFFu);
-        const uint32_t code = nonuniform ? quantize<BITS, TQ_GRID_NONUNIFORM>(x[j], (float)r, alpha, inv_step, lv, tab)
-                                         : quantize<BITS, TQ_GRID_UNIFORM>(x[j], (float)r, alpha, inv_step, lv, tab);
-        y[j] = tab.e[code & S].x;
-    }
-    float* o = out + e0;
-    if (n_valid == kGroup) {
-        float4* o4 = reinterpret_cast<float4*>(o);
-        float4 a = make_float4(y[0], y[1], y[2], y[3]), b = make_float4(y[4], y[5], y[6], y[7]);
-        if constexpr (ACC) {
-            const float4 pa = o4[0], pb = o4[1];
-            a.x = pa.x + a.x; a.y = pa.y + a.y; a.z = pa.z + a.z; a.w = pa.w + a.w;
-            b.x = pb.x + b.x; b.y = pb.y + b.y; b.z = pb.z + b.z; b.w = pb.w + b.w;
+        for (int t = 0; t < T; ++t) {
+            draw_tile(gbase + (uint64_t)t * kTile, lane, worker, step, seed_lo, seed_hi, rw[t]);
+            asm volatile("" : "+v"(rw[t][0]));                 // computed here, under the loads
         }
-        o4[0] = a;
-        o4[1] = b;
-    } else {
-#pragma clang loop unroll(disable)
-        for (int j = 0; j < n_valid; ++j) {
-            float v = y[0];
 #pragma unroll
-            for (int k = 1; k < 8; ++k) v = (j == k) ? y[k] : v;
-            o[j] = ACC ? o[j] + v : v;
+        for (int t = 0; t < T; ++t) {
+            const uint64_t e0 = gbase + (uint64_t)t * kTile + (uint64_t)lane * kGroup;
+            replace_nan(x[t]);
+            const uint32_t word = encode_whole<BITS>(x[t], rw[t], cb, cells);
+            float y[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) y[j] = levels[(word >> (j * BITS)) & S];
+            if constexpr (ACC) {
+                const float4* o4 = reinterpret_cast<const float4*>(out + e0);
+                const float4 pa = o4[0], pb = o4[1];
+                y[0] = pa.x + y[0]; y[1] = pa.y + y[1]; y[2] = pa.z + y[2]; y[3] = pa.w + y[3];
+                y[4] = pb.x + y[4]; y[5] = pb.y + y[5]; y[6] = pb.z + y[6]; y[7] = pb.w + y[7];
+            }
+            store8_wave<PAST_CACHES>(out + e0 - (uint64_t)(lane & 63u) * kGroup, (int)(lane & 63u), y, xbuf[lane >> 6]);
+        }
+        return;
+    }
+
+    // the last workgroup of a bucket, and codebooks that are not regular: tile by tile
+    float lv[16];
+    if (cb.nonuniform) {
+        fill_level_lds(tab, P, S);
+#pragma unroll
+        for (int j = 0; j < 16; ++j) lv[j] = P->level[j];       // wave-uniform: scalar loads
+        __syncthreads();
+    }
+    for (int t = 0; t < T; ++t) {
+        const uint64_t ebase = gbase + (uint64_t)t * kTile;
+        const uint64_t e0 = ebase + (uint64_t)lane * kGroup;
+        if (e0 >= bend) continue;
+        const int n_valid = bend - e0 >= (uint64_t)kGroup ? kGroup : (int)(bend - e0);
+        float x[8];
+        if (n_valid == kGroup) {
+            load_group<DTYPE, false>(g, e0, x);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x[j] = (j < n_valid) ? load_one<DTYPE>(g, e0 + j) : 0.0f;
+        }
+        uint32_t rw[4];
+        draw_tile(ebase, lane, worker, step, seed_lo, seed_hi, rw);
+        replace_nan(x);
+        float* o = out + e0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint32_t r = (j & 1) ? (rw[j >> 1] >> 16) : (rw[j >> 1] & 0xFFFFu);
+            const uint32_t code = cb.nonuniform ? quantize<BITS, TQ_GRID_NONUNIFORM>(x[j], (float)r, cb.alpha, cb.inv_step, lv, tab)
+                                                : quantize<BITS, TQ_GRID_UNIFORM>(x[j], (float)r, cb.alpha, cb.inv_step, lv, tab);
+            const float y = levels[code & S];
+            if (j < n_valid) o[j] = ACC ? o[j] + y : y;
         }
     }
 }
@@ -797,20 +828,22 @@ hipError_t tq_launch_simulate(const void* g, int dtype, uint64_t d, uint64_t buc
     const uint64_t d_pad = (d + 127) / 128 * 128;
     const uint64_t be = bucket_elems ? bucket_elems : d_pad;
     const uint64_t nb = (d_pad + be - 1) / be;
-    const uint64_t tpb = (be + tq::kTile - 1) / tq::kTile;
+    const uint64_t tt = (uint64_t)tq::simulate_tiles(dtype);
+    const uint64_t tpb = ((be + tq::kTile - 1) / tq::kTile + tt - 1) / tt;    // workgroups per bucket
     const uint64_t nblocks = nb * tpb;
     dim3 blocks;
     if (!tq::fold_grid(nblocks, tq::kBlock, 1, blocks)) return hipErrorInvalidValue;
     const uint32_t slo = (uint32_t)seed, shi = (uint32_t)(seed >> 32);
     const dim3 threads(tq::kBlock);
-#define TQ_LAUNCH_SIM(DT, B)                                                                                      \
-    do {                                                                                                          \
-        if (accumulate)                                                                                           \
-            hipLaunchKernelGGL((tq::tq_simulate_kernel<DT, B, true>), blocks, threads, 0, st, g, d, d_pad, be,    \
-                               (uint32_t)tpb, params, slo, shi, worker, step, out);                               \
-        else                                                                                                      \
-            hipLaunchKernelGGL((tq::tq_simulate_kernel<DT, B, false>), blocks, threads, 0, st, g, d, d_pad, be,   \
-                               (uint32_t)tpb, params, slo, shi, worker, step, out);                               \
+    const bool past = !accumulate && tq::output_past_caches(d * sizeof(float));
+#define TQ_LAUNCH_SIM_AS(DT, B, ACC, PAST)                                                                         \
+    hipLaunchKernelGGL((tq::tq_simulate_kernel<DT, B, ACC, PAST, tq::simulate_tiles(DT)>), blocks, threads, 0, st, g, d, \
+                       d_pad, be, (uint32_t)tpb, params, slo, shi, worker, step, out)
+#define TQ_LAUNCH_SIM(DT, B)                                                   \
+    do {                                                                       \
+        if (accumulate) TQ_LAUNCH_SIM_AS(DT, B, true, false);                  \
+        else if (past) TQ_LAUNCH_SIM_AS(DT, B, false, true);                   \
+        else TQ_LAUNCH_SIM_AS(DT, B, false, false);                            \
     } while (0)
 #define TQ_LAUNCH_SIM_B(DT)                      \
     switch (bits) {                              \
@@ -821,6 +854,7 @@ hipError_t tq_launch_simulate(const void* g, int dtype, uint64_t d, uint64_t buc
     if (dtype == TQ_F32) { TQ_LAUNCH_SIM_B(TQ_F32) } else { TQ_LAUNCH_SIM_B(TQ_BF16) }
 #undef TQ_LAUNCH_SIM_B
 #undef TQ_LAUNCH_SIM
+#undef TQ_LAUNCH_SIM_AS
     return hipGetLastError();
 }
 

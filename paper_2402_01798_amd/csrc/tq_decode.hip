@@ -86,8 +86,6 @@ __device__ __forceinline__ void load8(const float* p, float (&x)[8])
     x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
 }
 
-typedef float float4_native __attribute__((ext_vector_type(4)));
-
 // STREAM: stored with the non-temporal hint.  Used for a plain aggregate small enough to stay
 // in the memory-side cache: written normally it stays behind as dirty lines, and their
 // write-back then competes with the next kernel's reads (12 us on the statistics launch that
@@ -117,28 +115,6 @@ __device__ __forceinline__ void finish_group(float* o, uint64_t e0, float (&acc)
     for (int j = 0; j < 8; ++j) acc[j] = finish<MODE>(acc[j], prev[j], vel[j], up);
     store8<MODE == kStoreStream>(o, acc);
     if constexpr (MODE == kSgdMomentum) store8<false>(up.velocity + e0, vel);
-}
-
-// The same 32 bytes per lane, stored by a WHOLE wavefront (every lane owns a group; `o` is lane
-// 0's address).  Stored directly, each of the wavefront's two 16-byte store instructions would
-// touch every line of its 2 KiB half-way; exchanged through LDS, lane l stores the l-th and the
-// (64 + l)-th 16 bytes, so that each store instruction writes 1 KiB in one piece (measured: the
-// aggregate of 8 x 124 M elements 139 us -> 118 us, of 8 x 11.2 M 20.8 -> 15.6 us).  `wb` is the
-// wavefront's own 2 KiB of LDS; a wavefront's LDS operations complete in order, so no barrier.
-template <bool STREAM>
-__device__ __forceinline__ void store8_wave(float* o, int lane, const float (&x)[8], float4* wb)
-{
-    wb[2 * lane] = make_float4(x[0], x[1], x[2], x[3]);
-    wb[2 * lane + 1] = make_float4(x[4], x[5], x[6], x[7]);
-    const float4 a = wb[lane], b = wb[64 + lane];
-    if constexpr (STREAM) {
-        float4_native an = {a.x, a.y, a.z, a.w}, bn = {b.x, b.y, b.z, b.w};
-        __builtin_nontemporal_store(an, reinterpret_cast<float4_native*>(o) + lane);
-        __builtin_nontemporal_store(bn, reinterpret_cast<float4_native*>(o) + 64 + lane);
-    } else {
-        reinterpret_cast<float4*>(o)[lane] = a;
-        reinterpret_cast<float4*>(o)[64 + lane] = b;
-    }
 }
 
 template <int MODE>

@@ -89,6 +89,38 @@ inline bool fold_grid(uint64_t nblocks, unsigned threads, unsigned count, dim3& 
     return true;
 }
 
+// Whether an fp32 output of so many bytes is stored past the caches (non-temporally).  Above half the
+// 256 MiB of the memory-side cache little of it would be found there by whoever reads it next, and
+// written back late it costs more than written out at once.  Average of N payloads alone, and with a
+// reader of the output behind it, us: 80 M elements (N = 4) 72 -> 58.5 and 239.5 -> 232, 50 M 53 -> 42.5 and
+// 159 -> 154, but 25.6 M (N = 8) 46 -> 34 and 90 -> 96.5: that reader paid for it.  Whole wavefronts
+// storing whole lines only (store8_wave): half lines written this way cost up to 1.8 times.
+inline bool output_past_caches(uint64_t bytes) { return bytes > (128ull << 20); }
+
+typedef float float4_native __attribute__((ext_vector_type(4)));
+
+// 32 bytes per lane, stored by a WHOLE wavefront (every lane owns a group; `o` is lane
+// 0's address).  Stored directly, each of the wavefront's two 16-byte store instructions would
+// touch every line of its 2 KiB half-way; exchanged through LDS, lane l stores the l-th and the
+// (64 + l)-th 16 bytes, so that each store instruction writes 1 KiB in one piece (measured: the
+// aggregate of 8 x 124 M elements 139 us -> 118 us, of 8 x 11.2 M 20.8 -> 15.6 us).  `wb` is the
+// wavefront's own 2 KiB of LDS; a wavefront's LDS operations complete in order, so no barrier.
+template <bool STREAM>
+__device__ __forceinline__ void store8_wave(float* o, int lane, const float (&x)[8], float4* wb)
+{
+    wb[2 * lane] = make_float4(x[0], x[1], x[2], x[3]);
+    wb[2 * lane + 1] = make_float4(x[4], x[5], x[6], x[7]);
+    const float4 a = wb[lane], b = wb[64 + lane];
+    if constexpr (STREAM) {
+        float4_native an = {a.x, a.y, a.z, a.w}, bn = {b.x, b.y, b.z, b.w};
+        __builtin_nontemporal_store(an, reinterpret_cast<float4_native*>(o) + lane);
+        __builtin_nontemporal_store(bn, reinterpret_cast<float4_native*>(o) + 64 + lane);
+    } else {
+        reinterpret_cast<float4*>(o)[lane] = a;
+        reinterpret_cast<float4*>(o)[64 + lane] = b;
+    }
+}
+
 // Tile geometry shared by compress and decode.  Workgroup `blk` owns elements
 // [ebase, ebase + kTile) of bucket `bucket`, cut at `eend` (the bucket's end, the last
 // bucket's end being d rounded up to a multiple of 128 so the payload padding is covered).

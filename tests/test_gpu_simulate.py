@@ -47,3 +47,26 @@ def test_bf16_and_special_values():
     assert (got == want).all()
     a = float(P["alpha"][0])
     assert got[7] == np.float32(a) and got[4999] == np.float32(-a)          # +-Inf -> +-alpha
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("d,bucket", [(2047, 0), (2048, 0), (4096, 0), (4097, 0), (8192 + 2048 + 9, 0), (5 * 4096, 4096),
+                                      (33_554_432 + 4096 + 11, 1 << 20)])
+def test_ranges_of_whole_and_cut_tiles_and_large_outputs(dtype, d, bucket):
+    """Workgroup ranges that are whole, cut inside a tile or between two tiles, and an output just above
+    128 MiB (stored past the caches): the values of the compress -> decode round trip, nothing behind them."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d)
+    g = torch.randn(d, generator=gen, device="cuda").to(dtype)
+    stats, params = B.alloc_stats(d, bucket), B.alloc_params(d, bucket)
+    B.tq_stats(g, stats, B.alloc_stats_workspace(d, bucket), bucket)
+    for grid in (B.GRID_UNIFORM, B.GRID_NONUNIFORM):
+        B.tq_params(stats, params, 3, grid)
+        out = torch.full((d + 64,), 7.0, device="cuda")
+        B.tq_quantize_dequantize(g, params, out[:d], 3, 21, 4, 2, bucket)
+        pay, rt = B.alloc_payload(d, 3), torch.empty(d, device="cuda")
+        B.tq_compress(g, params, pay, 3, 21, 4, 2, bucket, grid)
+        B.tq_decompress_aggregate([pay], [params], rt, 3, bucket)
+        assert torch.equal(out[:d], rt) and bool((out[d:] == 7.0).all())
+        B.tq_quantize_dequantize(g, params, out[:d], 3, 21, 4, 2, bucket, accumulate=True)
+        assert torch.equal(out[:d], rt + rt) and bool((out[d:] == 7.0).all())

@@ -443,6 +443,14 @@ __global__ __launch_bounds__(kBlock) void tq_decode_segments_kernel(
 
 namespace {
 
+// A plain aggregate is streamed past the caches when it is small (see store8) or, where whole lines are
+// stored (tq_decode_fast_kernel), too large for them.
+bool streams_output(uint64_t d, int N, int bits)
+{
+    const bool fast = N <= 16 && !(bits == 4 && N > 8);
+    return d * sizeof(float) <= (64ull << 20) || (fast && tq::output_past_caches(d * sizeof(float)));
+}
+
 struct DecodeGeom {
     tq::DecodeArgs args;
     int N, weighted, bits;
@@ -538,8 +546,7 @@ hipError_t tq_launch_decode(const void* const* payload, const tq_params_t* const
     g.tpb = (g.be + tq::kTile - 1) / tq::kTile;                        // tiles per bucket
     g.pbytes = tq_payload_bytes(d, bits);
     const tq::Update up{eta, momentum, weight_decay, velocity};
-    // outputs up to 64 MiB are streamed past the caches (see store8)
-    if (mode == tq::kStore && d * sizeof(float) <= (64ull << 20)) mode = tq::kStoreStream;
+    if (mode == tq::kStore && streams_output(d, N, bits)) mode = tq::kStoreStream;
     switch (mode) {
         case tq::kStore: return launch_mode<tq::kStore>(g, out, up, st);
         case tq::kStoreStream: return launch_mode<tq::kStoreStream>(g, out, up, st);
@@ -583,8 +590,11 @@ hipError_t tq_launch_decode_segments(const void* const* payload, const tq_params
 #define TQ_LAUNCH_FSEG(B, UU, M)                                                                                  \
     hipLaunchKernelGGL((tq::tq_decode_fast_kernel<B, UU, T, M, true>), fblocks, threads, 0, st, args, N, weighted, \
                        scale, d, d_pad, (uint64_t)0, 0u, pbytes, out, up, seg_off, (uint32_t)nseg, hints)
-#define TQ_LAUNCH_FSEG_M(B, UU) \
-    if (accumulate) TQ_LAUNCH_FSEG(B, UU, tq::kAccumulate); else TQ_LAUNCH_FSEG(B, UU, tq::kStore)
+        const bool stream = streams_output(d, N, bits);
+#define TQ_LAUNCH_FSEG_M(B, UU)                               \
+    if (accumulate) TQ_LAUNCH_FSEG(B, UU, tq::kAccumulate);   \
+    else if (stream) TQ_LAUNCH_FSEG(B, UU, tq::kStoreStream); \
+    else TQ_LAUNCH_FSEG(B, UU, tq::kStore)
 #define TQ_LAUNCH_FSEG_U(B)                          \
     switch (U) {                                     \
         case 1: TQ_LAUNCH_FSEG_M(B, 1); break;       \

@@ -113,3 +113,26 @@ def test_round_trip_is_unbiased_for_the_truncated_gradient():
     err = out.cpu().numpy().astype(np.float64) - np.clip(g_np, -alpha, alpha)
     assert np.abs(err).max() < 6 * width / 2 / np.sqrt(N)
     assert abs(err.mean()) < 4 * width / 2 / np.sqrt(N * d)
+
+
+@pytest.mark.parametrize("d", [33_554_432 - 8, 33_554_432 + 4096 + 3])
+def test_outputs_on_both_sides_of_the_cache_limit(d):
+    """Averages of just under and just over 128 MiB (the larger one is stored past the caches): equal to
+    the average taken in two halves, nothing written behind it; bucketed and segment calls."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1)
+    cut = 1 << 24
+    P = oracle_params(np.linspace(-1, 1, 4096, dtype=np.float32) ** 3, 2, B.GRID_NONUNIFORM)
+    params = [B.params_from_numpy(P)] * 4
+    pays = [torch.randint(0, 256, (B.payload_bytes(d, 2),), generator=gen, device="cuda", dtype=torch.uint8) for _ in params]
+    out = torch.full((d + 64,), 3.0, device="cuda")
+    B.tq_decompress_aggregate(pays, params, out[:d], 2)
+    halves = torch.empty(d, device="cuda")
+    B.tq_decompress_aggregate([p[: cut // 4] for p in pays], params, halves[:cut], 2)
+    B.tq_decompress_aggregate([p[cut // 4:] for p in pays], params, halves[cut:], 2)
+    assert torch.equal(out[:d], halves) and bool((out[d:] == 3.0).all())
+    seg = B.Segments(np.array([0, 4096 + 128, cut, d], dtype=np.uint64))
+    three = [torch.cat([p, p, p]) for p in params]
+    out.fill_(3.0)
+    B.tq_decompress_aggregate_segments(pays, three, seg, out[:d], 2)
+    assert torch.equal(out[:d], halves) and bool((out[d:] == 3.0).all())

@@ -10,8 +10,7 @@
 //                            indexed by TWO adjacent codes (2^(2b) entries of float2), so one
 //                            8-byte LDS read serves two elements; a single memory round trip
 //                            per workgroup.
-//   tq_decode_kernel         the general path (any N up to 64 at any b): one 4-byte LDS read
-//                            per code from the plain 16-entry tables.
+//   tq_decode_many_kernel    any N up to 64 at any b: the workers taken eight at a time.
 #include <type_traits>
 
 #include "tq_device.h"
@@ -348,44 +347,120 @@ __global__ __launch_bounds__(kBlock) void tq_decode_fast_kernel(
     }
 }
 
-template <int BITS, int MODE>
-__global__ __launch_bounds__(kBlock) void tq_decode_kernel(
-    const DecodeArgs args, int N, int weighted, float scale, uint64_t d, uint64_t d_pad,
-    uint64_t bucket_elems, uint32_t tiles_per_bucket, uint64_t payload_bytes, float* __restrict__ out,
-    const Update up)
+// More workers than the fast kernel holds code words and pair tables for (N > 16, N > 8 at b = 4), up to
+// U.  The tables of all workers are built once per workgroup -- pair entries at b = 2; at b = 3 and 4, where
+// pairs take 512 B or 2 KiB a worker and their random rows meet in the banks, the plain levels, which lie
+// in banks of their own -- and the workers are taken eight at a time, straight-line: the next eight's
+// code words are on their way while the current ones are looked up, and every table address is a
+// constant beside the masked code.  Sums in worker order.
+// Bound by the rate of LDS reads (one per four clocks and compute unit, 4 bytes wide as well as 8).  11.2 M
+// elements, N = 32, before (a loop over the workers, a load and eight look-ups each) -> now: b = 4 57.2 -> 44.7 us,
+// b = 3 56.1 -> 45.4 (50.6 with pairs), b = 2 46.3 -> 28.7; N = 64 106 -> 79.5, N = 12 at b = 4 21.6 -> 20.8.
+template <int BITS, int U, int T, int MODE>
+__global__ __launch_bounds__(kBlock) void tq_decode_many_kernel(
+    const DecodeArgs args, int N, int weighted, float scale, uint64_t d, uint64_t d_pad, uint64_t bucket_elems,
+    uint32_t groups_per_bucket, uint64_t payload_bytes, float* __restrict__ out, const Update up)
 {
-    constexpr uint32_t MASK = (1u << BITS) - 1u;
-    const TileGeom t = tile_geom(linear_block(), d_pad, bucket_elems, tiles_per_bucket);
-    if (t.ebase >= t.eend) return;
+    constexpr int C = 8;                                       // workers at a time
+    constexpr bool PAIR = BITS == 2;
+    constexpr int ENTRIES = PAIR ? 16 : 1 << BITS;             // of 8 or 4 bytes
+    constexpr int ROW = ENTRIES * (PAIR ? 8 : 4);              // bytes of a worker's table
+    constexpr int CMASK = (1 << BITS) - 1;
+    __shared__ __align__(16) char table[U * ROW];
+    __shared__ float4 xbuf[kBlock / 64][128];                  // store8_wave's exchange buffers
 
-    __shared__ float table[TQ_MAX_WORKERS * 16];
-    fill_level_rows(table, args, N, weighted, t.bucket);
+    const uint32_t blk = linear_block();
+    const uint32_t bucket = blk / groups_per_bucket;
+    const uint32_t grp = blk - bucket * groups_per_bucket;
+    const uint64_t bstart = (uint64_t)bucket * bucket_elems;
+    uint64_t bend = bstart + bucket_elems < d_pad ? bstart + bucket_elems : d_pad;
+    bend = bend < d ? bend : d;
+    const uint64_t gstart = bstart + (uint64_t)grp * T * kTile;
+    if (gstart >= bend) return;
+
+    // this lane's group in each tile; lanes past the end read group 0 (always present)
+    uint64_t e0[T];
+    CodeLoad cl[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        e0[t] = gstart + (uint64_t)t * kTile + (uint64_t)threadIdx.x * kGroup;
+        cl[t] = code_load(e0[t] < bend ? e0[t] >> 3 : 0, BITS, payload_bytes);
+    }
+    // past the last worker its words again (looked up in tables of zeros)
+    auto request = [&](uint32_t (&w)[T][C], int c) {
+#pragma unroll
+        for (int u = 0; u < C; ++u) {
+            const uint8_t* stream = args.payload[c + u < N ? c + u : N - 1];
+#pragma unroll
+            for (int t = 0; t < T; ++t) w[t][u] = load_code_word<BITS>(stream, cl[t]);
+        }
+    };
+    uint32_t w[2][T][C];
+    request(w[0], 0);
+    float prev[T][8], vel[T][8], acc[T][8];
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) { prev[t][j] = 0.0f; vel[t][j] = 0.0f; acc[t][j] = 0.0f; }
+        if (e0[t] + kGroup <= bend) {
+            if constexpr (MODE != kStore && MODE != kStoreStream) load8(out + e0[t], prev[t]);
+            if constexpr (MODE == kSgdMomentum) load8(up.velocity + e0[t], vel[t]);
+        }
+    }
+    for (int idx = threadIdx.x; idx < U * ENTRIES; idx += kBlock) {
+        const int i = idx / ENTRIES, e = idx % ENTRIES;
+        float lo = 0.0f, hi = 0.0f;
+        if (i < N) {
+            const float* level = args.params[i][bucket].level;
+            const float wsel = weighted ? args.weight[i] : 1.0f;   // x * 1.0f is exact
+            lo = wsel * level[e & CMASK];
+            if constexpr (PAIR) hi = wsel * level[e >> BITS];
+        }
+        if constexpr (PAIR) reinterpret_cast<float2*>(table)[idx] = make_float2(lo, hi);
+        else reinterpret_cast<float*>(table)[idx] = lo;
+    }
     __syncthreads();
 
-    const uint64_t e0 = t.ebase + (uint64_t)threadIdx.x * kGroup;
-    if (e0 >= t.eend || e0 >= d) return;
-    const CodeLoad cl = code_load(e0 >> 3, BITS, payload_bytes);
-
-    const bool whole = e0 + kGroup <= d;
-    float acc[8], prev[8], vel[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) { acc[j] = 0.0f; prev[j] = 0.0f; vel[j] = 0.0f; }
-    if (whole) {
-        if constexpr (MODE != kStore && MODE != kStoreStream) load8(out + e0, prev);
-        if constexpr (MODE == kSgdMomentum) load8(up.velocity + e0, vel);
-    }
-    for (int i = 0; i < N; ++i) {
-        const uint32_t w = load_code_word<BITS>(args.payload[i], cl) >> cl.first_bit;
-        const float* row = table + i * 16;
+    for (int c = 0; c < U; c += C) {
+        if (c >= N) break;                                     // the same for every lane
+        if (c + C < U) request(w[(c / C + 1) & 1], c + C);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] = acc[j] + row[(w >> (j * BITS)) & MASK];
-    }
-    if (!weighted) {
+        for (int t = 0; t < T; ++t)
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] = acc[j] * scale;
+            for (int u = 0; u < C; ++u) {
+                const uint32_t word = w[(c / C) & 1][t][u];
+                const uint32_t codes = BITS == 3 ? word >> cl[t].first_bit : word;
+                const char* row = table + (c + u) * ROW;
+                // the byte offset of an entry is the code (or two) in place, shifted and masked
+                if constexpr (PAIR) {
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) {
+                        const uint32_t off = (m == 0 ? codes << 3 : codes >> (2 * BITS * m - 3)) & (uint32_t)(ROW - 8);
+                        const float2 v = *reinterpret_cast<const float2*>(row + off);
+                        acc[t][2 * m] = acc[t][2 * m] + v.x;
+                        acc[t][2 * m + 1] = acc[t][2 * m + 1] + v.y;
+                    }
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const uint32_t off = (j == 0 ? codes << 2 : codes >> (BITS * j - 2)) & (uint32_t)(ROW - 4);
+                        acc[t][j] = acc[t][j] + *reinterpret_cast<const float*>(row + off);
+                    }
+                }
+            }
     }
-    if (whole) finish_group<MODE>(out + e0, e0, acc, prev, vel, up);
-    else finish_ragged<MODE>(out + e0, e0, acc, (int)(d - e0), up);
+    const float post = weighted ? 1.0f : scale;                // x * 1.0f is exact
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const bool whole = gstart + (uint64_t)T * kTile <= bend;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[t][j] = acc[t][j] * post;
+        if (whole) finish_group_wave<MODE>(out, e0[t], lane, acc[t], prev[t], vel[t], up, xbuf[wave]);
+        else if (e0[t] + kGroup <= bend) finish_group<MODE>(out + e0[t], e0[t], acc[t], prev[t], vel[t], up);
+        else if (e0[t] < bend) finish_ragged<MODE>(out + e0[t], e0[t], acc[t], (int)(bend - e0[t]), up);
+    }
 }
 
 // tq_decompress_aggregate_segments: the server step with one codebook per variable-size
@@ -443,12 +518,10 @@ __global__ __launch_bounds__(kBlock) void tq_decode_segments_kernel(
 
 namespace {
 
-// A plain aggregate is streamed past the caches when it is small (see store8) or, where whole lines are
-// stored (tq_decode_fast_kernel), too large for them.
-bool streams_output(uint64_t d, int N, int bits)
+// A plain aggregate is streamed past the caches when it is small (see store8) or too large for them.
+bool streams_output(uint64_t d)
 {
-    const bool fast = N <= 16 && !(bits == 4 && N > 8);
-    return d * sizeof(float) <= (64ull << 20) || (fast && tq::output_past_caches(d * sizeof(float)));
+    return d * sizeof(float) <= (64ull << 20) || tq::output_past_caches(d * sizeof(float));
 }
 
 struct DecodeGeom {
@@ -504,18 +577,24 @@ hipError_t launch_mode(const DecodeGeom& g, float* out, const tq::Update& up, hi
         return hipGetLastError();
     }
 
-    const uint64_t nblocks = g.nb * g.tpb;
+    // two tiles per workgroup; one / two on 11.2 M elements, N = 32: b = 4 45.5 / 44.7 us, b = 2 29.6 / 28.7
+    constexpr int T = 2;
+    const uint64_t gpb = (g.tpb + T - 1) / T;
     dim3 blocks;
-    if (!tq::fold_grid(nblocks, tq::kBlock, 1, blocks)) return hipErrorInvalidValue;
-#define TQ_LAUNCH_GENERAL(B)                                                                                 \
-    hipLaunchKernelGGL((tq::tq_decode_kernel<B, MODE>), blocks, threads, 0, st, g.args, N, g.weighted,       \
-                       g.scale, g.d, g.d_pad, g.be, (uint32_t)g.tpb, g.pbytes, out, up)
+    if (!tq::fold_grid(g.nb * gpb, tq::kBlock, 1, blocks)) return hipErrorInvalidValue;
+#define TQ_LAUNCH_MANY(B, UU)                                                                                  \
+    hipLaunchKernelGGL((tq::tq_decode_many_kernel<B, UU, T, MODE>), blocks, threads, 0, st, g.args, N, g.weighted, \
+                       g.scale, g.d, g.d_pad, g.be, (uint32_t)gpb, g.pbytes, out, up)
     switch (g.bits) {
-        case 2: TQ_LAUNCH_GENERAL(2); break;
-        case 3: TQ_LAUNCH_GENERAL(3); break;
-        default: TQ_LAUNCH_GENERAL(4); break;
+        case 2: if (N <= 32) TQ_LAUNCH_MANY(2, 32); else TQ_LAUNCH_MANY(2, 64); break;
+        case 3: if (N <= 32) TQ_LAUNCH_MANY(3, 32); else TQ_LAUNCH_MANY(3, 64); break;
+        default:
+            if (N <= 16) TQ_LAUNCH_MANY(4, 16);
+            else if (N <= 32) TQ_LAUNCH_MANY(4, 32);
+            else TQ_LAUNCH_MANY(4, 64);
+            break;
     }
-#undef TQ_LAUNCH_GENERAL
+#undef TQ_LAUNCH_MANY
     return hipGetLastError();
 }
 
@@ -546,7 +625,7 @@ hipError_t tq_launch_decode(const void* const* payload, const tq_params_t* const
     g.tpb = (g.be + tq::kTile - 1) / tq::kTile;                        // tiles per bucket
     g.pbytes = tq_payload_bytes(d, bits);
     const tq::Update up{eta, momentum, weight_decay, velocity};
-    if (mode == tq::kStore && streams_output(d, N, bits)) mode = tq::kStoreStream;
+    if (mode == tq::kStore && streams_output(d)) mode = tq::kStoreStream;
     switch (mode) {
         case tq::kStore: return launch_mode<tq::kStore>(g, out, up, st);
         case tq::kStoreStream: return launch_mode<tq::kStoreStream>(g, out, up, st);
@@ -590,7 +669,7 @@ hipError_t tq_launch_decode_segments(const void* const* payload, const tq_params
 #define TQ_LAUNCH_FSEG(B, UU, M)                                                                                  \
     hipLaunchKernelGGL((tq::tq_decode_fast_kernel<B, UU, T, M, true>), fblocks, threads, 0, st, args, N, weighted, \
                        scale, d, d_pad, (uint64_t)0, 0u, pbytes, out, up, seg_off, (uint32_t)nseg, hints)
-        const bool stream = streams_output(d, N, bits);
+        const bool stream = streams_output(d);
 #define TQ_LAUNCH_FSEG_M(B, UU)                               \
     if (accumulate) TQ_LAUNCH_FSEG(B, UU, tq::kAccumulate);   \
     else if (stream) TQ_LAUNCH_FSEG(B, UU, tq::kStoreStream); \

@@ -136,3 +136,32 @@ def test_outputs_on_both_sides_of_the_cache_limit(d):
     out.fill_(3.0)
     B.tq_decompress_aggregate_segments(pays, three, seg, out[:d], 2)
     assert torch.equal(out[:d], halves) and bool((out[d:] == 3.0).all())
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("N", [9, 16, 17, 24, 32, 33, 64])
+@pytest.mark.parametrize("d", [5, 2048, 4096, 4097, 3 * 4096 + 2048 + 11])
+def test_many_workers_in_batches_of_eight(bits, N, d):
+    """Numbers of workers around the batches and table sizes of the kernel for many of them, ranges that
+    are whole, cut and ragged, with and without weights, bucketed and not: bit for bit the oracle's."""
+    rng = np.random.default_rng(N * 100 + bits)
+    bucket = 4096 if d > 4097 else 0
+    nb = B.num_buckets(d, bucket)
+    pays, recs = [], []
+    for i in range(N):
+        P = np.zeros(nb, dtype=O.PARAMS_DTYPE)
+        s = (1 << bits) - 1
+        P["alpha"], P["bits"], P["s"], P["grid"] = 1.0, bits, s, O.GRID_NONUNIFORM
+        P["level"][:, : s + 1] = np.sort(rng.standard_normal((nb, s + 1)).astype(np.float32), axis=1)
+        recs.append(P)
+        pay = np.zeros(B.payload_bytes(d, bits), dtype=np.uint8)
+        used = (d * bits + 7) // 8
+        pay[:used] = rng.integers(0, 256, used)
+        pays.append(pay)
+    pays_dev = [torch.from_numpy(p).cuda() for p in pays]
+    recs_dev = [B.params_from_numpy(P) for P in recs]
+    for w in (None, [float(x) for x in np.float32(rng.uniform(0.01, 0.1, N))]):
+        out = torch.full((d + 64,), 3.0, device="cuda")
+        B.tq_decompress_aggregate(pays_dev, recs_dev, out[:d], bits, bucket, w)
+        want = O.decompress_aggregate(pays, recs, d, bits, bucket_elems=bucket, weights=w)
+        assert (out[:d].cpu().numpy() == want).all() and bool((out[d:] == 3.0).all())

@@ -101,17 +101,24 @@ TQ_HD uint32_t find_segment(const uint64_t* __restrict__ seg_off, uint32_t nseg,
     return lo;
 }
 
+// a / b.  A 64-bit division is 150 instructions of one serial chain on the device; nearly every
+// quotient taken here has operands below 2^32 and takes the 32-bit one.
+TQ_HD uint64_t quotient(uint64_t a, uint64_t b)
+{
+    return ((a | b) >> 32) == 0 ? (uint64_t)((uint32_t)a / (uint32_t)b) : a / b;
+}
+
 // Equal shares of a batch counted in tiles (the statistics kernels): share w of `groups` is the
 // tiles [share_start(w), share_start(w + 1)) of `total_tiles`.
 TQ_HD uint64_t share_start(uint64_t w, uint64_t total_tiles, uint32_t groups)
 {
-    return w * total_tiles / groups;
+    return quotient(w * total_tiles, groups);
 }
 
 // The share that holds a tile: the largest w with share_start(w) <= tile.
 TQ_HD uint32_t share_of_tile(uint64_t tile, uint64_t total_tiles, uint32_t groups)
 {
-    return (uint32_t)(((tile + 1) * groups - 1) / total_tiles);
+    return (uint32_t)quotient((tile + 1) * groups - 1, total_tiles);
 }
 
 }  // namespace tq

@@ -62,22 +62,57 @@ __host__ __device__ inline uint64_t stats_ws_hist_words(uint64_t nb, uint32_t sl
     return nb * TQ_NBINS * (uint64_t)slices;
 }
 
+// Reductions over a wavefront by moves inside the vector unit (a shift within rows of 16 lanes, then the
+// rows' last lanes passed on), the total read from lane 63: 6 steps of a few clocks each, where a
+// shuffle through LDS takes about a hundred.  Lanes without a source see 0, the identity of both.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+}
+
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned long long dpp_or_zero(unsigned long long v)
+{
+    return (unsigned long long)dpp_or_zero<CTRL, ROWS>((uint32_t)v) |
+           (unsigned long long)dpp_or_zero<CTRL, ROWS>((uint32_t)(v >> 32)) << 32;
+}
+
+__device__ __forceinline__ uint32_t from_lane63(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, 63); }
+
+__device__ __forceinline__ unsigned long long from_lane63(unsigned long long v)
+{
+    return (unsigned long long)from_lane63((uint32_t)v) | (unsigned long long)from_lane63((uint32_t)(v >> 32)) << 32;
+}
+
+// Called with the whole wavefront active; every lane gets the result.
 template <typename T>
 __device__ __forceinline__ T wave_reduce_add(T v)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    v += dpp_or_zero<0x111, 0xF>(v);                                   // row_shr:1
+    v += dpp_or_zero<0x112, 0xF>(v);
+    v += dpp_or_zero<0x114, 0xF>(v);
+    v += dpp_or_zero<0x118, 0xF>(v);
+    v += dpp_or_zero<0x142, 0xA>(v);                                   // row_bcast:15 into rows 1 and 3
+    v += dpp_or_zero<0x143, 0xC>(v);                                   // row_bcast:31 into rows 2 and 3
+    return from_lane63(v);
+}
+
+__device__ __forceinline__ long long wave_reduce_add(long long v)
+{
+    return (long long)wave_reduce_add((unsigned long long)v);
 }
 
 __device__ __forceinline__ uint32_t wave_reduce_max(uint32_t v)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const uint32_t o = __shfl_xor(v, off, 64);
-        v = o > v ? o : v;
-    }
-    return v;
+    auto take = [&](uint32_t o) { v = o > v ? o : v; };
+    take(dpp_or_zero<0x111, 0xF>(v));
+    take(dpp_or_zero<0x112, 0xF>(v));
+    take(dpp_or_zero<0x114, 0xF>(v));
+    take(dpp_or_zero<0x118, 0xF>(v));
+    take(dpp_or_zero<0x142, 0xA>(v));
+    take(dpp_or_zero<0x143, 0xC>(v));
+    return from_lane63(v);
 }
 
 // One lane's group of 8 consecutive elements as it is loaded (32 bytes of fp32, 16 of bf16), and
@@ -516,13 +551,13 @@ __global__ __launch_bounds__(kStatsBlock) void tq_stats_balanced_kernel(
     __shared__ StatsLds L;
     bool first = true;
     while (tile < tile_end) {                                          // one pass per tensor the share touches
-        const uint64_t t = tile / tiles_per_tensor, i = tile - t * tiles_per_tensor;
+        const uint64_t t = quotient(tile, tiles_per_tensor), i = tile - t * tiles_per_tensor;
         const uint64_t i_end = i + (tile_end - tile) < tiles_per_tensor ? i + (tile_end - tile) : tiles_per_tensor;
         const uint64_t e0 = i * kStatsTile;
         const uint64_t e1 = i_end * kStatsTile < d ? i_end * kStatsTile : d;
         const void* __restrict__ g = g_tab.p[t];
         tq_stats_t* __restrict__ stats = static_cast<tq_stats_t*>(stats_tab.p[t]);
-        for (uint64_t b = e0 / be; b * be < e1; ++b) {
+        for (uint64_t b = quotient(e0, be); b * be < e1; ++b) {
             const uint64_t lo = b * be, hi = lo + be < d ? lo + be : d;
             const uint64_t cs = e0 > lo ? e0 : lo, ce = e1 < hi ? e1 : hi;
             const bool whole = cs == lo && ce == hi;                   // no other share has a piece of this bucket
@@ -553,12 +588,12 @@ __device__ __forceinline__ SplitBucket split_bucket(uint64_t unit, uint32_t by_b
     SplitBucket k{0, 0, 0, 0, 0, false};
     if (by_boundary) {
         const uint64_t tile = share_start(unit + 1, total_tiles, groups);
-        k.t = tile / tiles_per_tensor;
+        k.t = quotient(tile, tiles_per_tensor);
         const uint64_t e = (tile - k.t * tiles_per_tensor) * kStatsTile;
-        k.b = e / be;
+        k.b = quotient(e, be);
         if (e == k.b * be) return k;                                   // the shares meet where a bucket (or tensor) begins
     } else {
-        k.t = unit / nb;
+        k.t = quotient(unit, nb);
         k.b = unit - k.t * nb;
     }
     const uint64_t lo = k.b * be, hi = lo + be < d ? lo + be : d;
@@ -574,7 +609,7 @@ __device__ __forceinline__ SplitBucket split_bucket(uint64_t unit, uint32_t by_b
 }
 
 // The same for buckets of a few rows each (at most kNarrowRows): one small workgroup per unit.
-constexpr int kNarrowBlock = 256;
+constexpr int kNarrowBlock = 512;
 constexpr uint32_t kNarrowRows = 8;
 __global__ __launch_bounds__(kNarrowBlock) void tq_stats_balanced_reduce_narrow_kernel(
     uint64_t d, uint64_t be, uint64_t nb, uint64_t tiles_per_tensor, uint64_t total_tiles, uint32_t groups,
@@ -586,22 +621,37 @@ __global__ __launch_bounds__(kNarrowBlock) void tq_stats_balanced_reduce_narrow_
     const SplitBucket k = split_bucket(unit, by_boundary, d, be, nb, tiles_per_tensor, total_tiles, groups);
     if (!k.any) return;
     tq_stats_t* __restrict__ S = static_cast<tq_stats_t*>(stats_tab.p[k.t]) + k.b;
-    for (int bin = threadIdx.x; bin < TQ_NBINS; bin += kNarrowBlock) {
-        uint32_t total = 0u;
-        for (uint32_t r = 0; r < k.rows; ++r) total += ws_hist[(k.row0 + r) * TQ_NBINS + bin];
-        S->hist[bin] = total;
+    // the rows past the bucket's last are that one again, not added: every load is on its way at once
+    const uint32_t last = k.rows - 1u;
+    constexpr int kPasses = (TQ_NBINS + kNarrowBlock - 1) / kNarrowBlock;
+    uint32_t v[kPasses][kNarrowRows];
+#pragma unroll
+    for (int i = 0; i < kPasses; ++i) {
+        const int bin = (int)threadIdx.x + i * kNarrowBlock;
+#pragma unroll
+        for (uint32_t r = 0; r < kNarrowRows; ++r)
+            v[i][r] = ws_hist[(k.row0 + (r < last ? r : last)) * TQ_NBINS + (bin < TQ_NBINS ? bin : 0)];
     }
-    if (threadIdx.x == 0) {
-        StatsExtra x{0u, 0u, 0ull, 0ll, 0ull};
-        for (uint32_t r = 0; r < k.rows; ++r) {
-            const StatsExtra y = ws_extra[k.row0 + r];
-            x.absmax_bits = y.absmax_bits > x.absmax_bits ? y.absmax_bits : x.absmax_bits;
-            x.n_nonfinite += y.n_nonfinite;
-            x.n_tail += y.n_tail;
-            x.exp_sum += y.exp_sum;
-            x.log2m_fix += y.log2m_fix;
+    if (threadIdx.x < 64) {                                            // a lane per row
+        const StatsExtra y = ws_extra[k.row0 + (threadIdx.x < last ? threadIdx.x : last)];
+        const bool mine = threadIdx.x <= last;
+        const uint32_t amax = wave_reduce_max(mine ? y.absmax_bits : 0u);
+        const uint32_t nonfinite = wave_reduce_add(mine ? y.n_nonfinite : 0u);
+        const unsigned long long n_tail = wave_reduce_add(mine ? y.n_tail : 0ull);
+        const long long exp_sum = wave_reduce_add(mine ? y.exp_sum : 0ll);
+        const unsigned long long log2m_fix = wave_reduce_add(mine ? y.log2m_fix : 0ull);
+        if (threadIdx.x == 0) {
+            const StatsExtra x{amax, nonfinite, n_tail, exp_sum, log2m_fix};
+            write_scalars(S, x, k.n, g_min);
         }
-        write_scalars(S, x, k.n, g_min);
+    }
+#pragma unroll
+    for (int i = 0; i < kPasses; ++i) {
+        const int bin = (int)threadIdx.x + i * kNarrowBlock;
+        uint32_t total = 0u;
+#pragma unroll
+        for (uint32_t r = 0; r < kNarrowRows; ++r) total += r <= last ? v[i][r] : 0u;
+        if (bin < TQ_NBINS) S->hist[bin] = total;
     }
 }
 
@@ -645,7 +695,7 @@ __global__ __launch_bounds__(kStatsBlock) void tq_stats_segments_partial_kernel(
     __shared__ StatsLds L;
     bool first = true;
     while (tile < tile_end) {                                          // one pass per tensor the share touches
-        const uint64_t t = tile / tiles_per_tensor, i = tile - t * tiles_per_tensor;
+        const uint64_t t = quotient(tile, tiles_per_tensor), i = tile - t * tiles_per_tensor;
         const uint64_t i_end = i + (tile_end - tile) < tiles_per_tensor ? i + (tile_end - tile) : tiles_per_tensor;
         const uint64_t cstart = i * kStatsTile;
         const uint64_t cend = i_end * kStatsTile < d ? i_end * kStatsTile : d;

@@ -798,9 +798,15 @@ hipError_t tq_launch_compress(const void* const* g, int count, int dtype, uint64
     const uint64_t d_pad = (d + 127) / 128 * 128;
     const uint64_t be = bucket_elems ? bucket_elems : d_pad;
     const uint64_t nb = (d_pad + be - 1) / be;
-    const bool table_path = grid != TQ_GRID_UNIFORM;
+    bool table_path = grid != TQ_GRID_UNIFORM;
+    const uint64_t tiles = (be + tq::kTile - 1) / tq::kTile;                  // of a bucket
+    // A launch that is resident at once in the smaller shape (2048 workgroups, eight per compute unit) waits for
+    // latencies alone and takes it for tables too.  1.2 M elements: bf16 6.7 -> 5.7 us, fp32 at b = 2 5.1 ->
+    // 4.2; 5 M bf16 8.9 -> 8.1, but 5 M fp32 8.0 -> 8.2 and 10 M 12.0 -> 12.6 (2048 fp32 workgroups are 4.2 M).
+    const uint64_t all_tiles = nb * tiles * (uint64_t)(count < 1 ? 1 : count);
+    if (all_tiles <= 2048ull * (uint64_t)tq::compress_tiles(dtype, false)) table_path = false;
     const uint64_t tt = (uint64_t)tq::compress_tiles(dtype, table_path);
-    const uint64_t tpb = ((be + tq::kTile - 1) / tq::kTile + tt - 1) / tt;    // workgroups per bucket
+    const uint64_t tpb = (tiles + tt - 1) / tt;                               // workgroups per bucket
     const uint64_t nblocks = nb * tpb;
     dim3 blocks;
     if (count < 1 || count > tq::kMaxBatch || !tq::fold_grid(nblocks, tq::kBlock, (unsigned)count, blocks))

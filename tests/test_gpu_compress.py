@@ -244,14 +244,14 @@ def test_codebooks_on_both_sides_of_the_mirrored_path(kind, bits, dtype):
     near = np.concatenate([(ends.view(np.int32) + k).view(np.float32) for k in (-40, -3, -2, -1, 0, 1, 2, 3, 40)])
     mid = np.concatenate([(lv[1:] + lv[:-1]) / 2, [0.0, -0.0, 1.0, -1.0, np.inf, -np.inf, np.nan]]).astype(np.float32)
     values = np.concatenate([near, mid])
-    d = 40 * 8192 + 333
+    d = 1050 * 8192 + 333                                        # the launch shape of large tensors, ...
     g = values[rng.integers(0, values.size, d)]
     g[::5] = rng.uniform(-1.1, 1.1, g[::5].size).astype(np.float32) * lv[-1]
     tens = torch.from_numpy(g).to(dtype)
     g_np = tens.view(torch.int16).numpy().view("uint16") if dtype == torch.bfloat16 else tens.numpy()
-    for seed in (3, 77):
-        got = device_compress(tens.cuda(), P, bits, seed, 1, 5).cpu().numpy()
-        assert (got == O.compress(g_np, P, seed, 1, 5)).all()
+    for seed, n in ((3, d), (77, 40 * 8192 + 333)):                # ... and of small ones
+        got = device_compress(tens[:n].cuda(), P, bits, seed, 1, 5).cpu().numpy()
+        assert (got == O.compress(g_np[:n], P, seed, 1, 5, threads=16)).all()
 
 
 @pytest.mark.parametrize("bits", [2, 3, 4])
@@ -276,3 +276,30 @@ def test_batches_too_large_for_the_caches_write_the_same_bytes(bits, grid):
     for i in range(2):
         assert torch.equal(bufs[i], bufs[2 + i])
         assert bool((bufs[i][nbytes:] == 0xA5).all())
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("cut", [0, 1, 2047, 2048 + 9, 3 * 2048 - 40, 4 * 2048 - 8])
+def test_both_shapes_of_the_table_launch_write_the_same_bytes(cut, bits, dtype):
+    """Small launches of level tables take fewer tiles per workgroup than large ones: a batch large enough
+    for the second shape against its tensors taken one by one, with every kind of range at the end."""
+    n, d = 64, 68 * 2048 - cut
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(cut + bits)
+    gs = [torch.randn(d, generator=gen, device="cuda").to(dtype) for _ in range(n)]
+    stats, params = B.alloc_stats(d), [B.alloc_params(d) for _ in gs]
+    ws = B.alloc_stats_workspace(d)
+    for g, p in zip(gs, params):
+        B.tq_stats(g, stats, ws)
+        B.tq_params(stats, p, bits, B.GRID_NONUNIFORM)
+    nbytes = B.payload_bytes(d, bits)
+    many = [torch.full((nbytes + 64,), 0xA5, dtype=torch.uint8, device="cuda") for _ in gs]
+    B.tq_compress_multi(gs, params, [y[:nbytes] for y in many], bits, 12, 0, 3, 0, B.GRID_NONUNIFORM)
+    for i in range(n):
+        one = torch.full((nbytes + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+        B.tq_compress(gs[i], params[i], one[:nbytes], bits, 12, i, 3, 0, B.GRID_NONUNIFORM)
+        assert torch.equal(one, many[i])
+    want = O.compress(gs[1].view(torch.int16).cpu().numpy().view("uint16") if dtype == torch.bfloat16 else gs[1].cpu().numpy(),
+                      B.params_to_numpy(params[1]).view(O.PARAMS_DTYPE), 12, 1, 3)
+    assert (many[1][:nbytes].cpu().numpy() == want).all()

@@ -365,14 +365,13 @@ __device__ __forceinline__ void store_codes_wave(uint8_t* out, uint32_t word)
 
 // Tiles per workgroup (256 threads, every thread one group in every tile, all reads requested
 // first).  The two codebook families want different numbers, measured on MI355X:
-//   * the uniform path costs few instructions per element and runs at the speed of its memory
-//     traffic when the running wavefronts together cover a small window of the gradient: on
-//     8 x 124 M fp32, 670 us with one tile per workgroup against 745 us with two, whether the
-//     two are requested together, one after the other, adjacent or far apart;
-//   * the level-table path costs twice the instructions, and a wavefront that holds only one
-//     group has nothing in flight while it computes: with two tiles 8 x 124 M fp32 at b = 2 take
-//     718 us instead of 785, 16 x 25.6 M at b = 3 307 instead of 346, and 4 x 10^9 bf16 with four
-//     tiles (a bf16 tile is half the bytes) 1790 instead of 2440.
+//   * the uniform path runs at the speed of its memory traffic when the running wavefronts together
+//     cover a small window of the gradient: on 8 x 124 M fp32, 670 us (641 with the payload stored past the
+//     caches) with one tile per workgroup against 745 us with two, whether the two are requested
+//     together, one after the other, adjacent or far apart;
+//   * the level-table path sets up its codebook before the first read, once per workgroup: with one / two /
+//     four tiles 16 x 25.6 M fp32 at b = 3 take 370 / 323 / 325 us, with two / four / six 4 x 10^9 bf16 at
+//     b = 2 (a bf16 tile is half the bytes) 1970 / 1775 / 1819.
 // The family is a property of the parameter records, which live on the device, so the host
 // chooses by the family the caller names (tq_compress's `grid`); the kernel itself reads every
 // bucket's record and computes what the record says, whatever shape it was launched in.

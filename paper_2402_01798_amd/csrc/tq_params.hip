@@ -447,7 +447,8 @@ __global__ __launch_bounds__(kParamsBlock) void tq_params_kernel(const PtrTable 
             per_ln = (float)(rw * (double)a);
         }
         const uint2 hc = L.hc[ja];
-        const float inv_nf = (float)inv_n, part = (float)hc.x * frac, inv_a = rcp_hw(a);
+        // 16 / a: the hardware's reciprocal has no subnormal results, which 1 / a is from 2^126 on
+        const float inv_nf = (float)inv_n, part = (float)hc.x * frac, inv_a16 = rcp_hw(0.0625f * a);
         const float inv_a23 = exp2_hw(log2_hw(a) * (-2.0f / 3.0f));
         float v = __builtin_inff(), b_mass = 0.0f, b_rest = 1.0f, b_lo = 0.0f, b_in = 0.0f;
 #pragma unroll
@@ -455,7 +456,7 @@ __global__ __launch_bounds__(kParamsBlock) void tq_params_kernel(const PtrTable 
             v_f[k] = __builtin_inff();
             if (__builtin_amdgcn_ballot_w64(lo_f[k] < a) == 0ull) continue;
             // mass between the edge and a, from an exact difference of counts; 1 - k of the formula
-            const float mass = ((float)(hc.y - cum[k]) + part) * inv_nf, rest = (a - lo_f[k]) * inv_a;
+            const float mass = ((float)(hc.y - cum[k]) + part) * inv_nf, rest = (0.0625f * (a - lo_f[k])) * inv_a16;
             const float in = in13_f[k] * inv_a23;
             const float vk = exp2_hw((log2_hw(mass) + 2.0f * log2_hw(rest)) * (1.0f / 3.0f)) + in;
             v_f[k] = lo_f[k] < a ? vk : __builtin_inff();
@@ -465,7 +466,7 @@ __global__ __launch_bounds__(kParamsBlock) void tq_params_kernel(const PtrTable 
         const unsigned long long at = __builtin_amdgcn_ballot_w64(v == m);
         // v = s1 + s2: d ln(s1) = dmass / (3 mass) + 2/3 k / (1 - k), d ln(s2) = -2/3
         const float s1 = v - b_in;
-        const float d1 = b_mass > 0.0f ? (float)hc.x * per_ln * inv_nf * rcp_hw(b_mass) + 2.0f * b_lo * inv_a * rcp_hw(b_rest) : 0.0f;
+        const float d1 = b_mass > 0.0f ? (float)hc.x * per_ln * inv_nf * rcp_hw(b_mass) + 0.125f * b_lo * inv_a16 * rcp_hw(b_rest) : 0.0f;
         const float slope = (s1 * d1 - 2.0f * b_in) * rcp_hw(v);
         if (lane == (at ? __builtin_ctzll(at) : 0)) { L.search_q[flip][wave] = m; L.search_slope[flip][wave] = slope; }
         __syncthreads();

@@ -69,3 +69,27 @@ def test_designed_histograms(bits, grid):
     assert steady.sum() >= (st.size if grid == B.GRID_UNIFORM else st.size - 8)
     assert (got["flags"][steady] == want["flags"][steady]).all()
     assert_params_close(got[steady], want[steady])
+
+
+def design(st, bits, grid, override=0.0):
+    dev = torch.from_numpy(st.view(np.uint8).reshape(-1).copy()).cuda()
+    pr = torch.full((st.size * B.PARAMS_BYTES,), 0x77, dtype=torch.uint8, device="cuda")
+    B.tq_params(dev, pr, bits, grid, override)
+    torch.cuda.synchronize()
+    return B.params_to_numpy(pr), OP.tq_params(st.view(O.STATS_DTYPE), bits, grid, override)
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("grid", [B.GRID_UNIFORM, B.GRID_NONUNIFORM, B.GRID_BISCALED])
+def test_thresholds_whose_reciprocal_is_subnormal(bits, grid):
+    """From 2^126 on 1 / alpha is subnormal in binary32: ordinary values and one huge one, alpha = max|g| or
+    given, on both sides of that line and at the top of the range."""
+    values = np.abs(np.random.default_rng(3).standard_normal(1_000_000))
+    h = np.bincount(np.clip((values.astype(np.float32).view(np.uint32) >> 19).astype(np.int64) - 1391, 0, 897), minlength=898)
+    h[897] += 1
+    tops = np.float32([2e37, 2.0 ** 126, 8.6e37, 1e38, 3.4028234663852886e38])
+    got, want = design(np.concatenate([record(h, t) for t in tops]), bits, grid, -1.0)
+    assert_params_close(got, want)
+    for alpha in tops:
+        got, want = design(record(h, 1e38), bits, grid, float(min(alpha, np.float32(3e38))))   # 3e38: the largest accepted
+        assert_params_close(got, want)

@@ -201,7 +201,8 @@ __device__ __forceinline__ uint32_t encode_group(const float (&x)[8], const uint
 //
 // Regular (checked once per workgroup with the very arithmetic of p_r): for every cell k, with
 // p_k(x) = (x - l_k) inv_w[k], and lo_k, hi_k the ends the search gives it,
-//   |p_k(l_{k+1}) - 1| <= 2^-18,  |p_k(hi_k) - 1| <= 2^-18,  |p_k(lo_k)| <= 2^-18,  0 < inv_w[k] <= 2^90.
+//   |p_k(l_{k+1}) - 1| <= 2^-18,  |p_k(hi_k) - 1| <= 2^-18,  |p_k(lo_k)| <= 2^-18,  0 < inv_w[k] <= 2^90,
+// and no level lies beyond +-alpha, so that the codes saturate where Eq. (1) truncates.
 // p_k is monotone and 2^-17 <= u <= 1 - 2^-17.  So inside a cell no sum reaches the code k + 2, and where the
 // search and the definition disagree about the cell (levels that mirror each other only to within
 // rounding) they agree about the code: a value that the search leaves in cell k although it has reached
@@ -235,7 +236,7 @@ __device__ __forceinline__ CellReads read_cells(const tq_params_t* P, uint32_t l
 
 // Called by one whole wavefront (lane = its lane).
 template <int BITS>
-__device__ __forceinline__ void fill_cells(CellLds& tab, const tq_params_t* P, const CellReads& c, uint32_t lane)
+__device__ __forceinline__ void fill_cells(CellLds& tab, const tq_params_t* P, const CellReads& c, float alpha, uint32_t lane)
 {
     constexpr uint32_t H = 1u << (BITS - 1), M = H - 1;
     const uint32_t j = lane & (2u * H - 1u), i = H - 1u - (j & (H - 1u));
@@ -245,7 +246,8 @@ __device__ __forceinline__ void fill_cells(CellLds& tab, const tq_params_t* P, c
     const float lo = neg ? -c.outer : inner, hi = neg ? -inner : c.outer;
     const float p_next = (c.l_next - c.l) * c.inv, p_hi = (hi - c.l) * c.inv, p_lo = (lo - c.l) * c.inv;
     const bool ok = fabsf(p_next - 1.0f) <= kRegularSlack && fabsf(p_hi - 1.0f) <= kRegularSlack &&
-                    fabsf(p_lo) <= kRegularSlack && c.inv > 0.0f && c.inv <= kRegularMaxInv;
+                    fabsf(p_lo) <= kRegularSlack && c.inv > 0.0f && c.inv <= kRegularMaxInv &&
+                    fabsf(c.l) <= alpha && fabsf(c.l_next) <= alpha;
     if (lane < 2u * H)
         tab.e[j] = make_float4(c.l, c.inv * (float)(1u << (32 - BITS)),
                                __uint_as_float((k << (32 - BITS)) + (1u << (15 - BITS))), 0.0f);
@@ -414,7 +416,7 @@ __device__ __forceinline__ Codebook set_up_codebook(const tq_params_t* P, CellLd
             if (lane < 64) reads = read_cells<BITS>(P, lane);
             load_pivots<BITS>(P, cb.pv);
         }
-        if (lane < 64) fill_cells<BITS>(cells, P, reads, lane);
+        if (lane < 64) fill_cells<BITS>(cells, P, reads, cb.alpha, lane);
         // compared from vector registers: with a scalar operand the subtraction runs at 36 T/s, without at 59
         asm volatile("" : "+v"(cb.pv[0]), "+v"(cb.pv[1]), "+v"(cb.pv[2]));
         __syncthreads();

@@ -217,11 +217,11 @@ def test_the_family_named_to_tq_compress_shapes_the_launch_only(wl, dtype_name, 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("bits", [2, 3, 4])
-@pytest.mark.parametrize("kind", ["mirrored", "ulps", "lopsided", "reciprocals", "far"])
+@pytest.mark.parametrize("kind", ["mirrored", "ulps", "lopsided", "reciprocals", "far", "alpha inside"])
 def test_codebooks_on_both_sides_of_the_mirrored_path(kind, bits, dtype):
     """Designed codebooks mirror their levels about 0 and take a path of their own.  Codebooks that do so
-    exactly, to within ulps of a level, not at all, with reciprocals that do not fit their cells, and with
-    levels far apart: many draws of every value at and next to a level of either sign, codes equal to the
+    exactly, to within ulps of a level, not at all, with reciprocals that do not fit their cells, with
+    levels far apart, and with levels beyond alpha: many draws of every value at and next to a level of either sign, codes equal to the
     oracle's."""
     s = (1 << bits) - 1
     rng = np.random.default_rng(bits * 10 + len(kind))
@@ -240,6 +240,8 @@ def test_codebooks_on_both_sides_of_the_mirrored_path(kind, bits, dtype):
     P = np.zeros(1, dtype=O.PARAMS_DTYPE)
     P["alpha"], P["bits"], P["s"], P["grid"] = lv[-1], bits, s, O.GRID_NONUNIFORM
     P["level"][0, : s + 1], P["inv_w"][0, :s] = lv, inv
+    if kind == "alpha inside":                                   # Eq. (1) truncates at alpha, wherever the levels end
+        P["alpha"] = (lv[-2] + lv[-1]) / 2
     ends = np.concatenate([lv, -lv])
     near = np.concatenate([(ends.view(np.int32) + k).view(np.float32) for k in (-40, -3, -2, -1, 0, 1, 2, 3, 40)])
     mid = np.concatenate([(lv[1:] + lv[:-1]) / 2, [0.0, -0.0, 1.0, -1.0, np.inf, -np.inf, np.nan]]).astype(np.float32)

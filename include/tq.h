@@ -132,7 +132,8 @@ int tq_stats_static(const void* g_dev, int dtype, uint64_t d, uint64_t bucket_el
  * it like any non-uniform codebook.  p inside
  * [-alpha, alpha] is the histogram's density; gamma, rho come from the tail
  * terms of tq_stats or, without g_min, from the bins above the 0.9-quantile.
- *   stats_dev       [nb] from tq_stats
+ *   stats_dev       [nb] from tq_stats, or sums of its records (counts, n and tail terms added, the
+ *                   larger absmax, the same g_min; n may exceed 2^32, a bin may not)
  *   bits            b in {2,3,4}
  *   alpha_override  0: the paper's formula; > 0: use this alpha;
  *                   < 0: alpha = max|g| (quantization without truncation)

@@ -136,9 +136,23 @@ __constant__ OctaveLogs kOctaveLogs = {
      0.55961578793542266, 0.59470710774669278, 0.62860865942237409, 0.66139848224536502}
 };
 
-template <bool ROOTS>
+// Count of a bin and of all bins below it, exact.  Every bucket has n < 2^32; WIDE is for records that a caller
+// has summed beyond that (their bins are 32-bit still): the fp64 sums for every record cost 0.5 to 1.9 us a launch.
+template <bool WIDE> struct BinCounts;
+template <> struct BinCounts<false> {
+    uint2 hc[kNB];
+    struct Bin { uint32_t here, below; };
+    __device__ __forceinline__ Bin at(int i) const { const uint2 v = hc[i]; return {v.x, v.y}; }
+};
+template <> struct BinCounts<true> {
+    double cum[kNB + 1];
+    struct Bin { double here, below; };
+    __device__ __forceinline__ Bin at(int i) const { const double b = cum[i]; return {cum[i + 1] - b, b}; }
+};
+
+template <bool ROOTS, bool WIDE>
 struct ParamsLds {
-    uint2 hc[kNB];                         // count of bin i, and of all bins below it (exact: n < 2^32)
+    BinCounts<WIDE> bins;
     double H[ROOTS ? kNB + 1 : 1];         // H[i] = int_0^{lo_i} p^(1/3), times (2n)^(1/3)
     uint32_t chunk_count[16];              // per 64 consecutive bins
     double chunk_h[16];
@@ -228,9 +242,9 @@ __device__ __forceinline__ T bin_scan(T (&v)[kBinsPerLane], T* chunk)
 }
 
 // The density's integrals up to x, in fp64.
-template <bool ROOTS>
+template <bool ROOTS, bool WIDE>
 struct DensityView {
-    const ParamsLds<ROOTS>& L;
+    const ParamsLds<ROOTS, WIDE>& L;
     double inv_n, absmax;
     // part of bin j below x, as a fraction of the bin; rw = 1 / its width
     __device__ __forceinline__ void covered(int j, double x, double& frac, double& rw) const
@@ -255,7 +269,8 @@ struct DensityView {
         const int j = bin_of(a);
         double frac, rw;
         covered(j, a, frac, rw);
-        const double h = (double)L.hc[j].x, mass = (double)L.hc[j].y + h * frac;
+        const auto bin = L.bins.at(j);
+        const double h = (double)bin.here, mass = (double)bin.below + h * frac;
         elasticity = h * rw * a * recip(mass);
         return mass * inv_n;
     }
@@ -303,25 +318,23 @@ constexpr int kSeekSteps = 60;
 constexpr float kSureSteps = 90.0f;
 __device__ __forceinline__ bool certified_slope(float r) { return fabsf(r) <= kCertifiedSlope; }
 
-template <int GRID>
-__global__ __launch_bounds__(kParamsBlock) void tq_params_kernel(const PtrTable stats_tab, uint32_t nb, int bits,
-                                                           float alpha_override, const MutPtrTable params_tab)
+// One record.  WIDE: its counts may add up to more than 32 bits hold.
+template <int GRID, bool WIDE>
+__device__ __forceinline__ void design(ParamsLds<GRID != TQ_GRID_UNIFORM, WIDE>& L, const tq_stats_t* __restrict__ S, int bits,
+                                       float alpha_override, tq_params_t* __restrict__ P)
 {
     constexpr bool kRoots = GRID != TQ_GRID_UNIFORM;       // the integral of p^(1/3) is needed
     constexpr bool kBiscaled = GRID == TQ_GRID_BISCALED;
-    __shared__ ParamsLds<kRoots> L;
-    // one workgroup per bucket, blockIdx.y = tensor of the batch
-    const uint32_t bucket = linear_block();
-    if (bucket >= nb) return;
-    const tq_stats_t* __restrict__ S = static_cast<const tq_stats_t*>(stats_tab.p[blockIdx.y]) + bucket;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    uint32_t h[kBinsPerLane], cum[kBinsPerLane];
+    uint32_t h[kBinsPerLane], cum[kBinsPerLane];           // of the lane's bins, unless WIDE
+    if constexpr (!WIDE) {
 #pragma unroll
-    for (int k = 0; k < kBinsPerLane; ++k) {
-        const int i = kParamsBlock * k + tid;
-        h[k] = i < kNB ? S->hist[i] : 0u;
+        for (int k = 0; k < kBinsPerLane; ++k) {
+            const int i = kParamsBlock * k + tid;
+            h[k] = i < kNB ? S->hist[i] : 0u;
+        }
     }
     const double centre_log = kOctaveLogs.centre[(tid - 1) & 15], edge_log = kOctaveLogs.edge[(tid - 1) & 15];
     const double absmax = (double)S->absmax;
@@ -331,22 +344,44 @@ __global__ __launch_bounds__(kParamsBlock) void tq_params_kernel(const PtrTable 
     const bool fixed_gmin = given_g_min > 0.0f;
     if (tid == 0) L.tail_bin = kNB;
 
-    // counts below each bin
+    // Counts below each bin.  Without a caller-fixed g_min the tail starts at the lower edge of the first bin at
+    // which the cumulative count reaches the 0.9-quantile of |g|: exactly one bin has the
+    // count below the mark before it and at or above the mark with it.
+    double n;
+    if constexpr (WIDE) {
+        if (wave == 0) {                                   // one wavefront, 64 bins at a time
+            double sum = 0.0;
+#pragma unroll 1
+            for (int i = lane; i < 64 * ((kNB + 63) / 64); i += 64) {
+                const double here = i < kNB ? (double)S->hist[i] : 0.0, upto = wave_scan(here);
+                if (i < kNB) L.bins.cum[i] = sum + (upto - here);
+                sum += lane_value(upto, 63);
+            }
+            if (lane == 0) L.bins.cum[kNB] = sum;
+        }
+        __syncthreads();
+        n = L.bins.cum[kNB];
+#pragma unroll 1
+        for (int i = tid; i < kNB; i += kParamsBlock) {
+            if (10.0 * L.bins.cum[i] < 9.0 * n && 10.0 * L.bins.cum[i + 1] >= 9.0 * n) {
+                L.tail_bin = i;
+                L.tail_edge_log = i < kNB - 1 ? edge_log : 0.0;
+            }
+        }
+    } else {
 #pragma unroll
-    for (int k = 0; k < kBinsPerLane; ++k) cum[k] = h[k];
-    const uint32_t n_count = bin_scan(cum, L.chunk_count);
-    const double n = (double)n_count;
+        for (int k = 0; k < kBinsPerLane; ++k) cum[k] = h[k];
+        const uint32_t n_count = bin_scan(cum, L.chunk_count);
+        n = (double)n_count;
 #pragma unroll
-    for (int k = 0; k < kBinsPerLane; ++k) {
-        const int i = kParamsBlock * k + tid;
-        if (i < kNB) L.hc[i] = make_uint2(h[k], cum[k]);
-        // Without a caller-fixed g_min the tail starts at the lower edge of the first bin at
-        // which the cumulative count reaches the 0.9-quantile of |g|: exactly one bin has the
-        // count below the mark before it and at or above the mark with it.
-        const uint64_t mark = 9ull * n_count;
-        if (10ull * cum[k] < mark && 10ull * ((uint64_t)cum[k] + h[k]) >= mark) {
-            L.tail_bin = i;
-            L.tail_edge_log = i < kNB - 1 ? edge_log : 0.0;
+        for (int k = 0; k < kBinsPerLane; ++k) {
+            const int i = kParamsBlock * k + tid;
+            if (i < kNB) L.bins.hc[i] = make_uint2(h[k], cum[k]);
+            const uint64_t mark = 9ull * n_count;
+            if (10ull * cum[k] < mark && 10ull * ((uint64_t)cum[k] + h[k]) >= mark) {
+                L.tail_bin = i;
+                L.tail_edge_log = i < kNB - 1 ? edge_log : 0.0;
+            }
         }
     }
     __syncthreads();
@@ -367,8 +402,11 @@ __global__ __launch_bounds__(kParamsBlock) void tq_params_kernel(const PtrTable 
         for (int k = 0; k < kBinsPerLane; ++k) {
             const int i = kParamsBlock * k + tid;
             const double from_octave = i < kNB - 1 ? centre_log : 0.0;
+            double here = 0.0;
+            if constexpr (!WIDE) here = (double)h[k];
+            else if (i < kNB) here = (double)S->hist[i];
             if (i >= tail_bin)
-                local_t += (double)h[k] * ((double)(((i - 1) >> 4) - octave0) * kLn2 + (from_octave - L.tail_edge_log));
+                local_t += here * ((double)(((i - 1) >> 4) - octave0) * kLn2 + (from_octave - L.tail_edge_log));
         }
         local_t = wave_scan(local_t);
         if (lane == 63) L.wave_tail[wave] = local_t;
@@ -378,16 +416,16 @@ __global__ __launch_bounds__(kParamsBlock) void tq_params_kernel(const PtrTable 
         // one bin after the other (a loop, not unrolled: its code is fetched once), through LDS
 #pragma unroll 1
         for (int i = tid; i < kNB; i += kParamsBlock) {
-            const uint32_t count = L.hc[i].x;
+            const auto count = L.bins.at(i).here;
             double c = 0.0;
-            if (__builtin_amdgcn_ballot_w64(count != 0u) != 0ull) {
+            if (__builtin_amdgcn_ballot_w64(count != 0) != 0ull) {
                 // (count / w)^(1/3) w = count^(1/3) w^(2/3); the bin is w = 2^e wide, e = 3 third + rem
                 c = cube_root((double)count);
                 if (i < kNB - 1) {
                     const int e = i > 0 ? ((i - 1) >> 4) - 44 : -40;
                     const int third = (e + 63) / 3 - 21, rem = e - 3 * third;
                     c = ldexp(c * (rem == 0 ? 1.0 : (rem == 1 ? 1.58740105196819947475 : 2.51984209978974632953)), 2 * third);
-                } else if (count != 0u) {
+                } else if (count != 0) {
                     const double wr = cube_root(last_bin_width(absmax));
                     c = c * wr * wr;
                 }
@@ -413,11 +451,15 @@ __global__ __launch_bounds__(kParamsBlock) void tq_params_kernel(const PtrTable 
     if (!kBiscaled && wave != 0) return;
 
     const double inv_n = n > 0.0 ? recip(n) : 0.0;
-    const DensityView<kRoots> D{L, inv_n, absmax};
+    const DensityView<kRoots, WIDE> D{L, inv_n, absmax};
 
     // BiScaled search, collective: the edge lo_j < a (j = 0: beta = 0) that minimises Q_B(a, lo_j / a) =
     // v^3, v = ((mass outside beta) (1 - k)^2)^(1/3) + ((mass inside) k^2)^(1/3), the smallest such edge on a tie.
     // Each lane keeps, for its bins, what does not depend on a.
+    auto below_edge = [&](int k) {                         // the count below the lane's k-th edge
+        if constexpr (WIDE) return L.bins.cum[kParamsBlock * k + tid < kNB ? kParamsBlock * k + tid : kNB];
+        else return cum[k];
+    };
     float lo_f[kBinsPerLane], in13_f[kBinsPerLane];        // the edge, (mass below it * edge^2)^(1/3)
     int flip = 0;
     if constexpr (kBiscaled) {
@@ -425,7 +467,7 @@ __global__ __launch_bounds__(kParamsBlock) void tq_params_kernel(const PtrTable 
         for (int k = 0; k < kBinsPerLane; ++k) {
             const int i = kParamsBlock * k + tid;
             lo_f[k] = i < kNB ? (float)bin_lo(i) : __builtin_inff();
-            in13_f[k] = cum[k] && i < kNB ? exp2_hw((log2_hw((float)cum[k] * (float)inv_n) + 2.0f * log2_hw(lo_f[k])) * (1.0f / 3.0f)) : 0.0f;
+            in13_f[k] = below_edge(k) > 0 && i < kNB ? exp2_hw((log2_hw((float)below_edge(k) * (float)inv_n) + 2.0f * log2_hw(lo_f[k])) * (1.0f / 3.0f)) : 0.0f;
         }
     }
     // the fp32 search at threshold a: min_k v, and the elasticity of Q_B = v^3 in a with the best edge held
@@ -446,9 +488,9 @@ __global__ __launch_bounds__(kParamsBlock) void tq_params_kernel(const PtrTable 
             frac = (float)f;
             per_ln = (float)(rw * (double)a);
         }
-        const uint2 hc = L.hc[ja];
+        const auto bin = L.bins.at(ja);
         // 16 / a: the hardware's reciprocal has no subnormal results, which 1 / a is from 2^126 on
-        const float inv_nf = (float)inv_n, part = (float)hc.x * frac, inv_a16 = rcp_hw(0.0625f * a);
+        const float inv_nf = (float)inv_n, part = (float)bin.here * frac, inv_a16 = rcp_hw(0.0625f * a);
         const float inv_a23 = exp2_hw(log2_hw(a) * (-2.0f / 3.0f));
         float v = __builtin_inff(), b_mass = 0.0f, b_rest = 1.0f, b_lo = 0.0f, b_in = 0.0f;
 #pragma unroll
@@ -456,7 +498,7 @@ __global__ __launch_bounds__(kParamsBlock) void tq_params_kernel(const PtrTable 
             v_f[k] = __builtin_inff();
             if (__builtin_amdgcn_ballot_w64(lo_f[k] < a) == 0ull) continue;
             // mass between the edge and a, from an exact difference of counts; 1 - k of the formula
-            const float mass = ((float)(hc.y - cum[k]) + part) * inv_nf, rest = (0.0625f * (a - lo_f[k])) * inv_a16;
+            const float mass = ((float)(bin.below - below_edge(k)) + part) * inv_nf, rest = (0.0625f * (a - lo_f[k])) * inv_a16;
             const float in = in13_f[k] * inv_a23;
             const float vk = exp2_hw((log2_hw(mass) + 2.0f * log2_hw(rest)) * (1.0f / 3.0f)) + in;
             v_f[k] = lo_f[k] < a ? vk : __builtin_inff();
@@ -466,7 +508,7 @@ __global__ __launch_bounds__(kParamsBlock) void tq_params_kernel(const PtrTable 
         const unsigned long long at = __builtin_amdgcn_ballot_w64(v == m);
         // v = s1 + s2: d ln(s1) = dmass / (3 mass) + 2/3 k / (1 - k), d ln(s2) = -2/3
         const float s1 = v - b_in;
-        const float d1 = b_mass > 0.0f ? (float)hc.x * per_ln * inv_nf * rcp_hw(b_mass) + 0.125f * b_lo * inv_a16 * rcp_hw(b_rest) : 0.0f;
+        const float d1 = b_mass > 0.0f ? (float)bin.here * per_ln * inv_nf * rcp_hw(b_mass) + 0.125f * b_lo * inv_a16 * rcp_hw(b_rest) : 0.0f;
         const float slope = (s1 * d1 - 2.0f * b_in) * rcp_hw(v);
         if (lane == (at ? __builtin_ctzll(at) : 0)) { L.search_q[flip][wave] = m; L.search_slope[flip][wave] = slope; }
         __syncthreads();
@@ -487,23 +529,24 @@ __global__ __launch_bounds__(kParamsBlock) void tq_params_kernel(const PtrTable 
         const int ja = bin_of(a);
         double frac, rw;
         D.covered(ja, a, frac, rw);
-        const double part = (double)L.hc[ja].x * frac, inv_a = recip(a);
+        const auto bin = L.bins.at(ja);
+        const double part = (double)bin.here * frac, inv_a = recip(a);
         double q = 1.0e300;
         int jbest = kNB;
 #pragma unroll 1
         for (int k = 0; k < kBinsPerLane; ++k) {
             float v32 = v_f[0];
             double lo = (double)lo_f[0];
-            uint32_t below = cum[0];
+            auto below = below_edge(0);
 #pragma unroll
             for (int m = 1; m < kBinsPerLane; ++m)
-                if (m == k) { v32 = v_f[m]; lo = (double)lo_f[m]; below = cum[m]; }
+                if (m == k) { v32 = v_f[m]; lo = (double)lo_f[m]; below = below_edge(m); }
             // an edge between a and a rounded to fp32 counts as close
             const bool close = lo < a && (v32 <= bound || !(lo < (double)(float)a));
             unsigned long long left = __builtin_amdgcn_ballot_w64(close);
             if (left == 0ull) continue;
             const double kk = lo * inv_a, rest = (a - lo) * inv_a;
-            const double out_mass = ((double)(L.hc[ja].y - below) + part) * inv_n, in_mass = (double)below * inv_n;
+            const double out_mass = ((double)(bin.below - below) + part) * inv_n, in_mass = (double)below * inv_n;
             const double v = cube_root(out_mass * rest * rest) + cube_root(in_mass * kk * kk);
             while (left) {                                 // a few candidates, in ascending order
                 const int l = __builtin_ctzll(left);
@@ -540,9 +583,9 @@ __global__ __launch_bounds__(kParamsBlock) void tq_params_kernel(const PtrTable 
         const float frac = (float)(bits_a & 0x7FFFFu) * (1.0f / 524288.0f);
         const float mant = __uint_as_float((bits_a & 0x7FFFFFu) | 0x41800000u);    // a / (bin width) = 16 + m + frac
         if constexpr (GRID == TQ_GRID_UNIFORM) {
-            const uint2 hc = L.hc[j];
-            const float mass = (float)hc.y + (float)hc.x * frac;
-            elasticity = (float)hc.x * mant * rcp_hw(mass);
+            const auto bin = L.bins.at(j);
+            const float mass = (float)bin.below + (float)bin.here * frac;
+            elasticity = (float)bin.here * mant * rcp_hw(mass);
             return log2_hw(mass * (float)inv_n);
         } else if constexpr (kBiscaled) {
             return 3.0f * log2_hw(search_f(a, elasticity));
@@ -570,7 +613,7 @@ __global__ __launch_bounds__(kParamsBlock) void tq_params_kernel(const PtrTable 
             n_tail = (double)given_n_tail;
             sum_log = given_sum_log;
         } else {
-            n_tail = g_min > 0.0 ? n - (double)L.hc[tail_bin].y : 0.0;
+            n_tail = g_min > 0.0 ? n - (double)L.bins.at(tail_bin).below : 0.0;
             sum_log = g_min > 0.0 ? sum_log_binned : 0.0;
         }
         const bool tail_ok = g_min > 0.0 && n_tail > 0.0 && sum_log > 0.0 && g_min < absmax;
@@ -676,7 +719,7 @@ __global__ __launch_bounds__(kParamsBlock) void tq_params_kernel(const PtrTable 
     } else if constexpr (kBiscaled) {
         const double beta = bin_lo(best_bin), kk = beta / af;
         double el;
-        const double c_b = (double)L.hc[best_bin].y * inv_n, c_a = D.Q_U(af, el);
+        const double c_b = (double)L.bins.at(best_bin).below * inv_n, c_a = D.Q_U(af, el);
         const double p1 = c_b / (2.0 * beta);
         const double rest = c_a - c_b > 0.0 ? c_a - c_b : 0.0;
         const double p2 = rest / (2.0 * (af - beta));
@@ -715,7 +758,6 @@ __global__ __launch_bounds__(kParamsBlock) void tq_params_kernel(const PtrTable 
             }
         }
     }
-    tq_params_t* P = static_cast<tq_params_t*>(params_tab.p[blockIdx.y]) + bucket;
     if (lane < 16) {
         P->level[lane] = lv;
         P->inv_w[lane] = iw;
@@ -730,6 +772,25 @@ __global__ __launch_bounds__(kParamsBlock) void tq_params_kernel(const PtrTable 
         P->g_min = (float)g_min;
         P->flags = flags;
     }
+}
+
+template <int GRID>
+__global__ __launch_bounds__(kParamsBlock, GRID == TQ_GRID_BISCALED ? 5 : 7) void tq_params_kernel(const PtrTable stats_tab, uint32_t nb, int bits,
+                                                           float alpha_override, const MutPtrTable params_tab)
+{
+    constexpr bool kRoots = GRID != TQ_GRID_UNIFORM;
+    __shared__ union Lds {
+        ParamsLds<kRoots, false> narrow;
+        ParamsLds<kRoots, true> wide;
+        __device__ Lds() {}
+    } L;
+    // one workgroup per bucket, blockIdx.y = tensor of the batch
+    const uint32_t bucket = linear_block();
+    if (bucket >= nb) return;
+    const tq_stats_t* S = static_cast<const tq_stats_t*>(stats_tab.p[blockIdx.y]) + bucket;
+    tq_params_t* P = static_cast<tq_params_t*>(params_tab.p[blockIdx.y]) + bucket;
+    if (__builtin_expect((S->n >> 32) == 0, 1)) design<GRID, false>(L.narrow, S, bits, alpha_override, P);
+    else design<GRID, true>(L.wide, S, bits, alpha_override, P);
 }
 
 }  // namespace tq

@@ -93,3 +93,16 @@ def test_thresholds_whose_reciprocal_is_subnormal(bits, grid):
     for alpha in tops:
         got, want = design(record(h, 1e38), bits, grid, float(min(alpha, np.float32(3e38))))   # 3e38: the largest accepted
         assert_params_close(got, want)
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("grid", [B.GRID_UNIFORM, B.GRID_NONUNIFORM, B.GRID_BISCALED])
+def test_counts_that_add_up_beyond_32_bits(bits, grid):
+    """A record summed over many tensors: every bin fits 32 bits, their sum does not."""
+    h = np.zeros(898, dtype=np.int64)
+    h[300:700] = np.round(4e9 * 2.0 ** (-2.0 * np.arange(400) / 16))
+    assert h.sum() > 2 ** 35 and h.max() < 2 ** 32
+    big = h.copy()
+    big[300:320] = 4_000_000_000
+    got, want = design(np.concatenate([record(h, edge(690)), record(big, edge(690))]), bits, grid)
+    assert_params_close(got, want)

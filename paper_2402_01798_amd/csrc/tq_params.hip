@@ -566,7 +566,13 @@ __device__ __forceinline__ void design(ParamsLds<GRID != TQ_GRID_UNIFORM, WIDE>&
             if (oq < q || (oq == q && oj < jbest)) { q = oq; jbest = oj; }
         }
         best_bin = jbest;
-        elasticity = (double)el;
+        // the elasticity of the edge that won here: near a tie the fp32 search may have taken another one's
+        const double lo = bin_lo(jbest), rest = (a - lo) * inv_a;
+        const double below = (double)L.bins.at(jbest).below, mass = ((double)bin.below - below + part) * inv_n;
+        const float inside = (float)(below * inv_n), kk = (float)(lo * inv_a);
+        const float s2 = inside > 0.0f ? exp2_hw((log2_hw(inside) + 2.0f * log2_hw(kk)) * (1.0f / 3.0f)) : 0.0f;
+        const float d1 = mass > 0.0 ? (float)((double)bin.here * rw * a * inv_n) * rcp_hw((float)mass) + 2.0f * kk * rcp_hw((float)rest) : 0.0f;
+        elasticity = (double)((((float)q - s2) * d1 - 2.0f * s2) * rcp_hw((float)q));
         return q * q * q;
     };
     // Q of the family at a, and dlnQ/dlna
@@ -599,6 +605,7 @@ __device__ __forceinline__ void design(ParamsLds<GRID != TQ_GRID_UNIFORM, WIDE>&
     };
 
     const int s = (1 << bits) - 1;
+    bool have_split = false;                               // BiScaled: best_bin belongs to alpha rounded to fp32
     uint32_t flags = 0;
     double gamma = 0.0, rho = 0.0, alpha;
     if (n <= 0.0 || absmax <= 0.0) {
@@ -663,6 +670,7 @@ __device__ __forceinline__ void design(ParamsLds<GRID != TQ_GRID_UNIFORM, WIDE>&
                 a = t >= t_max ? a_max : clampa(g_min * (double)exp2_hw(t));
                 for (int it = 0; it < 5 && near && !converged; ++it) {
                     double el;
+                    have_split = false;
                     const double q = Q(a, el);
                     if (!(q > 0.0)) break;
                     const double part = ln(((lane & 1) ? q : a) * recip((lane & 1) ? C : g_min));    // the two logarithms at once, in even and odd lanes
@@ -675,11 +683,19 @@ __device__ __forceinline__ void design(ParamsLds<GRID != TQ_GRID_UNIFORM, WIDE>&
                     if (plain + 27.6f * rcp_hw(-log2_hw(r)) > kSureSteps) break;   // log2(kNearStep / kRelTol) = 27.6
                     // quadratic convergence inside a bin: what is left is of the order of delta^2
                     converged = fabs(delta) <= 1e-5 && bin_of(an) == bin_of(a);
+                    if constexpr (kBiscaled) {
+                        // and where the best edge changes Q_B has a kink: it has to be the same at the end of the step
+                        const int from = best_bin;
+                        have_split = converged;
+                        if (converged) (void)search_d((double)(float)an, el);
+                        converged = (converged && best_bin == from) || fabs(residual) <= kRelTol;
+                    }
                     a = an;
                 }
             }
             if (!converged) {
                 // the definition's iteration, step by step
+                have_split = false;
                 const double log_c = ln(C);
                 a = clampa(g_min * exp(ex * log_c));       // alpha' of Sec. IV-A (Q = 1)
                 for (int it = 0; it < kMaxIter; ++it) {
@@ -709,7 +725,7 @@ __device__ __forceinline__ void design(ParamsLds<GRID != TQ_GRID_UNIFORM, WIDE>&
     }
     if constexpr (kBiscaled) {
         double el;
-        if (half > 0.0) (void)search_d(af, el);            // the split belongs to the rounded threshold
+        if (half > 0.0 && !have_split) (void)search_d(af, el);   // the split belongs to the rounded threshold
         if (wave != 0) return;
     }
     const int k = lane;                                    // this lane's level, 0 .. s

@@ -106,3 +106,86 @@ def test_counts_that_add_up_beyond_32_bits(bits, grid):
     big[300:320] = 4_000_000_000
     got, want = design(np.concatenate([record(h, edge(690)), record(big, edge(690))]), bits, grid)
     assert_params_close(got, want)
+
+
+def two_modes(rng):
+    """Counts of a histogram with two separated modes, and the edge above them."""
+    w, gap = int(rng.integers(10, 60)), int(rng.integers(10, 80))
+    h = np.zeros(898, dtype=np.int64)
+    h[560:560 + w] = rng.uniform(0.5, 1.0, w) * 10 ** rng.uniform(3, 6)
+    h[560 + w + gap:600 + w + gap] = rng.uniform(0.5, 1.0, 40) * 10 ** rng.uniform(2, 6)
+    return h, edge(600 + w + gap)
+
+
+def splits_change_beside_the_fixed_point(count):
+    """BiScaled records (b = 3) whose fixed point lies within 1e-6 of a threshold at which the best edge changes
+    and the slope of ln Q_B with it, the slopes of the iterated map on both sides within +-0.7."""
+    rng, out, targets = np.random.default_rng(8), [], []
+    while len(out) < count:
+        h, top = two_modes(rng)
+        dens = OP.Density(h, top)
+        below = np.concatenate([[0.0], np.cumsum(dens.hist)]) / dens.n
+
+        def v(a):
+            lo = dens.lo[dens.lo < a]
+            k, inside = lo / a, below[:lo.size]
+            mass = below[lo.size - 1] + dens.hist[lo.size - 1] / dens.n * (a - lo[-1]) / dens.w[lo.size - 1]
+            return np.cbrt((mass - inside) * (1 - k) ** 2) + np.cbrt(inside * k * k)
+
+        def slope(j, a):
+            return 3e6 * np.log(v(a * (1 + 5e-7))[j] / v(a * (1 - 5e-7))[j])
+
+        grid = np.exp(np.linspace(np.log(edge(575)), np.log(top * 0.99), 400))
+        best = [int(np.argmin(v(a))) for a in grid]
+        for i in np.nonzero(np.diff(best))[0]:
+            l, r = grid[i], grid[i + 1]
+            for _ in range(50):
+                m = 0.5 * (l + r)
+                l, r = (m, r) if int(np.argmin(v(m))) == best[i] else (l, m)
+            on_edge = np.abs(dens.lo / l - 1).min() < 1e-4
+            e0, e1 = slope(best[i], l * (1 - 1e-6)), slope(int(np.argmin(v(r))), r * (1 + 1e-6))
+            if on_edge or abs(e0 - e1) < 0.5 or max(abs(e0), abs(e1)) > 20:
+                continue
+            ex = min(0.7 / max(abs(e0), abs(e1)), 0.9)
+            target = l * (1 + rng.uniform(-1e-6, 1e-6))
+            # ln(target / g) = ex (ln C - ln Q), C = 2 rho s^2 / (gamma - 2): by g, then by the log-sum through gamma
+            gamma, n_tail = 1 + 1 / ex, dens.n // 10
+            ln_q = 3 * np.log(v(target).min())
+            rho = n_tail / (2 * dens.n)
+            g = np.float32(target * np.exp(-ex * (np.log(2 * rho * 49 / (gamma - 2)) - ln_q)))
+            if not 2.0 ** -40 <= g < 0.8 * target:
+                continue
+            f = lambda gm: np.log(target / float(g)) * (gm - 1) - (np.log(2 * rho * 49 / (gm - 2)) - ln_q)
+            lo_g, hi_g = max(2.03, gamma * 0.99), gamma * 1.01
+            if f(lo_g) * f(hi_g) > 0:
+                continue
+            for _ in range(80):
+                m = 0.5 * (lo_g + hi_g)
+                lo_g, hi_g = (m, hi_g) if f(m) * f(lo_g) > 0 else (lo_g, m)
+            st = record(h, top)
+            st["g_min"], st["n_tail"], st["sum_log_tail"] = g, int(n_tail), int(n_tail) / (lo_g - 1)
+            a, log_c = float(g) * 1.01, np.log(2 * rho * 49 / (lo_g - 2))
+            for _ in range(100):                              # the definition's iteration
+                before = a
+                a = float(np.clip(float(g) * np.exp((log_c - 3 * np.log(max(v(a).min(), 1e-99))) / (lo_g - 1)), g * (1 + 2.0 ** -10), top))
+            if abs(a / target - 1) > 1e-10 or abs(a / before - 1) > 1e-12:
+                continue                                      # it goes elsewhere, or stays undecided
+            out.append(st)
+            targets.append(target)
+            break
+    return np.concatenate(out), np.float32(targets)
+
+
+def test_the_best_split_changes_beside_the_fixed_point():
+    """Where the best edge of the BiScaled search changes, ln Q_B has a kink, and a step taken with the slope of
+    one side does not land on the other.  The threshold is fp64's, rounded: the fixed
+    point's binary32, or its neighbour where fp64 rounds the other way."""
+    st, alpha = splits_change_beside_the_fixed_point(48)
+    dev = torch.from_numpy(st.view(np.uint8).reshape(-1).copy()).cuda()
+    pr = torch.full((st.size * B.PARAMS_BYTES,), 0x77, dtype=torch.uint8, device="cuda")
+    B.tq_params(dev, pr, 3, B.GRID_BISCALED)
+    torch.cuda.synchronize()
+    got = B.params_to_numpy(pr)
+    assert (got["flags"] == 0).all()
+    off = np.abs(got["alpha"].astype(np.float64) - alpha) / np.spacing(alpha)
+    assert off.max() <= 1.0, off

@@ -355,8 +355,12 @@ __global__ __launch_bounds__(kBlock) void tq_decode_fast_kernel(
 // constant beside the masked code.  Sums in worker order.
 // Bound by the rate of LDS reads (one per four clocks and compute unit, 4 bytes wide as well as 8).  11.2 M
 // elements, N = 32, before (a loop over the workers, a load and eight look-ups each) -> now: b = 4 57.2 -> 44.7 us,
-// b = 3 56.1 -> 45.4 (50.6 with pairs), b = 2 46.3 -> 28.7; N = 64 106 -> 79.5, N = 12 at b = 4 21.6 -> 20.8.
-template <int BITS, int U, int T, int MODE>
+// b = 3 56.1 -> 45.4 (50.6 with pairs), b = 2 46.3 -> 28.7; N = 64 106 -> 79.5, N = 12 at b = 4 21.6 -> 18.9.
+// PART: the last eight end after the pair that holds the last worker; without it they are looked up whole.  The branches
+// cost whole batches up to 6 % at b = 2 and 3 with two tiles (11.2 M, N = 24 at b = 3 28.0 -> 29.9 us) and give what the
+// rows past the last worker would take: N = 9 at b = 4 20.6 -> 17.2, N = 17 28.2 -> 25.6; 61,706 elements (one tile),
+// N = 17 at b = 3 7.0 -> 4.5.
+template <int BITS, int U, int T, int MODE, bool PART>
 __global__ __launch_bounds__(kBlock) void tq_decode_many_kernel(
     const DecodeArgs args, int N, int weighted, float scale, uint64_t d, uint64_t d_pad, uint64_t bucket_elems,
     uint32_t groups_per_bucket, uint64_t payload_bytes, float* __restrict__ out, const Update up)
@@ -426,9 +430,11 @@ __global__ __launch_bounds__(kBlock) void tq_decode_many_kernel(
         if (c >= N) break;                                     // the same for every lane
         if (c + C < U) request(w[(c / C + 1) & 1], c + C);
 #pragma unroll
-        for (int t = 0; t < T; ++t)
+        for (int u = 0; u < C; ++u) {
+            // tables past the last worker hold zeros
+            if (PART && u % 2 == 0 && c + u >= N) break;
 #pragma unroll
-            for (int u = 0; u < C; ++u) {
+            for (int t = 0; t < T; ++t) {
                 const uint32_t word = w[(c / C) & 1][t][u];
                 const uint32_t codes = BITS == 3 ? word >> cl[t].first_bit : word;
                 const char* row = table + (c + u) * ROW;
@@ -449,6 +455,7 @@ __global__ __launch_bounds__(kBlock) void tq_decode_many_kernel(
                     }
                 }
             }
+        }
     }
     const float post = weighted ? 1.0f : scale;                // x * 1.0f is exact
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -577,14 +584,21 @@ hipError_t launch_mode(const DecodeGeom& g, float* out, const tq::Update& up, hi
         return hipGetLastError();
     }
 
-    // two tiles per workgroup; one / two on 11.2 M elements, N = 32: b = 4 45.5 / 44.7 us, b = 2 29.6 / 28.7
-    constexpr int T = 2;
-    const uint64_t gpb = (g.tpb + T - 1) / T;
+    // two tiles per workgroup, one where all workgroups are resident at once (eight per compute unit); one / two on
+    // 11.2 M elements, N = 32: b = 4 45.5 / 44.7 us, b = 2 29.6 / 28.7
+    const bool one_tile = g.nb * g.tpb <= 2048, part = g.bits == 4 && N % 8 != 0;
+    const uint64_t gpb = one_tile ? g.tpb : (g.tpb + 1) / 2;
     dim3 blocks;
     if (!tq::fold_grid(g.nb * gpb, tq::kBlock, 1, blocks)) return hipErrorInvalidValue;
-#define TQ_LAUNCH_MANY(B, UU)                                                                                  \
-    hipLaunchKernelGGL((tq::tq_decode_many_kernel<B, UU, T, MODE>), blocks, threads, 0, st, g.args, N, g.weighted, \
+#define TQ_LAUNCH_MANY_AS(B, UU, T, PART)                                                                      \
+    hipLaunchKernelGGL((tq::tq_decode_many_kernel<B, UU, T, MODE, PART>), blocks, threads, 0, st, g.args, N, g.weighted, \
                        g.scale, g.d, g.d_pad, g.be, (uint32_t)gpb, g.pbytes, out, up)
+#define TQ_LAUNCH_MANY(B, UU)                                          \
+    do {                                                               \
+        if (one_tile) TQ_LAUNCH_MANY_AS(B, UU, 1, true);               \
+        else if (part) TQ_LAUNCH_MANY_AS(B, UU, 2, (B == 4));          \
+        else TQ_LAUNCH_MANY_AS(B, UU, 2, false);                       \
+    } while (0)
     switch (g.bits) {
         case 2: if (N <= 32) TQ_LAUNCH_MANY(2, 32); else TQ_LAUNCH_MANY(2, 64); break;
         case 3: if (N <= 32) TQ_LAUNCH_MANY(3, 32); else TQ_LAUNCH_MANY(3, 64); break;
@@ -595,6 +609,7 @@ hipError_t launch_mode(const DecodeGeom& g, float* out, const tq::Update& up, hi
             break;
     }
 #undef TQ_LAUNCH_MANY
+#undef TQ_LAUNCH_MANY_AS
     return hipGetLastError();
 }
 

@@ -139,11 +139,11 @@ def test_outputs_on_both_sides_of_the_cache_limit(d):
 
 
 @pytest.mark.parametrize("bits", [2, 3, 4])
-@pytest.mark.parametrize("N", [9, 16, 17, 24, 32, 33, 64])
-@pytest.mark.parametrize("d", [5, 2048, 4096, 4097, 3 * 4096 + 2048 + 11])
+@pytest.mark.parametrize("N", [9, 11, 16, 17, 24, 32, 33, 64])
+@pytest.mark.parametrize("d", [5, 2048, 4096, 4097, 3 * 4096 + 2048 + 11, 2049 * 2048 + 5])
 def test_many_workers_in_batches_of_eight(bits, N, d):
     """Numbers of workers around the batches and table sizes of the kernel for many of them, ranges that
-    are whole, cut and ragged, with and without weights, bucketed and not: bit for bit the oracle's."""
+    are whole, cut and ragged, both tile counts, with and without weights, bucketed and not: bit for bit the oracle's."""
     rng = np.random.default_rng(N * 100 + bits)
     bucket = 4096 if d > 4097 else 0
     nb = B.num_buckets(d, bucket)

@@ -148,7 +148,8 @@ __device__ __forceinline__ uint32_t quantize(float x, float rf, float alpha, flo
 
 // Codes of one lane's 8 elements, packed little-endian into the low 8*BITS bits.
 // PARTIAL: only the first n_valid elements exist; the others encode as 0 (pad bits).
-template <int BITS, int GRID, bool PARTIAL>
+// CLAMP (level tables): whether the truncation of Eq. (1) is written out; see truncates_itself.
+template <int BITS, int GRID, bool PARTIAL, bool CLAMP = true>
 __device__ __forceinline__ uint32_t encode_group(const float (&x)[8], const uint32_t (&rw)[4], int n_valid,
                                                  float alpha, float inv_step, const float (&lv)[16],
                                                  const LevelLds& tab)
@@ -170,7 +171,7 @@ __device__ __forceinline__ uint32_t encode_group(const float (&x)[8], const uint
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const uint32_t r = (j & 1) ? (rw[j >> 1] >> 16) : (rw[j >> 1] & 0xFFFFu);
-            const float xc = __builtin_amdgcn_fmed3f(x[j], -alpha, alpha);   // Eq. (1); NaN is gone
+            const float xc = CLAMP ? __builtin_amdgcn_fmed3f(x[j], -alpha, alpha) : x[j];   // Eq. (1); NaN is gone
             uint32_t a = cell_offset<BITS>(xc, lv, tab);
             bool up = rounds_up(xc, (float)r, a, tab);
             if (PARTIAL && j >= n_valid) { a = 0; up = false; }
@@ -371,15 +372,15 @@ __device__ __forceinline__ void store_codes_wave(uint8_t* out, uint32_t word)
 //     cover a small window of the gradient: on 8 x 124 M fp32, 670 us (641 with the payload stored past the
 //     caches) with one tile per workgroup against 745 us with two, whether the two are requested
 //     together, one after the other, adjacent or far apart;
-//   * the level-table path sets up its codebook before the first read, once per workgroup: with one / two /
-//     four tiles 16 x 25.6 M fp32 at b = 3 take 370 / 323 / 325 us, with two / four / six 4 x 10^9 bf16 at
-//     b = 2 (a bf16 tile is half the bytes) 1970 / 1775 / 1819.
+//   * the level-table path sets up its codebook before the first read, once per workgroup, and needs reads in
+//     flight while it computes: with one / two / four tiles 16 x 25.6 M fp32 at b = 3 take 370 / 300 / 325 us, with two /
+//     four / six 4 x 10^9 bf16 at b = 2 (a bf16 tile is half the bytes) 1970 / 1775 / 1819.
 // The family is a property of the parameter records, which live on the device, so the host
 // chooses by the family the caller names (tq_compress's `grid`); the kernel itself reads every
 // bucket's record and computes what the record says, whatever shape it was launched in.
-constexpr int compress_tiles(int dtype, bool table_path)
+constexpr int compress_tiles(int dtype, bool table_tiles)
 {
-    return dtype == TQ_F32 ? (table_path ? 2 : 1) : (table_path ? 4 : 2);
+    return dtype == TQ_F32 ? (table_tiles ? 2 : 1) : (table_tiles ? 4 : 2);
 }
 
 // The same for segments, whose family the caller does not name: the level table's numbers.  One step of
@@ -395,27 +396,20 @@ struct Codebook {
     float pv[3];
 };
 
-// Reads the record and, for a level table, fills `cells` (one barrier).  EXPECT_TABLE: a launch shaped for
-// the level-table path reads the codebook before it knows the record's family.
-template <int BITS, bool EXPECT_TABLE>
+// Reads the record and, for a level table, fills `cells` (one barrier).  The codebook is read before the record's
+// family is known: the launch expects a level table.
+template <int BITS>
 __device__ __forceinline__ Codebook set_up_codebook(const tq_params_t* P, CellLds& cells, uint32_t lane)
 {
     Codebook cb;
     CellReads reads = {};
-    cb.pv[0] = cb.pv[1] = cb.pv[2] = 0.0f;
-    if constexpr (EXPECT_TABLE) {
-        if (lane < 64) reads = read_cells<BITS>(P, lane);
-        load_pivots<BITS>(P, cb.pv);
-    }
+    if (lane < 64) reads = read_cells<BITS>(P, lane);
+    load_pivots<BITS>(P, cb.pv);
     cb.alpha = P->alpha;
     cb.inv_step = P->inv_w[0];
     cb.nonuniform = P->grid != TQ_GRID_UNIFORM;
     cb.regular = true;
     if (cb.nonuniform) {
-        if constexpr (!EXPECT_TABLE) {
-            if (lane < 64) reads = read_cells<BITS>(P, lane);
-            load_pivots<BITS>(P, cb.pv);
-        }
         if (lane < 64) fill_cells<BITS>(cells, P, reads, cb.alpha, lane);
         // compared from vector registers: with a scalar operand the subtraction runs at 36 T/s, without at 59
         asm volatile("" : "+v"(cb.pv[0]), "+v"(cb.pv[1]), "+v"(cb.pv[2]));
@@ -452,7 +446,93 @@ __device__ __forceinline__ uint32_t encode_whole(const float (&x)[8], const uint
     return word;
 }
 
-template <int DTYPE, int BITS, bool STREAM, int T>
+// The general path's table: 16 scalar levels and, behind one barrier, the entries in LDS.
+template <int BITS>
+__device__ __forceinline__ void set_up_levels(const tq_params_t* P, LevelLds& tab, float (&lv)[16])
+{
+    fill_level_lds(tab, P, (1u << BITS) - 1u);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) lv[j] = P->level[j];           // wave-uniform: scalar loads
+    __syncthreads();
+}
+
+// Whether a level table encodes every value as it encodes the truncated one, so that Eq. (1) need not be written out
+// (one of 13 to 18 instructions per element: 16 x 25.6 M fp32 at b = 4 351 -> 344 us).  Below -alpha the cell is the
+// first one, not empty, and p_r < 0; beyond +alpha it is the last one and p_r at least the largest u, 1 - 2^-17, or 0
+// if it is empty (Inf times a zero reciprocal is NaN, and u <= NaN is false).
+template <int BITS>
+__device__ __forceinline__ bool truncates_itself(const tq_params_t* P, float alpha)
+{
+    constexpr int S = (1 << BITS) - 1;
+    const float first = P->level[0], last = P->level[S], inv = P->inv_w[S - 1];
+    const bool full = (last - P->level[S - 1]) * inv >= 1.0f - 7.62939453125e-06f;
+    return P->level[1] > first && first >= -alpha && P->inv_w[0] >= 0.0f && last <= alpha && (full || inv == 0.0f);
+}
+
+__device__ __forceinline__ Codebook read_codebook(const tq_params_t* P)
+{
+    Codebook cb;
+    cb.alpha = P->alpha;
+    cb.inv_step = P->inv_w[0];
+    cb.nonuniform = P->grid != TQ_GRID_UNIFORM;                // uniform over the workgroup
+    cb.regular = false;
+    cb.pv[0] = cb.pv[1] = cb.pv[2] = 0.0f;
+    return cb;
+}
+
+// A lane's whole group on the general path.
+template <int BITS, bool CLAMP>
+__device__ __forceinline__ uint32_t encode_general(const float (&x)[8], const uint32_t (&rw)[4], const Codebook& cb,
+                                                   const float (&lv)[16], const LevelLds& tab)
+{
+    return cb.nonuniform ? encode_group<BITS, TQ_GRID_NONUNIFORM, false, CLAMP>(x, rw, 8, cb.alpha, cb.inv_step, lv, tab)
+                         : encode_group<BITS, TQ_GRID_UNIFORM, false>(x, rw, 8, cb.alpha, cb.inv_step, lv, tab);
+}
+
+// N tiles from `base` on in which every lane owns a whole group: all reads first, the draws under them (requesting the
+// reads even earlier, before the codebook is set up, was slower: 708 us against 668 on 8 x 124 M fp32).
+template <int DTYPE, int BITS, bool STREAM, int N, typename Draw, typename Encode>
+__device__ __forceinline__ void encode_tiles(const void* g, uint8_t* payload, uint64_t base, uint32_t lane, Draw draw, Encode encode)
+{
+    float x[N][8];
+    uint32_t rw[N][4];
+#pragma unroll
+    for (int t = 0; t < N; ++t) load_group<DTYPE, STREAM>(g, base + (uint64_t)t * kTile + (uint64_t)lane * kGroup, x[t]);
+#pragma unroll
+    for (int t = 0; t < N; ++t) {
+        draw(base + (uint64_t)t * kTile, rw[t]);
+        asm volatile("" : "+v"(rw[t][0]));                     // computed here, under the loads
+    }
+#pragma unroll
+    for (int t = 0; t < N; ++t) {
+        replace_nan(x[t]);
+        const uint32_t word = encode(x[t], rw[t]);
+        store_codes_wave<BITS, !STREAM>(payload + (((base + (uint64_t)t * kTile) >> 3) + lane) * (uint64_t)BITS, word);
+    }
+}
+
+// A workgroup's T whole tiles on the general path.
+template <int DTYPE, int BITS, bool STREAM, int T, bool MIRROR, typename Draw>
+__device__ __forceinline__ void encode_tiles_general(const void* g, uint8_t* payload, uint64_t base, uint32_t lane, Draw draw,
+                                                     const tq_params_t* P, const Codebook& cb, const float (&lv)[16], const LevelLds& tab)
+{
+    auto clamped = [&](const float (&x)[8], const uint32_t (&rw)[4]) { return encode_general<BITS, true>(x, rw, cb, lv, tab); };
+    auto plain = [&](const float (&x)[8], const uint32_t (&rw)[4]) { return encode_general<BITS, false>(x, rw, cb, lv, tab); };
+    if constexpr (MIRROR) {                                    // two tiles at a time: no more registers than the mirrored path
+        constexpr int N = T < 2 ? T : 2;
+#pragma unroll 1
+        for (int t = 0; t < T; t += N) encode_tiles<DTYPE, BITS, STREAM, N>(g, payload, base + (uint64_t)t * kTile, lane, draw, clamped);
+    } else {
+        if (T == compress_tiles(DTYPE, true) && cb.nonuniform && truncates_itself<BITS>(P, cb.alpha))
+            encode_tiles<DTYPE, BITS, STREAM, T>(g, payload, base, lane, draw, plain);
+        else
+            encode_tiles<DTYPE, BITS, STREAM, T>(g, payload, base, lane, draw, clamped);
+    }
+}
+
+// MIRROR: level tables are checked for the mirrored path and take it if they are regular; else every record is
+// encoded on the general one.
+template <int DTYPE, int BITS, bool STREAM, int T, bool MIRROR>
 __global__ __launch_bounds__(kBlock) void tq_compress_kernel(
     const PtrTable g_tab, uint64_t d, uint64_t d_pad, uint64_t bucket_elems,
     uint32_t groups_per_bucket, const PtrTable params_tab, uint32_t seed_lo,
@@ -471,43 +551,31 @@ __global__ __launch_bounds__(kBlock) void tq_compress_kernel(
     uint8_t* __restrict__ payload = static_cast<uint8_t*>(payload_tab.p[blockIdx.y]);
     const uint32_t worker = first_worker + blockIdx.y;
     const tq_params_t* P = static_cast<const tq_params_t*>(params_tab.p[blockIdx.y]) + bucket;
-
-    __shared__ LevelLds tab;
-    __shared__ CellLds cells;
     const uint32_t lane = threadIdx.x;                         // this thread's group within a tile
-    const Codebook cb = set_up_codebook<BITS, T == compress_tiles(DTYPE, true)>(P, cells, lane);
-    const float alpha = cb.alpha, inv_step = cb.inv_step;
-    const bool nonuniform = cb.nonuniform;
     auto draw = [&](uint64_t ebase, uint32_t (&rw)[4]) { draw_tile(ebase, lane, worker, step, seed_lo, seed_hi, rw); };
 
     const uint64_t lim = bend < d ? bend : d;
-    if (cb.regular && gbase + (uint64_t)T * kTile <= lim) {
-        // every lane owns a whole group in every tile: all reads first, the draws under them
-        // (requesting the reads even earlier, before the codebook is set up, was slower: 708 us
-        // against 668 on 8 x 124 M fp32)
-        float x[T][8];
-        uint32_t rw[T][4];
-#pragma unroll
-        for (int t = 0; t < T; ++t) load_group<DTYPE, STREAM>(g, gbase + (uint64_t)t * kTile + (uint64_t)lane * kGroup, x[t]);
-#pragma unroll
-        for (int t = 0; t < T; ++t) {
-            draw(gbase + (uint64_t)t * kTile, rw[t]);
-            asm volatile("" : "+v"(rw[t][0]));                 // computed here, under the loads
+    const bool whole = gbase + (uint64_t)T * kTile <= lim;
+
+    Codebook cb;
+    if constexpr (MIRROR) {
+        __shared__ CellLds cells;
+        cb = set_up_codebook<BITS>(P, cells, lane);
+        if (cb.regular && whole) {
+            encode_tiles<DTYPE, BITS, STREAM, T>(g, payload, gbase, lane, draw, [&](const float (&x)[8], const uint32_t (&rw)[4]) {
+                return encode_whole<BITS>(x, rw, cb, cells);
+            });
+            return;
         }
-#pragma unroll
-        for (int t = 0; t < T; ++t) {
-            replace_nan(x[t]);
-            const uint32_t word = encode_whole<BITS>(x[t], rw[t], cb, cells);
-            store_codes_wave<BITS, !STREAM>(payload + (((gbase + (uint64_t)t * kTile) >> 3) + lane) * (uint64_t)BITS, word);
-        }
-        return;
+    } else {
+        cb = read_codebook(P);
     }
+    __shared__ LevelLds tab;
     float lv[16];
-    if (nonuniform) {
-        fill_level_lds(tab, P, (1u << BITS) - 1u);
-#pragma unroll
-        for (int j = 0; j < 16; ++j) lv[j] = P->level[j];       // wave-uniform: scalar loads
-        __syncthreads();
+    if (cb.nonuniform) set_up_levels<BITS>(P, tab, lv);
+    if (whole) {
+        encode_tiles_general<DTYPE, BITS, STREAM, T, MIRROR>(g, payload, gbase, lane, draw, P, cb, lv, tab);
+        return;
     }
 
     // the last workgroup of a bucket: tile by tile, lanes past the end idle, the tensor's
@@ -524,8 +592,7 @@ __global__ __launch_bounds__(kBlock) void tq_compress_kernel(
             uint32_t rw[4];
             draw(ebase, rw);
             replace_nan(x);
-            word = nonuniform ? encode_group<BITS, TQ_GRID_NONUNIFORM, false>(x, rw, 8, alpha, inv_step, lv, tab)
-                              : encode_group<BITS, TQ_GRID_UNIFORM, false>(x, rw, 8, alpha, inv_step, lv, tab);
+            word = encode_general<BITS, true>(x, rw, cb, lv, tab);
         } else if (e0 < d) {
             const int n_valid = (int)(d - e0);
             float x[8];
@@ -534,8 +601,8 @@ __global__ __launch_bounds__(kBlock) void tq_compress_kernel(
             uint32_t rw[4];
             draw(ebase, rw);
             replace_nan(x);
-            word = nonuniform ? encode_group<BITS, TQ_GRID_NONUNIFORM, true>(x, rw, n_valid, alpha, inv_step, lv, tab)
-                              : encode_group<BITS, TQ_GRID_UNIFORM, true>(x, rw, n_valid, alpha, inv_step, lv, tab);
+            word = cb.nonuniform ? encode_group<BITS, TQ_GRID_NONUNIFORM, true>(x, rw, n_valid, cb.alpha, cb.inv_step, lv, tab)
+                                 : encode_group<BITS, TQ_GRID_UNIFORM, true>(x, rw, n_valid, cb.alpha, cb.inv_step, lv, tab);
         }
         store_codes<BITS>(payload + byte_off, word, payload_bytes - byte_off);
     }
@@ -573,7 +640,7 @@ __global__ __launch_bounds__(kBlock) void tq_compress_segments_kernel(
         const uint64_t seg_hi = s0 + 1 < nseg ? seg_off[s0 + 1] : d_pad;
         const uint64_t gend = gbase + (uint64_t)T * kTile;
         if (seg_lo <= gbase && seg_hi >= gend && gend <= d) {  // whole groups, and their codes lie inside the payload
-            const Codebook cb = set_up_codebook<BITS, true>(params + s0, cells, lane);
+            const Codebook cb = set_up_codebook<BITS>(params + s0, cells, lane);
             if (cb.regular) {
                 float x[T][8];
                 uint32_t rw[T][4];
@@ -685,7 +752,7 @@ __global__ __launch_bounds__(kBlock) void tq_simulate_kernel(
     __shared__ float4 xbuf[kBlock / 64][128];                  // store8_wave's exchange buffers
     const uint32_t lane = threadIdx.x;
     if (lane >= 64 && lane < 80) levels[lane - 64] = P->level[lane - 64];
-    const Codebook cb = set_up_codebook<BITS, true>(P, cells, lane);
+    const Codebook cb = set_up_codebook<BITS>(P, cells, lane);
     if (!cb.nonuniform) __syncthreads();                       // a level table has had its barrier
 
     if (cb.regular && gbase + (uint64_t)T * kTile <= bend) {   // whole groups in every tile
@@ -763,27 +830,59 @@ bool compress_streams(int count, uint64_t d, int dtype)
     return (uint64_t)count * d * (dtype == TQ_F32 ? 4u : 2u) <= (512ull << 20);
 }
 
-template <int DTYPE, bool STREAM, int T>
-hipError_t launch(int bits, dim3 blocks, hipStream_t st, const tq::PtrTable& g, uint64_t d, uint64_t d_pad,
-                  uint64_t be, uint32_t tpb, const tq::PtrTable& params, uint64_t seed, uint32_t first_worker,
-                  uint32_t step, const tq::MutPtrTable& payload, uint64_t pbytes)
+// Whether level tables are checked for the mirrored path.  Its fewer instructions pay at b = 3 and, for bf16, at b = 2; the
+// general path otherwise reads a lighter table and starts sooner.  General / mirrored, us: 16 x 25.6 M fp32 at
+// b = 2 / 3 / 4 279 / 278, 326 / 300, 333 / 336, bf16 196 / 196, 263 / 227, 274 / 284; 11.2 M at b = 2 fp32 10.4 / 10.8,
+// bf16 8.9 / 8.5.
+constexpr bool mirrored_pays(int dtype, int bits) { return bits == 3 || (bits == 2 && dtype == TQ_BF16); }
+
+struct CompressShape { bool table_tiles, mirror; };
+
+// The shape of a launch of level tables.
+//   * Launches whose workgroups are all resident at once wait for latencies and take the tiles and the general path
+//     of the uniform codebook: up to 512 tiles (fp32) or 4096 (bf16; at b = 3 the mirrored path from 1024 on).  General
+//     with few tiles / general / mirrored with many, us: 250,000 fp32 at b = 3 2.9 / 3.5 / 3.4, 1.2 M 4.0 / 3.9 / 4.2,
+//     3 M 4.7 / 4.7 / 4.4; 1.2 M bf16 at b = 4 4.4 / 5.7 / 6.1, 8 M 8.3 / 8.9 / 9.0, 11.2 M at b = 3 10.0 / 10.9 / 9.1.
+//   * So do buckets shorter than a tile (fp32) or than four (bf16), of which every workgroup is a cut one: 25.6 M at b = 3
+//     in buckets of 1024 fp32 30.4 / 33.0 / 35.2, bf16 31.5 / 43.3 / 44.1, of 4096 bf16 20.3 / 23.2 / 23.1.
+CompressShape table_shape(int dtype, int bits, uint64_t bucket_elems, uint64_t all_tiles)
 {
-    const uint32_t slo = (uint32_t)seed, shi = (uint32_t)(seed >> 32);
-    const dim3 threads(tq::kBlock);
-    switch (bits) {
-        case 2:
-            hipLaunchKernelGGL((tq::tq_compress_kernel<DTYPE, 2, STREAM, T>), blocks, threads, 0, st, g, d, d_pad, be,
-                               tpb, params, slo, shi, first_worker, step, payload, pbytes);
-            break;
-        case 3:
-            hipLaunchKernelGGL((tq::tq_compress_kernel<DTYPE, 3, STREAM, T>), blocks, threads, 0, st, g, d, d_pad, be,
-                               tpb, params, slo, shi, first_worker, step, payload, pbytes);
-            break;
-        default:
-            hipLaunchKernelGGL((tq::tq_compress_kernel<DTYPE, 4, STREAM, T>), blocks, threads, 0, st, g, d, d_pad, be,
-                               tpb, params, slo, shi, first_worker, step, payload, pbytes);
-            break;
+    const bool f32 = dtype == TQ_F32;
+    if (bucket_elems < (f32 ? 1u : 4u) * (uint64_t)tq::kTile) return {false, false};
+    if (all_tiles <= (f32 ? 512u : 4096u)) return {false, !f32 && bits == 3 && all_tiles > 1024};
+    return {true, mirrored_pays(dtype, bits)};
+}
+
+struct CompressArgs {
+    dim3 blocks;
+    hipStream_t st;
+    tq::PtrTable g, params;
+    tq::MutPtrTable payload;
+    uint64_t d, d_pad, be, seed, pbytes;
+    uint32_t groups_per_bucket, first_worker, step;
+};
+
+template <int DTYPE, int BITS, bool STREAM, bool TABLE_TILES, bool MIRROR>
+void launch_as(const CompressArgs& a)
+{
+    hipLaunchKernelGGL((tq::tq_compress_kernel<DTYPE, BITS, STREAM, tq::compress_tiles(DTYPE, TABLE_TILES), MIRROR>), a.blocks,
+                       dim3(tq::kBlock), 0, a.st, a.g, a.d, a.d_pad, a.be, a.groups_per_bucket, a.params, (uint32_t)a.seed,
+                       (uint32_t)(a.seed >> 32), a.first_worker, a.step, a.payload, a.pbytes);
+}
+
+template <int DTYPE, int BITS, bool STREAM>
+hipError_t launch(const CompressShape& shape, const CompressArgs& a)
+{
+    if constexpr (mirrored_pays(DTYPE, BITS)) {
+        if (shape.mirror && shape.table_tiles) { launch_as<DTYPE, BITS, STREAM, true, true>(a); return hipGetLastError(); }
+        if constexpr (DTYPE == TQ_BF16 && BITS == 3) {
+            if (shape.mirror) { launch_as<DTYPE, BITS, STREAM, false, true>(a); return hipGetLastError(); }
+        }
+    } else if (shape.table_tiles) {
+        launch_as<DTYPE, BITS, STREAM, true, false>(a);
+        return hipGetLastError();
     }
+    launch_as<DTYPE, BITS, STREAM, false, false>(a);
     return hipGetLastError();
 }
 
@@ -799,31 +898,26 @@ hipError_t tq_launch_compress(const void* const* g, int count, int dtype, uint64
     const uint64_t d_pad = (d + 127) / 128 * 128;
     const uint64_t be = bucket_elems ? bucket_elems : d_pad;
     const uint64_t nb = (d_pad + be - 1) / be;
-    bool table_path = grid != TQ_GRID_UNIFORM;
     const uint64_t tiles = (be + tq::kTile - 1) / tq::kTile;                  // of a bucket
-    // A launch that is resident at once in the smaller shape (2048 workgroups, eight per compute unit) waits for
-    // latencies alone and takes it for tables too.  1.2 M elements: bf16 6.7 -> 5.7 us, fp32 at b = 2 5.1 ->
-    // 4.2; 5 M bf16 8.9 -> 8.1, but 5 M fp32 8.0 -> 8.2 and 10 M 12.0 -> 12.6 (2048 fp32 workgroups are 4.2 M).
-    const uint64_t all_tiles = nb * tiles * (uint64_t)(count < 1 ? 1 : count);
-    if (all_tiles <= 2048ull * (uint64_t)tq::compress_tiles(dtype, false)) table_path = false;
-    const uint64_t tt = (uint64_t)tq::compress_tiles(dtype, table_path);
-    const uint64_t tpb = (tiles + tt - 1) / tt;                               // workgroups per bucket
-    const uint64_t nblocks = nb * tpb;
-    dim3 blocks;
-    if (count < 1 || count > tq::kMaxBatch || !tq::fold_grid(nblocks, tq::kBlock, (unsigned)count, blocks))
+    CompressShape shape{false, false};
+    if (grid != TQ_GRID_UNIFORM) shape = table_shape(dtype, bits, be, nb * tiles * (uint64_t)(count < 1 ? 1 : count));
+    const uint64_t tt = (uint64_t)tq::compress_tiles(dtype, shape.table_tiles);
+    CompressArgs a{};
+    a.groups_per_bucket = (uint32_t)((tiles + tt - 1) / tt);
+    if (count < 1 || count > tq::kMaxBatch ||
+        !tq::fold_grid(nb * ((tiles + tt - 1) / tt), tq::kBlock, (unsigned)count, a.blocks))
         return hipErrorInvalidValue;
-    const uint64_t pbytes = tq_payload_bytes(d, bits);
-    tq::PtrTable gt{}, pt{};
-    tq::MutPtrTable yt{};
-    for (int i = 0; i < count; ++i) { gt.p[i] = g[i]; pt.p[i] = params[i]; yt.p[i] = payload[i]; }
+    for (int i = 0; i < count; ++i) { a.g.p[i] = g[i]; a.params.p[i] = params[i]; a.payload.p[i] = payload[i]; }
+    a.st = st;
+    a.d = d; a.d_pad = d_pad; a.be = be; a.seed = seed;
+    a.pbytes = tq_payload_bytes(d, bits);
+    a.first_worker = first_worker; a.step = step;
     const bool stream = compress_streams(count, d, dtype);
-#define TQ_LAUNCH_COMPRESS(DT, ST, TP) \
-    launch<DT, ST, tq::compress_tiles(DT, TP)>(bits, blocks, st, gt, d, d_pad, be, (uint32_t)tpb, pt, seed, \
-                                               first_worker, step, yt, pbytes)
-#define TQ_LAUNCH_COMPRESS_ST(DT, TP) (stream ? TQ_LAUNCH_COMPRESS(DT, true, TP) : TQ_LAUNCH_COMPRESS(DT, false, TP))
-    if (dtype == TQ_F32) return table_path ? TQ_LAUNCH_COMPRESS_ST(TQ_F32, true) : TQ_LAUNCH_COMPRESS_ST(TQ_F32, false);
-    return table_path ? TQ_LAUNCH_COMPRESS_ST(TQ_BF16, true) : TQ_LAUNCH_COMPRESS_ST(TQ_BF16, false);
-#undef TQ_LAUNCH_COMPRESS_ST
+#define TQ_LAUNCH_COMPRESS(DT, B) (stream ? launch<DT, B, true>(shape, a) : launch<DT, B, false>(shape, a))
+#define TQ_LAUNCH_COMPRESS_B(DT) \
+    (bits == 2 ? TQ_LAUNCH_COMPRESS(DT, 2) : (bits == 3 ? TQ_LAUNCH_COMPRESS(DT, 3) : TQ_LAUNCH_COMPRESS(DT, 4)))
+    return dtype == TQ_F32 ? TQ_LAUNCH_COMPRESS_B(TQ_F32) : TQ_LAUNCH_COMPRESS_B(TQ_BF16);
+#undef TQ_LAUNCH_COMPRESS_B
 #undef TQ_LAUNCH_COMPRESS
 }
 

@@ -217,11 +217,13 @@ def test_the_family_named_to_tq_compress_shapes_the_launch_only(wl, dtype_name, 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("bits", [2, 3, 4])
-@pytest.mark.parametrize("kind", ["mirrored", "ulps", "lopsided", "reciprocals", "far", "alpha inside"])
+@pytest.mark.parametrize("kind", ["mirrored", "ulps", "lopsided", "reciprocals", "far", "alpha inside", "empty ends",
+                                  "short last"])
 def test_codebooks_on_both_sides_of_the_mirrored_path(kind, bits, dtype):
     """Designed codebooks mirror their levels about 0 and take a path of their own.  Codebooks that do so
     exactly, to within ulps of a level, not at all, with reciprocals that do not fit their cells, with
-    levels far apart, and with levels beyond alpha: many draws of every value at and next to a level of either sign, codes equal to the
+    levels far apart, with levels beyond alpha, with empty outer cells and with a last cell whose reciprocal
+    does not reach 1 at its end: many draws of every value at and next to a level of either sign, codes equal to the
     oracle's."""
     s = (1 << bits) - 1
     rng = np.random.default_rng(bits * 10 + len(kind))
@@ -237,6 +239,12 @@ def test_codebooks_on_both_sides_of_the_mirrored_path(kind, bits, dtype):
     if kind == "reciprocals":
         inv[s // 2] *= np.float32(1.0 - 2.0 ** -10)
         inv[0] *= np.float32(1.0 + 2.0 ** -9)
+    if kind == "empty ends":
+        lv[1], lv[s - 1] = lv[0], lv[s]
+        width = np.diff(lv.astype(np.float64))
+        inv = np.where(width > 0, 1.0 / np.where(width > 0, width, 1.0), 0.0).astype(np.float32)
+    if kind == "short last":
+        inv[s - 1] *= np.float32(1.0 - 2.0 ** -7)
     P = np.zeros(1, dtype=O.PARAMS_DTYPE)
     P["alpha"], P["bits"], P["s"], P["grid"] = lv[-1], bits, s, O.GRID_NONUNIFORM
     P["level"][0, : s + 1], P["inv_w"][0, :s] = lv, inv
@@ -251,7 +259,7 @@ def test_codebooks_on_both_sides_of_the_mirrored_path(kind, bits, dtype):
     g[::5] = rng.uniform(-1.1, 1.1, g[::5].size).astype(np.float32) * lv[-1]
     tens = torch.from_numpy(g).to(dtype)
     g_np = tens.view(torch.int16).numpy().view("uint16") if dtype == torch.bfloat16 else tens.numpy()
-    for seed, n in ((3, d), (77, 40 * 8192 + 333)):                # ... and of small ones
+    for seed, n in ((3, d), (5, 300 * 8192 + 333), (77, 40 * 8192 + 333)):   # ... of ordinary and of small ones
         got = device_compress(tens[:n].cuda(), P, bits, seed, 1, 5).cpu().numpy()
         assert (got == O.compress(g_np[:n], P, seed, 1, 5, threads=16)).all()
 
@@ -305,3 +313,22 @@ def test_both_shapes_of_the_table_launch_write_the_same_bytes(cut, bits, dtype):
     want = O.compress(gs[1].view(torch.int16).cpu().numpy().view("uint16") if dtype == torch.bfloat16 else gs[1].cpu().numpy(),
                       B.params_to_numpy(params[1]).view(O.PARAMS_DTYPE), 12, 1, 3)
     assert (many[1][:nbytes].cpu().numpy() == want).all()
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("bucket", [128, 1920, 2048, 4096 + 128, 8192 - 128, 8192])
+def test_short_buckets_of_large_tensors(bucket, bits, dtype):
+    """Buckets on both sides of the lengths below which a level table's launch takes the smaller shape."""
+    d = 1100 * 8192 + 77
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(bucket + bits)
+    g = torch.randn(d, generator=gen, device="cuda").to(dtype)
+    stats, params = B.alloc_stats(d, bucket), B.alloc_params(d, bucket)
+    B.tq_stats(g, stats, B.alloc_stats_workspace(d, bucket), bucket)
+    B.tq_params(stats, params, bits, B.GRID_NONUNIFORM)
+    pay = B.alloc_payload(d, bits).fill_(0xA5)
+    B.tq_compress(g, params, pay, bits, 12, 1, 3, bucket, B.GRID_NONUNIFORM)
+    want = O.compress(g.view(torch.int16).cpu().numpy().view("uint16") if dtype == torch.bfloat16 else g.cpu().numpy(),
+                      B.params_to_numpy(params).view(O.PARAMS_DTYPE), 12, 1, 3, bucket_elems=bucket, threads=16)
+    assert (pay.cpu().numpy() == want).all()

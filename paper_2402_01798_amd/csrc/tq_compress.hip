@@ -385,9 +385,9 @@ constexpr int compress_tiles(int dtype, bool table_tiles)
 
 // The same for segments, whose family the caller does not name: the level table's numbers.  One step of
 // 8 x 124 M with 68 layers, one (two at bf16) / two (four) / three / four (six) tiles: fp32 b = 2 tables 1605 / 1555 /
-// 1566 / 1577 us and 1679 before the mirrored path, b = 3 1866 / 1688 / 1671 / 1663 (1941), bf16 b = 2 1088 / 1013 /
-// 1035 / 1003 (1342); fp32 b = 2 uniform 1497 / 1529 / 1600 / 1586 (1593).
-constexpr int segment_tiles(int dtype) { return dtype == TQ_F32 ? 2 : 4; }
+// 1566 / 1577 us, b = 3 1866 / 1688 / 1671 / 1663, bf16 b = 2 1088 / 1013 / 1035 / 1003; fp32 b = 2 uniform
+// 1497 / 1529 / 1600 / 1586.
+constexpr int segment_tiles(int dtype) { return compress_tiles(dtype, true); }
 
 // What a workgroup knows of its record.
 struct Codebook {
@@ -616,7 +616,7 @@ __global__ __launch_bounds__(kBlock) void tq_compress_kernel(
 // one, the offsets being multiples of 128).  The last segment also owns the
 // padding up to a multiple of 128 elements.  No access depends on the table being well-formed:
 // the segment index stays inside [0, nseg) and every element access is bounded by d.
-template <int DTYPE, int BITS, bool STREAM, int T>
+template <int DTYPE, int BITS, bool STREAM, int T, bool MIRROR>
 __global__ __launch_bounds__(kBlock) void tq_compress_segments_kernel(
     const PtrTable g_tab, uint64_t d, uint64_t d_pad, const uint64_t* __restrict__ seg_off, uint32_t nseg,
     const SegHints hints, const PtrTable params_tab, uint32_t seed_lo, uint32_t seed_hi, uint32_t first_worker, uint32_t step,
@@ -631,7 +631,24 @@ __global__ __launch_bounds__(kBlock) void tq_compress_segments_kernel(
     const uint32_t worker = first_worker + blockIdx.y;
     const uint32_t lane = threadIdx.x;
     __shared__ LevelLds tab;
-    __shared__ CellLds cells;
+    auto draw = [&](uint64_t ebase, uint32_t (&rw)[4]) { draw_tile(ebase, lane, worker, step, seed_lo, seed_hi, rw); };
+
+    // One tile: the values are requested and the draws computed before the segment is looked up, a chain of
+    // dependent scalar loads (they depend on the lane's position alone).
+    float x[8];
+    uint32_t rw[4];
+    auto request = [&](uint64_t ebase) {
+        const uint64_t e0 = ebase + (uint64_t)lane * kGroup;
+        if (e0 + kGroup <= d) {
+            load_group<DTYPE, false>(g, e0, x);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x[j] = e0 + j < d ? load_one<DTYPE>(g, e0 + j) : 0.0f;
+        }
+        draw(ebase, rw);
+        asm volatile("" : "+v"(rw[0]));                        // computed here, under the loads
+    };
+    if constexpr (T == 1) request(gbase);
 
     const uint32_t s0 = find_segment(seg_off, nseg, gbase < d ? gbase : d - 1, hints);
     {
@@ -640,25 +657,29 @@ __global__ __launch_bounds__(kBlock) void tq_compress_segments_kernel(
         const uint64_t seg_hi = s0 + 1 < nseg ? seg_off[s0 + 1] : d_pad;
         const uint64_t gend = gbase + (uint64_t)T * kTile;
         if (seg_lo <= gbase && seg_hi >= gend && gend <= d) {  // whole groups, and their codes lie inside the payload
-            const Codebook cb = set_up_codebook<BITS>(params + s0, cells, lane);
-            if (cb.regular) {
-                float x[T][8];
-                uint32_t rw[T][4];
-#pragma unroll
-                for (int t = 0; t < T; ++t) load_group<DTYPE, STREAM>(g, gbase + (uint64_t)t * kTile + (uint64_t)lane * kGroup, x[t]);
-#pragma unroll
-                for (int t = 0; t < T; ++t) {
-                    draw_tile(gbase + (uint64_t)t * kTile, lane, worker, step, seed_lo, seed_hi, rw[t]);
-                    asm volatile("" : "+v"(rw[t][0]));         // computed here, under the loads
+            const tq_params_t* P = params + s0;
+            Codebook cb;
+            if constexpr (MIRROR) {
+                __shared__ CellLds cells;
+                cb = set_up_codebook<BITS>(P, cells, lane);
+                if (cb.regular) {
+                    encode_tiles<DTYPE, BITS, STREAM, T>(g, payload, gbase, lane, draw, [&](const float (&v)[8], const uint32_t (&r)[4]) {
+                        return encode_whole<BITS>(v, r, cb, cells);
+                    });
+                    return;
                 }
-#pragma unroll
-                for (int t = 0; t < T; ++t) {
-                    replace_nan(x[t]);
-                    const uint32_t word = encode_whole<BITS>(x[t], rw[t], cb, cells);
-                    store_codes_wave<BITS, !STREAM>(payload + (((gbase + (uint64_t)t * kTile) >> 3) + lane) * (uint64_t)BITS, word);
-                }
-                return;
+            } else {
+                cb = read_codebook(P);
             }
+            float lv[16];
+            if (cb.nonuniform) set_up_levels<BITS>(P, tab, lv);
+            if constexpr (T == 1) {
+                replace_nan(x);
+                store_codes_wave<BITS, !STREAM>(payload + ((gbase >> 3) + lane) * (uint64_t)BITS, encode_general<BITS, true>(x, rw, cb, lv, tab));
+            } else {
+                encode_tiles_general<DTYPE, BITS, STREAM, T, MIRROR>(g, payload, gbase, lane, draw, P, cb, lv, tab);
+            }
+            return;
         }
     }
     for (int t = 0; t < T; ++t) {
@@ -674,15 +695,7 @@ __global__ __launch_bounds__(kBlock) void tq_compress_segments_kernel(
             tile_byte < payload_bytes ? (uint32_t)(payload_bytes - tile_byte < (uint64_t)kTile ? payload_bytes - tile_byte : kTile) : 0u;
         const uint32_t byte_rel = lane * (uint32_t)BITS;
         const int n_valid = rel >= d_rel ? 0 : (d_rel - rel >= (uint32_t)kGroup ? kGroup : (int)(d_rel - rel));
-        float x[8];
-        if (n_valid == kGroup) {
-            load_group<DTYPE, false>(g, ebase + rel, x);
-        } else {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) x[j] = (j < n_valid) ? load_one<DTYPE>(g, ebase + rel + j) : 0.0f;
-        }
-        uint32_t rw[4];
-        draw_tile(ebase, lane, worker, step, seed_lo, seed_hi, rw);
+        if constexpr (T > 1) request(ebase);
         uint32_t s = t == 0 ? s0 : find_segment(seg_off, nseg, ebase < d ? ebase : d - 1, hints);
         replace_nan(x);
         for (;;) {
@@ -699,7 +712,7 @@ __global__ __launch_bounds__(kBlock) void tq_compress_segments_kernel(
             if (nonuniform) {
                 __syncthreads();                               // the table of the segment before is done with
                 fill_level_lds(tab, P, (1u << BITS) - 1u);
-    #pragma unroll
+#pragma unroll
                 for (int j = 0; j < 16; ++j) lv[j] = P->level[j];   // wave-uniform: scalar loads
                 __syncthreads();
             }
@@ -960,13 +973,31 @@ hipError_t tq_launch_simulate(const void* g, int dtype, uint64_t d, uint64_t buc
 }
 
 
+namespace {
+
+// One tile per workgroup, requested before its segment is looked up, on the general path; else two (fp32) or four.
+//   * Launches that are resident at once: 61,706 fp32 at b = 3 4.2 us against 5.2, bf16 4.3 against 8.3; 3 M fp32 5.6 / 6.2,
+//     5 M 8.7 / 8.6; 11.2 M bf16 in segments of 20,000 13.1 / 16.1, of 10^6 11.6 / 13.3, 25.6 M 28.1 / 27.1 and 23.7 / 20.2.
+//   * Segments so short that most larger ranges are cut and taken tile by tile: 124 M in segments of 5000 at b = 2 fp32 154 /
+//     164, bf16 144 / 151, at b = 3 bf16 176 / 190, but fp32 178 / 163 and at b = 4 205 / 187 and 204 / 193; of 20,000 at
+//     b = 2 121 / 109 and 114 / 86.
+bool segments_one_tile(int count, int dtype, int bits, uint64_t d, uint64_t nseg)
+{
+    const uint64_t tiles = (uint64_t)(count < 1 ? 1 : count) * ((d + tq::kTile - 1) / tq::kTile);
+    if (tiles <= (dtype == TQ_F32 ? 2048u : 8192u)) return true;
+    return d / nseg < 12288 && (bits == 2 || (bits == 3 && dtype == TQ_BF16));
+}
+
+}  // namespace
+
 // Host side of tq_compress_segments after the argument checks of the C entry point.
 hipError_t tq_launch_compress_segments(const void* const* g, int count, int dtype, uint64_t d, const uint64_t* seg_off,
                                        const uint64_t* seg_host, uint64_t nseg, const tq_params_t* const* params, int bits, uint64_t seed,
                                        uint32_t first_worker, uint32_t step, void* const* payload, hipStream_t st)
 {
     const uint64_t d_pad = (d + 127) / 128 * 128;
-    const uint64_t range = (uint64_t)tq::segment_tiles(dtype) * tq::kTile;        // elements per workgroup
+    const bool one_tile = segments_one_tile(count, dtype, bits, d, nseg);
+    const uint64_t range = (one_tile ? 1u : (uint64_t)tq::segment_tiles(dtype)) * tq::kTile;        // elements per workgroup
     const uint64_t nblocks = (d_pad + range - 1) / range;
     dim3 blocks;
     if (count < 1 || count > tq::kMaxBatch || nseg > 0xFFFFFFFFull ||
@@ -980,10 +1011,15 @@ hipError_t tq_launch_compress_segments(const void* const* g, int count, int dtyp
     const dim3 threads(tq::kBlock);
     const tq::SegHints hints = tq::make_seg_hints(seg_host, nseg, d);
     const bool stream = compress_streams(count, d, dtype);
-#define TQ_LAUNCH_CSEG(DT, B, ST)                                                                               \
-    hipLaunchKernelGGL((tq::tq_compress_segments_kernel<DT, B, ST, tq::segment_tiles(DT)>), blocks, threads, 0, st, gt, d, \
+#define TQ_LAUNCH_CSEG(DT, B, ST, T, MI)                                                                        \
+    hipLaunchKernelGGL((tq::tq_compress_segments_kernel<DT, B, ST, T, MI>), blocks, threads, 0, st, gt, d,      \
                        d_pad, seg_off, (uint32_t)nseg, hints, pt, slo, shi, first_worker, step, yt, pbytes)
-#define TQ_LAUNCH_CSEG_ST(DT, B) if (stream) TQ_LAUNCH_CSEG(DT, B, true); else TQ_LAUNCH_CSEG(DT, B, false)
+#define TQ_LAUNCH_CSEG_T(DT, B, ST)                                                                    \
+    do {                                                                                               \
+        if (one_tile) TQ_LAUNCH_CSEG(DT, B, ST, 1, false);                                             \
+        else TQ_LAUNCH_CSEG(DT, B, ST, tq::segment_tiles(DT), mirrored_pays(DT, B));                   \
+    } while (0)
+#define TQ_LAUNCH_CSEG_ST(DT, B) if (stream) TQ_LAUNCH_CSEG_T(DT, B, true); else TQ_LAUNCH_CSEG_T(DT, B, false)
 #define TQ_LAUNCH_CSEG_B(DT)                         \
     switch (bits) {                                  \
         case 2: TQ_LAUNCH_CSEG_ST(DT, 2); break;     \
@@ -993,6 +1029,7 @@ hipError_t tq_launch_compress_segments(const void* const* g, int count, int dtyp
     if (dtype == TQ_F32) { TQ_LAUNCH_CSEG_B(TQ_F32) } else { TQ_LAUNCH_CSEG_B(TQ_BF16) }
 #undef TQ_LAUNCH_CSEG_B
 #undef TQ_LAUNCH_CSEG_ST
+#undef TQ_LAUNCH_CSEG_T
 #undef TQ_LAUNCH_CSEG
     return hipGetLastError();
 }

@@ -166,11 +166,12 @@ def test_more_workers_than_the_fast_decode_takes():
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("bits", [2, 3, 4])
-def test_segment_ends_next_to_workgroup_ranges_and_mixed_codebooks(bits, dtype):
+def test_segment_ends_next_to_workgroup_ranges_and_mixed_codebooks(bits, dtype, front=0):
     """Compression takes ranges of 4096 (fp32) or 8192 (bf16) elements: segments that end on a range's
     end, 128 elements before and behind it and on a tile inside it, of uniform codebooks, mirrored tables
     and tables that do not mirror, side by side; the payload equal to the oracle's."""
     ends = [128, 2048, 4096, 8192 - 128, 16384, 16384 + 128, 24576, 24576 + 2048, 32768 + 128, 49152, 57344 + 40]
+    ends = [front + e for e in ends]
     seg = B.Segments(np.array([0] + ends, dtype=np.uint64))
     s, d = (1 << bits) - 1, ends[-1]
     rng = np.random.default_rng(bits)
@@ -195,3 +196,32 @@ def test_segment_ends_next_to_workgroup_ranges_and_mixed_codebooks(bits, dtype):
     pay = B.alloc_payload(d, bits).fill_(0xA5)
     B.tq_compress_segments(g.cuda(), seg, B.params_from_numpy(P), pay, bits, 9, 2, 4)
     assert (pay.cpu().numpy() == O.compress_segments(g_np, seg.host, P, 9, 2, 4)).all()
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("bits", [2, 3, 4])
+def test_segment_ends_at_the_end_of_a_large_tensor(bits, dtype):
+    """The same ends behind a first segment of 17 M elements: small launches take one tile per workgroup,
+    large ones two or four."""
+    test_segment_ends_next_to_workgroup_ranges_and_mixed_codebooks(bits, dtype, front=2100 * 8192)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("size", [1152, 12_288 - 128, 12_288 + 128])
+def test_many_segments_on_both_sides_of_the_length_that_picks_the_shape(size, bits, dtype):
+    d = 8400 * 2048 + 5
+    seg = B.Segments(np.array(list(range(0, d - size, size)) + [d], dtype=np.uint64))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(size + bits)
+    g = torch.randn(d, generator=gen, device="cuda").to(dtype)
+    stats = torch.empty(seg.nseg * B.STATS_BYTES, dtype=torch.uint8, device="cuda")
+    params = torch.empty(seg.nseg * B.PARAMS_BYTES, dtype=torch.uint8, device="cuda")
+    ws = torch.empty(B.stats_segments_workspace_bytes(d, seg.nseg), dtype=torch.uint8, device="cuda")
+    B.tq_stats_segments(g, seg, stats, ws)
+    B.tq_params(stats, params, bits, B.GRID_NONUNIFORM)
+    pay = B.alloc_payload(d, bits).fill_(0xA5)
+    B.tq_compress_segments(g, seg, params, pay, bits, 9, 2, 4)
+    g_np = g.view(torch.int16).cpu().numpy().view("uint16") if dtype == torch.bfloat16 else g.cpu().numpy()
+    want = O.compress_segments(g_np, seg.host, B.params_to_numpy(params).view(O.PARAMS_DTYPE), 9, 2, 4)
+    assert (pay.cpu().numpy() == want).all()

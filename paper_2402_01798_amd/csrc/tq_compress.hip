@@ -217,7 +217,6 @@ __device__ __forceinline__ uint32_t encode_group(const float (&x)[8], const uint
 // the second 1640 / 1625, with both left out 307 / 1618 -- the pattern of its memory traffic.
 struct CellLds {
     float4 e[16];            // entry neg * H + (H - 1 - i): cell m + i (x >= 0) or m - i, H = 2^(b-1), m = H - 1
-    float4 pivots[4];        // b = 4: entry 2 * neg + [|x| < l_11]: l_8, l_9, l_10 or l_12, l_13, l_14
     uint32_t regular;
 };
 
@@ -237,7 +236,7 @@ __device__ __forceinline__ CellReads read_cells(const tq_params_t* P, uint32_t l
 
 // Called by one whole wavefront (lane = its lane).
 template <int BITS>
-__device__ __forceinline__ void fill_cells(CellLds& tab, const tq_params_t* P, const CellReads& c, float alpha, uint32_t lane)
+__device__ __forceinline__ void fill_cells(CellLds& tab, const CellReads& c, float alpha, uint32_t lane)
 {
     constexpr uint32_t H = 1u << (BITS - 1), M = H - 1;
     const uint32_t j = lane & (2u * H - 1u), i = H - 1u - (j & (H - 1u));
@@ -252,12 +251,6 @@ __device__ __forceinline__ void fill_cells(CellLds& tab, const tq_params_t* P, c
     if (lane < 2u * H)
         tab.e[j] = make_float4(c.l, c.inv * (float)(1u << (32 - BITS)),
                                __uint_as_float((k << (32 - BITS)) + (1u << (15 - BITS))), 0.0f);
-    if constexpr (BITS == 4) {
-        if (lane < 4u) {
-            const float* q = P->level + ((lane & 1u) ? 8 : 12);
-            tab.pivots[lane] = make_float4(q[0], q[1], q[2], 0.0f);
-        }
-    }
     const bool regular = __builtin_amdgcn_ballot_w64(!ok) == 0ull;
     if (lane == 0) tab.regular = regular ? 1u : 0u;
 }
@@ -277,14 +270,8 @@ __device__ __forceinline__ uint32_t code_on_top(float x, uint32_t rw, const floa
     if constexpr (BITS == 2) {
         index = push_sign(index, y - pv[0]);
     } else {
-        float p0 = pv[0], p1 = pv[1], p2 = pv[2];
-        if constexpr (BITS == 4) {
-            index = push_sign(index, y - pv[0]);
-            const float4 q = tab.pivots[index];
-            p0 = q.x; p1 = q.y; p2 = q.z;
-        }
-        // |x| below p0 / p1 / p2: the two index bits are [below p1] and, of the three signs, their parity
-        const float d0 = y - p0, d1 = y - p1, d2 = y - p2;
+        // |x| below l_4 / l_5 / l_6: the two index bits are [below l_5] and, of the three signs, their parity
+        const float d0 = y - pv[0], d1 = y - pv[1], d2 = y - pv[2];
         index = push_sign(index, d1);
         index = push_sign(index, __uint_as_float(xor3(__float_as_uint(d0), __float_as_uint(d1), __float_as_uint(d2))));
     }
@@ -320,8 +307,7 @@ template <int BITS>
 __device__ __forceinline__ void load_pivots(const tq_params_t* P, float (&pv)[3])
 {
     if constexpr (BITS == 2) { pv[0] = P->level[2]; pv[1] = pv[2] = 0.0f; }
-    else if constexpr (BITS == 3) { pv[0] = P->level[4]; pv[1] = P->level[5]; pv[2] = P->level[6]; }
-    else { pv[0] = P->level[11]; pv[1] = pv[2] = 0.0f; }
+    else { pv[0] = P->level[4]; pv[1] = P->level[5]; pv[2] = P->level[6]; }
 }
 
 // `room` = bytes of the payload from `out` on.  A payload is a multiple of 16 bytes, so a
@@ -410,7 +396,7 @@ __device__ __forceinline__ Codebook set_up_codebook(const tq_params_t* P, CellLd
     cb.nonuniform = P->grid != TQ_GRID_UNIFORM;
     cb.regular = true;
     if (cb.nonuniform) {
-        if (lane < 64) fill_cells<BITS>(cells, P, reads, cb.alpha, lane);
+        if (lane < 64) fill_cells<BITS>(cells, reads, cb.alpha, lane);
         // compared from vector registers: with a scalar operand the subtraction runs at 36 T/s, without at 59
         asm volatile("" : "+v"(cb.pv[0]), "+v"(cb.pv[1]), "+v"(cb.pv[2]));
         __syncthreads();
@@ -734,14 +720,13 @@ __global__ __launch_bounds__(kBlock) void tq_compress_segments_kernel(
 
 // tq_quantize_dequantize: out[e] = Q[T_alpha(g[e])] as the server would reconstruct it from
 // this worker's message (the level of the code tq_compress_kernel would have written: same
-// draws, same arithmetic), without the round trip through a payload.  T tiles per workgroup, the
-// encoding of the compress kernel, and the decode kernel's whole-line stores, past the caches if the
-// output is large (PAST_CACHES; never when accumulating).  Bound by its memory traffic and, at 25 M elements, by
-// filling and draining the chip.  One / two / four tiles at bf16, 25.6 M elements at b = 3: 30.6 / 30.0 / 32.1 us
-// (32.2 with half-line stores, compares and one tile); fp32 one / two / three 37.2 / 38.5 / 39.9 (38.2);
-// 124 M bf16 136.5 -> 121.
-constexpr int simulate_tiles(int dtype) { return dtype == TQ_F32 ? 1 : 2; }
-
+// draws, same arithmetic), without the round trip through a payload.  T tiles per workgroup, the compress kernel's
+// general path, and the decode kernel's whole-line stores wherever a whole wavefront has whole
+// groups: past the caches if the output is large (PAST_CACHES), except that large sums are stored a lane's 32 bytes at
+// a time, into lines that were just read.  Bound by its memory traffic and, at 25 M elements, by filling and draining the
+// chip.  The mirrored path of the compress kernel, half-line stores / this: 61,706 fp32 at b = 3 3.8 / 3.4 / 2.9 us, 25.6 M
+// bf16 24.4 / 26.1 / 24.5, accumulating 37.5 / 40.1 / 37.3, in buckets of 1024 64 / 31.6 / 31.1, 124 M bf16 104 / 138 / 103.5;
+// 124 M fp32 accumulating 268 with whole lines, 260 without, bf16 220 both, 11.2 M bf16 17.0 / 18.0.
 template <int DTYPE, int BITS, bool ACC, bool PAST_CACHES, int T>
 __global__ __launch_bounds__(kBlock) void tq_simulate_kernel(
     const void* __restrict__ g, uint64_t d, uint64_t d_pad, uint64_t bucket_elems, uint32_t groups_per_bucket,
@@ -759,75 +744,71 @@ __global__ __launch_bounds__(kBlock) void tq_simulate_kernel(
     if (gbase >= bend) return;
     const tq_params_t* P = params + bucket;
 
-    __shared__ LevelLds tab;                                   // the general path's table
-    __shared__ CellLds cells;
-    __shared__ float levels[16];                               // what a code stands for
+    __shared__ LevelLds tab;                                   // the table, and what a code stands for
     __shared__ float4 xbuf[kBlock / 64][128];                  // store8_wave's exchange buffers
-    const uint32_t lane = threadIdx.x;
-    if (lane >= 64 && lane < 80) levels[lane - 64] = P->level[lane - 64];
-    const Codebook cb = set_up_codebook<BITS>(P, cells, lane);
-    if (!cb.nonuniform) __syncthreads();                       // a level table has had its barrier
-
-    if (cb.regular && gbase + (uint64_t)T * kTile <= bend) {   // whole groups in every tile
-        float x[T][8];
-        uint32_t rw[T][4];
-#pragma unroll
-        for (int t = 0; t < T; ++t) load_group<DTYPE, false>(g, gbase + (uint64_t)t * kTile + (uint64_t)lane * kGroup, x[t]);
-#pragma unroll
-        for (int t = 0; t < T; ++t) {
-            draw_tile(gbase + (uint64_t)t * kTile, lane, worker, step, seed_lo, seed_hi, rw[t]);
-            asm volatile("" : "+v"(rw[t][0]));                 // computed here, under the loads
-        }
-#pragma unroll
-        for (int t = 0; t < T; ++t) {
-            const uint64_t e0 = gbase + (uint64_t)t * kTile + (uint64_t)lane * kGroup;
-            replace_nan(x[t]);
-            const uint32_t word = encode_whole<BITS>(x[t], rw[t], cb, cells);
-            float y[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) y[j] = levels[(word >> (j * BITS)) & S];
-            if constexpr (ACC) {
-                const float4* o4 = reinterpret_cast<const float4*>(out + e0);
-                const float4 pa = o4[0], pb = o4[1];
-                y[0] = pa.x + y[0]; y[1] = pa.y + y[1]; y[2] = pa.z + y[2]; y[3] = pa.w + y[3];
-                y[4] = pb.x + y[4]; y[5] = pb.y + y[5]; y[6] = pb.z + y[6]; y[7] = pb.w + y[7];
-            }
-            store8_wave<PAST_CACHES>(out + e0 - (uint64_t)(lane & 63u) * kGroup, (int)(lane & 63u), y, xbuf[lane >> 6]);
-        }
-        return;
-    }
-
-    // the last workgroup of a bucket, and codebooks that are not regular: tile by tile
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    const Codebook cb = read_codebook(P);
     float lv[16];
-    if (cb.nonuniform) {
-        fill_level_lds(tab, P, S);
+    set_up_levels<BITS>(P, tab, lv);
+    const uint64_t wave_base = gbase + (uint64_t)wave * (64 * kGroup);    // this wavefront's part of the first tile
+    if (wave_base >= bend) return;                             // and of the others
+
+    // all reads first, the draws under them
+    float x[T][8], prev[T][8];
+    uint32_t rw[T][4];
+    auto load_prev = [&](int t) {
+        const uint64_t e0 = wave_base + (uint64_t)t * kTile + (uint64_t)lane * kGroup;
+        if (e0 + kGroup <= bend) {
+            const float4* o4 = reinterpret_cast<const float4*>(out + e0);
+            const float4 a = o4[0], b = o4[1];
+            prev[t][0] = a.x; prev[t][1] = a.y; prev[t][2] = a.z; prev[t][3] = a.w;
+            prev[t][4] = b.x; prev[t][5] = b.y; prev[t][6] = b.z; prev[t][7] = b.w;
+        } else if (e0 < bend) {
 #pragma unroll
-        for (int j = 0; j < 16; ++j) lv[j] = P->level[j];       // wave-uniform: scalar loads
-        __syncthreads();
-    }
-    for (int t = 0; t < T; ++t) {
-        const uint64_t ebase = gbase + (uint64_t)t * kTile;
-        const uint64_t e0 = ebase + (uint64_t)lane * kGroup;
-        if (e0 >= bend) continue;
-        const int n_valid = bend - e0 >= (uint64_t)kGroup ? kGroup : (int)(bend - e0);
-        float x[8];
-        if (n_valid == kGroup) {
-            load_group<DTYPE, false>(g, e0, x);
-        } else {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) x[j] = (j < n_valid) ? load_one<DTYPE>(g, e0 + j) : 0.0f;
+            for (int j = 0; j < 7; ++j)
+                if (e0 + j < bend) prev[t][j] = out[e0 + j];
         }
-        uint32_t rw[4];
-        draw_tile(ebase, lane, worker, step, seed_lo, seed_hi, rw);
-        replace_nan(x);
-        float* o = out + e0;
+    };
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        const uint64_t e0 = wave_base + (uint64_t)t * kTile + (uint64_t)lane * kGroup;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) { x[t][j] = 0.0f; prev[t][j] = 0.0f; }
+        if (e0 + kGroup <= bend) {
+            load_group<DTYPE, false>(g, e0, x[t]);
+        } else if (e0 < bend) {
+#pragma unroll
+            for (int j = 0; j < 7; ++j)                        // a ragged group has at most 7 elements
+                if (e0 + j < bend) x[t][j] = load_one<DTYPE>(g, e0 + j);
+        }
+        if constexpr (ACC) load_prev(t);
+    }
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        draw_tile(gbase + (uint64_t)t * kTile, tid, worker, step, seed_lo, seed_hi, rw[t]);
+        asm volatile("" : "+v"(rw[t][0]));                     // computed here, under the loads
+    }
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        const uint64_t base = wave_base + (uint64_t)t * kTile, e0 = base + (uint64_t)lane * kGroup;
+        if (base >= bend) break;
+        replace_nan(x[t]);
+        const uint32_t word = encode_general<BITS, true>(x[t], rw[t], cb, lv, tab);
+        float y[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const uint32_t r = (j & 1) ? (rw[j >> 1] >> 16) : (rw[j >> 1] & 0xFFFFu);
-            const uint32_t code = cb.nonuniform ? quantize<BITS, TQ_GRID_NONUNIFORM>(x[j], (float)r, cb.alpha, cb.inv_step, lv, tab)
-                                                : quantize<BITS, TQ_GRID_UNIFORM>(x[j], (float)r, cb.alpha, cb.inv_step, lv, tab);
-            const float y = levels[code & S];
-            if (j < n_valid) o[j] = ACC ? o[j] + y : y;
+            y[j] = tab.e[(word >> (j * BITS)) & S].x;
+            if constexpr (ACC) y[j] = prev[t][j] + y[j];
+        }
+        if (!(ACC && PAST_CACHES) && base + 64 * kGroup <= bend) {
+            store8_wave<PAST_CACHES>(out + base, (int)lane, y, xbuf[wave]);
+        } else if (e0 + kGroup <= bend) {
+            reinterpret_cast<float4*>(out + e0)[0] = make_float4(y[0], y[1], y[2], y[3]);
+            reinterpret_cast<float4*>(out + e0)[1] = make_float4(y[4], y[5], y[6], y[7]);
+        } else if (e0 < bend) {
+#pragma unroll
+            for (int j = 0; j < 7; ++j)
+                if (e0 + j < bend) out[e0 + j] = y[j];
         }
     }
 }
@@ -942,22 +923,27 @@ hipError_t tq_launch_simulate(const void* g, int dtype, uint64_t d, uint64_t buc
     const uint64_t d_pad = (d + 127) / 128 * 128;
     const uint64_t be = bucket_elems ? bucket_elems : d_pad;
     const uint64_t nb = (d_pad + be - 1) / be;
-    const uint64_t tt = (uint64_t)tq::simulate_tiles(dtype);
+    const bool past = tq::output_past_caches(d * sizeof(float));
+    // one tile per workgroup; two for bf16 whose output leaves the caches, in buckets of at least four: 124 M at b = 3
+    // 107 / 103.5 us, but 25.6 M 24.5 / 25.7 and 124 M in buckets of 2048 111 / 174
+    const bool two = dtype == TQ_BF16 && past && !accumulate && be >= 4 * (uint64_t)tq::kTile;
+    const uint64_t tt = two ? 2 : 1;
     const uint64_t tpb = ((be + tq::kTile - 1) / tq::kTile + tt - 1) / tt;    // workgroups per bucket
     const uint64_t nblocks = nb * tpb;
     dim3 blocks;
     if (!tq::fold_grid(nblocks, tq::kBlock, 1, blocks)) return hipErrorInvalidValue;
     const uint32_t slo = (uint32_t)seed, shi = (uint32_t)(seed >> 32);
     const dim3 threads(tq::kBlock);
-    const bool past = !accumulate && tq::output_past_caches(d * sizeof(float));
-#define TQ_LAUNCH_SIM_AS(DT, B, ACC, PAST)                                                                         \
-    hipLaunchKernelGGL((tq::tq_simulate_kernel<DT, B, ACC, PAST, tq::simulate_tiles(DT)>), blocks, threads, 0, st, g, d, \
-                       d_pad, be, (uint32_t)tpb, params, slo, shi, worker, step, out)
+#define TQ_LAUNCH_SIM_AS(DT, B, ACC, PAST, T)                                                                       \
+    hipLaunchKernelGGL((tq::tq_simulate_kernel<DT, B, ACC, PAST, T>), blocks, threads, 0, st, g, d, d_pad, be,      \
+                       (uint32_t)tpb, params, slo, shi, worker, step, out)
 #define TQ_LAUNCH_SIM(DT, B)                                                   \
     do {                                                                       \
-        if (accumulate) TQ_LAUNCH_SIM_AS(DT, B, true, false);                  \
-        else if (past) TQ_LAUNCH_SIM_AS(DT, B, false, true);                   \
-        else TQ_LAUNCH_SIM_AS(DT, B, false, false);                            \
+        if (accumulate && past) TQ_LAUNCH_SIM_AS(DT, B, true, true, 1);        \
+        else if (accumulate) TQ_LAUNCH_SIM_AS(DT, B, true, false, 1);          \
+        else if (two) TQ_LAUNCH_SIM_AS(DT, B, false, true, DT == TQ_BF16 ? 2 : 1); \
+        else if (past) TQ_LAUNCH_SIM_AS(DT, B, false, true, 1);                \
+        else TQ_LAUNCH_SIM_AS(DT, B, false, false, 1);                         \
     } while (0)
 #define TQ_LAUNCH_SIM_B(DT)                      \
     switch (bits) {                              \

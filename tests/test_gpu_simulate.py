@@ -70,3 +70,41 @@ def test_ranges_of_whole_and_cut_tiles_and_large_outputs(dtype, d, bucket):
         assert torch.equal(out[:d], rt) and bool((out[d:] == 7.0).all())
         B.tq_quantize_dequantize(g, params, out[:d], 3, 21, 4, 2, bucket, accumulate=True)
         assert torch.equal(out[:d], rt + rt) and bool((out[d:] == 7.0).all())
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("kind", ["uniform", "mirrored", "lopsided", "empty ends"])
+@pytest.mark.parametrize("d,bucket", [(3 * 2048 + 517, 0), (9 * 1024 + 5, 1024), (12 * 2048 + 300, 2048), (4 * 3072 + 9, 3072),
+                                      (2 * 8192 + 2048 + 7, 8192)])
+def test_any_codebook_in_short_buckets(d, bucket, kind, bits, dtype):
+    """Codebooks that mirror, do not mirror and have empty outer cells, buckets shorter than a workgroup's range and
+    wavefronts that are whole, cut and empty, with and without accumulation: the oracle's values, nothing behind them."""
+    s, nb = (1 << bits) - 1, B.num_buckets(d, bucket)
+    t = 2.0 * np.arange(s + 1) / s - 1.0
+    P = np.zeros(nb, dtype=O.PARAMS_DTYPE)
+    for k in range(nb):
+        alpha = np.float32(0.5 + 0.25 * k)
+        lv = (alpha * (t if kind == "uniform" else np.sign(t) * np.abs(t) ** 1.7)).astype(np.float32)
+        if kind == "lopsided":
+            lv[1:s] += np.float32(0.07) * alpha / s
+        if kind == "empty ends":
+            lv[1], lv[s - 1] = -alpha, alpha
+        lv[0], lv[s] = -alpha, alpha
+        width = np.diff(lv.astype(np.float64))
+        P["level"][k, : s + 1] = lv
+        P["inv_w"][k, :s] = np.where(width > 0, 1.0 / np.where(width > 0, width, 1.0), 0.0)
+        P["alpha"][k], P["bits"][k], P["s"][k] = alpha, bits, s
+        P["grid"][k] = O.GRID_UNIFORM if kind == "uniform" else O.GRID_NONUNIFORM
+        if kind == "uniform":
+            P["inv_w"][k] = np.float32(s / (2.0 * float(alpha)))
+    g = (torch.randn(d, generator=torch.Generator().manual_seed(bits)) * 1.5).to(dtype)
+    g_np = g.view(torch.int16).numpy().view("uint16") if dtype == torch.bfloat16 else g.numpy()
+    out = torch.full((d + 64,), 7.0, device="cuda")
+    params = B.params_from_numpy(P)
+    B.tq_quantize_dequantize(g.cuda(), params, out[:d], bits, 21, 4, 2, bucket)
+    want = O.quantize_dequantize(g_np, P, 21, 4, 2, bucket_elems=bucket)
+    assert (out[:d].cpu().numpy() == want).all()
+    B.tq_quantize_dequantize(g.cuda(), params, out[:d], bits, 21, 5, 2, bucket, accumulate=True)
+    want = want + O.quantize_dequantize(g_np, P, 21, 5, 2, bucket_elems=bucket)
+    assert (out[:d].cpu().numpy() == want).all() and bool((out[d:] == 7.0).all())

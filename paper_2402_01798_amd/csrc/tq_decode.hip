@@ -38,7 +38,7 @@ __device__ __forceinline__ uint32_t load_code_word(const uint8_t* stream, const 
 
 // What happens to the aggregate g_bar of an element (the MODE of the kernels below):
 //   kStore        out = g_bar                           Alg. 1, server step "aggregate"
-//   kStoreStream  the same, stored with the non-temporal hint (small outputs, see store8)
+//   kStoreStream  the same, stored with the non-temporal hint (small and very large outputs, see streams_output)
 //   kAccumulate   out = out + g_bar
 //   kSgd          theta = theta - eta * u,  u = g_bar + weight_decay * theta
 //                                                       Alg. 1, server step "update", fused
@@ -85,13 +85,10 @@ __device__ __forceinline__ void load8(const float* p, float (&x)[8])
     x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
 }
 
-// STREAM: stored with the non-temporal hint.  Used for a plain aggregate small enough to stay
-// in the memory-side cache: written normally it stays behind as dirty lines, and their
-// write-back then competes with the next kernel's reads (12 us on the statistics launch that
-// follows a 45 MB output).  The hint has a price -- the two 16-byte halves of a lane's 32 bytes
-// leave L2 as separate partial writes, and a write-bound launch with a large output runs up to
-// 1.8x slower with it -- so large outputs, which are evicted while the kernel runs anyway, and
-// the buffers of the fused update, which the next step reads again, are stored normally.
+// STREAM: stored with the non-temporal hint.  Here, in ranges that are cut, the two 16-byte halves of a lane's 32 bytes
+// leave L2 as separate partial writes with it; whole wavefronts store whole lines (store8_wave).  Storing the halves
+// through the caches instead: 124 M in buckets of 1536 128 -> 132 us and in segments of 2176 142 -> 215, 11.2 M in buckets
+// of 384 36.5 -> 38.8, but in segments of 512 29.4 -> 26.2.
 template <bool STREAM>
 __device__ __forceinline__ void store8(float* p, const float (&x)[8])
 {
@@ -471,7 +468,7 @@ __global__ __launch_bounds__(kBlock) void tq_decode_many_kernel(
 }
 
 // tq_decompress_aggregate_segments: the server step with one codebook per variable-size
-// segment (and worker).  Shape of tq_compress_segments_kernel: one tile per workgroup, the
+// segment (and worker), for more workers than the fast kernel takes.  One tile per workgroup, the
 // segments that overlap it taken one after the other, each with the N workers' level rows of
 // that segment in LDS.
 template <int BITS, int MODE>
@@ -525,7 +522,9 @@ __global__ __launch_bounds__(kBlock) void tq_decode_segments_kernel(
 
 namespace {
 
-// A plain aggregate is streamed past the caches when it is small (see store8) or too large for them.
+// A plain aggregate is streamed past the caches when it is small -- written normally it stays behind as dirty lines of the
+// memory-side cache, and their write-back competes with the next kernel's reads (12 us on the statistics launch that follows
+// a 45 MB output) -- or too large for them.  The buffers of the fused update, which the next step reads again, never are.
 bool streams_output(uint64_t d)
 {
     return d * sizeof(float) <= (64ull << 20) || tq::output_past_caches(d * sizeof(float));

@@ -89,13 +89,18 @@ inline bool fold_grid(uint64_t nblocks, unsigned threads, unsigned count, dim3& 
     return true;
 }
 
-// Whether an fp32 output of so many bytes is stored past the caches (non-temporally).  Above half the
+// Whether an fp32 output of so many bytes is stored past the caches (non-temporally).  Well above half the
 // 256 MiB of the memory-side cache little of it would be found there by whoever reads it next, and
-// written back late it costs more than written out at once.  Average of N payloads alone, and with a
-// reader of the output behind it, us: 80 M elements (N = 4) 72 -> 58.5 and 239.5 -> 232, 50 M 53 -> 42.5 and
-// 159 -> 154, but 25.6 M (N = 8) 46 -> 34 and 90 -> 96.5: that reader paid for it.  Whole wavefronts
-// storing whole lines only (store8_wave): half lines written this way cost up to 1.8 times.
-inline bool output_past_caches(uint64_t bytes) { return bytes > (128ull << 20); }
+// written back late it costs more than written out at once.  The average of N payloads, us, through / past the caches,
+// repeated alone, after another kernel has left the cache full of its own dirty lines, and there with a reader of the
+// output behind it:
+//   40 M  b = 2, N = 8   39 / 40    65 / 61    116 / 127        b = 4, N = 1   27.5 / 27   39 / 37.5   91 / 110
+//   50 M                 57 / 49    80 / 75.5  149.5 / 152                     33.5 / 33.5 47 / 45     123 / 130.5
+//   80 M                 92 / 77    110 / 116  225 / 222                       63 / 51     70 / 70     190 / 191
+//   124 M                135 / 114  154 / 183  325 / 333                       94.5 / 78   101 / 105   280 / 281
+// So the call by itself gains or, after such a kernel, loses, and from 50 M on what follows it gets that back: a whole
+// step of 8 x 124 M 1438 / 1409.  Below, a reader pays up to a quarter.
+inline bool output_past_caches(uint64_t bytes) { return bytes > (160ull << 20); }
 
 typedef float float4_native __attribute__((ext_vector_type(4)));
 

@@ -115,9 +115,9 @@ def test_round_trip_is_unbiased_for_the_truncated_gradient():
     assert abs(err.mean()) < 4 * width / 2 / np.sqrt(N * d)
 
 
-@pytest.mark.parametrize("d", [33_554_432 - 8, 33_554_432 + 4096 + 3])
+@pytest.mark.parametrize("d", [33_554_432 - 8, 33_554_432 + 4096 + 3, 41_943_040 - 8, 41_943_040 + 4096 + 3])
 def test_outputs_on_both_sides_of_the_cache_limit(d):
-    """Averages of just under and just over 128 MiB (the larger one is stored past the caches): equal to
+    """Averages of around 128 MiB and just under and just over 160 MiB (stored past the caches): equal to
     the average taken in two halves, nothing written behind it; bucketed and segment calls."""
     gen = torch.Generator(device="cuda")
     gen.manual_seed(1)

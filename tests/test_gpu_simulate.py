@@ -51,10 +51,11 @@ def test_bf16_and_special_values():
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("d,bucket", [(2047, 0), (2048, 0), (4096, 0), (4097, 0), (8192 + 2048 + 9, 0), (5 * 4096, 4096),
-                                      (33_554_432 + 4096 + 11, 1 << 20)])
+                                      (33_554_432 + 4096 + 11, 1 << 20), (41_943_040 + 4096 + 11, 1 << 20),
+                                      (41_943_040 + 4096 + 11, 4096)])
 def test_ranges_of_whole_and_cut_tiles_and_large_outputs(dtype, d, bucket):
-    """Workgroup ranges that are whole, cut inside a tile or between two tiles, and an output just above
-    128 MiB (stored past the caches): the values of the compress -> decode round trip, nothing behind them."""
+    """Workgroup ranges that are whole, cut inside a tile or between two tiles, and outputs just above
+    128 and 160 MiB (the latter stored past the caches): the values of the compress -> decode round trip, nothing behind them."""
     gen = torch.Generator(device="cuda")
     gen.manual_seed(d)
     g = torch.randn(d, generator=gen, device="cuda").to(dtype)

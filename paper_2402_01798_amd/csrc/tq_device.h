@@ -126,27 +126,52 @@ __device__ __forceinline__ void store8_wave(float* o, int lane, const float (&x)
     }
 }
 
-// Tile geometry shared by compress and decode.  Workgroup `blk` owns elements
-// [ebase, ebase + kTile) of bucket `bucket`, cut at `eend` (the bucket's end, the last
-// bucket's end being d rounded up to a multiple of 128 so the payload padding is covered).
-struct TileGeom {
-    uint64_t bucket;
-    uint64_t ebase;
-    uint64_t eend;
-};
-
-__device__ __forceinline__ TileGeom tile_geom(uint32_t blk, uint64_t d_pad, uint64_t bucket_elems,
-                                              uint32_t tiles_per_bucket)
+// Inclusive prefix sums over a wavefront by moves inside the vector unit: inside rows of 16 lanes, then the
+// rows' totals handed on (lane 15 of a row to the next row, lane 31 to the upper half).  6 steps of a few clocks each,
+// where a shuffle through LDS takes about a hundred.  Lanes without a source see 0.  The whole wavefront is active.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v)
 {
-    TileGeom t;
-    const uint32_t b = blk / tiles_per_bucket;
-    const uint32_t tile = blk - b * tiles_per_bucket;
-    t.bucket = b;
-    const uint64_t bstart = (uint64_t)b * bucket_elems;
-    t.ebase = bstart + (uint64_t)tile * kTile;
-    const uint64_t bend = bstart + bucket_elems;
-    t.eend = bend < d_pad ? bend : d_pad;
-    return t;
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned long long dpp_or_zero(unsigned long long v)
+{
+    return (unsigned long long)dpp_or_zero<CTRL, ROWS>((uint32_t)v) |
+           (unsigned long long)dpp_or_zero<CTRL, ROWS>((uint32_t)(v >> 32)) << 32;
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_or_zero(double v)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+template <typename T>
+__device__ __forceinline__ T row_scan(T v)
+{
+    v += dpp_or_zero<0x111, 0xf>(v);
+    v += dpp_or_zero<0x112, 0xf>(v);
+    v += dpp_or_zero<0x114, 0xf>(v);
+    v += dpp_or_zero<0x118, 0xf>(v);
+    return v;
+}
+template <typename T>
+__device__ __forceinline__ T wave_scan(T v)
+{
+    v = row_scan(v);
+    v += dpp_or_zero<0x142, 0xa>(v);
+    v += dpp_or_zero<0x143, 0xc>(v);
+    return v;
+}
+__device__ __forceinline__ uint32_t lane_value(uint32_t v, int lane) { return (uint32_t)__builtin_amdgcn_readlane((int)v, lane); }
+__device__ __forceinline__ unsigned long long lane_value(unsigned long long v, int lane)
+{
+    return (unsigned long long)lane_value((uint32_t)v, lane) | (unsigned long long)lane_value((uint32_t)(v >> 32), lane) << 32;
+}
+__device__ __forceinline__ double lane_value(double v, int lane)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane), __builtin_amdgcn_readlane(__double2loint(v), lane));
 }
 
 }  // namespace tq

@@ -164,37 +164,6 @@ struct ParamsLds {
     int best_j[kParamsWaves];
 };
 
-// Inclusive prefix sums over a wavefront by cross-lane moves: inside rows of 16 lanes, then the
-// rows' totals handed on (lane 15 of a row to the next row, lane 31 to the upper half).
-template <int CTRL, int ROWS>
-__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v)
-{
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
-}
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_or_zero(double v)
-{
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false);
-    return __hiloint2double(hi, lo);
-}
-template <typename T>
-__device__ __forceinline__ T row_scan(T v)
-{
-    v += dpp_or_zero<0x111, 0xf>(v);
-    v += dpp_or_zero<0x112, 0xf>(v);
-    v += dpp_or_zero<0x114, 0xf>(v);
-    v += dpp_or_zero<0x118, 0xf>(v);
-    return v;
-}
-template <typename T>
-__device__ __forceinline__ T wave_scan(T v)
-{
-    v = row_scan(v);
-    v += dpp_or_zero<0x142, 0xa>(v);
-    v += dpp_or_zero<0x143, 0xc>(v);
-    return v;
-}
 template <int CTRL, int ROWS>
 __device__ __forceinline__ float min_with_dpp(float v)
 {
@@ -209,11 +178,6 @@ __device__ __forceinline__ float wave_min(float v)
     v = min_with_dpp<0x142, 0xa>(v);
     v = min_with_dpp<0x143, 0xc>(v);
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
-}
-__device__ __forceinline__ uint32_t lane_value(uint32_t v, int lane) { return (uint32_t)__builtin_amdgcn_readlane((int)v, lane); }
-__device__ __forceinline__ double lane_value(double v, int lane)
-{
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane), __builtin_amdgcn_readlane(__double2loint(v), lane));
 }
 
 // Exclusive prefix sums over the bins: lane values v[k] of bins kParamsBlock k + tid.  On return v[k] is

@@ -62,40 +62,11 @@ __host__ __device__ inline uint64_t stats_ws_hist_words(uint64_t nb, uint32_t sl
     return nb * TQ_NBINS * (uint64_t)slices;
 }
 
-// Reductions over a wavefront by moves inside the vector unit (a shift within rows of 16 lanes, then the
-// rows' last lanes passed on), the total read from lane 63: 6 steps of a few clocks each, where a
-// shuffle through LDS takes about a hundred.  Lanes without a source see 0, the identity of both.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v)
-{
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
-}
-
-template <int CTRL, int ROWS>
-__device__ __forceinline__ unsigned long long dpp_or_zero(unsigned long long v)
-{
-    return (unsigned long long)dpp_or_zero<CTRL, ROWS>((uint32_t)v) |
-           (unsigned long long)dpp_or_zero<CTRL, ROWS>((uint32_t)(v >> 32)) << 32;
-}
-
-__device__ __forceinline__ uint32_t from_lane63(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, 63); }
-
-__device__ __forceinline__ unsigned long long from_lane63(unsigned long long v)
-{
-    return (unsigned long long)from_lane63((uint32_t)v) | (unsigned long long)from_lane63((uint32_t)(v >> 32)) << 32;
-}
-
 // Called with the whole wavefront active; every lane gets the result.
 template <typename T>
 __device__ __forceinline__ T wave_reduce_add(T v)
 {
-    v += dpp_or_zero<0x111, 0xF>(v);                                   // row_shr:1
-    v += dpp_or_zero<0x112, 0xF>(v);
-    v += dpp_or_zero<0x114, 0xF>(v);
-    v += dpp_or_zero<0x118, 0xF>(v);
-    v += dpp_or_zero<0x142, 0xA>(v);                                   // row_bcast:15 into rows 1 and 3
-    v += dpp_or_zero<0x143, 0xC>(v);                                   // row_bcast:31 into rows 2 and 3
-    return from_lane63(v);
+    return lane_value(wave_scan(v), 63);
 }
 
 __device__ __forceinline__ long long wave_reduce_add(long long v)
@@ -112,7 +83,7 @@ __device__ __forceinline__ uint32_t wave_reduce_max(uint32_t v)
     take(dpp_or_zero<0x118, 0xF>(v));
     take(dpp_or_zero<0x142, 0xA>(v));
     take(dpp_or_zero<0x143, 0xC>(v));
-    return from_lane63(v);
+    return lane_value(v, 63);
 }
 
 // One lane's group of 8 consecutive elements as it is loaded (32 bytes of fp32, 16 of bf16), and

@@ -189,3 +189,29 @@ def test_the_best_split_changes_beside_the_fixed_point():
     assert (got["flags"] == 0).all()
     off = np.abs(got["alpha"].astype(np.float64) - alpha) / np.spacing(alpha)
     assert off.max() <= 1.0, off
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("grid", [B.GRID_NONUNIFORM, B.GRID_BISCALED])
+def test_records_whose_iteration_does_not_settle(bits, grid):
+    """The records left out above: the tail estimates are the oracle's, alpha lies in its range and is a fixed point
+    unless the flag says that none was reached, and the codebook is the one the oracle designs for that alpha."""
+    st = records()
+    got, want = design(st, bits, grid)
+    s = (1 << bits) - 1
+    for i in np.nonzero(want["flags"] & 4)[0]:
+        g, w = got[i], want[i]
+        for f in ("gamma_hat", "rho_hat", "g_min"):
+            assert np.isclose(g[f], w[f], rtol=1e-6, atol=0), (i, f)
+        alpha, g_min, top = float(g["alpha"]), float(w["g_min"]), float(st["absmax"][i])
+        assert g_min < alpha <= top and (g["flags"] & ~np.uint32(4 | 1 | 32)) == (w["flags"] & ~np.uint32(4 | 1 | 32))
+        dens = OP.Density(st["hist"][i], top)
+        if not g["flags"] & 4:
+            gamma = max(float(w["gamma_hat"]), OP.GAMMA_FLOOR)
+            q = dens.Q_N(alpha) if grid == B.GRID_NONUNIFORM else dens.best_k(alpha)[1]
+            f_alpha = g_min * (2 * float(w["rho_hat"]) * s * s / (gamma - 2) / q) ** (1 / (gamma - 1))
+            # alpha, gamma and rho are rounded to binary32, which moves the map by less than 1e-5 here
+            assert abs(min(max(f_alpha, g_min * (1 + 2.0 ** -10)), top) / alpha - 1) < 1e-5, i
+        own = OP.tq_params(st[i:i + 1].view(O.STATS_DTYPE), bits, grid, alpha)[0]
+        assert np.allclose(g["level"], own["level"], rtol=1e-6, atol=0), i
+        assert np.allclose(g["inv_w"], own["inv_w"], rtol=2e-6, atol=0), i

@@ -108,6 +108,16 @@ __device__ __forceinline__ float log2_hw(float x) { return __builtin_amdgcn_logf
 __device__ __forceinline__ float exp2_hw(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float rcp_hw(float x) { return __builtin_amdgcn_rcpf(x); }
 
+// exp(x) for |x| < 170 from its own logarithm: y from the hardware's exp2, then y exp(r), r = x / 2 - ln y, |r| < 1e-4, by
+// four terms, squared.  Without the library's constants the code that seldom runs leaves the rest its registers.
+__device__ __forceinline__ double exp_by_ln(double x)
+{
+    const double y = (double)exp2_hw((float)(x * (0.5 / kLn2)));
+    const double r = __builtin_fma(0.5, x, -ln(y));
+    const double root = __builtin_fma(y, r * (1.0 + r * (0.5 + r * (1.0 / 6.0))), y);
+    return root * root;
+}
+
 // Cube root of x >= 0: fp32 seed, two Newton steps in fp64 (the reciprocal of the derivative is
 // needed to the seed's precision only); below the range of binary32 the library's.
 __device__ __forceinline__ double cube_root(double x)
@@ -661,12 +671,13 @@ __device__ __forceinline__ void design(ParamsLds<GRID != TQ_GRID_UNIFORM, WIDE>&
                 // the definition's iteration, step by step
                 have_split = false;
                 const double log_c = ln(C);
-                a = clampa(g_min * exp(ex * log_c));       // alpha' of Sec. IV-A (Q = 1)
+                auto power = [](double x) { return WIDE ? exp_by_ln(x) : exp(x); };
+                a = clampa(g_min * power(ex * log_c));     // alpha' of Sec. IV-A (Q = 1)
                 for (int it = 0; it < kMaxIter; ++it) {
                     double el;
                     const double q = Q(a, el);
                     // (C/q)^ex evaluated as exp(ex (ln C - ln q))
-                    const double an = q > 0.0 ? clampa(g_min * exp(ex * (log_c - ln(q)))) : a_max;
+                    const double an = q > 0.0 ? clampa(g_min * power(ex * (log_c - ln(q)))) : a_max;
                     const bool done = fabs(an - a) <= kRelTol * an;
                     a = an;
                     if (done) { converged = true; break; }
@@ -755,7 +766,7 @@ __device__ __forceinline__ void design(ParamsLds<GRID != TQ_GRID_UNIFORM, WIDE>&
 }
 
 template <int GRID>
-__global__ __launch_bounds__(kParamsBlock, GRID == TQ_GRID_BISCALED ? 5 : 7) void tq_params_kernel(const PtrTable stats_tab, uint32_t nb, int bits,
+__global__ __launch_bounds__(kParamsBlock) void tq_params_kernel(const PtrTable stats_tab, uint32_t nb, int bits,
                                                            float alpha_override, const MutPtrTable params_tab)
 {
     constexpr bool kRoots = GRID != TQ_GRID_UNIFORM;
@@ -767,8 +778,8 @@ __global__ __launch_bounds__(kParamsBlock, GRID == TQ_GRID_BISCALED ? 5 : 7) voi
     // one workgroup per bucket, blockIdx.y = tensor of the batch
     const uint32_t bucket = linear_block();
     if (bucket >= nb) return;
-    const tq_stats_t* S = static_cast<const tq_stats_t*>(stats_tab.p[blockIdx.y]) + bucket;
-    tq_params_t* P = static_cast<tq_params_t*>(params_tab.p[blockIdx.y]) + bucket;
+    const tq_stats_t* __restrict__ S = static_cast<const tq_stats_t*>(stats_tab.p[blockIdx.y]) + bucket;
+    tq_params_t* __restrict__ P = static_cast<tq_params_t*>(params_tab.p[blockIdx.y]) + bucket;
     if (__builtin_expect((S->n >> 32) == 0, 1)) design<GRID, false>(L.narrow, S, bits, alpha_override, P);
     else design<GRID, true>(L.wide, S, bits, alpha_override, P);
 }

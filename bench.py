@@ -41,8 +41,8 @@ VARIANTS = [("cfg4", 2, 0), ("cfg4", 2, 1), ("cfg2", 2, 0), ("cfg2", 4, 0), ("cf
 
 # vector-ALU lane-operations per element of the compress kernel's variants, as rocprofv3's
 # SQ_INSTS_VALU counts them (profiles/valu_instructions.txt): they decide which ceiling binds
-COMPRESS_VALU_PER_ELEM = {"f32/b2/g0": 15.6, "f32/b2/g1": 18.9, "f32/b4/g0": 20.2, "f32/b3/g1": 24.0,
-                          "bf16/b2/g1": 18.6}
+COMPRESS_VALU_PER_ELEM = {"f32/b2/g0": 15.5, "f32/b2/g1": 20.7, "f32/b4/g0": 20.2, "f32/b3/g1": 24.0,
+                          "bf16/b2/g1": 18.5}
 
 
 def parse():

@@ -42,7 +42,7 @@ enum { TQ_GRID_UNIFORM = 0, TQ_GRID_NONUNIFORM = 1, TQ_GRID_BISCALED = 2 };  /* 
 /* tq_params_t.flags */
 #define TQ_F_ALPHA_CLAMPED_MAX 1u  /* fixed point at or beyond max|g|: alpha = max|g| */
 #define TQ_F_GAMMA_CLAMPED     2u  /* tail index estimate below 2.02, lifted to it   */
-#define TQ_F_NOT_CONVERGED     4u  /* 100 iterations without meeting 1e-10           */
+#define TQ_F_NOT_CONVERGED     4u  /* the iteration does not meet 1e-10 in 100 steps  */
 #define TQ_F_DEGENERATE        8u  /* no finite non-zero data (alpha = 2^-64 unless the
                                       caller gave one), or no usable tail (alpha = max|g|) */
 #define TQ_F_ALPHA_OVERRIDE   16u  /* alpha given by the caller                       */
@@ -138,7 +138,8 @@ int tq_stats_static(const void* g_dev, int dtype, uint64_t d, uint64_t bucket_el
  *   alpha_override  0: the paper's formula; > 0: use this alpha;
  *                   < 0: alpha = max|g| (quantization without truncation)
  *   params_dev      [nb] written in full
- * All arithmetic is fp64 on the device, one workgroup per bucket.
+ * alpha, the split and the levels are fp64 results on the device, rounded once; binary32 only brings the iteration
+ * near its fixed point and leaves out edges that cannot be the best split.  One workgroup per bucket.
  */
 int tq_params(const tq_stats_t* stats_dev, uint64_t nb, int bits, int grid,
               float alpha_override, tq_params_t* params_dev, void* stream);
@@ -255,8 +256,8 @@ int tq_quantize_dequantize(const void* g_dev, int dtype, uint64_t d, uint64_t bu
  *                     results, never an access outside the caller's buffers.
  *   stats_dev / params_dev  [nseg] records
  *   workspace_dev     tq_stats_segments_workspace_bytes(d, nseg) bytes, rules as for tq_stats
- * tq_compress_segments takes no `grid`: it has one launch shape.  The segment kernels favour
- * generality over the last tenth of speed (one tile per workgroup, plain level tables).
+ * tq_compress_segments takes no `grid`: its launch is shaped by the sizes alone, for level tables.  Ranges that
+ * a segment's end cuts are taken piece by piece.
  * tq_stats_segments needs d < 2^32 (the counts of a record are 32-bit).
  * The *_multi forms take `count` tensors of the same d and dtype that share ONE segment table
  * (the N workers' gradients of one model) in one launch each, as tq_stats_multi and

@@ -211,12 +211,12 @@ __device__ __forceinline__ uint32_t encode_group(const float (&x)[8], const uint
 // puts into cell k although it is below l_k is encoded k by both (p_k < u and p_{k-1} >= u).  The empty and the
 // lopsided codebooks take the general path.
 //
-// Measured, before -> after: 16 x 25.6 M fp32 at b = 3 350 -> 323 us, 4 x 10^9 bf16 at b = 2
-// 1920 -> 1775 us, 25.6 M at b = 3 22.0 -> 20.2 us, 4 x 11.2 M at b = 3 in buckets of 16384
-// 35.5 -> 32.2 us.  What bounds it now: with the draws or the encoding left out the first takes 312 / 309 us,
-// the second 1640 / 1625, with both left out 307 / 1618 -- the pattern of its memory traffic.
+// Measured, general path -> this, with the same tiles: 16 x 25.6 M at b = 3 fp32 326 -> 300 us, bf16 263 -> 227, 25.6 M
+// bf16 at b = 3 19.9 -> 16.8, at b = 2 15.0 -> 14.6; where it does not pay it is not checked for (mirrored_pays: b = 2 and
+// 3 only).  What bounds it now is the pattern of its memory traffic: with the draws left out, the encoding left out, both,
+// a launch of 16 x 25.6 M fp32 of 320 us took 313 / 309 / 307, one of 4 x 10^9 bf16 at b = 2 of 1780 1640 / 1625 / 1618.
 struct CellLds {
-    float4 e[16];            // entry neg * H + (H - 1 - i): cell m + i (x >= 0) or m - i, H = 2^(b-1), m = H - 1
+    float4 e[8];             // entry neg * H + (H - 1 - i): cell m + i (x >= 0) or m - i, H = 2^(b-1), m = H - 1
     uint32_t regular;
 };
 
@@ -519,7 +519,7 @@ __device__ __forceinline__ void encode_tiles_general(const void* g, uint8_t* pay
 // MIRROR: level tables are checked for the mirrored path and take it if they are regular; else every record is
 // encoded on the general one.
 template <int DTYPE, int BITS, bool STREAM, int T, bool MIRROR>
-__global__ __launch_bounds__(kBlock) void tq_compress_kernel(
+__global__ __launch_bounds__(kBlock, !MIRROR && T <= 2 && !(DTYPE == TQ_BF16 && BITS == 4) ? 8 : 1) void tq_compress_kernel(
     const PtrTable g_tab, uint64_t d, uint64_t d_pad, uint64_t bucket_elems,
     uint32_t groups_per_bucket, const PtrTable params_tab, uint32_t seed_lo,
     uint32_t seed_hi, uint32_t first_worker, uint32_t step, const MutPtrTable payload_tab,
@@ -603,7 +603,7 @@ __global__ __launch_bounds__(kBlock) void tq_compress_kernel(
 // padding up to a multiple of 128 elements.  No access depends on the table being well-formed:
 // the segment index stays inside [0, nseg) and every element access is bounded by d.
 template <int DTYPE, int BITS, bool STREAM, int T, bool MIRROR>
-__global__ __launch_bounds__(kBlock) void tq_compress_segments_kernel(
+__global__ __launch_bounds__(kBlock, T == 1 ? 6 : 1) void tq_compress_segments_kernel(
     const PtrTable g_tab, uint64_t d, uint64_t d_pad, const uint64_t* __restrict__ seg_off, uint32_t nseg,
     const SegHints hints, const PtrTable params_tab, uint32_t seed_lo, uint32_t seed_hi, uint32_t first_worker, uint32_t step,
     const MutPtrTable payload_tab, uint64_t payload_bytes)
@@ -668,6 +668,7 @@ __global__ __launch_bounds__(kBlock) void tq_compress_segments_kernel(
             return;
         }
     }
+    bool table_used = false;                                   // the same for the whole workgroup
     for (int t = 0; t < T; ++t) {
         const uint64_t ebase = gbase + (uint64_t)t * kTile;
         if (ebase >= d_pad) break;
@@ -696,7 +697,8 @@ __global__ __launch_bounds__(kBlock) void tq_compress_segments_kernel(
             const float inv_step = P->inv_w[0];
             const bool nonuniform = P->grid != TQ_GRID_UNIFORM;    // uniform over the workgroup
             if (nonuniform) {
-                __syncthreads();                               // the table of the segment before is done with
+                if (table_used) __syncthreads();               // the table of the segment before is done with
+                table_used = true;
                 fill_level_lds(tab, P, (1u << BITS) - 1u);
 #pragma unroll
                 for (int j = 0; j < 16; ++j) lv[j] = P->level[j];   // wave-uniform: scalar loads
@@ -834,16 +836,17 @@ struct CompressShape { bool table_tiles, mirror; };
 
 // The shape of a launch of level tables.
 //   * Launches whose workgroups are all resident at once wait for latencies and take the tiles and the general path
-//     of the uniform codebook: up to 512 tiles (fp32) or 4096 (bf16; at b = 3 the mirrored path from 1024 on).  General
+//     of the uniform codebook: up to 512 tiles (fp32; 1024 at b = 3) or 4096 (bf16; at b = 3 the mirrored path from 1024 on).  General
 //     with few tiles / general / mirrored with many, us: 250,000 fp32 at b = 3 2.9 / 3.5 / 3.4, 1.2 M 4.0 / 3.9 / 4.2,
 //     3 M 4.7 / 4.7 / 4.4; 1.2 M bf16 at b = 4 4.4 / 5.7 / 6.1, 8 M 8.3 / 8.9 / 9.0, 11.2 M at b = 3 10.0 / 10.9 / 9.1.
-//   * So do buckets shorter than a tile (fp32) or than four (bf16), of which every workgroup is a cut one: 25.6 M at b = 3
-//     in buckets of 1024 fp32 30.4 / 33.0 / 35.2, bf16 31.5 / 43.3 / 44.1, of 4096 bf16 20.3 / 23.2 / 23.1.
+//   * So do buckets shorter than a tile (fp32) or of at most two (bf16), of which every larger range is a cut one: 25.6 M at
+//     b = 3 in buckets of 1024 fp32 30.4 / 33.0 / 35.2, bf16 31.5 / 43.3 / 44.1, of 4096 bf16 20.3 / 23.2 / 23.1 (but of 6144, a
+//     whole and a half range in the smaller shape, 25.3 / 22.8 / 22.8).
 CompressShape table_shape(int dtype, int bits, uint64_t bucket_elems, uint64_t all_tiles)
 {
     const bool f32 = dtype == TQ_F32;
-    if (bucket_elems < (f32 ? 1u : 4u) * (uint64_t)tq::kTile) return {false, false};
-    if (all_tiles <= (f32 ? 512u : 4096u)) return {false, !f32 && bits == 3 && all_tiles > 1024};
+    if (f32 ? bucket_elems < (uint64_t)tq::kTile : bucket_elems <= 2 * (uint64_t)tq::kTile) return {false, false};
+    if (all_tiles <= (f32 ? (bits == 3 ? 1024u : 512u) : 4096u)) return {false, !f32 && bits == 3 && all_tiles > 1024};
     return {true, mirrored_pays(dtype, bits)};
 }
 

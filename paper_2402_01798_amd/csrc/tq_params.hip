@@ -1,5 +1,5 @@
 // tq_params: parameter design of the truncated quantizer (arXiv 2402.01798, Sec. IV) from
-// the per-bucket statistics, in fp64, one workgroup per bucket.
+// the per-bucket statistics, one workgroup per bucket; results in fp64, rounded once.
 //
 //   tail index      gamma = 1 + n_tail / sum ln(|g|/g_min)            (Sec. V, MLE)
 //   tail mass       rho   = n_tail / (2 n)                            (one-sided, Sec. IV-A)
@@ -33,8 +33,9 @@
 //   - one kernel per codebook family: what a family does not need costs it no LDS and no
 //     instruction fetch.
 // Measured on MI355X, us for one launch, against all-fp64 iteration on lane 0 of one kernel for
-// all families: uniform, 4 records 11.2 -> 4.7, 952 records 30.3 -> 7.0; non-uniform, 1 record
-// 18.7 -> 7.4, 768 records 34.3 -> 9.7, 2736 records 78 -> 24.5; BiScaled, 391 records 128 -> 19.0.
+// all families: uniform, 4 records 11.2 -> 4.7, 952 records 30.3 -> 7.2; non-uniform, 1 record
+// 18.7 -> 7.7, 768 records 34.3 -> 10.4, 2736 records 78 -> 25.3; BiScaled, 391 records 128 -> 19.3.
+// Records whose iteration does not converge pay for both ways: BiScaled, 391 records with one such among them 234.
 // 512 or 1024 threads per record instead of 256 gain 0.4 us on a single non-uniform record and lose
 // 6 and 18 us on 2736 of them.
 #include "tq_device.h"
@@ -147,7 +148,7 @@ __constant__ OctaveLogs kOctaveLogs = {
 };
 
 // Count of a bin and of all bins below it, exact.  Every bucket has n < 2^32; WIDE is for records that a caller
-// has summed beyond that (their bins are 32-bit still): the fp64 sums for every record cost 0.5 to 1.9 us a launch.
+// has summed beyond that (their bins are 32-bit still): the fp64 sums for every record cost 0.5 to 1.9 us a launch, the test for such a record 0.2 to 0.4.
 template <bool WIDE> struct BinCounts;
 template <> struct BinCounts<false> {
     uint2 hc[kNB];

@@ -637,10 +637,10 @@ __global__ __launch_bounds__(kBlock, T == 1 ? 6 : 1) void tq_compress_segments_k
     if constexpr (T == 1) request(gbase);
 
     const uint32_t s0 = find_segment(seg_off, nseg, gbase < d ? gbase : d - 1, hints);
+    // The test uses the very segment ends the loop below uses, so both ways write the same bytes.
+    uint64_t seg_lo = seg_off[s0];
+    uint64_t seg_hi = s0 + 1 < nseg ? seg_off[s0 + 1] : d_pad;
     {
-        // The test uses the very segment ends the loop below would use, so both ways write the same bytes.
-        const uint64_t seg_lo = seg_off[s0];
-        const uint64_t seg_hi = s0 + 1 < nseg ? seg_off[s0 + 1] : d_pad;
         const uint64_t gend = gbase + (uint64_t)T * kTile;
         if (seg_lo <= gbase && seg_hi >= gend && gend <= d) {  // whole groups, and their codes lie inside the payload
             const tq_params_t* P = params + s0;
@@ -683,11 +683,14 @@ __global__ __launch_bounds__(kBlock, T == 1 ? 6 : 1) void tq_compress_segments_k
         const uint32_t byte_rel = lane * (uint32_t)BITS;
         const int n_valid = rel >= d_rel ? 0 : (d_rel - rel >= (uint32_t)kGroup ? kGroup : (int)(d_rel - rel));
         if constexpr (T > 1) request(ebase);
-        uint32_t s = t == 0 ? s0 : find_segment(seg_off, nseg, ebase < d ? ebase : d - 1, hints);
+        uint32_t s = s0;
+        if (t > 0) {
+            s = find_segment(seg_off, nseg, ebase < d ? ebase : d - 1, hints);
+            seg_lo = seg_off[s];
+            seg_hi = s + 1 < nseg ? seg_off[s + 1] : d_pad;
+        }
         replace_nan(x);
         for (;;) {
-            const uint64_t seg_lo = seg_off[s];
-            const uint64_t seg_hi = s + 1 < nseg ? seg_off[s + 1] : d_pad;
             // the part of the tile that belongs to this segment, as offsets from the tile's start
             const uint32_t lo_rel = (uint32_t)(seg_lo > ebase ? (seg_lo - ebase < (uint64_t)tile_len ? seg_lo - ebase : tile_len) : 0);
             const uint32_t hi_rel = (uint32_t)(seg_hi > ebase ? (seg_hi - ebase < (uint64_t)tile_len ? seg_hi - ebase : tile_len) : 0);
@@ -716,6 +719,8 @@ __global__ __launch_bounds__(kBlock, T == 1 ? 6 : 1) void tq_compress_segments_k
             }
             if (hi_rel >= tile_len || s + 1 >= nseg) break;
             ++s;
+            seg_lo = seg_hi;
+            seg_hi = s + 1 < nseg ? seg_off[s + 1] : d_pad;
         }
     }
 }

@@ -417,12 +417,9 @@ __device__ __forceinline__ void draw_tile(uint64_t ebase, uint32_t lane, uint32_
     else philox4x32_10(q_lo, qb_hi + (q_lo < qb_lo ? 1u : 0u), worker, step, seed_lo, seed_hi, rw);
 }
 
-// The packed codes of a lane's whole group, uniform or regular codebook.
 template <int BITS>
-__device__ __forceinline__ uint32_t encode_whole(const float (&x)[8], const uint32_t (&rw)[4], const Codebook& cb,
-                                                 const CellLds& cells)
+__device__ __forceinline__ uint32_t encode_uniform(const float (&x)[8], const uint32_t (&rw)[4], const Codebook& cb)
 {
-    if (cb.nonuniform) return encode_regular<BITS>(x, rw, cb.pv, cells);
     uint32_t word = 0;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -430,6 +427,14 @@ __device__ __forceinline__ uint32_t encode_whole(const float (&x)[8], const uint
         word |= quantize_uniform<BITS>(x[j], (float)r, cb.alpha, cb.inv_step) << (j * BITS);
     }
     return word;
+}
+
+// The packed codes of a lane's whole group, uniform or regular codebook.
+template <int BITS>
+__device__ __forceinline__ uint32_t encode_whole(const float (&x)[8], const uint32_t (&rw)[4], const Codebook& cb,
+                                                 const CellLds& cells)
+{
+    return cb.nonuniform ? encode_regular<BITS>(x, rw, cb.pv, cells) : encode_uniform<BITS>(x, rw, cb);
 }
 
 // The general path's table: 16 scalar levels and, behind one barrier, the entries in LDS.
@@ -555,6 +560,14 @@ __global__ __launch_bounds__(kBlock, !MIRROR && T <= 2 && !(DTYPE == TQ_BF16 && 
         }
     } else {
         cb = read_codebook(P);
+        // bf16: the uniform codebook apart from the tables' code, which costs it 1 us of 14 on 25.6 M at b = 3 and 4 (fp32
+        // the other way round: tables at b = 2 20.9 us with it, 21.9 without)
+        if (DTYPE == TQ_BF16 && whole && !cb.nonuniform) {
+            encode_tiles<DTYPE, BITS, STREAM, T>(g, payload, gbase, lane, draw, [&](const float (&x)[8], const uint32_t (&rw)[4]) {
+                return encode_uniform<BITS>(x, rw, cb);
+            });
+            return;
+        }
     }
     __shared__ LevelLds tab;
     float lv[16];
@@ -594,6 +607,14 @@ __global__ __launch_bounds__(kBlock, !MIRROR && T <= 2 && !(DTYPE == TQ_BF16 && 
     }
 }
 
+// Wavefronts per SIMD of the segments' kernel: held to the registers of one more where that needs no scratch memory
+// (8 x 124 M fp32 with 68 layers at b = 2, one step: 1532 -> 1506 us).
+constexpr int segment_waves(int dtype, int bits, int tiles)
+{
+    if (tiles == 1) return 6;
+    return bits == 2 ? (dtype == TQ_F32 ? 7 : 6) : (dtype == TQ_F32 ? 6 : 5);
+}
+
 // tq_compress_segments: the same client step with one (alpha, codebook) per variable-size
 // segment of the flat gradient (Sec. V: the layers of a network are quantized independently).
 // T tiles per workgroup wherever the segments fall.  Large layers are the rule: nearly every workgroup's
@@ -603,7 +624,7 @@ __global__ __launch_bounds__(kBlock, !MIRROR && T <= 2 && !(DTYPE == TQ_BF16 && 
 // padding up to a multiple of 128 elements.  No access depends on the table being well-formed:
 // the segment index stays inside [0, nseg) and every element access is bounded by d.
 template <int DTYPE, int BITS, bool STREAM, int T, bool MIRROR>
-__global__ __launch_bounds__(kBlock, T == 1 ? 6 : 1) void tq_compress_segments_kernel(
+__global__ __launch_bounds__(kBlock, segment_waves(DTYPE, BITS, T)) void tq_compress_segments_kernel(
     const PtrTable g_tab, uint64_t d, uint64_t d_pad, const uint64_t* __restrict__ seg_off, uint32_t nseg,
     const SegHints hints, const PtrTable params_tab, uint32_t seed_lo, uint32_t seed_hi, uint32_t first_worker, uint32_t step,
     const MutPtrTable payload_tab, uint64_t payload_bytes)

@@ -88,18 +88,32 @@ __device__ __forceinline__ uint32_t wave_reduce_max(uint32_t v)
 
 // One lane's group of 8 consecutive elements as it is loaded (32 bytes of fp32, 16 of bf16), and
 // as fp32 bit patterns.  The two are separate so that nothing that needs the loaded value stands
-// between a request and the work it is meant to overlap.
-template <int DTYPE> struct RawGroup { uint4 q[DTYPE == TQ_F32 ? 2 : 1]; };
+// between a request and the work it is meant to overlap.  PAST_CACHES: non-temporal loads.
+typedef uint32_t uint4_native __attribute__((ext_vector_type(4)));
+template <int DTYPE> struct RawGroup { uint4_native q[DTYPE == TQ_F32 ? 2 : 1]; };
 
-template <int DTYPE>
+template <int DTYPE, bool PAST_CACHES>
 __device__ __forceinline__ void load_raw(const void* g, uint64_t e0, RawGroup<DTYPE>& r)
 {
-    if constexpr (DTYPE == TQ_F32) {
-        const uint4* p = reinterpret_cast<const uint4*>(static_cast<const float*>(g) + e0);
-        r.q[0] = p[0];
-        r.q[1] = p[1];
-    } else {
-        r.q[0] = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(g) + e0);
+    const uint4_native* p = reinterpret_cast<const uint4_native*>(static_cast<const char*>(g) + e0 * (DTYPE == TQ_F32 ? 4u : 2u));
+#pragma unroll
+    for (int i = 0; i < (DTYPE == TQ_F32 ? 2 : 1); ++i) {
+        if constexpr (PAST_CACHES) r.q[i] = __builtin_nontemporal_load(p + i);
+        else r.q[i] = p[i];
+    }
+}
+
+// fp32, a whole wavefront: `e` is the lane's first element of the wavefront's 512, four apart from lane to lane, so
+// that each of the two loads reads 1 KiB in one piece; the lane holds half of two groups.  (Non-temporal lines are not
+// kept for the second half of a load that leaves every other 16 bytes: 8 x 124 M 660 us that way, 590 this way.)
+template <bool PAST_CACHES>
+__device__ __forceinline__ void load_lines(const void* g, uint64_t e, RawGroup<TQ_F32>& r)
+{
+    const uint4_native* p = reinterpret_cast<const uint4_native*>(static_cast<const float*>(g) + e);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        if constexpr (PAST_CACHES) r.q[i] = __builtin_nontemporal_load(p + 64 * i);
+        else r.q[i] = p[64 * i];
     }
 }
 
@@ -142,10 +156,11 @@ struct StatsLds {
 
 // One workgroup (kStatsBlock threads) takes the elements [cstart, cend) of one tensor: their
 // histogram goes to `row` (TQ_NBINS counts, every bin written), and thread 0 returns the other
-// sums (meaningless in the other threads).  cstart is a multiple of 8 elements.
-template <int DTYPE, bool TAIL>
+// sums (meaningless in the other threads).  cstart is a multiple of 8 elements.  What lies before past_end is
+// read past the caches (but for the first trip and what the loop leaves).
+template <int DTYPE, bool TAIL, bool PAST>
 __device__ __forceinline__ StatsExtra stats_slice(const void* __restrict__ g, uint64_t cstart, uint64_t cend,
-                                                  float g_min, StatsLds& L, uint32_t* __restrict__ row)
+                                                  uint64_t past_end, float g_min, StatsLds& L, uint32_t* __restrict__ row)
 {
     // Full trips of kTrip tiles each, two register buffers: the next trip's 16-byte loads are
     // requested before the current trip's values are histogrammed.  The trip count is the same
@@ -162,7 +177,9 @@ __device__ __forceinline__ StatsExtra stats_slice(const void* __restrict__ g, ui
     //    does for a plain read loop once arithmetic is added to it.
     constexpr int kTrip = DTYPE == TQ_F32 ? 4 : 2;
     constexpr bool kWaitAll = DTYPE == TQ_F32;
+    constexpr bool kLines = PAST && DTYPE == TQ_F32;                   // the loads of the full trips, see load_lines
     const uint64_t lane_e = cstart + (uint64_t)threadIdx.x * kGroup;
+    const uint64_t line_e = cstart + (threadIdx.x & ~63u) * kGroup + (threadIdx.x & 63u) * 4u;
     const uint32_t n_trips = (uint32_t)((cend - cstart) / ((uint64_t)kTrip * kStatsTile));
     // Two register buffers that swap roles (no copies: a copy would wait for the loads in
     // flight); sched_barrier keeps each request ahead of the work it overlaps.  The requests
@@ -171,20 +188,24 @@ __device__ __forceinline__ StatsExtra stats_slice(const void* __restrict__ g, ui
     // after the full trips is at most kTrip tiles; there a lane requests the whole groups it has.
     RawGroup<DTYPE> bufA[kTrip], bufB[kTrip];
     const uint64_t rest = lane_e + (uint64_t)n_trips * kTrip * kStatsTile;
-    auto request = [&](RawGroup<DTYPE> (&buf)[kTrip], uint32_t trip) {
+    auto request = [&](RawGroup<DTYPE> (&buf)[kTrip], uint32_t trip, auto past_caches) {
+        constexpr bool PAST_CACHES = decltype(past_caches)::value;
 #pragma unroll
-        for (int t = 0; t < kTrip; ++t)
-            load_raw<DTYPE>(g, lane_e + ((uint64_t)trip * kTrip + t) * kStatsTile, buf[t]);
+        for (int t = 0; t < kTrip; ++t) {
+            const uint64_t tile = ((uint64_t)trip * kTrip + t) * kStatsTile;
+            if constexpr (kLines) load_lines<PAST_CACHES>(g, line_e + tile, buf[t]);
+            else load_raw<DTYPE, PAST_CACHES>(g, lane_e + tile, buf[t]);
+        }
     };
     auto request_rest = [&](RawGroup<DTYPE> (&buf)[kTrip]) {
 #pragma unroll
         for (int t = 0; t < kTrip; ++t) {
             const uint64_t e0 = rest + (uint64_t)t * kStatsTile;
-            if (e0 + kGroup <= cend) load_raw<DTYPE>(g, e0, buf[t]);
+            if (e0 + kGroup <= cend) load_raw<DTYPE, false>(g, e0, buf[t]);
         }
     };
     // on its way while the histograms are cleared
-    if (n_trips > 0) request(bufA, 0); else request_rest(bufA);
+    if (n_trips > 0) request(bufA, 0, std::false_type{}); else request_rest(bufA);
     __builtin_amdgcn_sched_barrier(0);
 
     uint32_t* hist = L.hist;
@@ -266,7 +287,14 @@ __device__ __forceinline__ StatsExtra stats_slice(const void* __restrict__ g, ui
                 const uint32_t am = in_tail ? a[j] : 0u;              // mantissa 1.0 outside the tail
                 mant[j] = __uint_as_float((am & 0x007FFFFFu) | 0x3F800000u);
             }
-            const float prod = ((mant[0] * mant[1]) * (mant[2] * mant[3])) * ((mant[4] * mant[5]) * (mant[6] * mant[7]));
+            float low = (mant[0] * mant[1]) * (mant[2] * mant[3]), high = (mant[4] * mant[5]) * (mant[6] * mant[7]);
+            if constexpr (ALL_LANES && kLines) {                       // the halves of two groups: even lanes finish the first
+                const bool odd = (threadIdx.x & 1u) != 0u;
+                const float given = odd ? low : high;
+                low = odd ? high : low;
+                high = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(given), 0xB1, 0xf, 0xf, true));
+            }
+            const float prod = low * high;
             log2m_fix += (uint32_t)(__log2f(prod) * 268435456.0f);     // prod in [1, 256]: at most 2^31
         }
     };
@@ -307,18 +335,24 @@ __device__ __forceinline__ StatsExtra stats_slice(const void* __restrict__ g, ui
     };
     // bufA holds trip 2p; the loop ends with the last or the last but one full trip in bufA
     const uint32_t loops = n_trips > 0 ? (n_trips - 1) >> 1 : 0;
-    for (uint32_t p = 0; p < loops; ++p) {
-        request(bufB, 2 * p + 1);
+    auto two_trips = [&](uint32_t p, auto past_caches) {
+        request(bufB, 2 * p + 1, past_caches);
         if constexpr (kWaitAll) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
         consume(bufA);
         __builtin_amdgcn_sched_barrier(0);
-        request(bufA, 2 * p + 2);
+        request(bufA, 2 * p + 2, past_caches);
         if constexpr (kWaitAll) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
         consume(bufB);
         __builtin_amdgcn_sched_barrier(0);
+    };
+    uint32_t p = 0;
+    if constexpr (PAST) {
+        const uint32_t past_loops = past_end > cstart ? (uint32_t)((past_end - cstart) / (2ull * kTrip * kStatsTile)) : 0u;
+        for (const uint32_t n = past_loops < loops ? past_loops : loops; p < n; ++p) two_trips(p, std::true_type{});
     }
+    for (; p < loops; ++p) two_trips(p, std::false_type{});
     if (n_trips == 0) {                                                // bufA holds the rest
         consume_rest(bufA);
     } else if (n_trips & 1u) {                                         // bufA holds the last full trip
@@ -328,7 +362,7 @@ __device__ __forceinline__ StatsExtra stats_slice(const void* __restrict__ g, ui
         __builtin_amdgcn_sched_barrier(0);
         consume_rest(bufB);
     } else {                                                           // bufA holds the last but one
-        request(bufB, n_trips - 1);
+        request(bufB, n_trips - 1, std::false_type{});
         __builtin_amdgcn_sched_barrier(0);
         consume(bufA);
         __builtin_amdgcn_sched_barrier(0);
@@ -419,7 +453,7 @@ __global__ __launch_bounds__(kStatsBlock) void tq_stats_partial_kernel(
     const bool final_record = slices == 1u;
     tq_stats_t* S = static_cast<tq_stats_t*>(stats_tab.p[blockIdx.y]) + bucket;
     uint32_t* row = final_record ? S->hist : ws_hist + ((uint64_t)bucket * slices + slice) * TQ_NBINS;
-    const StatsExtra x = stats_slice<DTYPE, TAIL>(g, cstart, cend, g_min, L, row);
+    const StatsExtra x = stats_slice<DTYPE, TAIL, false>(g, cstart, cend, 0, g_min, L, row);
     if (threadIdx.x == 0) {
         if (final_record) write_scalars(S, x, bend - bstart, g_min);
         else ws_extra[(uint64_t)bucket * slices + slice] = x;
@@ -511,14 +545,15 @@ __global__ __launch_bounds__(kReduceBlock) void tq_stats_reduce_kernel(
 
 constexpr uint64_t kBalancedMinBucket = 32768;
 
-template <int DTYPE, bool TAIL>
+template <int DTYPE, bool TAIL, bool PAST>
 __global__ __launch_bounds__(kStatsBlock) void tq_stats_balanced_kernel(
     const PtrTable g_tab, uint64_t d, uint64_t be, uint64_t nb, uint64_t tiles_per_tensor, uint64_t total_tiles,
-    float g_min, uint32_t* __restrict__ ws_hist, StatsExtra* __restrict__ ws_extra, const MutPtrTable stats_tab)
+    uint64_t kept_tiles, float g_min, uint32_t* __restrict__ ws_hist, StatsExtra* __restrict__ ws_extra, const MutPtrTable stats_tab)
 {
     const uint32_t w = blockIdx.x;
     uint64_t tile = share_start(w, total_tiles, gridDim.x);
     const uint64_t tile_end = share_start((uint64_t)w + 1, total_tiles, gridDim.x);
+    const uint64_t past_tile = PAST && tile_end > kept_tiles ? tile_end - kept_tiles : 0;
     __shared__ StatsLds L;
     bool first = true;
     while (tile < tile_end) {                                          // one pass per tensor the share touches
@@ -527,6 +562,7 @@ __global__ __launch_bounds__(kStatsBlock) void tq_stats_balanced_kernel(
         const uint64_t e0 = i * kStatsTile;
         const uint64_t e1 = i_end * kStatsTile < d ? i_end * kStatsTile : d;
         const void* __restrict__ g = g_tab.p[t];
+        const uint64_t past_end = past_tile > t * tiles_per_tensor ? (past_tile - t * tiles_per_tensor) * kStatsTile : 0;
         tq_stats_t* __restrict__ stats = static_cast<tq_stats_t*>(stats_tab.p[t]);
         for (uint64_t b = quotient(e0, be); b * be < e1; ++b) {
             const uint64_t lo = b * be, hi = lo + be < d ? lo + be : d;
@@ -535,7 +571,7 @@ __global__ __launch_bounds__(kStatsBlock) void tq_stats_balanced_kernel(
             const uint64_t r = (uint64_t)w + t * nb + b;
             if (!first) __syncthreads();                               // the histograms are cleared again
             first = false;
-            const StatsExtra x = stats_slice<DTYPE, TAIL>(g, cs, ce, g_min, L, whole ? stats[b].hist : ws_hist + r * TQ_NBINS);
+            const StatsExtra x = stats_slice<DTYPE, TAIL, PAST>(g, cs, ce, past_end, g_min, L, whole ? stats[b].hist : ws_hist + r * TQ_NBINS);
             if (threadIdx.x == 0) {
                 if (whole) write_scalars(stats + b, x, hi - lo, g_min);
                 else ws_extra[r] = x;
@@ -654,15 +690,16 @@ __global__ __launch_bounds__(kReduceBlock) void tq_stats_balanced_reduce_kernel(
 // consecutive); a second kernel adds each segment's rows.  Every access is bounded by d, nseg
 // and the number of rows, whatever the table holds.
 
-template <int DTYPE, bool TAIL>
+template <int DTYPE, bool TAIL, bool PAST>
 __global__ __launch_bounds__(kStatsBlock) void tq_stats_segments_partial_kernel(
     const PtrTable g_tab, uint64_t d, uint64_t tiles_per_tensor, uint64_t total_tiles,
-    const uint64_t* __restrict__ seg_off, uint32_t nseg, float g_min,
+    const uint64_t* __restrict__ seg_off, uint32_t nseg, uint64_t kept_tiles, float g_min,
     uint32_t* __restrict__ ws_hist, StatsExtra* __restrict__ ws_extra)
 {
     const uint32_t w = blockIdx.x;
     uint64_t tile = share_start(w, total_tiles, gridDim.x);
     const uint64_t tile_end = share_start((uint64_t)w + 1, total_tiles, gridDim.x);
+    const uint64_t past_tile = PAST && tile_end > kept_tiles ? tile_end - kept_tiles : 0;
     __shared__ StatsLds L;
     bool first = true;
     while (tile < tile_end) {                                          // one pass per tensor the share touches
@@ -671,6 +708,7 @@ __global__ __launch_bounds__(kStatsBlock) void tq_stats_segments_partial_kernel(
         const uint64_t cstart = i * kStatsTile;
         const uint64_t cend = i_end * kStatsTile < d ? i_end * kStatsTile : d;
         const void* __restrict__ g = g_tab.p[t];
+        const uint64_t past_end = past_tile > t * tiles_per_tensor ? (past_tile - t * tiles_per_tensor) * kStatsTile : 0;
         uint32_t s = find_segment(seg_off, nseg, cstart);
         for (;;) {
             // the last segment ends at d whatever the table says: the loop ends with the share
@@ -681,7 +719,7 @@ __global__ __launch_bounds__(kStatsBlock) void tq_stats_segments_partial_kernel(
             const uint64_t r = (uint64_t)w + t * nseg + s;
             if (!first) __syncthreads();                               // the histograms are cleared again
             first = false;
-            const StatsExtra x = stats_slice<DTYPE, TAIL>(g, seg_lo, seg_hi, g_min, L, ws_hist + r * TQ_NBINS);
+            const StatsExtra x = stats_slice<DTYPE, TAIL, PAST>(g, seg_lo, seg_hi, past_end, g_min, L, ws_hist + r * TQ_NBINS);
             if (threadIdx.x == 0) ws_extra[r] = x;
             if (seg_hi >= cend || s + 1 >= nseg) break;
             ++s;
@@ -790,6 +828,24 @@ bool uses_shares(uint64_t d, uint64_t bucket_elems)
     return be >= tq::kBalancedMinBucket;
 }
 
+// Whether a batch is read past the caches, and the tiles at the end of every share that are read through them all the same.
+// A batch larger than the memory-side cache (256 MiB) read through it leaves there what the next call displaces before
+// reaching it, and reads slower: with non-temporal loads, whole lines at a time, a persistent read loop of this shape reaches
+// 7.0 TB/s instead of 6.2.  What compress reads again should stay, so 192 MiB of the batch are read the ordinary
+// way, last.  Steps of 8 x 124 M fp32 (b = 2), 16 x 25.6 M (b = 3, tables), 8 x 11.2 M (b = 4) and 4 x 10^9 bf16, everything
+// through the caches / nothing / 192 MiB, compress reading past the caches: 1404 / 1347 / 1334, 658 / 636 / 628, 154.2 / 148.4 / 147.6,
+// 4007 / 3917 / 3916 us (160 to 240 MiB: the same).  A batch that fits is read through the caches whole: past them 25.6 M
+// fp32 65.9 -> 69.0, 4 x 11.2 M 102 -> 112 (and with whole-line loads from the caches 65.7 -> 66.4).
+bool stats_past_caches(int count, uint64_t d, int dtype)
+{
+    return (uint64_t)count * d * (dtype == TQ_F32 ? 4u : 2u) > (256ull << 20);
+}
+
+uint64_t stats_kept_tiles(int dtype, uint32_t groups)
+{
+    return (192ull << 20) / (tq::kStatsTile * (dtype == TQ_F32 ? 4u : 2u)) / groups;
+}
+
 }  // namespace
 
 uint64_t tq_stats_workspace_bytes_impl(uint64_t d, uint64_t bucket_elems)
@@ -852,17 +908,22 @@ hipError_t tq_launch_stats(const void* const* g, int count, int dtype, uint64_t 
         const uint64_t fit = total_tiles * tq::kStatsTile / tq::kStatsMinSlice;   // shares of at least 16384 elements
         const uint32_t groups = (uint32_t)(fit < 1 ? 1 : (fit < resident ? fit : resident));
         const uint64_t rows = groups + nb * (uint64_t)count;
+        const bool past = stats_past_caches(count, d, dtype);
+        const uint64_t kept = stats_kept_tiles(dtype, groups);
         uint32_t* ws_hist = static_cast<uint32_t*>(workspace);
         tq::StatsExtra* ws_extra = reinterpret_cast<tq::StatsExtra*>(static_cast<char*>(workspace) + rows * TQ_NBINS * 4);
-#define TQ_LAUNCH_SHARES(DT, TL)                                                                                  \
-    hipLaunchKernelGGL((tq::tq_stats_balanced_kernel<DT, TL>), dim3(groups), dim3(tq::kStatsBlock), 0, st, gt, d, be, \
-                       nb, tiles_per_tensor, total_tiles, g_min, ws_hist, ws_extra, stt)
+#define TQ_LAUNCH_SHARES_AS(DT, TL, PA)                                                                                 \
+    hipLaunchKernelGGL((tq::tq_stats_balanced_kernel<DT, TL, PA>), dim3(groups), dim3(tq::kStatsBlock), 0, st, gt, d, be, \
+                       nb, tiles_per_tensor, total_tiles, kept, g_min, ws_hist, ws_extra, stt)
+#define TQ_LAUNCH_SHARES(DT, TL)   \
+    do { if (past) TQ_LAUNCH_SHARES_AS(DT, TL, true); else TQ_LAUNCH_SHARES_AS(DT, TL, false); } while (0)
         if (dtype == TQ_F32) {
             if (g_min > 0.0f) { TQ_LAUNCH_SHARES(TQ_F32, true); } else { TQ_LAUNCH_SHARES(TQ_F32, false); }
         } else {
             if (g_min > 0.0f) { TQ_LAUNCH_SHARES(TQ_BF16, true); } else { TQ_LAUNCH_SHARES(TQ_BF16, false); }
         }
 #undef TQ_LAUNCH_SHARES
+#undef TQ_LAUNCH_SHARES_AS
         hipError_t err = hipGetLastError();
         if (err != hipSuccess || groups == 1) return err;
         const uint32_t gpb = (TQ_NBINS + tq::kReduceBins - 1) / tq::kReduceBins + 1;
@@ -940,19 +1001,24 @@ hipError_t tq_launch_stats_segments(const void* const* g, int count, int dtype, 
     const uint64_t fit = total_tiles * tq::kStatsTile / tq::kStatsMinSlice;       // shares of at least 16384 elements
     const uint32_t groups = (uint32_t)(fit < 1 ? 1 : (fit < resident ? fit : resident));
     const uint64_t rows = groups + nseg * (uint64_t)count;
+    const bool past = stats_past_caches(count, d, dtype);
+    const uint64_t kept = stats_kept_tiles(dtype, groups);
     uint32_t* ws_hist = static_cast<uint32_t*>(workspace);
     tq::StatsExtra* ws_extra = reinterpret_cast<tq::StatsExtra*>(static_cast<char*>(workspace) + rows * TQ_NBINS * 4);
     dim3 rgrid;
     if (!tq::fold_grid(nseg * (uint64_t)count, tq::kStatsBlock, 1, rgrid)) return hipErrorInvalidValue;
-#define TQ_LAUNCH_SEG_PARTIAL(DT, TL)                                                                              \
-    hipLaunchKernelGGL((tq::tq_stats_segments_partial_kernel<DT, TL>), dim3(groups), dim3(tq::kStatsBlock), 0, st, gt, \
-                       d, tiles_per_tensor, total_tiles, seg_off, (uint32_t)nseg, g_min, ws_hist, ws_extra)
+#define TQ_LAUNCH_SEG_PARTIAL_AS(DT, TL, PA)                                                                             \
+    hipLaunchKernelGGL((tq::tq_stats_segments_partial_kernel<DT, TL, PA>), dim3(groups), dim3(tq::kStatsBlock), 0, st, gt, \
+                       d, tiles_per_tensor, total_tiles, seg_off, (uint32_t)nseg, kept, g_min, ws_hist, ws_extra)
+#define TQ_LAUNCH_SEG_PARTIAL(DT, TL)   \
+    do { if (past) TQ_LAUNCH_SEG_PARTIAL_AS(DT, TL, true); else TQ_LAUNCH_SEG_PARTIAL_AS(DT, TL, false); } while (0)
     if (dtype == TQ_F32) {
         if (g_min > 0.0f) TQ_LAUNCH_SEG_PARTIAL(TQ_F32, true); else TQ_LAUNCH_SEG_PARTIAL(TQ_F32, false);
     } else {
         if (g_min > 0.0f) TQ_LAUNCH_SEG_PARTIAL(TQ_BF16, true); else TQ_LAUNCH_SEG_PARTIAL(TQ_BF16, false);
     }
 #undef TQ_LAUNCH_SEG_PARTIAL
+#undef TQ_LAUNCH_SEG_PARTIAL_AS
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL(tq::tq_stats_segments_reduce_kernel, rgrid, dim3(tq::kStatsBlock), 0, st, d, tiles_per_tensor,

@@ -11,12 +11,11 @@
 
 namespace tq {
 
-// STREAM: non-temporal loads.  This is the last read of the gradient; when the whole batch is
-// small enough that the memory-side cache still holds much of what the statistics pass read,
-// the hint keeps this kernel's misses from displacing the lines it is about to hit (-6 % on
-// 8 x 45 MB).  On data that cannot be cached anyway the same hint costs 12 % (misses are
-// slower with it), so the host turns it on by size.
-template <int DTYPE, bool STREAM>
+// NT: non-temporal loads.  In the main path this is the last read of the gradient.  While the batch is small enough
+// that the memory-side cache still holds much of what the statistics pass read, the hint keeps this kernel's misses
+// from displacing the lines it is about to hit (-6 % on 8 x 45 MB); a larger batch gains by it too, if its
+// lines are read whole (see load_groups_wave).
+template <int DTYPE, bool NT>
 __device__ __forceinline__ void load_group(const void* g, uint64_t e0, float (&x)[8])
 {
     typedef float f4 __attribute__((ext_vector_type(4)));
@@ -24,14 +23,14 @@ __device__ __forceinline__ void load_group(const void* g, uint64_t e0, float (&x
     if constexpr (DTYPE == TQ_F32) {
         const f4* p = reinterpret_cast<const f4*>(static_cast<const float*>(g) + e0);
         f4 a, b;
-        if constexpr (STREAM) { a = __builtin_nontemporal_load(p); b = __builtin_nontemporal_load(p + 1); }
+        if constexpr (NT) { a = __builtin_nontemporal_load(p); b = __builtin_nontemporal_load(p + 1); }
         else { a = p[0]; b = p[1]; }
         x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
         x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
     } else {
         const u4* p = reinterpret_cast<const u4*>(static_cast<const uint16_t*>(g) + e0);
         u4 v;
-        if constexpr (STREAM) v = __builtin_nontemporal_load(p);
+        if constexpr (NT) v = __builtin_nontemporal_load(p);
         else v = p[0];
         const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
@@ -39,6 +38,32 @@ __device__ __forceinline__ void load_group(const void* g, uint64_t e0, float (&x
             x[2 * i] = __uint_as_float(w[i] << 16);
             x[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u);
         }
+    }
+}
+
+// fp32, a whole wavefront whose lanes own the 64 groups from element `base` on: the two loads read 1 KiB in one piece
+// each, the lower 32 lanes the even 16-byte pieces of it and the upper ones the odd, and settle_group gives every
+// lane the two pieces of its own group.  A non-temporal line is not kept for a second load that wants its other
+// half: 8 x 124 M at b = 2, one step, a lane's own 32 bytes through the caches / past them / this way past them
+// 1356 / 1441 / 1338 us (with 68 layers 1458 / 1516 / 1406), 16 x 25.6 M at b = 3 with tables 642 / 664 / 625; pieces in the
+// lanes' order exchanged by DPP moves 1338 / 1410 / 628.  On batches that the memory-side cache still holds the lane's own
+// 32 bytes are as good or better: 8 x 11.2 M 144.3 / 147.0.
+__device__ __forceinline__ void load_groups_wave(const void* g, uint64_t base, uint32_t lane, float (&x)[8])
+{
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    const f4* p = reinterpret_cast<const f4*>(static_cast<const float*>(g) + base) + (2u * (lane & 31u) + (lane >> 5));
+    const f4 a = __builtin_nontemporal_load(p), b = __builtin_nontemporal_load(p + 64);
+    x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
+    x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
+}
+
+__device__ __forceinline__ void settle_group(float (&x)[8])
+{
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {                              // the upper half of the first load against the lower half of the second
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[j]), __float_as_uint(x[4 + j]), false, false);
+        x[j] = __uint_as_float(r[0]);
+        x[4 + j] = __uint_as_float(r[1]);
     }
 }
 
@@ -332,7 +357,7 @@ __device__ __forceinline__ void store_codes(uint8_t* out, uint32_t word, uint64_
 // reads them: they leave the caches to the gradient and go out as they come.  8 x 124 M fp32 uniform at
 // b = 2 / 3 / 4: 671 -> 641, 689 -> 672, 700 -> 677 us; with a payload that the decode finds in the
 // memory-side cache the hint costs the decode more than it gives here (4 x 11.2 M at b = 3: 1 us
-// against 3.6), so the host turns it on with the same line as the hint on the loads, the other way.
+// against 3.6), so the host turns it on with the whole-line loads (compress_cached).
 // b = 3: the 12 bytes of four lanes leave as three 4-byte stores of the first three (bytes sent past
 // the caches one by one cost 1.6 times the whole launch); through the caches single bytes are as good.
 template <int BITS, bool PAST_CACHES>
@@ -482,13 +507,18 @@ __device__ __forceinline__ uint32_t encode_general(const float (&x)[8], const ui
 
 // N tiles from `base` on in which every lane owns a whole group: all reads first, the draws under them (requesting the
 // reads even earlier, before the codebook is set up, was slower: 708 us against 668 on 8 x 124 M fp32).
-template <int DTYPE, int BITS, bool STREAM, int N, typename Draw, typename Encode>
+template <int DTYPE, int BITS, bool CACHED, int N, typename Draw, typename Encode>
 __device__ __forceinline__ void encode_tiles(const void* g, uint8_t* payload, uint64_t base, uint32_t lane, Draw draw, Encode encode)
 {
+    constexpr bool kLines = DTYPE == TQ_F32 && !CACHED;
     float x[N][8];
     uint32_t rw[N][4];
 #pragma unroll
-    for (int t = 0; t < N; ++t) load_group<DTYPE, STREAM>(g, base + (uint64_t)t * kTile + (uint64_t)lane * kGroup, x[t]);
+    for (int t = 0; t < N; ++t) {
+        const uint64_t tile = base + (uint64_t)t * kTile;
+        if constexpr (kLines) load_groups_wave(g, tile + (lane & ~63u) * kGroup, lane & 63u, x[t]);
+        else load_group<DTYPE, true>(g, tile + (uint64_t)lane * kGroup, x[t]);
+    }
 #pragma unroll
     for (int t = 0; t < N; ++t) {
         draw(base + (uint64_t)t * kTile, rw[t]);
@@ -496,14 +526,15 @@ __device__ __forceinline__ void encode_tiles(const void* g, uint8_t* payload, ui
     }
 #pragma unroll
     for (int t = 0; t < N; ++t) {
+        if constexpr (kLines) settle_group(x[t]);
         replace_nan(x[t]);
         const uint32_t word = encode(x[t], rw[t]);
-        store_codes_wave<BITS, !STREAM>(payload + (((base + (uint64_t)t * kTile) >> 3) + lane) * (uint64_t)BITS, word);
+        store_codes_wave<BITS, !CACHED>(payload + (((base + (uint64_t)t * kTile) >> 3) + lane) * (uint64_t)BITS, word);
     }
 }
 
 // A workgroup's T whole tiles on the general path.
-template <int DTYPE, int BITS, bool STREAM, int T, bool MIRROR, typename Draw>
+template <int DTYPE, int BITS, bool CACHED, int T, bool MIRROR, typename Draw>
 __device__ __forceinline__ void encode_tiles_general(const void* g, uint8_t* payload, uint64_t base, uint32_t lane, Draw draw,
                                                      const tq_params_t* P, const Codebook& cb, const float (&lv)[16], const LevelLds& tab)
 {
@@ -512,18 +543,18 @@ __device__ __forceinline__ void encode_tiles_general(const void* g, uint8_t* pay
     if constexpr (MIRROR) {                                    // two tiles at a time: no more registers than the mirrored path
         constexpr int N = T < 2 ? T : 2;
 #pragma unroll 1
-        for (int t = 0; t < T; t += N) encode_tiles<DTYPE, BITS, STREAM, N>(g, payload, base + (uint64_t)t * kTile, lane, draw, clamped);
+        for (int t = 0; t < T; t += N) encode_tiles<DTYPE, BITS, CACHED, N>(g, payload, base + (uint64_t)t * kTile, lane, draw, clamped);
     } else {
         if (T == compress_tiles(DTYPE, true) && cb.nonuniform && truncates_itself<BITS>(P, cb.alpha))
-            encode_tiles<DTYPE, BITS, STREAM, T>(g, payload, base, lane, draw, plain);
+            encode_tiles<DTYPE, BITS, CACHED, T>(g, payload, base, lane, draw, plain);
         else
-            encode_tiles<DTYPE, BITS, STREAM, T>(g, payload, base, lane, draw, clamped);
+            encode_tiles<DTYPE, BITS, CACHED, T>(g, payload, base, lane, draw, clamped);
     }
 }
 
 // MIRROR: level tables are checked for the mirrored path and take it if they are regular; else every record is
 // encoded on the general one.
-template <int DTYPE, int BITS, bool STREAM, int T, bool MIRROR>
+template <int DTYPE, int BITS, bool CACHED, int T, bool MIRROR>
 __global__ __launch_bounds__(kBlock, !MIRROR && T <= 2 && !(DTYPE == TQ_BF16 && BITS == 4) ? 8 : 1) void tq_compress_kernel(
     const PtrTable g_tab, uint64_t d, uint64_t d_pad, uint64_t bucket_elems,
     uint32_t groups_per_bucket, const PtrTable params_tab, uint32_t seed_lo,
@@ -553,7 +584,7 @@ __global__ __launch_bounds__(kBlock, !MIRROR && T <= 2 && !(DTYPE == TQ_BF16 && 
         __shared__ CellLds cells;
         cb = set_up_codebook<BITS>(P, cells, lane);
         if (cb.regular && whole) {
-            encode_tiles<DTYPE, BITS, STREAM, T>(g, payload, gbase, lane, draw, [&](const float (&x)[8], const uint32_t (&rw)[4]) {
+            encode_tiles<DTYPE, BITS, CACHED, T>(g, payload, gbase, lane, draw, [&](const float (&x)[8], const uint32_t (&rw)[4]) {
                 return encode_whole<BITS>(x, rw, cb, cells);
             });
             return;
@@ -563,7 +594,7 @@ __global__ __launch_bounds__(kBlock, !MIRROR && T <= 2 && !(DTYPE == TQ_BF16 && 
         // bf16: the uniform codebook apart from the tables' code, which costs it 1 us of 14 on 25.6 M at b = 3 and 4 (fp32
         // the other way round: tables at b = 2 20.9 us with it, 21.9 without)
         if (DTYPE == TQ_BF16 && whole && !cb.nonuniform) {
-            encode_tiles<DTYPE, BITS, STREAM, T>(g, payload, gbase, lane, draw, [&](const float (&x)[8], const uint32_t (&rw)[4]) {
+            encode_tiles<DTYPE, BITS, CACHED, T>(g, payload, gbase, lane, draw, [&](const float (&x)[8], const uint32_t (&rw)[4]) {
                 return encode_uniform<BITS>(x, rw, cb);
             });
             return;
@@ -573,7 +604,7 @@ __global__ __launch_bounds__(kBlock, !MIRROR && T <= 2 && !(DTYPE == TQ_BF16 && 
     float lv[16];
     if (cb.nonuniform) set_up_levels<BITS>(P, tab, lv);
     if (whole) {
-        encode_tiles_general<DTYPE, BITS, STREAM, T, MIRROR>(g, payload, gbase, lane, draw, P, cb, lv, tab);
+        encode_tiles_general<DTYPE, BITS, CACHED, T, MIRROR>(g, payload, gbase, lane, draw, P, cb, lv, tab);
         return;
     }
 
@@ -623,7 +654,7 @@ constexpr int segment_waves(int dtype, int bits, int tiles)
 // one, the offsets being multiples of 128).  The last segment also owns the
 // padding up to a multiple of 128 elements.  No access depends on the table being well-formed:
 // the segment index stays inside [0, nseg) and every element access is bounded by d.
-template <int DTYPE, int BITS, bool STREAM, int T, bool MIRROR>
+template <int DTYPE, int BITS, bool CACHED, int T, bool MIRROR>
 __global__ __launch_bounds__(kBlock, segment_waves(DTYPE, BITS, T)) void tq_compress_segments_kernel(
     const PtrTable g_tab, uint64_t d, uint64_t d_pad, const uint64_t* __restrict__ seg_off, uint32_t nseg,
     const SegHints hints, const PtrTable params_tab, uint32_t seed_lo, uint32_t seed_hi, uint32_t first_worker, uint32_t step,
@@ -670,7 +701,7 @@ __global__ __launch_bounds__(kBlock, segment_waves(DTYPE, BITS, T)) void tq_comp
                 __shared__ CellLds cells;
                 cb = set_up_codebook<BITS>(P, cells, lane);
                 if (cb.regular) {
-                    encode_tiles<DTYPE, BITS, STREAM, T>(g, payload, gbase, lane, draw, [&](const float (&v)[8], const uint32_t (&r)[4]) {
+                    encode_tiles<DTYPE, BITS, CACHED, T>(g, payload, gbase, lane, draw, [&](const float (&v)[8], const uint32_t (&r)[4]) {
                         return encode_whole<BITS>(v, r, cb, cells);
                     });
                     return;
@@ -682,9 +713,9 @@ __global__ __launch_bounds__(kBlock, segment_waves(DTYPE, BITS, T)) void tq_comp
             if (cb.nonuniform) set_up_levels<BITS>(P, tab, lv);
             if constexpr (T == 1) {
                 replace_nan(x);
-                store_codes_wave<BITS, !STREAM>(payload + ((gbase >> 3) + lane) * (uint64_t)BITS, encode_general<BITS, true>(x, rw, cb, lv, tab));
+                store_codes_wave<BITS, !CACHED>(payload + ((gbase >> 3) + lane) * (uint64_t)BITS, encode_general<BITS, true>(x, rw, cb, lv, tab));
             } else {
-                encode_tiles_general<DTYPE, BITS, STREAM, T, MIRROR>(g, payload, gbase, lane, draw, P, cb, lv, tab);
+                encode_tiles_general<DTYPE, BITS, CACHED, T, MIRROR>(g, payload, gbase, lane, draw, P, cb, lv, tab);
             }
             return;
         }
@@ -845,9 +876,10 @@ __global__ __launch_bounds__(kBlock) void tq_simulate_kernel(
 
 namespace {
 
-// Non-temporal loads while the batch can still be (partly) cached from the statistics pass: up to twice the
-// 256 MiB of the memory-side cache.  Above that, non-temporal stores (see store_codes_wave).
-bool compress_streams(int count, uint64_t d, int dtype)
+// Whether the memory-side cache (256 MiB) can still hold much of the batch from the statistics pass: up to twice its size.
+// Then a lane reads its own 32 bytes and the payload is stored through the caches, else lines are read whole
+// (load_groups_wave) and the payload goes past them (store_codes_wave).
+bool compress_cached(int count, uint64_t d, int dtype)
 {
     return (uint64_t)count * d * (dtype == TQ_F32 ? 4u : 2u) <= (512ull << 20);
 }
@@ -885,27 +917,27 @@ struct CompressArgs {
     uint32_t groups_per_bucket, first_worker, step;
 };
 
-template <int DTYPE, int BITS, bool STREAM, bool TABLE_TILES, bool MIRROR>
+template <int DTYPE, int BITS, bool CACHED, bool TABLE_TILES, bool MIRROR>
 void launch_as(const CompressArgs& a)
 {
-    hipLaunchKernelGGL((tq::tq_compress_kernel<DTYPE, BITS, STREAM, tq::compress_tiles(DTYPE, TABLE_TILES), MIRROR>), a.blocks,
+    hipLaunchKernelGGL((tq::tq_compress_kernel<DTYPE, BITS, CACHED, tq::compress_tiles(DTYPE, TABLE_TILES), MIRROR>), a.blocks,
                        dim3(tq::kBlock), 0, a.st, a.g, a.d, a.d_pad, a.be, a.groups_per_bucket, a.params, (uint32_t)a.seed,
                        (uint32_t)(a.seed >> 32), a.first_worker, a.step, a.payload, a.pbytes);
 }
 
-template <int DTYPE, int BITS, bool STREAM>
+template <int DTYPE, int BITS, bool CACHED>
 hipError_t launch(const CompressShape& shape, const CompressArgs& a)
 {
     if constexpr (mirrored_pays(DTYPE, BITS)) {
-        if (shape.mirror && shape.table_tiles) { launch_as<DTYPE, BITS, STREAM, true, true>(a); return hipGetLastError(); }
+        if (shape.mirror && shape.table_tiles) { launch_as<DTYPE, BITS, CACHED, true, true>(a); return hipGetLastError(); }
         if constexpr (DTYPE == TQ_BF16 && BITS == 3) {
-            if (shape.mirror) { launch_as<DTYPE, BITS, STREAM, false, true>(a); return hipGetLastError(); }
+            if (shape.mirror) { launch_as<DTYPE, BITS, CACHED, false, true>(a); return hipGetLastError(); }
         }
     } else if (shape.table_tiles) {
-        launch_as<DTYPE, BITS, STREAM, true, false>(a);
+        launch_as<DTYPE, BITS, CACHED, true, false>(a);
         return hipGetLastError();
     }
-    launch_as<DTYPE, BITS, STREAM, false, false>(a);
+    launch_as<DTYPE, BITS, CACHED, false, false>(a);
     return hipGetLastError();
 }
 
@@ -935,8 +967,8 @@ hipError_t tq_launch_compress(const void* const* g, int count, int dtype, uint64
     a.d = d; a.d_pad = d_pad; a.be = be; a.seed = seed;
     a.pbytes = tq_payload_bytes(d, bits);
     a.first_worker = first_worker; a.step = step;
-    const bool stream = compress_streams(count, d, dtype);
-#define TQ_LAUNCH_COMPRESS(DT, B) (stream ? launch<DT, B, true>(shape, a) : launch<DT, B, false>(shape, a))
+    const bool cached = compress_cached(count, d, dtype);
+#define TQ_LAUNCH_COMPRESS(DT, B) (cached ? launch<DT, B, true>(shape, a) : launch<DT, B, false>(shape, a))
 #define TQ_LAUNCH_COMPRESS_B(DT) \
     (bits == 2 ? TQ_LAUNCH_COMPRESS(DT, 2) : (bits == 3 ? TQ_LAUNCH_COMPRESS(DT, 3) : TQ_LAUNCH_COMPRESS(DT, 4)))
     return dtype == TQ_F32 ? TQ_LAUNCH_COMPRESS_B(TQ_F32) : TQ_LAUNCH_COMPRESS_B(TQ_BF16);
@@ -1025,7 +1057,7 @@ hipError_t tq_launch_compress_segments(const void* const* g, int count, int dtyp
     const uint64_t pbytes = tq_payload_bytes(d, bits);
     const dim3 threads(tq::kBlock);
     const tq::SegHints hints = tq::make_seg_hints(seg_host, nseg, d);
-    const bool stream = compress_streams(count, d, dtype);
+    const bool cached = compress_cached(count, d, dtype);
 #define TQ_LAUNCH_CSEG(DT, B, ST, T, MI)                                                                        \
     hipLaunchKernelGGL((tq::tq_compress_segments_kernel<DT, B, ST, T, MI>), blocks, threads, 0, st, gt, d,      \
                        d_pad, seg_off, (uint32_t)nseg, hints, pt, slo, shi, first_worker, step, yt, pbytes)
@@ -1034,7 +1066,7 @@ hipError_t tq_launch_compress_segments(const void* const* g, int count, int dtyp
         if (one_tile) TQ_LAUNCH_CSEG(DT, B, ST, 1, false);                                             \
         else TQ_LAUNCH_CSEG(DT, B, ST, tq::segment_tiles(DT), mirrored_pays(DT, B));                   \
     } while (0)
-#define TQ_LAUNCH_CSEG_ST(DT, B) if (stream) TQ_LAUNCH_CSEG_T(DT, B, true); else TQ_LAUNCH_CSEG_T(DT, B, false)
+#define TQ_LAUNCH_CSEG_ST(DT, B) if (cached) TQ_LAUNCH_CSEG_T(DT, B, true); else TQ_LAUNCH_CSEG_T(DT, B, false)
 #define TQ_LAUNCH_CSEG_B(DT)                         \
     switch (bits) {                                  \
         case 2: TQ_LAUNCH_CSEG_ST(DT, 2); break;     \

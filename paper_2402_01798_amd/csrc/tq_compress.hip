@@ -42,8 +42,7 @@ __device__ __forceinline__ void load_group(const void* g, uint64_t e0, float (&x
 }
 
 // fp32, a whole wavefront whose lanes own the 64 groups from element `base` on: the two loads read 1 KiB in one piece
-// each, the lower 32 lanes the even 16-byte pieces of it and the upper ones the odd, and settle_group gives every
-// lane the two pieces of its own group.  A non-temporal line is not kept for a second load that wants its other
+// each, and swap_pieces gives every lane the two pieces of its own group.  A non-temporal line is not kept for a second load that wants its other
 // half: 8 x 124 M at b = 2, one step, a lane's own 32 bytes through the caches / past them / this way past them
 // 1356 / 1441 / 1338 us (with 68 layers 1458 / 1516 / 1406), 16 x 25.6 M at b = 3 with tables 642 / 664 / 625; pieces in the
 // lanes' order exchanged by DPP moves 1338 / 1410 / 628.  On batches that the memory-side cache still holds the lane's own
@@ -51,20 +50,10 @@ __device__ __forceinline__ void load_group(const void* g, uint64_t e0, float (&x
 __device__ __forceinline__ void load_groups_wave(const void* g, uint64_t base, uint32_t lane, float (&x)[8])
 {
     typedef float f4 __attribute__((ext_vector_type(4)));
-    const f4* p = reinterpret_cast<const f4*>(static_cast<const float*>(g) + base) + (2u * (lane & 31u) + (lane >> 5));
+    const f4* p = reinterpret_cast<const f4*>(static_cast<const float*>(g) + base) + wave_piece(lane);
     const f4 a = __builtin_nontemporal_load(p), b = __builtin_nontemporal_load(p + 64);
     x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
     x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
-}
-
-__device__ __forceinline__ void settle_group(float (&x)[8])
-{
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {                              // the upper half of the first load against the lower half of the second
-        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[j]), __float_as_uint(x[4 + j]), false, false);
-        x[j] = __uint_as_float(r[0]);
-        x[4 + j] = __uint_as_float(r[1]);
-    }
 }
 
 template <int DTYPE>
@@ -526,7 +515,7 @@ __device__ __forceinline__ void encode_tiles(const void* g, uint8_t* payload, ui
     }
 #pragma unroll
     for (int t = 0; t < N; ++t) {
-        if constexpr (kLines) settle_group(x[t]);
+        if constexpr (kLines) swap_pieces(x[t]);
         replace_nan(x[t]);
         const uint32_t word = encode(x[t], rw[t]);
         store_codes_wave<BITS, !CACHED>(payload + (((base + (uint64_t)t * kTile) >> 3) + lane) * (uint64_t)BITS, word);
@@ -804,7 +793,6 @@ __global__ __launch_bounds__(kBlock) void tq_simulate_kernel(
     const tq_params_t* P = params + bucket;
 
     __shared__ LevelLds tab;                                   // the table, and what a code stands for
-    __shared__ float4 xbuf[kBlock / 64][128];                  // store8_wave's exchange buffers
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane((int)(tid >> 6));
     const Codebook cb = read_codebook(P);
     float lv[16];
@@ -860,7 +848,7 @@ __global__ __launch_bounds__(kBlock) void tq_simulate_kernel(
             if constexpr (ACC) y[j] = prev[t][j] + y[j];
         }
         if (!(ACC && PAST_CACHES) && base + 64 * kGroup <= bend) {
-            store8_wave<PAST_CACHES>(out + base, (int)lane, y, xbuf[wave]);
+            store8_wave<PAST_CACHES>(out + base, lane, y);
         } else if (e0 + kGroup <= bend) {
             reinterpret_cast<float4*>(out + e0)[0] = make_float4(y[0], y[1], y[2], y[3]);
             reinterpret_cast<float4*>(out + e0)[1] = make_float4(y[4], y[5], y[6], y[7]);

@@ -114,15 +114,14 @@ __device__ __forceinline__ void finish_group(float* o, uint64_t e0, float (&acc)
 }
 
 template <int MODE>
-__device__ __forceinline__ void finish_group_wave(float* out, uint64_t e0, int lane, float (&acc)[8],
-                                                  const float (&prev)[8], float (&vel)[8], const Update& up,
-                                                  float4* wb)
+__device__ __forceinline__ void finish_group_wave(float* out, uint64_t e0, uint32_t lane, float (&acc)[8],
+                                                  const float (&prev)[8], float (&vel)[8], const Update& up)
 {
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] = finish<MODE>(acc[j], prev[j], vel[j], up);
     const uint64_t wave_e0 = e0 - (uint64_t)lane * kGroup;
-    store8_wave<MODE == kStoreStream>(out + wave_e0, lane, acc, wb);
-    if constexpr (MODE == kSgdMomentum) store8_wave<false>(up.velocity + wave_e0, lane, vel, wb);
+    store8_wave<MODE == kStoreStream>(out + wave_e0, lane, acc);
+    if constexpr (MODE == kSgdMomentum) store8_wave<false>(up.velocity + wave_e0, lane, vel);
 }
 
 // The ragged end of the tensor, element by element (only in the last workgroup of the tensor;
@@ -184,7 +183,6 @@ __global__ __launch_bounds__(kBlock) void tq_decode_fast_kernel(
     constexpr uint32_t PMASK = PAIRS - 1;
     constexpr uint32_t CMASK = (1u << BITS) - 1u;
     __shared__ float2 pair_tab[U * PAIRS];
-    __shared__ float4 xbuf[kBlock / 64][128];                  // store8_wave's exchange buffers
 
     const uint32_t blk = linear_block();
     uint32_t bucket = 0;                                       // the record of the workgroup's range
@@ -330,7 +328,7 @@ __global__ __launch_bounds__(kBlock) void tq_decode_fast_kernel(
         for (int t = 0; t < T; ++t) {
             float acc[8];
             lookup(t, acc);
-            finish_group_wave<MODE>(out, e0[t], lane, acc, prev[t], vel[t], up, xbuf[wave]);
+            finish_group_wave<MODE>(out, e0[t], (uint32_t)lane, acc, prev[t], vel[t], up);
         }
     } else {
         // the last workgroup of a bucket: tile by tile (one tile's values live at a time)
@@ -368,7 +366,6 @@ __global__ __launch_bounds__(kBlock) void tq_decode_many_kernel(
     constexpr int ROW = ENTRIES * (PAIR ? 8 : 4);              // bytes of a worker's table
     constexpr int CMASK = (1 << BITS) - 1;
     __shared__ __align__(16) char table[U * ROW];
-    __shared__ float4 xbuf[kBlock / 64][128];                  // store8_wave's exchange buffers
 
     const uint32_t blk = linear_block();
     const uint32_t bucket = blk / groups_per_bucket;
@@ -455,13 +452,13 @@ __global__ __launch_bounds__(kBlock) void tq_decode_many_kernel(
         }
     }
     const float post = weighted ? 1.0f : scale;                // x * 1.0f is exact
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint32_t lane = threadIdx.x & 63u;
     const bool whole = gstart + (uint64_t)T * kTile <= bend;
 #pragma unroll
     for (int t = 0; t < T; ++t) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) acc[t][j] = acc[t][j] * post;
-        if (whole) finish_group_wave<MODE>(out, e0[t], lane, acc[t], prev[t], vel[t], up, xbuf[wave]);
+        if (whole) finish_group_wave<MODE>(out, e0[t], lane, acc[t], prev[t], vel[t], up);
         else if (e0[t] + kGroup <= bend) finish_group<MODE>(out + e0[t], e0[t], acc[t], prev[t], vel[t], up);
         else if (e0[t] < bend) finish_ragged<MODE>(out + e0[t], e0[t], acc[t], (int)(bend - e0[t]), up);
     }

@@ -104,25 +104,44 @@ inline bool output_past_caches(uint64_t bytes) { return bytes > (160ull << 20); 
 
 typedef float float4_native __attribute__((ext_vector_type(4)));
 
+// Exchanges a wavefront's 32 bytes per lane between two layouts (it undoes itself; the whole wavefront is active):
+// x = the lane's own group of 8 fp32 values, and x = the pieces of 16 bytes with which a load or store instruction
+// covers 1 KiB in one piece: piece wave_piece(lane) of the wavefront's first 64 in x[0..3], of its second in x[4..7].
+// The lower half holds the even pieces of the first load (a group's first half), the upper half the odd ones, so one
+// v_permlane32_swap per register is all it takes.
+__device__ __forceinline__ uint32_t wave_piece(uint32_t lane) { return 2u * (lane & 31u) + (lane >> 5); }
+__device__ __forceinline__ void swap_pieces(float (&x)[8])
+{
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {                              // the upper half of x[j] against the lower half of x[4 + j]
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[j]), __float_as_uint(x[4 + j]), false, false);
+        x[j] = __uint_as_float(r[0]);
+        x[4 + j] = __uint_as_float(r[1]);
+    }
+}
+
 // 32 bytes per lane, stored by a WHOLE wavefront (every lane owns a group; `o` is lane
 // 0's address).  Stored directly, each of the wavefront's two 16-byte store instructions would
-// touch every line of its 2 KiB half-way; exchanged through LDS, lane l stores the l-th and the
-// (64 + l)-th 16 bytes, so that each store instruction writes 1 KiB in one piece (measured: the
-// aggregate of 8 x 124 M elements 139 us -> 118 us, of 8 x 11.2 M 20.8 -> 15.6 us).  `wb` is the
-// wavefront's own 2 KiB of LDS; a wavefront's LDS operations complete in order, so no barrier.
+// touch every line of its 2 KiB half-way; as pieces each writes 1 KiB in one piece (the
+// aggregate of 8 x 124 M elements 139 us -> 118, of 8 x 11.2 M 20.8 -> 15.6).  The exchange in registers instead of
+// through LDS, whose reads bound the look-ups: 8 x 11.2 M at b = 4 18.2 -> 16.2 us, 8 x 124 M in 68 layers 124.8 -> 119.3,
+// 8 x 25.6 M with momentum 82.6 -> 80.2, 32 x 11.2 M at b = 4 41.5 -> 40.1; 8 x 124 M 119.4 -> 122 and 4 x 10^9 808 -> 829 by
+// itself, the steps around them 1335 -> 1338 and 3894 -> 3883.
 template <bool STREAM>
-__device__ __forceinline__ void store8_wave(float* o, int lane, const float (&x)[8], float4* wb)
+__device__ __forceinline__ void store8_wave(float* o, uint32_t lane, const float (&x)[8])
 {
-    wb[2 * lane] = make_float4(x[0], x[1], x[2], x[3]);
-    wb[2 * lane + 1] = make_float4(x[4], x[5], x[6], x[7]);
-    const float4 a = wb[lane], b = wb[64 + lane];
+    float y[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) y[j] = x[j];
+    swap_pieces(y);
+    const float4_native a = {y[0], y[1], y[2], y[3]}, b = {y[4], y[5], y[6], y[7]};
+    float4_native* p = reinterpret_cast<float4_native*>(o) + wave_piece(lane);
     if constexpr (STREAM) {
-        float4_native an = {a.x, a.y, a.z, a.w}, bn = {b.x, b.y, b.z, b.w};
-        __builtin_nontemporal_store(an, reinterpret_cast<float4_native*>(o) + lane);
-        __builtin_nontemporal_store(bn, reinterpret_cast<float4_native*>(o) + 64 + lane);
+        __builtin_nontemporal_store(a, p);
+        __builtin_nontemporal_store(b, p + 64);
     } else {
-        reinterpret_cast<float4*>(o)[lane] = a;
-        reinterpret_cast<float4*>(o)[64 + lane] = b;
+        p[0] = a;
+        p[64] = b;
     }
 }
 

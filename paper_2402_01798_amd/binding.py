@@ -10,6 +10,11 @@ import os
 import numpy as np
 import torch
 
+try:
+    from . import _tq_marshal
+except ImportError:                     # not built: the loops below do the same, slower
+    _tq_marshal = None
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 # TQ_LIBRARY_PATH selects another build of the same library (the tests' grid-fold build)
 LIB_PATH = os.environ.get("TQ_LIBRARY_PATH") or os.path.join(HERE, "libtq.so")
@@ -199,7 +204,19 @@ def tq_quantize_dequantize(g, params, out, bits, seed, worker, step, bucket_elem
     return out
 
 
+# Batches of plain tensors are looked over by the host module: 61,706 elements x 4 workers, host time of the four calls of
+# a step 11.2 + 7.6 + 11.4 + 9.9 -> 8.4 + 5.3 + 6.4 + 6.4 us.  What it does not take, and every error, is left to the Python code.
+_ANY_SIZE = (1 << 63) - 1
+
+
+def _sized(tensors, count, low, high, dtype=None):
+    return _tq_marshal is not None and _tq_marshal.sized(tensors, count, low, high, dtype)
+
+
 def _ptr_array(tensors, what):
+    ptrs = None if _tq_marshal is None else _tq_marshal.pointers(tensors)
+    if ptrs is not None:
+        return ptrs
     return (C.c_void_p * len(tensors))(*[_dev(t, what) for t in tensors])
 
 
@@ -222,11 +239,13 @@ def tq_params_multi(stats, params, bits, grid, alpha_override=0.0):
 def tq_compress_multi(gs, params, payloads, bits, seed, first_worker, step, bucket_elems=0, grid=GRID_UNIFORM):
     d, dtype = gs[0].numel(), gs[0].dtype
     qsize, psize = num_buckets(d, bucket_elems) * PARAMS_BYTES, payload_bytes(d, bits)
-    for g, q, p in zip(gs, params, payloads):
-        if g.numel() != d or g.dtype != dtype:
-            raise ValueError("batched tensors must share shape and dtype")
-        if q.numel() != qsize or p.numel() < psize:
-            raise ValueError("params / payload buffer size does not match d")
+    if not (_sized(gs, len(gs), d, d, dtype) and _sized(params, len(gs), qsize, qsize)
+            and _sized(payloads, len(gs), psize, _ANY_SIZE)):
+        for g, q, p in zip(gs, params, payloads):
+            if g.numel() != d or g.dtype != dtype:
+                raise ValueError("batched tensors must share shape and dtype")
+            if q.numel() != qsize or p.numel() < psize:
+                raise ValueError("params / payload buffer size does not match d")
     _check(lib().tq_compress_multi(_ptr_array(gs, "g"), len(gs), _dtype_code(gs[0]), d, bucket_elems,
                                    _ptr_array(params, "params"), bits, grid, seed, first_worker, step,
                                    _ptr_array(payloads, "payload"), _stream()), "tq_compress_multi")
@@ -238,9 +257,10 @@ def _decode_args(payloads, params, d, bits, bucket_elems, weights):
     if len(params) != N:
         raise ValueError("one params buffer per payload")
     psize, qsize = payload_bytes(d, bits), num_buckets(d, bucket_elems) * PARAMS_BYTES
-    for p, q in zip(payloads, params):
-        if p.numel() < psize or q.numel() != qsize:
-            raise ValueError("payload / params buffer size does not match d")
+    if not (_sized(payloads, N, psize, _ANY_SIZE) and _sized(params, N, qsize, qsize)):
+        for p, q in zip(payloads, params):
+            if p.numel() < psize or q.numel() != qsize:
+                raise ValueError("payload / params buffer size does not match d")
     pp, qq = _ptr_array(payloads, "payload"), _ptr_array(params, "params")
     ww = None
     if weights is not None:
@@ -325,11 +345,13 @@ def tq_stats_segments_multi(gs, seg, stats, workspace, g_min=0.0):
 def tq_compress_segments_multi(gs, seg, params, payloads, bits, seed, first_worker, step):
     d, dtype = gs[0].numel(), gs[0].dtype
     qsize, psize = seg.nseg * PARAMS_BYTES, payload_bytes(d, bits)
-    for g, q, p in zip(gs, params, payloads):
-        if g.numel() != d or g.dtype != dtype:
-            raise ValueError("batched tensors must share shape and dtype")
-        if q.numel() != qsize or p.numel() < psize:
-            raise ValueError("params / payload buffer size does not match the segments")
+    if not (_sized(gs, len(gs), d, d, dtype) and _sized(params, len(gs), qsize, qsize)
+            and _sized(payloads, len(gs), psize, _ANY_SIZE)):
+        for g, q, p in zip(gs, params, payloads):
+            if g.numel() != d or g.dtype != dtype:
+                raise ValueError("batched tensors must share shape and dtype")
+            if q.numel() != qsize or p.numel() < psize:
+                raise ValueError("params / payload buffer size does not match the segments")
     dev, host, nseg = seg.args()
     _check(lib().tq_compress_segments_multi(_ptr_array(gs, "g"), len(gs), _dtype_code(gs[0]), d, dev, host, nseg,
                                             _ptr_array(params, "params"), bits, seed, first_worker, step,
@@ -343,9 +365,10 @@ def tq_decompress_aggregate_segments(payloads, params, seg, out, bits, weights=N
         raise TypeError("out must be float32")
     N = len(payloads)
     psize, qsize = payload_bytes(d, bits), seg.nseg * PARAMS_BYTES
-    for p, q in zip(payloads, params):
-        if p.numel() < psize or q.numel() != qsize:
-            raise ValueError("payload / params buffer size does not match the segments")
+    if not (_sized(payloads, N, psize, _ANY_SIZE) and _sized(params, N, qsize, qsize)):
+        for p, q in zip(payloads, params):
+            if p.numel() < psize or q.numel() != qsize:
+                raise ValueError("payload / params buffer size does not match the segments")
     pp, qq = _ptr_array(payloads, "payload"), _ptr_array(params, "params")
     ww = None if weights is None else (C.c_float * N)(*[float(w) for w in weights])
     dev, host, nseg = seg.args()

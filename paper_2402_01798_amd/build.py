@@ -1,4 +1,4 @@
-"""Build libtq.so (HIP, gfx950) in-tree with hipcc.
+"""Build libtq.so (HIP, gfx950) in-tree with hipcc, and the binding's host module _tq_marshal.so.
 
 Flags that are part of what the kernels mean:
   -ffp-contract=off   every binary32 operation on the element path is one IEEE rounding
@@ -16,6 +16,8 @@ OBJ_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libtq.so")
 # the same sources with the grid-fold test hook compiled in (tests/test_gpu_folded_grid.py only)
 FOLD_TEST_LIB = os.path.join(HERE, "libtq_foldtest.so")
+
+MARSHAL = os.path.join(HERE, "_tq_marshal.so")
 
 SOURCES = ["tq_api.hip", "tq_stats.hip", "tq_params.hip", "tq_compress.hip", "tq_decode.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -63,7 +65,32 @@ def build_fold_test(force: bool = False, verbose: bool = False) -> str:
     return build(force, ("-DTQ_TEST_GRID_FOLD",), verbose, FOLD_TEST_LIB, os.path.join(OBJ_DIR, "foldtest"))
 
 
+def build_marshal(force: bool = False, verbose: bool = False) -> str:
+    """The host module of the binding: tensors' sizes and addresses (csrc/tq_marshal.cpp; no device code)."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    src = os.path.join(CSRC, "tq_marshal.cpp")
+    if force or _stale(MARSHAL, [src, __file__]):
+        lib_dir = os.path.join(os.path.dirname(torch.__file__), "lib")
+        tmp = MARSHAL + ".tmp.%d" % os.getpid()
+        cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wno-attributes",
+               "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+               "-I", sysconfig.get_paths()["include"]]
+        for inc in cpp_extension.include_paths():
+            cmd += ["-isystem", inc]
+        cmd += [src, "-o", tmp, "-L", lib_dir, "-ltorch_python", "-ltorch_cpu", "-lc10"]
+        if verbose:
+            print(" ".join(cmd))
+        subprocess.check_call(cmd)
+        os.replace(tmp, MARSHAL)
+    return MARSHAL
+
+
 if __name__ == "__main__":
     import sys
     print(build(force="--force" in sys.argv, verbose=True))
     print(build_fold_test(force="--force" in sys.argv, verbose=True))
+    print(build_marshal(force="--force" in sys.argv, verbose=True))

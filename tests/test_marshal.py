@@ -1,0 +1,50 @@
+"""The binding's host module agrees with the Python code it stands in for, and leaves it what it does not know."""
+import pytest
+import torch
+
+from paper_2402_01798_amd import binding as B
+
+M = B._tq_marshal
+BIG = B._ANY_SIZE
+
+
+def test_built():
+    assert M is not None
+
+
+def test_sized():
+    ts = [torch.zeros(8), torch.nn.Parameter(torch.zeros(8)), torch.zeros(2, 4)]
+    for seq in (ts, tuple(ts)):
+        assert M.sized(seq, 3, 8, 8, None) and M.sized(seq, 3, 8, 8, torch.float32) and M.sized(seq, 3, 0, BIG, None)
+        assert not M.sized(seq, 2, 8, 8, None) and not M.sized(seq, 3, 8, 8, torch.bfloat16)
+        assert not M.sized(seq, 3, 9, BIG, None) and not M.sized(seq, 3, 0, 7, None)
+    assert M.sized([], 0, 1, 1, None)
+    # not a list, not a tensor, no dtype: the Python code's business
+    assert not M.sized(iter(ts), 3, 8, 8, None) and not M.sized([1, 2], 2, 0, BIG, None) and not M.sized(ts, 3, 8, 8, "f32")
+    with pytest.raises(TypeError):
+        M.sized(ts, 3)
+
+
+def test_pointers_are_left_to_python_off_the_device():
+    assert M.pointers([torch.zeros(8)]) is None and M.pointers([None]) is None and M.pointers(iter([])) is None
+    assert M.pointers([torch.zeros(8, device="meta")]) is None and M.pointers([]) == b""
+    with pytest.raises(ValueError, match="g must be a contiguous device tensor"):
+        B._ptr_array([torch.zeros(8)], "g")
+
+
+def test_sizes_are_still_refused():
+    d = 1024
+    g, q, p = torch.zeros(d), torch.zeros(B.PARAMS_BYTES, dtype=torch.uint8), torch.zeros(B.payload_bytes(d, 3), dtype=torch.uint8)
+    with pytest.raises(ValueError, match="share shape and dtype"):
+        B.tq_compress_multi([g, g.bfloat16()], [q, q], [p, p], 3, 1, 0, 0)
+    with pytest.raises(ValueError, match="does not match d"):
+        B.tq_compress_multi([g, g], [q, q], [p, p[:-1]], 3, 1, 0, 0)
+    with pytest.raises(ValueError, match="does not match d"):
+        B.tq_decompress_aggregate([p, p], [q, q[:-1]], g, 3)
+
+
+@pytest.mark.gpu
+def test_pointers_on_the_device():
+    a, b = torch.zeros(64, device="cuda"), torch.zeros(8, 8, device="cuda")
+    assert M.pointers([a, b]) == b"".join(t.data_ptr().to_bytes(8, "little") for t in (a, b))
+    assert M.pointers([a, b.t()]) is None and M.pointers([a, a.cpu()]) is None

@@ -14,7 +14,7 @@
 //      (scattering them bin-major cost ten times their size in partial-line HBM writes).
 //      Buckets of 32768 elements or more: tq_stats_balanced_kernel, the batch cut into equal
 //      shares whatever the buckets are.  Smaller buckets: tq_stats_partial_kernel, a
-//      workgroup per bucket or per slice of one.
+//      workgroup per bucket.
 //   2. a second kernel adds the rows of the buckets that were cut, with coalesced loads, and
 //      combines max, counts and the log-sum.
 // Counts are integers and the tail's log-sum travels as exact integer sums, so the result
@@ -41,6 +41,12 @@ constexpr int kStatsMinSlice = 4 * kStatsTile;         // smallest slice worth a
 constexpr int kStatsMaxSlices = 256;                   // slices per bucket at most
 constexpr int kStatsTargetGroups = 256;                // workgroups per tensor the workspace is sized for (one per CU)
 constexpr int kStatsResidentGroups = 1024;             // workgroups that can run at the same time (4 per CU)
+// A tensor of one record up to this size is one share, whose workgroup writes the record: no second kernel, which costs
+// more than the wider read gives.  Steps of small tensors are bound by the host, 3 us of it a launch: 1 x 20,000 fp32
+// 33.9 -> 31.1 us (the statistics 8.4 -> 5.5), 4 x 61,706 fp32 32.1 -> 29.3, each pass waited for 41.6 -> 38.7 (but the statistics
+// by themselves 12.0 -> 13.1), 32 x 61,706 37.3 -> 33.9, 4 x 61,706 bf16 33.9 -> 30.3.  At 100,000 the statistics by
+// themselves take 17.4 us instead of 11.9.
+constexpr uint64_t kWholeTensor = 65536;
 constexpr int kReduceBlock = 1024;                     // threads of the reduce kernel: 64 bins x 16 slice lanes
 constexpr int kReduceBins = 64;
 constexpr int kBinBias = 1391;                         // 16 * (biased exponent of 2^-40) - 1
@@ -425,39 +431,20 @@ __device__ __forceinline__ StatsExtra stats_slice(const void* __restrict__ g, ui
     return x;
 }
 
+// Buckets of fewer than 32768 elements: a workgroup takes one and writes its record.  (Cut in two they need the second
+// kernel, which costs more than the wider read gives: 1 x 20,000 fp32 8.4 us cut, 5.5 whole.)
 template <int DTYPE, bool TAIL>
 __global__ __launch_bounds__(kStatsBlock) void tq_stats_partial_kernel(
-    const PtrTable g_tab, uint64_t d, uint64_t bucket_elems, uint32_t slices, uint64_t slice_elems,
-    float g_min, char* __restrict__ ws, uint64_t ws_tensor_bytes, uint64_t ws_hist_bytes,
-    const MutPtrTable stats_tab)
+    const PtrTable g_tab, uint64_t d, uint64_t bucket_elems, float g_min, const MutPtrTable stats_tab)
 {
-    // blockIdx.y = tensor of the batch; each tensor has its own region of the workspace
-    const void* __restrict__ g = g_tab.p[blockIdx.y];
-    char* my_ws = ws + (uint64_t)blockIdx.y * ws_tensor_bytes;
-    uint32_t* __restrict__ ws_hist = reinterpret_cast<uint32_t*>(my_ws);
-    StatsExtra* __restrict__ ws_extra = reinterpret_cast<StatsExtra*>(my_ws + ws_hist_bytes);
-    const uint32_t blk = linear_block();
-    if ((uint64_t)(blk / slices) * bucket_elems >= d) return;          // padding of a folded grid
+    const uint64_t bucket = linear_block();
+    const uint64_t lo = bucket * bucket_elems;
+    if (lo >= d) return;                                               // padding of a folded grid
+    const uint64_t hi = lo + bucket_elems < d ? lo + bucket_elems : d;
     __shared__ StatsLds L;
-
-    const uint32_t bucket = blk / slices;
-    const uint32_t slice = blk - bucket * slices;
-    const uint64_t bstart = (uint64_t)bucket * bucket_elems;
-    const uint64_t bend = bstart + bucket_elems < d ? bstart + bucket_elems : d;
-    uint64_t cstart = bstart + (uint64_t)slice * slice_elems;
-    cstart = cstart < bend ? cstart : bend;
-    const uint64_t cend = cstart + slice_elems < bend ? cstart + slice_elems : bend;
-
-    // partial counts of this slice as one contiguous row of the workspace; a bucket that is one
-    // slice writes its record directly and no second kernel follows
-    const bool final_record = slices == 1u;
-    tq_stats_t* S = static_cast<tq_stats_t*>(stats_tab.p[blockIdx.y]) + bucket;
-    uint32_t* row = final_record ? S->hist : ws_hist + ((uint64_t)bucket * slices + slice) * TQ_NBINS;
-    const StatsExtra x = stats_slice<DTYPE, TAIL, false>(g, cstart, cend, 0, g_min, L, row);
-    if (threadIdx.x == 0) {
-        if (final_record) write_scalars(S, x, bend - bstart, g_min);
-        else ws_extra[(uint64_t)bucket * slices + slice] = x;
-    }
+    tq_stats_t* S = static_cast<tq_stats_t*>(stats_tab.p[blockIdx.y]) + bucket;      // blockIdx.y = tensor of the batch
+    const StatsExtra x = stats_slice<DTYPE, TAIL, false>(g_tab.p[blockIdx.y], lo, hi, 0, g_min, L, S->hist);
+    if (threadIdx.x == 0) write_scalars(S, x, hi - lo, g_min);
 }
 
 // Adds `rows` consecutive partial rows (row0 onwards) of one bucket into its record S.  The
@@ -508,25 +495,6 @@ __device__ __forceinline__ void reduce_rows(const uint32_t* __restrict__ ws_hist
             write_scalars(S, x, n, g_min);
         }
     }
-}
-
-__global__ __launch_bounds__(kReduceBlock) void tq_stats_reduce_kernel(
-    const char* __restrict__ ws, uint64_t ws_tensor_bytes, uint64_t ws_hist_bytes, uint32_t slices,
-    uint32_t groups_per_bucket, uint64_t d, uint64_t bucket_elems, float g_min, const MutPtrTable stats_tab)
-{
-    __shared__ uint32_t part[kReduceBlock];
-    const char* my_ws = ws + (uint64_t)blockIdx.y * ws_tensor_bytes;
-    const uint32_t* __restrict__ ws_hist = reinterpret_cast<const uint32_t*>(my_ws);
-    const StatsExtra* __restrict__ ws_extra = reinterpret_cast<const StatsExtra*>(my_ws + ws_hist_bytes);
-    tq_stats_t* __restrict__ stats = static_cast<tq_stats_t*>(stats_tab.p[blockIdx.y]);
-    const uint32_t blk = linear_block();
-    const uint32_t bucket = blk / groups_per_bucket;
-    const uint32_t grp = blk - bucket * groups_per_bucket;
-    if ((uint64_t)bucket * bucket_elems >= d) return;                  // padding of a folded grid
-    const uint64_t lo = (uint64_t)bucket * bucket_elems;
-    const uint64_t hi = lo + bucket_elems < d ? lo + bucket_elems : d;
-    reduce_rows(ws_hist, ws_extra, (uint64_t)bucket * slices, slices, grp, groups_per_bucket, stats + bucket,
-                hi - lo, g_min, part);
 }
 
 
@@ -778,14 +746,8 @@ __global__ __launch_bounds__(kStatsBlock) void tq_stats_segments_reduce_kernel(
 
 namespace {
 
-struct StatsPlan {
-    uint64_t be, nb, slice_elems;
-    uint32_t slices;
-};
-
-// Most slices a bucket is ever cut into: slices of at least 16384 elements, and no more than
-// about one workgroup per compute unit when a single tensor is processed.  The workspace is
-// sized for this many.
+// Rows of the workspace per bucket of fewer than 32768 elements: one for every 16384 elements, and no more than about
+// one per compute unit.  What callers size their workspaces by; such buckets leave it unused.
 uint32_t max_slices(uint64_t be, uint64_t nb)
 {
     const uint64_t want = (be + tq::kStatsMinSlice - 1) / tq::kStatsMinSlice;
@@ -795,33 +757,7 @@ uint32_t max_slices(uint64_t be, uint64_t nb)
     return (uint32_t)(m < 1 ? 1 : m);
 }
 
-// Slices per bucket for a batch of `count` tensors with buckets of fewer than 32768 elements.
-// Each workgroup pays for clearing and flushing its LDS histograms -- about what reading
-// 16384 elements costs -- so fewer, longer-lived workgroups win as long as the machine is full,
-// and a launch of W workgroups takes ceil(W / resident) times one workgroup's time, `resident`
-// being the workgroups the launch should keep running at the same time.  The slice count
-// minimises that product.
-StatsPlan plan_stats(uint64_t d, uint64_t bucket_elems, int count, uint64_t resident)
-{
-    StatsPlan p;
-    p.be = bucket_elems ? bucket_elems : d;
-    p.nb = (d + p.be - 1) / p.be;
-    const uint64_t units = p.nb * (uint64_t)(count < 1 ? 1 : count);
-    const uint32_t smax = max_slices(p.be, p.nb);
-    uint32_t best = 1;
-    uint64_t best_cost = ~0ull;
-    for (uint32_t sl = 1; sl <= smax; ++sl) {
-        const uint64_t rounds = (units * sl + resident - 1) / resident;
-        const uint64_t cost = rounds * ((p.be + sl - 1) / sl + (uint64_t)tq::kStatsMinSlice);
-        if (cost < best_cost) { best_cost = cost; best = sl; }
-    }
-    p.slices = best;
-    const uint64_t per = (p.be + p.slices - 1) / p.slices;
-    p.slice_elems = (per + tq::kStatsTile - 1) / tq::kStatsTile * tq::kStatsTile;
-    return p;
-}
-
-// Whether the launch is cut into equal shares (large buckets) or into buckets and their slices.
+// Whether the launch is cut into equal shares (large buckets) or into buckets.
 bool uses_shares(uint64_t d, uint64_t bucket_elems)
 {
     const uint64_t be = bucket_elems && bucket_elems < d ? bucket_elems : d;
@@ -853,7 +789,7 @@ uint64_t tq_stats_workspace_bytes_impl(uint64_t d, uint64_t bucket_elems)
     if (d == 0) return 0;
     const uint64_t be = bucket_elems ? bucket_elems : d;
     const uint64_t nb = (d + be - 1) / be;
-    const uint32_t slices = max_slices(be, nb);                        // no plan uses more
+    const uint32_t slices = max_slices(be, nb);
     const uint64_t hist_bytes = tq::stats_ws_hist_words(nb, slices) * 4;
     uint64_t bytes = (hist_bytes + 15) / 16 * 16 + nb * slices * sizeof(tq::StatsExtra);
     if (uses_shares(d, bucket_elems)) {
@@ -906,7 +842,8 @@ hipError_t tq_launch_stats(const void* const* g, int count, int dtype, uint64_t 
         const uint64_t tiles_per_tensor = (d + tq::kStatsTile - 1) / tq::kStatsTile;
         const uint64_t total_tiles = tiles_per_tensor * (uint64_t)count;
         const uint64_t fit = total_tiles * tq::kStatsTile / tq::kStatsMinSlice;   // shares of at least 16384 elements
-        const uint32_t groups = (uint32_t)(fit < 1 ? 1 : (fit < resident ? fit : resident));
+        const bool whole_tensors = nb == 1 && d <= tq::kWholeTensor;     // share i = tensor i
+        const uint32_t groups = whole_tensors ? (uint32_t)count : (uint32_t)(fit < 1 ? 1 : (fit < resident ? fit : resident));
         const uint64_t rows = groups + nb * (uint64_t)count;
         const bool past = stats_past_caches(count, d, dtype);
         const uint64_t kept = stats_kept_tiles(dtype, groups);
@@ -925,7 +862,7 @@ hipError_t tq_launch_stats(const void* const* g, int count, int dtype, uint64_t 
 #undef TQ_LAUNCH_SHARES
 #undef TQ_LAUNCH_SHARES_AS
         hipError_t err = hipGetLastError();
-        if (err != hipSuccess || groups == 1) return err;
+        if (err != hipSuccess || groups == 1 || whole_tensors) return err;   // every record is written
         const uint32_t gpb = (TQ_NBINS + tq::kReduceBins - 1) / tq::kReduceBins + 1;
         const uint64_t n_buckets = nb * (uint64_t)count;
         const uint32_t by_boundary = n_buckets > groups - 1 ? 1u : 0u;
@@ -944,35 +881,20 @@ hipError_t tq_launch_stats(const void* const* g, int count, int dtype, uint64_t 
                            tiles_per_tensor, total_tiles, groups, by_boundary, n_units, gpb, g_min, ws_hist, ws_extra, stt);
         return hipGetLastError();
     }
-    const StatsPlan p = plan_stats(d, bucket_elems, count, resident);
-    const uint64_t nblocks = p.nb * p.slices;
+    const uint64_t be = bucket_elems ? bucket_elems : d;
     dim3 pgrid;
-    if (!tq::fold_grid(nblocks, tq::kStatsBlock, (unsigned)count, pgrid))
-        return hipErrorInvalidValue;
-    const uint64_t hist_bytes = (tq::stats_ws_hist_words(p.nb, p.slices) * 4 + 15) / 16 * 16;
-    const uint64_t tensor_bytes = tq_stats_workspace_bytes_impl(d, bucket_elems);
+    if (!tq::fold_grid((d + be - 1) / be, tq::kStatsBlock, (unsigned)count, pgrid)) return hipErrorInvalidValue;
     tq::PtrTable gt{};
     tq::MutPtrTable stt{};
     for (int i = 0; i < count; ++i) { gt.p[i] = g[i]; stt.p[i] = stats[i]; }
-    char* ws = static_cast<char*>(workspace);
-#define TQ_LAUNCH_PARTIAL(DT, TL)                                                                             \
-    hipLaunchKernelGGL((tq::tq_stats_partial_kernel<DT, TL>), pgrid, dim3(tq::kStatsBlock), 0, st, gt, d, p.be,   \
-                       p.slices, p.slice_elems, g_min, ws, tensor_bytes, hist_bytes, stt)
+#define TQ_LAUNCH_PARTIAL(DT, TL) \
+    hipLaunchKernelGGL((tq::tq_stats_partial_kernel<DT, TL>), pgrid, dim3(tq::kStatsBlock), 0, st, gt, d, be, g_min, stt)
     if (dtype == TQ_F32) {
         if (g_min > 0.0f) TQ_LAUNCH_PARTIAL(TQ_F32, true); else TQ_LAUNCH_PARTIAL(TQ_F32, false);
     } else {
         if (g_min > 0.0f) TQ_LAUNCH_PARTIAL(TQ_BF16, true); else TQ_LAUNCH_PARTIAL(TQ_BF16, false);
     }
 #undef TQ_LAUNCH_PARTIAL
-    hipError_t err = hipGetLastError();
-    if (err != hipSuccess || p.slices == 1) return err;           // one slice per bucket: records are written
-    // one workgroup per 64 bins, plus one per bucket for the scalar fields
-    const uint32_t gpb = (TQ_NBINS + tq::kReduceBins - 1) / tq::kReduceBins + 1;
-    const uint64_t rblocks = p.nb * gpb;
-    dim3 rgrid;
-    if (!tq::fold_grid(rblocks, tq::kReduceBlock, (unsigned)count, rgrid)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(tq::tq_stats_reduce_kernel, rgrid, dim3(tq::kReduceBlock), 0,
-                       st, ws, tensor_bytes, hist_bytes, p.slices, gpb, d, p.be, g_min, stt);
     return hipGetLastError();
 }
 

@@ -43,10 +43,12 @@ constexpr int kStatsTargetGroups = 256;                // workgroups per tensor 
 constexpr int kStatsResidentGroups = 1024;             // workgroups that can run at the same time (4 per CU)
 // A tensor of one record up to this size is one share, whose workgroup writes the record: no second kernel, which costs
 // more than the wider read gives.  Steps of small tensors are bound by the host, 3 us of it a launch: 1 x 20,000 fp32
-// 33.9 -> 31.1 us (the statistics 8.4 -> 5.5), 4 x 61,706 fp32 32.1 -> 29.3, each pass waited for 41.6 -> 38.7 (but the statistics
-// by themselves 12.0 -> 13.1), 32 x 61,706 37.3 -> 33.9, 4 x 61,706 bf16 33.9 -> 30.3.  At 100,000 the statistics by
+// 33.9 -> 31.1 us (the statistics 8.4 -> 5.5), 4 x 61,706 fp32 32.1 -> 29.3, each pass waited for 41.6 -> 38.7 (the statistics
+// by themselves 12.0 -> 13.1, in trips of two tiles 11.4), 32 x 61,706 37.3 -> 33.9, 4 x 61,706 bf16 33.9 -> 30.3.  At 100,000 the statistics by
 // themselves take 17.4 us instead of 11.9.
 constexpr uint64_t kWholeTensor = 65536;
+// Tiles of a trip of the equal shares, see stats_slice.
+constexpr int share_trip(int dtype, bool past) { return dtype == TQ_F32 && past ? 4 : 2; }
 constexpr int kReduceBlock = 1024;                     // threads of the reduce kernel: 64 bins x 16 slice lanes
 constexpr int kReduceBins = 64;
 constexpr int kBinBias = 1391;                         // 16 * (biased exponent of 2^-40) - 1
@@ -164,11 +166,11 @@ struct StatsLds {
 // histogram goes to `row` (TQ_NBINS counts, every bin written), and thread 0 returns the other
 // sums (meaningless in the other threads).  cstart is a multiple of 8 elements.  What lies before past_end is
 // read past the caches (but for the first trip and what the loop leaves).
-template <int DTYPE, bool TAIL, bool PAST>
+template <int DTYPE, bool TAIL, bool PAST, int TRIP>
 __device__ __forceinline__ StatsExtra stats_slice(const void* __restrict__ g, uint64_t cstart, uint64_t cend,
                                                   uint64_t past_end, float g_min, StatsLds& L, uint32_t* __restrict__ row)
 {
-    // Full trips of kTrip tiles each, two register buffers: the next trip's 16-byte loads are
+    // Full trips of kTrip = TRIP tiles each, two register buffers: the next trip's 16-byte loads are
     // requested before the current trip's values are histogrammed.  The trip count is the same
     // for every lane of the workgroup; what is left after the full trips is less than a trip.
     //  - bf16 is bound by instruction issue: trips of two tiles, and the wavefront works on one
@@ -181,7 +183,13 @@ __device__ __forceinline__ StatsExtra stats_slice(const void* __restrict__ g, ui
     //    677-682 us this way (698 with trips of two tiles, 697 with six, 709 with eight); the
     //    memory system gives more with fewer requests outstanding per compute unit, as it
     //    does for a plain read loop once arithmetic is added to it.
-    constexpr int kTrip = DTYPE == TQ_F32 ? 4 : 2;
+    //    Batches that the caches can hold (PAST false) in equal shares are read in trips of two tiles, which start and
+    //    end sooner and find more of what they ask for in a cache; trips of four / three / two / one / two without the
+    //    wait, us: 4 x 61,706 13.1 / 12.7 / 11.4 / 11.6 / 11.2, 11.2 M 22.3 / 20.7 / 19.7 / 19.8 / 19.2 (one step 44.5 / 43.7 /
+    //    43.0 / 44.2 / 42.2), 4 x 11.2 M 35.6 / 34.6 / 32.9 / 33.0 / 33.7 (84.4 / 83.7 / 81.8 / 87.8 / 82.3), 60 M 48.5 / 46.1 /
+    //    43.7 / 47.8 / 44.9 (139.9 / 137.1 / 137.0 / 145.5 / 135.2).  Buckets of four tiles in one trip: 4 x 11.2 M in buckets
+    //    of 16384, one step 97.8 / 98.0 / 99.5 / 98.3 / 99.3.
+    constexpr int kTrip = TRIP;
     constexpr bool kWaitAll = DTYPE == TQ_F32;
     constexpr bool kLines = PAST && DTYPE == TQ_F32;                   // the loads of the full trips, see load_lines
     const uint64_t lane_e = cstart + (uint64_t)threadIdx.x * kGroup;
@@ -443,7 +451,7 @@ __global__ __launch_bounds__(kStatsBlock) void tq_stats_partial_kernel(
     const uint64_t hi = lo + bucket_elems < d ? lo + bucket_elems : d;
     __shared__ StatsLds L;
     tq_stats_t* S = static_cast<tq_stats_t*>(stats_tab.p[blockIdx.y]) + bucket;      // blockIdx.y = tensor of the batch
-    const StatsExtra x = stats_slice<DTYPE, TAIL, false>(g_tab.p[blockIdx.y], lo, hi, 0, g_min, L, S->hist);
+    const StatsExtra x = stats_slice<DTYPE, TAIL, false, DTYPE == TQ_F32 ? 4 : 2>(g_tab.p[blockIdx.y], lo, hi, 0, g_min, L, S->hist);
     if (threadIdx.x == 0) write_scalars(S, x, hi - lo, g_min);
 }
 
@@ -539,7 +547,7 @@ __global__ __launch_bounds__(kStatsBlock) void tq_stats_balanced_kernel(
             const uint64_t r = (uint64_t)w + t * nb + b;
             if (!first) __syncthreads();                               // the histograms are cleared again
             first = false;
-            const StatsExtra x = stats_slice<DTYPE, TAIL, PAST>(g, cs, ce, past_end, g_min, L, whole ? stats[b].hist : ws_hist + r * TQ_NBINS);
+            const StatsExtra x = stats_slice<DTYPE, TAIL, PAST, share_trip(DTYPE, PAST)>(g, cs, ce, past_end, g_min, L, whole ? stats[b].hist : ws_hist + r * TQ_NBINS);
             if (threadIdx.x == 0) {
                 if (whole) write_scalars(stats + b, x, hi - lo, g_min);
                 else ws_extra[r] = x;
@@ -687,7 +695,7 @@ __global__ __launch_bounds__(kStatsBlock) void tq_stats_segments_partial_kernel(
             const uint64_t r = (uint64_t)w + t * nseg + s;
             if (!first) __syncthreads();                               // the histograms are cleared again
             first = false;
-            const StatsExtra x = stats_slice<DTYPE, TAIL, PAST>(g, seg_lo, seg_hi, past_end, g_min, L, ws_hist + r * TQ_NBINS);
+            const StatsExtra x = stats_slice<DTYPE, TAIL, PAST, share_trip(DTYPE, PAST)>(g, seg_lo, seg_hi, past_end, g_min, L, ws_hist + r * TQ_NBINS);
             if (threadIdx.x == 0) ws_extra[r] = x;
             if (seg_hi >= cend || s + 1 >= nseg) break;
             ++s;

@@ -41,8 +41,8 @@ VARIANTS = [("cfg4", 2, 0), ("cfg4", 2, 1), ("cfg2", 2, 0), ("cfg2", 4, 0), ("cf
 
 # vector-ALU lane-operations per element of the compress kernel's variants, as rocprofv3's
 # SQ_INSTS_VALU counts them (profiles/valu_instructions.txt): they decide which ceiling binds
-COMPRESS_VALU_PER_ELEM = {"f32/b2/g0": 15.5, "f32/b2/g1": 20.7, "f32/b4/g0": 20.2, "f32/b3/g1": 24.0,
-                          "bf16/b2/g1": 18.5}
+COMPRESS_VALU_PER_ELEM = {"f32/b2/g0": 17.0, "f32/b2/g1": 21.7, "f32/b4/g0": 20.3, "f32/b3/g1": 25.2,
+                          "bf16/b2/g1": 18.6}
 
 
 def parse():
@@ -355,7 +355,7 @@ def compress_roofline(path, res):
 
 
 # vector-ALU lane-operations per element of the statistics kernel (profiles/valu_instructions.txt)
-STATS_VALU_PER_ELEM = {"f32": 5.3, "f32/tail": 10.9, "bf16/tail": 9.9}
+STATS_VALU_PER_ELEM = {"f32": 5.2, "f32/tail": 11.4, "bf16/tail": 10.0}
 
 
 def stats_roofline(path, res):

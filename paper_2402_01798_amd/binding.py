@@ -213,6 +213,12 @@ def _sized(tensors, count, low, high, dtype=None):
     return _tq_marshal is not None and _tq_marshal.sized(tensors, count, low, high, dtype)
 
 
+def _one_each(count, buffers, what):
+    """The library reads `count` addresses, however many the list holds: one that is too short is refused here."""
+    if len(buffers) < count:
+        raise ValueError("%d %s buffers for a batch of %d tensors" % (len(buffers), what, count))
+
+
 def _ptr_array(tensors, what):
     ptrs = None if _tq_marshal is None else _tq_marshal.pointers(tensors)
     if ptrs is not None:
@@ -222,6 +228,7 @@ def _ptr_array(tensors, what):
 
 def tq_stats_multi(gs, stats, workspace, bucket_elems=0, g_min=0.0):
     """Batched tq_stats: lists of same-shaped gradients and their stats buffers."""
+    _one_each(len(gs), stats, "stats")
     _check(lib().tq_stats_multi(_ptr_array(gs, "g"), len(gs), _dtype_code(gs[0]), gs[0].numel(),
                                 bucket_elems, g_min, _ptr_array(stats, "stats"),
                                 _dev(workspace, "workspace"), workspace.numel(), _stream()),
@@ -230,6 +237,7 @@ def tq_stats_multi(gs, stats, workspace, bucket_elems=0, g_min=0.0):
 
 
 def tq_params_multi(stats, params, bits, grid, alpha_override=0.0):
+    _one_each(len(stats), params, "params")
     nb = stats[0].numel() // STATS_BYTES
     _check(lib().tq_params_multi(_ptr_array(stats, "stats"), len(stats), nb, bits, grid, alpha_override,
                                  _ptr_array(params, "params"), _stream()), "tq_params_multi")
@@ -237,6 +245,8 @@ def tq_params_multi(stats, params, bits, grid, alpha_override=0.0):
 
 
 def tq_compress_multi(gs, params, payloads, bits, seed, first_worker, step, bucket_elems=0, grid=GRID_UNIFORM):
+    _one_each(len(gs), params, "params")
+    _one_each(len(gs), payloads, "payload")
     d, dtype = gs[0].numel(), gs[0].dtype
     qsize, psize = num_buckets(d, bucket_elems) * PARAMS_BYTES, payload_bytes(d, bits)
     if not (_sized(gs, len(gs), d, d, dtype) and _sized(params, len(gs), qsize, qsize)
@@ -335,6 +345,7 @@ def tq_compress_segments(g, seg, params, payload, bits, seed, worker, step):
 
 def tq_stats_segments_multi(gs, seg, stats, workspace, g_min=0.0):
     """Batched tq_stats_segments: same-shaped gradients that share the segment table."""
+    _one_each(len(gs), stats, "stats")
     dev, host, nseg = seg.args()
     _check(lib().tq_stats_segments_multi(_ptr_array(gs, "g"), len(gs), _dtype_code(gs[0]), gs[0].numel(), dev, host,
                                          nseg, g_min, _ptr_array(stats, "stats"), _dev(workspace, "workspace"),
@@ -343,6 +354,8 @@ def tq_stats_segments_multi(gs, seg, stats, workspace, g_min=0.0):
 
 
 def tq_compress_segments_multi(gs, seg, params, payloads, bits, seed, first_worker, step):
+    _one_each(len(gs), params, "params")
+    _one_each(len(gs), payloads, "payload")
     d, dtype = gs[0].numel(), gs[0].dtype
     qsize, psize = seg.nseg * PARAMS_BYTES, payload_bytes(d, bits)
     if not (_sized(gs, len(gs), d, d, dtype) and _sized(params, len(gs), qsize, qsize)
@@ -364,6 +377,7 @@ def tq_decompress_aggregate_segments(payloads, params, seg, out, bits, weights=N
     if out.dtype != torch.float32:
         raise TypeError("out must be float32")
     N = len(payloads)
+    _one_each(N, params, "params")
     psize, qsize = payload_bytes(d, bits), seg.nseg * PARAMS_BYTES
     if not (_sized(payloads, N, psize, _ANY_SIZE) and _sized(params, N, qsize, qsize)):
         for p, q in zip(payloads, params):

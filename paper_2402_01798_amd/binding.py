@@ -157,7 +157,18 @@ def alloc_payload(d, bits, device="cuda"):
     return torch.empty(payload_bytes(d, bits), dtype=torch.uint8, device=device)
 
 
+def _stats_bytes(d, bucket_elems):
+    """Bytes of the records tq_stats writes, without a call into the library."""
+    return (-(-d // bucket_elems) if bucket_elems > 0 else min(d, 1)) * STATS_BYTES
+
+
+def _holds(buf, nbytes, what):
+    if buf.nbytes < nbytes:
+        raise ValueError("%s buffer too small: %d bytes of %d" % (what, buf.nbytes, nbytes))
+
+
 def tq_stats(g, stats, workspace, bucket_elems=0, g_min=0.0):
+    _holds(stats, _stats_bytes(g.numel(), bucket_elems), "stats")
     _check(lib().tq_stats(_dev(g, "g"), _dtype_code(g), g.numel(), bucket_elems, g_min,
                           _dev(stats, "stats"), _dev(workspace, "workspace"), workspace.numel(),
                           _stream()), "tq_stats")
@@ -165,6 +176,7 @@ def tq_stats(g, stats, workspace, bucket_elems=0, g_min=0.0):
 
 
 def tq_stats_static(g, stats, bucket_elems=0, g_min=0.0):
+    _holds(stats, _stats_bytes(g.numel(), bucket_elems), "stats")
     _check(lib().tq_stats_static(_dev(g, "g"), _dtype_code(g), g.numel(), bucket_elems, g_min,
                                  _dev(stats, "stats"), _stream()), "tq_stats_static")
     return stats
@@ -219,6 +231,18 @@ def _one_each(count, buffers, what):
         raise ValueError("%d %s buffers for a batch of %d tensors" % (len(buffers), what, count))
 
 
+def _same_shape(gs):
+    d, dtype = gs[0].numel(), gs[0].dtype
+    if not _sized(gs, len(gs), d, d, dtype) and any(g.numel() != d or g.dtype != dtype for g in gs):
+        raise ValueError("batched tensors must share shape and dtype")
+
+
+def _each_holds(count, buffers, nbytes, what):
+    if not _sized(buffers, count, nbytes, _ANY_SIZE):
+        for _, buf in zip(range(count), buffers):
+            _holds(buf, nbytes, what)
+
+
 def _ptr_array(tensors, what):
     ptrs = None if _tq_marshal is None else _tq_marshal.pointers(tensors)
     if ptrs is not None:
@@ -229,6 +253,8 @@ def _ptr_array(tensors, what):
 def tq_stats_multi(gs, stats, workspace, bucket_elems=0, g_min=0.0):
     """Batched tq_stats: lists of same-shaped gradients and their stats buffers."""
     _one_each(len(gs), stats, "stats")
+    _same_shape(gs)
+    _each_holds(len(gs), stats, _stats_bytes(gs[0].numel(), bucket_elems), "stats")
     _check(lib().tq_stats_multi(_ptr_array(gs, "g"), len(gs), _dtype_code(gs[0]), gs[0].numel(),
                                 bucket_elems, g_min, _ptr_array(stats, "stats"),
                                 _dev(workspace, "workspace"), workspace.numel(), _stream()),
@@ -239,6 +265,8 @@ def tq_stats_multi(gs, stats, workspace, bucket_elems=0, g_min=0.0):
 def tq_params_multi(stats, params, bits, grid, alpha_override=0.0):
     _one_each(len(stats), params, "params")
     nb = stats[0].numel() // STATS_BYTES
+    _each_holds(len(stats), stats, nb * STATS_BYTES, "stats")
+    _each_holds(len(stats), params, nb * PARAMS_BYTES, "params")
     _check(lib().tq_params_multi(_ptr_array(stats, "stats"), len(stats), nb, bits, grid, alpha_override,
                                  _ptr_array(params, "params"), _stream()), "tq_params_multi")
     return params
@@ -325,6 +353,7 @@ def stats_segments_workspace_bytes(d, nseg):
 
 
 def tq_stats_segments(g, seg, stats, workspace, g_min=0.0):
+    _holds(stats, seg.nseg * STATS_BYTES, "stats")
     dev, host, nseg = seg.args()
     _check(lib().tq_stats_segments(_dev(g, "g"), _dtype_code(g), g.numel(), dev, host, nseg, g_min,
                                    _dev(stats, "stats"), _dev(workspace, "workspace"), workspace.numel(),
@@ -346,6 +375,8 @@ def tq_compress_segments(g, seg, params, payload, bits, seed, worker, step):
 def tq_stats_segments_multi(gs, seg, stats, workspace, g_min=0.0):
     """Batched tq_stats_segments: same-shaped gradients that share the segment table."""
     _one_each(len(gs), stats, "stats")
+    _same_shape(gs)
+    _each_holds(len(gs), stats, seg.nseg * STATS_BYTES, "stats")
     dev, host, nseg = seg.args()
     _check(lib().tq_stats_segments_multi(_ptr_array(gs, "g"), len(gs), _dtype_code(gs[0]), gs[0].numel(), dev, host,
                                          nseg, g_min, _ptr_array(stats, "stats"), _dev(workspace, "workspace"),

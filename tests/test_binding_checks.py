@@ -1,0 +1,105 @@
+"""What the binding refuses because the device would read or write past a buffer: lists shorter than the batch (the library
+reads one address per tensor of it), tensors of a batch that differ, buffers too small for their records."""
+import pytest
+import torch
+
+from paper_2402_01798_amd import binding as B
+
+D = 1024
+G = [torch.zeros(D) for _ in range(3)]
+STATS = [torch.zeros(B.STATS_BYTES, dtype=torch.uint8) for _ in range(3)]
+PARAMS = [torch.zeros(B.PARAMS_BYTES, dtype=torch.uint8) for _ in range(3)]
+PAYLOADS = [torch.zeros(B.payload_bytes(D, 3), dtype=torch.uint8) for _ in range(3)]
+WORKSPACE = torch.zeros(1 << 20, dtype=torch.uint8)
+SEG = B.Segments([0, 128, D], device="cpu")
+SEG_STATS = [torch.zeros(2 * B.STATS_BYTES, dtype=torch.uint8) for _ in range(3)]
+SEG_PARAMS = [torch.zeros(2 * B.PARAMS_BYTES, dtype=torch.uint8) for _ in range(3)]
+
+CALLS = {
+    "stats": lambda n: B.tq_stats_multi(G, STATS[:n], WORKSPACE),
+    "params": lambda n: B.tq_params_multi(STATS, PARAMS[:n], 3, B.GRID_UNIFORM),
+    "compress-params": lambda n: B.tq_compress_multi(G, PARAMS[:n], PAYLOADS, 3, 1, 0, 0),
+    "compress-payload": lambda n: B.tq_compress_multi(G, PARAMS, PAYLOADS[:n], 3, 1, 0, 0),
+    "segments-stats": lambda n: B.tq_stats_segments_multi(G, SEG, SEG_STATS[:n], WORKSPACE),
+    "segments-compress-params": lambda n: B.tq_compress_segments_multi(G, SEG, SEG_PARAMS[:n], PAYLOADS, 3, 1, 0, 0),
+    "segments-compress-payload": lambda n: B.tq_compress_segments_multi(G, SEG, SEG_PARAMS, PAYLOADS[:n], 3, 1, 0, 0),
+    "segments-decode": lambda n: B.tq_decompress_aggregate_segments(PAYLOADS, SEG_PARAMS[:n], SEG, torch.zeros(D), 3),
+}
+
+
+@pytest.fixture
+def reached(monkeypatch):
+    """The library's functions replaced: what a call would have handed to the device."""
+    counts = []
+
+    class Calls:
+        def __getattr__(self, name):
+            return lambda *args: counts.append(name) or B.OK
+
+    real = B.lib()
+    sizes = {n: getattr(real, n) for n in ("tq_num_buckets", "tq_payload_bytes")}
+    stub = Calls()
+    for name, f in sizes.items():
+        setattr(stub, name, f)
+    monkeypatch.setattr(B, "lib", lambda: stub)
+    monkeypatch.setattr(B, "_ptr_array", lambda tensors, what: tensors)
+    monkeypatch.setattr(B, "_dev", lambda t, what: t.data_ptr())
+    monkeypatch.setattr(B, "_stream", lambda: 0)
+    return counts
+
+
+@pytest.mark.parametrize("n", [0, 1, 2])
+@pytest.mark.parametrize("call", CALLS)
+def test_short_lists_are_refused(call, n, reached):
+    with pytest.raises(ValueError, match="%d [a-z]+ buffers for a batch of 3 tensors" % n):
+        CALLS[call](n)
+    assert not reached
+
+
+@pytest.mark.parametrize("call", CALLS)
+def test_a_buffer_for_each_tensor_is_enough(call, reached):
+    CALLS[call](3)
+    assert len(reached) == 1
+
+
+SHORT = torch.zeros(B.STATS_BYTES - 1, dtype=torch.uint8)
+SMALL = {
+    "stats": lambda: B.tq_stats(G[0], SHORT, WORKSPACE),
+    "stats-buckets": lambda: B.tq_stats(G[0], SEG_STATS[0], WORKSPACE, 384),                 # three records
+    "stats-static": lambda: B.tq_stats_static(G[0], SEG_STATS[0], 384),
+    "stats-multi": lambda: B.tq_stats_multi(G, STATS[:2] + [SHORT], WORKSPACE),
+    "stats-multi-buckets": lambda: B.tq_stats_multi(G, SEG_STATS, WORKSPACE, 384),
+    "params-multi-stats": lambda: B.tq_params_multi(SEG_STATS[:2] + STATS[:1], SEG_PARAMS, 3, B.GRID_UNIFORM),
+    "params-multi": lambda: B.tq_params_multi(SEG_STATS, SEG_PARAMS[:2] + PARAMS[:1], 3, B.GRID_UNIFORM),
+    "segments-stats": lambda: B.tq_stats_segments(G[0], SEG, STATS[0], WORKSPACE),
+    "segments-stats-multi": lambda: B.tq_stats_segments_multi(G, SEG, SEG_STATS[:2] + STATS[:1], WORKSPACE),
+}
+
+
+@pytest.mark.parametrize("call", SMALL)
+def test_small_buffers_are_refused(call, reached):
+    with pytest.raises(ValueError, match="buffer too small"):
+        SMALL[call]()
+    assert not reached
+
+
+@pytest.mark.parametrize("odd", [torch.zeros(D - 1), torch.zeros(D, dtype=torch.bfloat16)])
+@pytest.mark.parametrize("call", [lambda gs: B.tq_stats_multi(gs, STATS, WORKSPACE),
+                                  lambda gs: B.tq_stats_segments_multi(gs, SEG, SEG_STATS, WORKSPACE)])
+def test_batches_of_different_tensors_are_refused(call, odd, reached):
+    with pytest.raises(ValueError, match="share shape and dtype"):
+        call(G[:2] + [odd])
+    assert not reached
+
+
+@pytest.mark.parametrize("module", [True, False])
+def test_roomy_buffers_and_longer_lists_are_taken(module, reached, monkeypatch):
+    if not module:
+        monkeypatch.setattr(B, "_tq_marshal", None)
+    B.tq_stats(G[0], SEG_STATS[0], WORKSPACE)
+    B.tq_stats(G[0], torch.zeros(3 * B.STATS_BYTES, dtype=torch.uint8), WORKSPACE, 384)
+    B.tq_stats_multi(G[:2], SEG_STATS[:2] + [SHORT], WORKSPACE, 512)
+    B.tq_stats_multi(G, [t.view(torch.float64) for t in STATS], WORKSPACE)                    # bytes count, not elements
+    B.tq_params_multi(STATS, SEG_PARAMS, 3, B.GRID_UNIFORM)
+    B.tq_stats_segments_multi(G, SEG, SEG_STATS, WORKSPACE)
+    assert len(reached) == 6

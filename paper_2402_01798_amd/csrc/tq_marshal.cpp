@@ -11,7 +11,8 @@
 
 namespace {
 
-bool plain_sequence(PyObject* seq) { return PyList_Check(seq) || PyTuple_Check(seq); }
+// Not their subclasses: what one of those hands out may differ from what it stores.
+bool plain_sequence(PyObject* seq) { return PyList_CheckExact(seq) || PyTuple_CheckExact(seq); }
 
 // pointers(tensors) -> bytes: the addresses, 8 bytes each; None unless all are contiguous device tensors.
 PyObject* pointers(PyObject*, PyObject* seq)

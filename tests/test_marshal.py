@@ -25,6 +25,24 @@ def test_sized():
         M.sized(ts, 3)
 
 
+class Reversed(list):
+    """A list whose elements are not what it stores."""
+
+    def __iter__(self):
+        return reversed(list(super().__iter__()))
+
+
+class Pair(tuple):
+    def __len__(self):
+        return 1
+
+
+def test_lists_of_their_own_kind_are_left_to_python():
+    small = torch.zeros(4)
+    assert not M.sized(Reversed([small, small]), 2, 4, 4, None) and M.pointers(Reversed()) is None
+    assert not M.sized(Pair((small, small)), 2, 4, 4, None) and M.pointers(Pair()) is None
+
+
 def test_pointers_are_left_to_python_off_the_device():
     assert M.pointers([torch.zeros(8)]) is None and M.pointers([None]) is None and M.pointers(iter([])) is None
     assert M.pointers([torch.zeros(8, device="meta")]) is None and M.pointers([]) == b""

@@ -6,16 +6,20 @@ if the library is missing or a call fails, an exception is raised.
 """
 import ctypes as C
 import os
+import warnings
 
 import numpy as np
 import torch
 
+HERE = os.path.dirname(os.path.abspath(__file__))
 try:
     from . import _tq_marshal
-except ImportError:                     # not built: the loops below do the same, slower
+except ImportError as e:                # the loops below do the same, slower
     _tq_marshal = None
+    if os.path.exists(os.path.join(HERE, "_tq_marshal.so")):
+        warnings.warn("_tq_marshal.so does not load, batched calls take longer (build it again: "
+                      "`python -m paper_2402_01798_amd.build`): %s" % e, RuntimeWarning)
 
-HERE = os.path.dirname(os.path.abspath(__file__))
 # TQ_LIBRARY_PATH selects another build of the same library (the tests' grid-fold build)
 LIB_PATH = os.environ.get("TQ_LIBRARY_PATH") or os.path.join(HERE, "libtq.so")
 

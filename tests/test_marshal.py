@@ -1,4 +1,9 @@
 """The binding's host module agrees with the Python code it stands in for, and leaves it what it does not know."""
+import os
+import shutil
+import subprocess
+import sys
+
 import pytest
 import torch
 
@@ -10,6 +15,20 @@ BIG = B._ANY_SIZE
 
 def test_built():
     assert M is not None
+
+
+@pytest.mark.parametrize("built", [True, False])
+def test_a_module_that_does_not_load_is_told(built, tmp_path):
+    pkg = tmp_path / "paper_2402_01798_amd"
+    pkg.mkdir()
+    for name in ("__init__.py", "binding.py"):
+        shutil.copy(os.path.join(B.HERE, name), pkg)
+    if built:
+        (pkg / "_tq_marshal.so").write_bytes(b"not a library")
+    run = subprocess.run([sys.executable, "-c", "from paper_2402_01798_amd import binding as b; assert b._tq_marshal is None"],
+                         cwd=tmp_path, capture_output=True, text=True, timeout=300)
+    assert run.returncode == 0, run.stderr
+    assert ("_tq_marshal.so does not load" in run.stderr) == built
 
 
 def test_sized():

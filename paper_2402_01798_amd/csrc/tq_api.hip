@@ -46,6 +46,7 @@ int check_layout(uint64_t d, uint64_t bucket_elems)
     if (d == 0) return TQ_EINVAL;
     if (bucket_elems != 0 && bucket_elems % 128 != 0) return TQ_EINVAL;
     if (d > (1ull << 40)) return TQ_EUNSUPPORTED;
+    if (bucket_elems > ~0ull - d) return TQ_EUNSUPPORTED;      // d + bucket_elems - 1 has to be countable
     return TQ_OK;
 }
 

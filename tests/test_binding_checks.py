@@ -1,5 +1,9 @@
 """What the binding refuses because the device would read or write past a buffer: lists shorter than the batch (the library
 reads one address per tensor of it), tensors of a batch that differ, buffers too small for their records."""
+import os
+import subprocess
+import sys
+
 import pytest
 import torch
 
@@ -103,3 +107,21 @@ def test_roomy_buffers_and_longer_lists_are_taken(module, reached, monkeypatch):
     B.tq_params_multi(STATS, SEG_PARAMS, 3, B.GRID_UNIFORM)
     B.tq_stats_segments_multi(G, SEG, SEG_STATS, WORKSPACE)
     assert len(reached) == 6
+
+
+def test_bucket_sizes_that_cannot_be_added_to_are_refused():
+    """In a process of its own: a division by zero is a signal, not an exception."""
+    code = """
+import ctypes as C
+from paper_2402_01798_amd import binding as B
+L, p = B.lib(), C.c_void_p(0x1000)
+for be in (2**64 - 128, 2**64 - 896):
+    assert B.stats_workspace_bytes(1000, be) == 0
+    assert L.tq_stats(p, 0, 1000, be, 0.0, p, p, 1 << 30, None) == B.EUNSUPPORTED
+    assert L.tq_stats_static(p, 0, 1000, be, 0.0, p, None) == B.EUNSUPPORTED
+    assert L.tq_compress(p, 0, 1000, be, p, 3, 0, 0, 0, 0, p, None) == B.EUNSUPPORTED
+assert B.stats_workspace_bytes(1000, 2**64 - 1024) > 0
+"""
+    run = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=300,
+                         cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    assert run.returncode == 0, (run.returncode, run.stderr)

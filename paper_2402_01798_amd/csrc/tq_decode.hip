@@ -113,14 +113,16 @@ __device__ __forceinline__ void finish_group(float* o, uint64_t e0, float (&acc)
     if constexpr (MODE == kSgdMomentum) store8<false>(up.velocity + e0, vel);
 }
 
-template <int MODE>
+template <int MODE, bool LDS>
 __device__ __forceinline__ void finish_group_wave(float* out, uint64_t e0, uint32_t lane, float (&acc)[8],
-                                                  const float (&prev)[8], float (&vel)[8], const Update& up)
+                                                  const float (&prev)[8], float (&vel)[8], const Update& up,
+                                                  float4_native* wb)
 {
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] = finish<MODE>(acc[j], prev[j], vel[j], up);
     const uint64_t wave_e0 = e0 - (uint64_t)lane * kGroup;
-    store8_wave<MODE == kStoreStream>(out + wave_e0, lane, acc);
+    if constexpr (LDS) store8_wave_lds<MODE == kStoreStream>(out + wave_e0, lane, acc, wb);
+    else store8_wave<MODE == kStoreStream>(out + wave_e0, lane, acc);
     if constexpr (MODE == kSgdMomentum) store8_wave<false>(up.velocity + wave_e0, lane, vel);
 }
 
@@ -173,7 +175,9 @@ __device__ __forceinline__ void fill_level_rows(float* table, const DecodeArgs& 
 // when its whole range lies inside one segment (nearly always) the rest is the bucketed code
 // with that segment's record.  Otherwise it takes its tiles one by one, the segments that
 // overlap a tile one after the other, with plain level rows -- the same sums in the same order.
-template <int BITS, int U, int T, int MODE, bool SEG>
+//
+// LDS: whole wavefronts lay their results out through LDS instead of in registers (lds_above).
+template <int BITS, int U, int T, int MODE, bool SEG, bool LDS>
 __global__ __launch_bounds__(kBlock) void tq_decode_fast_kernel(
     const DecodeArgs args, int N, int weighted, float scale, uint64_t d, uint64_t d_pad, uint64_t bucket_elems,
     uint32_t groups_per_bucket, uint64_t payload_bytes, float* __restrict__ out, const Update up,
@@ -183,6 +187,11 @@ __global__ __launch_bounds__(kBlock) void tq_decode_fast_kernel(
     constexpr uint32_t PMASK = PAIRS - 1;
     constexpr uint32_t CMASK = (1u << BITS) - 1u;
     __shared__ float2 pair_tab[U * PAIRS];
+    float4_native* wb = nullptr;
+    if constexpr (LDS) {
+        __shared__ float4_native xbuf[kBlock / 64][128];
+        wb = xbuf[__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))];
+    }
 
     const uint32_t blk = linear_block();
     uint32_t bucket = 0;                                       // the record of the workgroup's range
@@ -328,7 +337,7 @@ __global__ __launch_bounds__(kBlock) void tq_decode_fast_kernel(
         for (int t = 0; t < T; ++t) {
             float acc[8];
             lookup(t, acc);
-            finish_group_wave<MODE>(out, e0[t], (uint32_t)lane, acc, prev[t], vel[t], up);
+            finish_group_wave<MODE, LDS>(out, e0[t], (uint32_t)lane, acc, prev[t], vel[t], up, wb);
         }
     } else {
         // the last workgroup of a bucket: tile by tile (one tile's values live at a time)
@@ -458,7 +467,7 @@ __global__ __launch_bounds__(kBlock) void tq_decode_many_kernel(
     for (int t = 0; t < T; ++t) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) acc[t][j] = acc[t][j] * post;
-        if (whole) finish_group_wave<MODE>(out, e0[t], lane, acc[t], prev[t], vel[t], up);
+        if (whole) finish_group_wave<MODE, false>(out, e0[t], lane, acc[t], prev[t], vel[t], up, nullptr);
         else if (e0[t] + kGroup <= bend) finish_group<MODE>(out + e0[t], e0[t], acc[t], prev[t], vel[t], up);
         else if (e0[t] < bend) finish_ragged<MODE>(out + e0[t], e0[t], acc[t], (int)(bend - e0[t]), up);
     }
@@ -527,6 +536,31 @@ bool streams_output(uint64_t d)
     return d * sizeof(float) <= (64ull << 20) || tq::output_past_caches(d * sizeof(float));
 }
 
+// Outputs of more bytes than this go through LDS on their way out, where the call is the plain average of buckets (U workers
+// of tq_decode_fast_kernel); by what both ways measured over 12 M to 930 M elements, in registers against through LDS, per cent:
+//   b = 2, 16 workers  +3 .. +19 everywhere        8 workers  +2 .. +6 above 64 MiB, -3 .. +2 below
+//   b = 4,  8 workers  +1 .. +5 above 160 MiB, -3 .. -11 below
+//   b = 4, up to 4     -4 .. +1 up to 1.5 GiB, +1 .. +11 above (one worker from 2.3 GiB on)
+//   b = 2, up to 4     -5 .. +4 up to 2.5 GiB; above, one worker -2, two +5 .. +7, four +1 .. +3
+//   b = 3, one worker  -5 .. +1 up to 2.5 GiB, +4 .. +8 above;   8 workers  -5 .. -14;   others  -2 .. +1
+// The updates and sums lose nothing in registers (16 workers at b = 2 with SGD -5 .. -15), nor do segments (8 x 124 M at
+// b = 2 in 68 layers 124 -> 114 us).
+constexpr uint64_t kNever = ~0ull;
+constexpr uint64_t lds_above(int bits, int U)
+{
+    if (U == 16) return bits == 2 ? 0 : kNever;
+    if (U == 8) return bits == 2 ? 64ull << 20 : (bits == 4 ? 160ull << 20 : kNever);
+    if (bits == 4) return 1536ull << 20;
+    return (bits == 2) == (U > 1) ? 2560ull << 20 : kNever;
+}
+
+// Whether launches of this kind can be above it: kStore is the mode of outputs of 64 to 160 MiB.
+template <int MODE>
+constexpr bool lds_possible(int bits, int U)
+{
+    return (MODE == tq::kStoreStream && lds_above(bits, U) != kNever) || (MODE == tq::kStore && lds_above(bits, U) < (160ull << 20));
+}
+
 struct DecodeGeom {
     tq::DecodeArgs args;
     int N, weighted, bits;
@@ -551,10 +585,16 @@ hipError_t launch_mode(const DecodeGeom& g, float* out, const tq::Update& up, hi
         dim3 blocks;
         if (!tq::fold_grid(nblocks, tq::kBlock, 1, blocks)) return hipErrorInvalidValue;
         const tq::SegHints no_hints{};
-#define TQ_LAUNCH_FAST(B, UU, TT)                                                                            \
-    hipLaunchKernelGGL((tq::tq_decode_fast_kernel<B, UU, TT, MODE, false>), blocks, threads, 0, st, g.args, N, \
-                       g.weighted, g.scale, g.d, g.d_pad, g.be, (uint32_t)gpb, g.pbytes, out, up,               \
+#define TQ_LAUNCH_FAST_AS(B, UU, TT, LDS)                                                                           \
+    hipLaunchKernelGGL((tq::tq_decode_fast_kernel<B, UU, TT, MODE, false, LDS>), blocks, threads, 0, st, g.args, N, \
+                       g.weighted, g.scale, g.d, g.d_pad, g.be, (uint32_t)gpb, g.pbytes, out, up,                   \
                        static_cast<const uint64_t*>(nullptr), 0u, no_hints)
+#define TQ_LAUNCH_FAST(B, UU, TT)                                                                 \
+    do {                                                                                          \
+        constexpr bool may = lds_possible<MODE>(B, UU), always = may && lds_above(B, UU) == 0;    \
+        if (g.d * sizeof(float) > lds_above(B, UU)) TQ_LAUNCH_FAST_AS(B, UU, TT, may);            \
+        else TQ_LAUNCH_FAST_AS(B, UU, TT, always);                                                \
+    } while (0)
 #define TQ_LAUNCH_FAST_U(B)                                          \
     switch (U) {                                                     \
         case 1: TQ_LAUNCH_FAST(B, 1, T); break;                      \
@@ -577,6 +617,7 @@ hipError_t launch_mode(const DecodeGeom& g, float* out, const tq::Update& up, hi
         }
 #undef TQ_LAUNCH_FAST_U
 #undef TQ_LAUNCH_FAST
+#undef TQ_LAUNCH_FAST_AS
         return hipGetLastError();
     }
 
@@ -678,7 +719,7 @@ hipError_t tq_launch_decode_segments(const void* const* payload, const tq_params
         if (!tq::fold_grid((d + (uint64_t)T * tq::kTile - 1) / ((uint64_t)T * tq::kTile), tq::kBlock, 1, fblocks))
             return hipErrorInvalidValue;
 #define TQ_LAUNCH_FSEG(B, UU, M)                                                                                  \
-    hipLaunchKernelGGL((tq::tq_decode_fast_kernel<B, UU, T, M, true>), fblocks, threads, 0, st, args, N, weighted, \
+    hipLaunchKernelGGL((tq::tq_decode_fast_kernel<B, UU, T, M, true, false>), fblocks, threads, 0, st, args, N, weighted, \
                        scale, d, d_pad, (uint64_t)0, 0u, pbytes, out, up, seg_off, (uint32_t)nseg, hints)
         const bool stream = streams_output(d);
 #define TQ_LAUNCH_FSEG_M(B, UU)                               \

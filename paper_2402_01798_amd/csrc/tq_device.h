@@ -123,10 +123,22 @@ __device__ __forceinline__ void swap_pieces(float (&x)[8])
 // 32 bytes per lane, stored by a WHOLE wavefront (every lane owns a group; `o` is lane
 // 0's address).  Stored directly, each of the wavefront's two 16-byte store instructions would
 // touch every line of its 2 KiB half-way; as pieces each writes 1 KiB in one piece (the
-// aggregate of 8 x 124 M elements 139 us -> 118, of 8 x 11.2 M 20.8 -> 15.6).  The exchange in registers instead of
-// through LDS, whose reads bound the look-ups: 8 x 11.2 M at b = 4 18.2 -> 16.2 us, 8 x 124 M in 68 layers 124.8 -> 119.3,
-// 8 x 25.6 M with momentum 82.6 -> 80.2, 32 x 11.2 M at b = 4 41.5 -> 40.1; 8 x 124 M 119.4 -> 122 and 4 x 10^9 808 -> 829 by
-// itself, the steps around them 1335 -> 1338 and 3894 -> 3883.
+// aggregate of 8 x 124 M elements 139 us -> 118, of 8 x 11.2 M 20.8 -> 15.6).  Two ways to lay the pieces out, neither better
+// everywhere: in registers, beside the look-ups whose LDS reads bound many launches, or through LDS, which takes fewer
+// registers where two tiles' values are live at once (16 workers at b = 2: 62 against 70, 8 wavefronts per SIMD against 7).
+// Who takes which: lds_above (tq_decode.hip).
+template <bool STREAM>
+__device__ __forceinline__ void store_pieces(float4_native* p, float4_native a, float4_native b)
+{
+    if constexpr (STREAM) {
+        __builtin_nontemporal_store(a, p);
+        __builtin_nontemporal_store(b, p + 64);
+    } else {
+        p[0] = a;
+        p[64] = b;
+    }
+}
+
 template <bool STREAM>
 __device__ __forceinline__ void store8_wave(float* o, uint32_t lane, const float (&x)[8])
 {
@@ -135,14 +147,19 @@ __device__ __forceinline__ void store8_wave(float* o, uint32_t lane, const float
     for (int j = 0; j < 8; ++j) y[j] = x[j];
     swap_pieces(y);
     const float4_native a = {y[0], y[1], y[2], y[3]}, b = {y[4], y[5], y[6], y[7]};
-    float4_native* p = reinterpret_cast<float4_native*>(o) + wave_piece(lane);
-    if constexpr (STREAM) {
-        __builtin_nontemporal_store(a, p);
-        __builtin_nontemporal_store(b, p + 64);
-    } else {
-        p[0] = a;
-        p[64] = b;
-    }
+    store_pieces<STREAM>(reinterpret_cast<float4_native*>(o) + wave_piece(lane), a, b);
+}
+
+// `wb` is the wavefront's own 2 KiB of LDS; a wavefront's LDS operations complete in order, so no
+// barrier.
+template <bool STREAM>
+__device__ __forceinline__ void store8_wave_lds(float* o, uint32_t lane, const float (&x)[8], float4_native* wb)
+{
+    wb[2 * lane] = float4_native{x[0], x[1], x[2], x[3]};
+    wb[2 * lane + 1] = float4_native{x[4], x[5], x[6], x[7]};
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // other lanes' halves: the compiler keeps the order, no instruction
+    const float4_native a = wb[lane], b = wb[64 + lane];
+    store_pieces<STREAM>(reinterpret_cast<float4_native*>(o) + lane, a, b);
 }
 
 // Inclusive prefix sums over a wavefront by moves inside the vector unit: inside rows of 16 lanes, then the

@@ -774,7 +774,9 @@ __global__ __launch_bounds__(kBlock, segment_waves(DTYPE, BITS, T)) void tq_comp
 // a time, into lines that were just read.  Bound by its memory traffic and, at 25 M elements, by filling and draining the
 // chip.  The mirrored path of the compress kernel, half-line stores / this: 61,706 fp32 at b = 3 3.8 / 3.4 / 2.9 us, 25.6 M
 // bf16 24.4 / 26.1 / 24.5, accumulating 37.5 / 40.1 / 37.3, in buckets of 1024 64 / 31.6 / 31.1, 124 M bf16 104 / 138 / 103.5;
-// 124 M fp32 accumulating 268 with whole lines, 260 without, bf16 220 both, 11.2 M bf16 17.0 / 18.0.
+// 124 M fp32 accumulating 268 with whole lines, 260 without, bf16 220 both, 11.2 M bf16 17.0 / 18.0.  Whole lines laid out
+// through LDS, of which it reads little otherwise; in registers / through LDS, bf16 25.6 M at b = 4 26.7 / 26.0, 60 M
+// 57.1 / 55.2, 124 M 117.0 / 112.9 (b = 3 108.9 / 105.0, b = 2 107.0 / 106.5), fp32 the same.
 template <int DTYPE, int BITS, bool ACC, bool PAST_CACHES, int T>
 __global__ __launch_bounds__(kBlock) void tq_simulate_kernel(
     const void* __restrict__ g, uint64_t d, uint64_t d_pad, uint64_t bucket_elems, uint32_t groups_per_bucket,
@@ -793,6 +795,7 @@ __global__ __launch_bounds__(kBlock) void tq_simulate_kernel(
     const tq_params_t* P = params + bucket;
 
     __shared__ LevelLds tab;                                   // the table, and what a code stands for
+    __shared__ float4_native xbuf[kBlock / 64][128];           // store8_wave_lds's exchange buffers
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane((int)(tid >> 6));
     const Codebook cb = read_codebook(P);
     float lv[16];
@@ -848,7 +851,7 @@ __global__ __launch_bounds__(kBlock) void tq_simulate_kernel(
             if constexpr (ACC) y[j] = prev[t][j] + y[j];
         }
         if (!(ACC && PAST_CACHES) && base + 64 * kGroup <= bend) {
-            store8_wave<PAST_CACHES>(out + base, lane, y);
+            store8_wave_lds<PAST_CACHES>(out + base, lane, y, xbuf[wave]);
         } else if (e0 + kGroup <= bend) {
             reinterpret_cast<float4*>(out + e0)[0] = make_float4(y[0], y[1], y[2], y[3]);
             reinterpret_cast<float4*>(out + e0)[1] = make_float4(y[4], y[5], y[6], y[7]);

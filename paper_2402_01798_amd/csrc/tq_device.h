@@ -126,7 +126,7 @@ __device__ __forceinline__ void swap_pieces(float (&x)[8])
 // aggregate of 8 x 124 M elements 139 us -> 118, of 8 x 11.2 M 20.8 -> 15.6).  Two ways to lay the pieces out, neither better
 // everywhere: in registers, beside the look-ups whose LDS reads bound many launches, or through LDS, which takes fewer
 // registers where two tiles' values are live at once (16 workers at b = 2: 62 against 70, 8 wavefronts per SIMD against 7).
-// Who takes which: lds_above (tq_decode.hip).
+// Who takes which: lds_above (tq_decode.hip); the simulation takes LDS.
 template <bool STREAM>
 __device__ __forceinline__ void store_pieces(float4_native* p, float4_native a, float4_native b)
 {

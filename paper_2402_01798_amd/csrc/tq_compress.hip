@@ -496,7 +496,8 @@ __device__ __forceinline__ uint32_t encode_general(const float (&x)[8], const ui
 
 // N tiles from `base` on in which every lane owns a whole group: all reads first, the draws under them (requesting the
 // reads even earlier, before the codebook is set up, was slower: 708 us against 668 on 8 x 124 M fp32).
-template <int DTYPE, int BITS, bool CACHED, int N, typename Draw, typename Encode>
+// THROUGH: bf16 lines are read through the caches (reads_through).
+template <int DTYPE, int BITS, bool CACHED, int N, bool THROUGH = false, typename Draw, typename Encode>
 __device__ __forceinline__ void encode_tiles(const void* g, uint8_t* payload, uint64_t base, uint32_t lane, Draw draw, Encode encode)
 {
     constexpr bool kLines = DTYPE == TQ_F32 && !CACHED;
@@ -506,7 +507,7 @@ __device__ __forceinline__ void encode_tiles(const void* g, uint8_t* payload, ui
     for (int t = 0; t < N; ++t) {
         const uint64_t tile = base + (uint64_t)t * kTile;
         if constexpr (kLines) load_groups_wave(g, tile + (lane & ~63u) * kGroup, lane & 63u, x[t]);
-        else load_group<DTYPE, true>(g, tile + (uint64_t)lane * kGroup, x[t]);
+        else load_group<DTYPE, !THROUGH>(g, tile + (uint64_t)lane * kGroup, x[t]);
     }
 #pragma unroll
     for (int t = 0; t < N; ++t) {
@@ -543,7 +544,7 @@ __device__ __forceinline__ void encode_tiles_general(const void* g, uint8_t* pay
 
 // MIRROR: level tables are checked for the mirrored path and take it if they are regular; else every record is
 // encoded on the general one.
-template <int DTYPE, int BITS, bool CACHED, int T, bool MIRROR>
+template <int DTYPE, int BITS, bool CACHED, int T, bool MIRROR, bool THROUGH>
 __global__ __launch_bounds__(kBlock, !MIRROR && T <= 2 && !(DTYPE == TQ_BF16 && BITS == 4) ? 8 : 1) void tq_compress_kernel(
     const PtrTable g_tab, uint64_t d, uint64_t d_pad, uint64_t bucket_elems,
     uint32_t groups_per_bucket, const PtrTable params_tab, uint32_t seed_lo,
@@ -583,7 +584,7 @@ __global__ __launch_bounds__(kBlock, !MIRROR && T <= 2 && !(DTYPE == TQ_BF16 && 
         // bf16: the uniform codebook apart from the tables' code, which costs it 1 us of 14 on 25.6 M at b = 3 and 4 (fp32
         // the other way round: tables at b = 2 20.9 us with it, 21.9 without)
         if (DTYPE == TQ_BF16 && whole && !cb.nonuniform) {
-            encode_tiles<DTYPE, BITS, CACHED, T>(g, payload, gbase, lane, draw, [&](const float (&x)[8], const uint32_t (&rw)[4]) {
+            encode_tiles<DTYPE, BITS, CACHED, T, THROUGH>(g, payload, gbase, lane, draw, [&](const float (&x)[8], const uint32_t (&rw)[4]) {
                 return encode_uniform<BITS>(x, rw, cb);
             });
             return;
@@ -875,6 +876,12 @@ bool compress_cached(int count, uint64_t d, int dtype)
     return (uint64_t)count * d * (dtype == TQ_F32 ? 4u : 2u) <= (512ull << 20);
 }
 
+// Whether the uniform codebook at bf16, b = 4, reads through the caches: batches above 2 GiB.  Past them it loses up to a
+// seventh of its speed at some sizes there (us, through / past, and the step around it): 12 x 110 M 575 / 617 (1174 / 1180),
+// 32 x 62 M 897 / 1020 (1726 / 1760), 8 x 248 M 886 / 983 (1837 / 1881), 4 x 10^9 1761 / 1770 (3969 / 4028); below, 4 x 100 M
+// 175 / 174 (409 / 398), 8 x 100 M 345 / 340 (747 / 738).  At b = 2 and 3 and with tables reading past them is as good or better.
+bool reads_through(int count, uint64_t d) { return (uint64_t)count * d * 2u > (2ull << 30); }
+
 // Whether level tables are checked for the mirrored path.  Its fewer instructions pay at b = 3 and, for bf16, at b = 2; the
 // general path otherwise reads a lighter table and starts sooner.  General / mirrored, us: 16 x 25.6 M fp32 at
 // b = 2 / 3 / 4 279 / 278, 326 / 300, 333 / 336, bf16 196 / 196, 263 / 227, 274 / 284; 11.2 M at b = 2 fp32 10.4 / 10.8,
@@ -906,12 +913,13 @@ struct CompressArgs {
     tq::MutPtrTable payload;
     uint64_t d, d_pad, be, seed, pbytes;
     uint32_t groups_per_bucket, first_worker, step;
+    bool through;
 };
 
-template <int DTYPE, int BITS, bool CACHED, bool TABLE_TILES, bool MIRROR>
+template <int DTYPE, int BITS, bool CACHED, bool TABLE_TILES, bool MIRROR, bool THROUGH = false>
 void launch_as(const CompressArgs& a)
 {
-    hipLaunchKernelGGL((tq::tq_compress_kernel<DTYPE, BITS, CACHED, tq::compress_tiles(DTYPE, TABLE_TILES), MIRROR>), a.blocks,
+    hipLaunchKernelGGL((tq::tq_compress_kernel<DTYPE, BITS, CACHED, tq::compress_tiles(DTYPE, TABLE_TILES), MIRROR, THROUGH>), a.blocks,
                        dim3(tq::kBlock), 0, a.st, a.g, a.d, a.d_pad, a.be, a.groups_per_bucket, a.params, (uint32_t)a.seed,
                        (uint32_t)(a.seed >> 32), a.first_worker, a.step, a.payload, a.pbytes);
 }
@@ -927,6 +935,9 @@ hipError_t launch(const CompressShape& shape, const CompressArgs& a)
     } else if (shape.table_tiles) {
         launch_as<DTYPE, BITS, CACHED, true, false>(a);
         return hipGetLastError();
+    }
+    if constexpr (DTYPE == TQ_BF16 && BITS == 4 && !CACHED) {
+        if (a.through) { launch_as<DTYPE, BITS, CACHED, false, false, true>(a); return hipGetLastError(); }
     }
     launch_as<DTYPE, BITS, CACHED, false, false>(a);
     return hipGetLastError();
@@ -959,6 +970,7 @@ hipError_t tq_launch_compress(const void* const* g, int count, int dtype, uint64
     a.pbytes = tq_payload_bytes(d, bits);
     a.first_worker = first_worker; a.step = step;
     const bool cached = compress_cached(count, d, dtype);
+    a.through = reads_through(count, d);
 #define TQ_LAUNCH_COMPRESS(DT, B) (cached ? launch<DT, B, true>(shape, a) : launch<DT, B, false>(shape, a))
 #define TQ_LAUNCH_COMPRESS_B(DT) \
     (bits == 2 ? TQ_LAUNCH_COMPRESS(DT, 2) : (bits == 3 ? TQ_LAUNCH_COMPRESS(DT, 3) : TQ_LAUNCH_COMPRESS(DT, 4)))

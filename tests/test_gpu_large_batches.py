@@ -42,6 +42,22 @@ def test_bucketed(d, dtype, bits, grid, bucket, g_min):
         assert torch.equal(payloads[i], one), i
 
 
+@pytest.mark.parametrize("bits,bucket", [(4, 0), (4, 1 << 20), (4, 2_048), (3, 0)])
+def test_bf16_beyond_two_gib(bits, bucket):
+    """64 times 34 MB: the uniform codebook at b = 4 reads through the caches again."""
+    d = 17_000_003
+    g = gradient(d, torch.bfloat16)
+    stats, params = B.alloc_stats(d, bucket), B.alloc_params(d, bucket)
+    B.tq_stats(g, stats, B.alloc_stats_workspace(d, bucket), bucket)
+    B.tq_params(stats, params, bits, B.GRID_UNIFORM)
+    payloads = [B.alloc_payload(d, bits).fill_(0x33) for _ in range(N)]
+    B.tq_compress_multi([g] * N, [params] * N, payloads, bits, SEED, 0, STEP, bucket)
+    one = B.alloc_payload(d, bits)
+    for i in range(N):
+        B.tq_compress(g, params, one.fill_(0x44), bits, SEED, i, STEP, bucket)
+        assert torch.equal(payloads[i], one), i
+
+
 @pytest.mark.parametrize("bits,grid,g_min", [(2, B.GRID_NONUNIFORM, 0.0), (3, B.GRID_NONUNIFORM, 1e-5), (4, B.GRID_UNIFORM, 0.0)])
 @pytest.mark.parametrize("d,dtype", [(2_100_003, torch.float32), (4_200_005, torch.bfloat16)])
 def test_segments(d, dtype, bits, grid, g_min):

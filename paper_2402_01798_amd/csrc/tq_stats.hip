@@ -37,17 +37,18 @@ constexpr int kStatsBlock = 512;                       // threads per workgroup 
 constexpr int kStatsTile = kStatsBlock * kGroup;       // elements per workgroup pass (4096)
 constexpr int kStatsReplicas = 8;
 constexpr int kStatsStride = 929;                      // >= TQ_NBINS and = 1 mod 32: replicas in different banks
-constexpr int kStatsMinSlice = 4 * kStatsTile;         // smallest slice worth a workgroup (16384 elements)
-constexpr int kStatsMaxSlices = 256;                   // slices per bucket at most
-constexpr int kStatsTargetGroups = 256;                // workgroups per tensor the workspace is sized for (one per CU)
+constexpr int kStatsMinSlice = 4 * kStatsTile;         // smallest share worth a workgroup (16384 elements)
+constexpr int kStatsTargetGroups = 256;                // workgroups of an fp32 launch (one per CU)
 constexpr int kStatsResidentGroups = 1024;             // workgroups that can run at the same time (4 per CU)
-// A tensor of one record up to this size is one share, whose workgroup writes the record: no second kernel, which costs
-// more than the wider read gives.  Steps of small tensors are bound by the host, 3 us of it a launch: 1 x 20,000 fp32
-// 33.9 -> 31.1 us (the statistics 8.4 -> 5.5), 4 x 61,706 fp32 32.1 -> 29.3, each pass waited for 41.6 -> 38.7 (the statistics
-// by themselves 12.0 -> 13.1, in trips of two tiles 11.4), 32 x 61,706 37.3 -> 33.9, 4 x 61,706 bf16 33.9 -> 30.3.  At 100,000 the statistics by
+// A tensor of one record up to this size is one share, whose workgroup writes the record: no second kernel.  Two launches / one,
+// us, in steps issued call by call (3 us of host time a launch): 1 x 32,768 fp32 29.7 / 27.2, 1 x 65,536 32.5 / 29.4,
+// 16 x 65,536 bf16 31.1 / 28.6.  The statistics by themselves, calls captured in a graph, trips as they are now: 1 x 32,768 fp32
+// 8.3 / 6.9, 1 x 49,152 8.3 / 8.1, 1 x 65,536 8.4 / 9.1 (with tail 10.0 / 11.7, bf16 10.0 / 11.4); several tensors whose shares
+// would not end where they do: 4 x 53,248 with tail 13.2 / 10.8, 4 x 61,440 13.2 / 11.4.  So a captured step loses 0.5 to
+// 1.5 us of 18 at the upper end of this range; the line is drawn for calls issued one by one.  At 100,000 the statistics by
 // themselves take 17.4 us instead of 11.9.
 constexpr uint64_t kWholeTensor = 65536;
-// Tiles of a trip of the equal shares, see stats_slice.
+// Tiles of a trip of the equal shares, of one record as of many and of segments, see stats_slice.
 constexpr int share_trip(int dtype, bool past) { return dtype == TQ_F32 && past ? 4 : 2; }
 constexpr int kReduceBlock = 1024;                     // threads of the reduce kernel: 64 bins x 16 slice lanes
 constexpr int kReduceBins = 64;
@@ -64,11 +65,6 @@ struct StatsExtra {            // 32 bytes
     long long exp_sum;             // sum of unbiased exponents of the tail elements
     unsigned long long log2m_fix;  // sum over groups of log2(product of the tail mantissas) * 2^28
 };
-
-__host__ __device__ inline uint64_t stats_ws_hist_words(uint64_t nb, uint32_t slices)
-{
-    return nb * TQ_NBINS * (uint64_t)slices;
-}
 
 // Called with the whole wavefront active; every lane gets the result.
 template <typename T>
@@ -187,8 +183,12 @@ __device__ __forceinline__ StatsExtra stats_slice(const void* __restrict__ g, ui
     //    end sooner and find more of what they ask for in a cache; trips of four / three / two / one / two without the
     //    wait, us: 4 x 61,706 13.1 / 12.7 / 11.4 / 11.6 / 11.2, 11.2 M 22.3 / 20.7 / 19.7 / 19.8 / 19.2 (one step 44.5 / 43.7 /
     //    43.0 / 44.2 / 42.2), 4 x 11.2 M 35.6 / 34.6 / 32.9 / 33.0 / 33.7 (84.4 / 83.7 / 81.8 / 87.8 / 82.3), 60 M 48.5 / 46.1 /
-    //    43.7 / 47.8 / 44.9 (139.9 / 137.1 / 137.0 / 145.5 / 135.2).  Buckets of four tiles in one trip: 4 x 11.2 M in buckets
-    //    of 16384, one step 97.8 / 98.0 / 99.5 / 98.3 / 99.3.
+    //    43.7 / 47.8 / 44.9 (139.9 / 137.1 / 137.0 / 145.5 / 135.2): the wait costs the kernel 2 to 3 % up to 45 MB and
+    //    gains it as much above; neither is the better one for every step, and it stays.  The same for shares of buckets, trips of four / two (and the step): 25.6 M in buckets of 32768 24.6 / 23.7
+    //    (77.5 / 77.6), of 65536 with tail 32.7 / 27.6 (85.3 / 81.0), of 2^20 24.6 / 23.1 (113.6 / 112.3), 4 x 11.2 M in buckets of
+    //    65536 with tail 46.1 / 38.9 (107.3 / 103.0), 1 M in buckets of 65536 with tail 12.2 / 10.9; and of segments: 25.6 M
+    //    44.3 / 40.8 (137.5 / 132.3), 4 x 11.2 M 48.0 / 45.7 (148.3 / 145.2), 1 M 20.9 / 19.3.  Buckets of four tiles in one trip
+    //    (tq_stats_partial_kernel): 4 x 11.2 M in buckets of 16384, one step 97.8 / 98.0 / 99.5 / 98.3 / 99.3.
     constexpr int kTrip = TRIP;
     constexpr bool kWaitAll = DTYPE == TQ_F32;
     constexpr bool kLines = PAST && DTYPE == TQ_F32;                   // the loads of the full trips, see load_lines
@@ -439,8 +439,11 @@ __device__ __forceinline__ StatsExtra stats_slice(const void* __restrict__ g, ui
     return x;
 }
 
-// Buckets of fewer than 32768 elements: a workgroup takes one and writes its record.  (Cut in two they need the second
-// kernel, which costs more than the wider read gives: 1 x 20,000 fp32 8.4 us cut, 5.5 whole.)
+// Buckets of fewer than 32768 elements: a workgroup takes one and writes its record.  Cut in two, a handful of them
+// needed the second kernel, which costs more than the wider read gives; captured calls, cut / whole, us: 1 x 17,001 fp32 with
+// tail 7.8 / 6.4, 1 x 24,000 6.4 / 5.1, 1 x 32,767 with tail 8.8 / 8.1, 1 x 60,000 in buckets of 16,512 6.5 / 4.5, 4 x 300,000 in
+// buckets of 32,640 8.1 / 5.8; bf16 7.5 / 5.8, 6.3 / 4.6, 8.3 / 7.8, 6.3 / 4.2, 7.9 / 5.4.  Read through the caches at any size: it has no
+// full trips below 16384 elements (fp32) and hardly any above.
 template <int DTYPE, bool TAIL>
 __global__ __launch_bounds__(kStatsBlock) void tq_stats_partial_kernel(
     const PtrTable g_tab, uint64_t d, uint64_t bucket_elems, float g_min, const MutPtrTable stats_tab)
@@ -754,17 +757,6 @@ __global__ __launch_bounds__(kStatsBlock) void tq_stats_segments_reduce_kernel(
 
 namespace {
 
-// Rows of the workspace per bucket of fewer than 32768 elements: one for every 16384 elements, and no more than about
-// one per compute unit.  What callers size their workspaces by; such buckets leave it unused.
-uint32_t max_slices(uint64_t be, uint64_t nb)
-{
-    const uint64_t want = (be + tq::kStatsMinSlice - 1) / tq::kStatsMinSlice;
-    uint64_t cap = (tq::kStatsTargetGroups + nb - 1) / nb;
-    cap = cap > tq::kStatsMaxSlices ? tq::kStatsMaxSlices : cap;
-    const uint64_t m = want < cap ? want : cap;
-    return (uint32_t)(m < 1 ? 1 : m);
-}
-
 // Whether the launch is cut into equal shares (large buckets) or into buckets.
 bool uses_shares(uint64_t d, uint64_t bucket_elems)
 {
@@ -772,13 +764,16 @@ bool uses_shares(uint64_t d, uint64_t bucket_elems)
     return be >= tq::kBalancedMinBucket;
 }
 
-// Whether a batch is read past the caches, and the tiles at the end of every share that are read through them all the same.
+// Whether a batch in equal shares is read past the caches, and the tiles at the end of every share that are read through them
+// all the same.  A piece's first full trip, the last one where their number is even, and what is left after them are always
+// read through them: of a bucket of 32768 fp32 elements everything, of 65536 two trips of four.  Smaller buckets always are.
 // A batch larger than the memory-side cache (256 MiB) read through it leaves there what the next call displaces before
 // reaching it, and reads slower: with non-temporal loads, whole lines at a time, a persistent read loop of this shape reaches
 // 7.0 TB/s instead of 6.2.  What compress reads again should stay, so 192 MiB of the batch are read the ordinary
 // way, last.  Steps of 8 x 124 M fp32 (b = 2), 16 x 25.6 M (b = 3, tables), 8 x 11.2 M (b = 4) and 4 x 10^9 bf16, everything
 // through the caches / nothing / 192 MiB, compress reading past the caches: 1404 / 1347 / 1334, 658 / 636 / 628, 154.2 / 148.4 / 147.6,
-// 4007 / 3917 / 3916 us (160 to 240 MiB: the same).  A batch that fits is read through the caches whole: past them 25.6 M
+// 4007 / 3917 / 3916 us (160 to 240 MiB: the same).  Statistics of 8 x 25.6 M in buckets of 32768 183.5 / - / 181.0, of 65536 with
+// tail 191.4 / - / 187.3, of 131072 153.1 / - / 139.0.  A batch that fits is read through the caches whole: past them 25.6 M
 // fp32 65.9 -> 69.0, 4 x 11.2 M 102 -> 112 (and with whole-line loads from the caches 65.7 -> 66.4).
 bool stats_past_caches(int count, uint64_t d, int dtype)
 {
@@ -792,20 +787,21 @@ uint64_t stats_kept_tiles(int dtype, uint32_t groups)
 
 }  // namespace
 
+// A batch of `count` tensors has count times this much.  Equal shares: one row per share and per bucket.  Buckets of fewer
+// than 32768 elements (and single records up to kWholeTensor) are written as finished records and use none of it; what is
+// asked for them, a row per 16384 elements of a bucket until there are about 256, is what the interface has always
+// answered: tq_stats and tq_stats_static go on refusing and accepting the same sizes.
 uint64_t tq_stats_workspace_bytes_impl(uint64_t d, uint64_t bucket_elems)
 {
     if (d == 0) return 0;
     const uint64_t be = bucket_elems ? bucket_elems : d;
     const uint64_t nb = (d + be - 1) / be;
-    const uint32_t slices = max_slices(be, nb);
-    const uint64_t hist_bytes = tq::stats_ws_hist_words(nb, slices) * 4;
-    uint64_t bytes = (hist_bytes + 15) / 16 * 16 + nb * slices * sizeof(tq::StatsExtra);
-    if (uses_shares(d, bucket_elems)) {
-        // one row per share and per bucket; a batch of `count` tensors has count times this much
-        const uint64_t shared = (tq::kStatsResidentGroups + nb) * (TQ_NBINS * 4 + sizeof(tq::StatsExtra));
-        bytes = bytes > shared ? bytes : shared;
+    uint64_t rows = tq::kStatsResidentGroups + nb;
+    if (!uses_shares(d, bucket_elems)) {
+        const uint64_t pieces = (be - 1) / tq::kStatsMinSlice + 1, most = (255 + nb) / nb;
+        rows = nb * (pieces < most ? pieces : most);
     }
-    return (bytes + 255) / 256 * 256;                                  // regions of a batch stay aligned
+    return (rows * (TQ_NBINS * 4 + sizeof(tq::StatsExtra)) + 255) / 256 * 256;      // regions of a batch stay aligned
 }
 
 // Device address of this device's copy of `scratch`, looked up once per device with that
@@ -830,8 +826,7 @@ hipError_t tq_stats_static_scratch(void** out)
 }
 
 // Host side of tq_stats / tq_stats_multi after the argument checks of the C entry points:
-// `count` same-shaped tensors in one pair of launches (grid.y), each with its own region of
-// tq_stats_workspace_bytes(d, bucket_elems) bytes of the workspace.
+// `count` same-shaped tensors in one launch, or in two that share the workspace (equal shares that cut records).
 hipError_t tq_launch_stats(const void* const* g, int count, int dtype, uint64_t d, uint64_t bucket_elems,
                            float g_min, tq_stats_t* const* stats, void* workspace, hipStream_t st)
 {

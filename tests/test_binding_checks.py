@@ -125,3 +125,11 @@ assert B.stats_workspace_bytes(1000, 2**64 - 1024) > 0
     run = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=300,
                          cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
     assert run.returncode == 0, (run.returncode, run.stderr)
+
+
+@pytest.mark.parametrize("d,bucket,rows", [
+    (1, 0, 1), (16_385, 0, 2), (32_767, 0, 2), (32_768, 0, 1025), (61_706, 0, 1025), (128 * 4096, 128, 4096), (20_000, 1 << 20, 64),
+    (100_000, 16_384, 7), (100_000, 32_640, 8), (11_200_000, 16_512, 679), (124_000_000, 1 << 20, 1024 + 119)])
+def test_workspace_sizes(d, bucket, rows):
+    """Rows of 898 counts and 32 bytes of sums, in multiples of 256 bytes: sizes that callers rely on."""
+    assert B.stats_workspace_bytes(d, bucket) == -(-rows * (B.NBINS * 4 + 32) // 256) * 256

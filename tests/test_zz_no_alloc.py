@@ -25,9 +25,11 @@ def both(g_dev, bucket, g_min):
 
 
 @pytest.mark.parametrize("wl,first,second", [
-    ("cfg4", ((3 << 20) + 999, 1 << 20, 0.0), (70_000, 16_384, 0.0)),       # several slices per bucket, then few
-    ("cfg2", (2_000_003, 0, 0.0), (61_706, 0, 1e-4)),                       # one bucket cut into many slices
+    ("cfg4", ((3 << 20) + 999, 1 << 20, 0.0), (70_000, 16_384, 0.0)),       # many rows, then none
+    ("cfg2", (2_000_003, 0, 0.0), (61_706, 0, 1e-4)),                       # one record in many rows, then in none
     ("cfg5", (5_000_000, 1 << 20, 1e-6), (1_000_003, 0, 1e-6)),             # bf16, tail terms
+    ("cfg4", ((3 << 20) + 999, 1 << 20, 0.0), (200_003, 32_768, 0.0)),      # many rows, then a few of the same
+    ("cfg2", (2_000_003, 0, 0.0), (300_001, 0, 1e-4)),
 ])
 def test_static_scratch_gives_the_same_statistics_twice_in_a_row(wl, first, second):
     for d, bucket, g_min in (first, second):
@@ -42,12 +44,18 @@ def test_static_scratch_gives_the_same_statistics_twice_in_a_row(wl, first, seco
 
 
 def test_sizes_beyond_the_scratch_array_are_refused():
-    d, bucket = 128 * 4096, 128                         # 4096 buckets need more rows than the array holds
+    d, bucket = 128 * 4096, 128                         # more is asked for 4096 buckets than the array holds
     assert B.stats_workspace_bytes(d, bucket) > (8 << 20)
     g = torch.zeros(d, dtype=torch.float32, device="cuda")
     st = B.alloc_stats(d, bucket)
     with pytest.raises(B.TqError) as e:
         B.tq_stats_static(g, st, bucket)
+    assert e.value.code == B.EUNSUPPORTED
+    # and 1400 buckets whose pieces do need the rows
+    d, bucket = 32_768 * 1_400, 32_768
+    assert B.stats_workspace_bytes(d, bucket) > (8 << 20)
+    with pytest.raises(B.TqError) as e:
+        B.tq_stats_static(torch.zeros(d, dtype=torch.bfloat16, device="cuda"), B.alloc_stats(d, bucket), bucket)
     assert e.value.code == B.EUNSUPPORTED
     # the largest benchmark shapes fit
     for dd, be in ((124_000_000, 1 << 20), (1_000_000_000, 0), (1_000_000_000, 1 << 20), (25_600_000, 1 << 20)):

@@ -39,10 +39,11 @@ ALU_PEAK_TLOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 # (workload, bits, grid) of every variant the benchmark plan names; the first is the headline
 VARIANTS = [("cfg4", 2, 0), ("cfg4", 2, 1), ("cfg2", 2, 0), ("cfg2", 4, 0), ("cfg3", 3, 1), ("cfg5", 2, 1)]
 
-# vector-ALU lane-operations per element of the compress kernel's variants, as rocprofv3's
-# SQ_INSTS_VALU counts them (profiles/valu_instructions.txt): they decide which ceiling binds
-COMPRESS_VALU_PER_ELEM = {"f32/b2/g0": 17.0, "f32/b2/g1": 21.7, "f32/b4/g0": 20.3, "f32/b3/g1": 25.2,
-                          "bf16/b2/g1": 18.6}
+# vector-ALU lane-operations per element of the compress kernel in each variant of the plan (the kernel's form goes by type,
+# bits, family and the size of the batch), as rocprofv3's SQ_INSTS_VALU counts them (profiles/valu_instructions.txt): they
+# decide which ceiling binds
+COMPRESS_VALU_PER_ELEM = {"cfg4/b2/g0": 17.0, "cfg4/b2/g1": 21.7, "cfg2/b2/g0": 15.5, "cfg2/b4/g0": 20.3, "cfg3/b3/g1": 25.2,
+                          "cfg5/b2/g1": 18.6}
 
 
 def parse():
@@ -334,11 +335,11 @@ def compress_roofline(path, res):
     N = path.N
     comp_us = res["stage_us_per_step"]["compress"]
     gbps = N * path.bytes_compress() / comp_us / 1e3
-    roof = {"kernel": "tq_compress_kernel", "bound": "hbm", "achieved": round(gbps, 1), "peak": HBM_PEAK_GBPS,
+    kernel = "tq_compress_segments_kernel" if path.seg is not None else "tq_compress_kernel"
+    roof = {"kernel": kernel, "bound": "hbm", "achieved": round(gbps, 1), "peak": HBM_PEAK_GBPS,
             "unit": "GB/s", "frac": round(gbps / HBM_PEAK_GBPS, 4),
-            "traffic": load_traffic("tq_compress_kernel", path.wl.name, path.bits, path.grid)}
-    key = "%s/b%d/g%d" % ("bf16" if path.g[0].element_size() == 2 else "f32", path.bits, min(path.grid, 1))
-    valu = COMPRESS_VALU_PER_ELEM.get(key)
+            "traffic": load_traffic(kernel, path.wl.name, path.bits, path.grid)}
+    valu = None if path.seg is not None else COMPRESS_VALU_PER_ELEM.get("%s/b%d/g%d" % (path.wl.name, path.bits, path.grid))
     if valu:
         t_alu = valu / (ALU_PEAK_TLOPS * 1e12)
         t_hbm = (path.bytes_compress() / path.d) / (HBM_PEAK_GBPS * 1e9)
@@ -355,7 +356,7 @@ def compress_roofline(path, res):
 
 
 # vector-ALU lane-operations per element of the statistics kernel (profiles/valu_instructions.txt)
-STATS_VALU_PER_ELEM = {"f32": 5.2, "f32/tail": 11.4, "bf16/tail": 10.0}
+STATS_VALU_PER_ELEM = {"cfg4": 5.2, "cfg2": 5.6, "cfg3": 11.4, "cfg5": 10.0}
 
 
 def stats_roofline(path, res):
@@ -367,9 +368,9 @@ def stats_roofline(path, res):
     kernel = "tq_stats_segments_partial_kernel" if path.seg is not None else "tq_stats_balanced_kernel"
     roof = {"kernel": kernel, "bound": "hbm", "achieved": round(gbps, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
             "frac": round(gbps / HBM_PEAK_GBPS, 4),
-            "traffic": load_traffic("tq_stats_balanced_kernel", path.wl.name, path.bits, path.grid),
+            "traffic": load_traffic(kernel, path.wl.name, path.bits, path.grid),
             "note": "duration of the statistics stage (both its kernels)"}
-    valu = STATS_VALU_PER_ELEM.get(("bf16" if sz == 2 else "f32") + ("/tail" if path.wl.g_min > 0 else ""))
+    valu = None if path.seg is not None else STATS_VALU_PER_ELEM.get(path.wl.name)
     if valu:
         roof["valu_ops_per_elem"] = valu
         roof["alu_frac"] = round(path.N * path.d * valu / (us * 1e-6) / 1e12 / ALU_PEAK_TLOPS, 4)
@@ -464,7 +465,6 @@ def main():
         torch.cuda.synchronize()
         r = measure(p2, a.other_steps, 3, 0)
         r["roofline"] = compress_roofline(p2, r)
-        r["roofline"]["kernel"] = "tq_compress_segments_kernel"
         r["roofline_stats"] = stats_roofline(p2, r)
         others["cfg4/b2/uniform/layer-segments"] = r
         del p2

@@ -163,25 +163,29 @@ def alloc_payload(d, bits, device="cuda"):
 
 def _stats_bytes(d, bucket_elems):
     """Bytes of the records tq_stats writes, without a call into the library."""
-    return (-(-d // bucket_elems) if bucket_elems > 0 else min(d, 1)) * STATS_BYTES
+    return -(-d // bucket_elems) * STATS_BYTES if bucket_elems > 0 else STATS_BYTES if d else 0
 
 
 def _holds(buf, nbytes, what):
-    if buf.nbytes < nbytes:
+    if buf.numel() < nbytes and buf.nbytes < nbytes:
         raise ValueError("%s buffer too small: %d bytes of %d" % (what, buf.nbytes, nbytes))
 
 
 def tq_stats(g, stats, workspace, bucket_elems=0, g_min=0.0):
-    _holds(stats, _stats_bytes(g.numel(), bucket_elems), "stats")
-    _check(lib().tq_stats(_dev(g, "g"), _dtype_code(g), g.numel(), bucket_elems, g_min,
+    d = g.numel()
+    if bucket_elems or stats.numel() < STATS_BYTES:        # one record: a look at the size is enough
+        _holds(stats, _stats_bytes(d, bucket_elems), "stats")
+    _check(lib().tq_stats(_dev(g, "g"), _dtype_code(g), d, bucket_elems, g_min,
                           _dev(stats, "stats"), _dev(workspace, "workspace"), workspace.numel(),
                           _stream()), "tq_stats")
     return stats
 
 
 def tq_stats_static(g, stats, bucket_elems=0, g_min=0.0):
-    _holds(stats, _stats_bytes(g.numel(), bucket_elems), "stats")
-    _check(lib().tq_stats_static(_dev(g, "g"), _dtype_code(g), g.numel(), bucket_elems, g_min,
+    d = g.numel()
+    if bucket_elems or stats.numel() < STATS_BYTES:        # one record: a look at the size is enough
+        _holds(stats, _stats_bytes(d, bucket_elems), "stats")
+    _check(lib().tq_stats_static(_dev(g, "g"), _dtype_code(g), d, bucket_elems, g_min,
                                  _dev(stats, "stats"), _stream()), "tq_stats_static")
     return stats
 

@@ -541,7 +541,8 @@ bool streams_output(uint64_t d)
 //   b = 2, 16 workers  +3 .. +19 everywhere        8 workers  +2 .. +6 above 64 MiB, -3 .. +2 below
 //   b = 4,  8 workers  +1 .. +5 above 160 MiB, -3 .. -11 below
 //   b = 4, up to 4     -4 .. +1 up to 1.5 GiB, +1 .. +11 above (one worker from 2.3 GiB on)
-//   b = 2, up to 4     -5 .. +4 up to 2.5 GiB; above, one worker -2, two +5 .. +7, four +1 .. +3
+//   b = 2, up to 4     -5 .. +4 up to 2.5 GiB; above, one worker -2, two +5 .. +7, four +1 .. +3 (but 4 x 10^9 bf16, one step,
+//                      3952 us in registers, 3964 through LDS)
 //   b = 3, one worker  -5 .. +1 up to 2.5 GiB, +4 .. +8 above;   8 workers  -5 .. -14;   others  -2 .. +1
 // The updates and sums lose nothing in registers (16 workers at b = 2 with SGD -5 .. -15), nor do segments (8 x 124 M at
 // b = 2 in 68 layers 124 -> 114 us).
@@ -551,7 +552,7 @@ constexpr uint64_t lds_above(int bits, int U)
     if (U == 16) return bits == 2 ? 0 : kNever;
     if (U == 8) return bits == 2 ? 64ull << 20 : (bits == 4 ? 160ull << 20 : kNever);
     if (bits == 4) return 1536ull << 20;
-    return (bits == 2) == (U > 1) ? 2560ull << 20 : kNever;
+    return U == (bits == 2 ? 2 : 1) ? 2560ull << 20 : kNever;
 }
 
 // Whether launches of this kind can be above it: kStore is the mode of outputs of 64 to 160 MiB.

@@ -240,8 +240,9 @@ def _one_each(count, buffers, what):
 
 
 def _same_shape(gs):
+    """The first tensor's elements are read of every tensor: longer ones have them."""
     d, dtype = gs[0].numel(), gs[0].dtype
-    if not _sized(gs, len(gs), d, d, dtype) and any(g.numel() != d or g.dtype != dtype for g in gs):
+    if not _sized(gs, len(gs), d, _ANY_SIZE, dtype) and any(g.numel() < d or g.dtype != dtype for g in gs):
         raise ValueError("batched tensors must share shape and dtype")
 
 

@@ -106,7 +106,10 @@ def test_roomy_buffers_and_longer_lists_are_taken(module, reached, monkeypatch):
     B.tq_stats_multi(G, [t.view(torch.float64) for t in STATS], WORKSPACE)                    # bytes count, not elements
     B.tq_params_multi(STATS, SEG_PARAMS, 3, B.GRID_UNIFORM)
     B.tq_stats_segments_multi(G, SEG, SEG_STATS, WORKSPACE)
-    assert len(reached) == 6
+    longer = G[:2] + [torch.zeros(D + 1)]
+    B.tq_stats_multi(longer, STATS, WORKSPACE)
+    B.tq_stats_segments_multi(longer, SEG, SEG_STATS, WORKSPACE)
+    assert len(reached) == 8
 
 
 def test_bucket_sizes_that_cannot_be_added_to_are_refused():

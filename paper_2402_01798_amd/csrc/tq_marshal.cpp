@@ -14,65 +14,85 @@ namespace {
 // Not their subclasses: what one of those hands out may differ from what it stores.
 bool plain_sequence(PyObject* seq) { return PyList_CheckExact(seq) || PyTuple_CheckExact(seq); }
 
-// pointers(tensors) -> bytes: the addresses, 8 bytes each; None unless all are contiguous device tensors.
-PyObject* pointers(PyObject*, PyObject* seq)
+// What is asked of the tensors of a list: how many there are (any number where count < 0), their elements and type.
+struct Wanted {
+    long long count = -1, low = 0, high = INT64_MAX;
+    PyObject* dtype = Py_None;
+};
+
+// Fills `w` from (count, low, high, dtype); false with an exception set.
+bool wanted(PyObject* const* args, Wanted& w)
 {
-    if (!plain_sequence(seq)) Py_RETURN_NONE;
+    w.count = PyLong_AsLongLong(args[0]);
+    w.low = PyLong_AsLongLong(args[1]);
+    w.high = PyLong_AsLongLong(args[2]);
+    w.dtype = args[3];
+    return !PyErr_Occurred();
+}
+
+// Whether `seq` is a list or tuple of as many tensors as are wanted, each of which is as wanted and `use` takes it.
+template <typename Use>
+bool all_as_wanted(PyObject* seq, const Wanted& w, Use use)
+{
+    if (!plain_sequence(seq)) return false;
     const Py_ssize_t n = PySequence_Fast_GET_SIZE(seq);
-    PyObject* out = PyBytes_FromStringAndSize(nullptr, n * (Py_ssize_t)sizeof(void*));
-    if (!out) return nullptr;
-    void** p = reinterpret_cast<void**>(PyBytes_AS_STRING(out));
+    if ((w.count >= 0 && n != w.count) || (w.dtype != Py_None && !THPDtype_Check(w.dtype))) return false;
     try {
         for (Py_ssize_t i = 0; i < n; ++i) {
             PyObject* o = PySequence_Fast_GET_ITEM(seq, i);
-            bool usable = THPVariable_CheckExact(o);
-            if (usable) {
-                const at::Tensor& t = THPVariable_Unpack(o);
-                usable = t.is_cuda() && t.is_contiguous();
-                if (usable) p[i] = t.data_ptr();
-            }
-            if (!usable) {
-                Py_DECREF(out);
-                Py_RETURN_NONE;
-            }
+            if (!THPVariable_CheckExact(o)) return false;
+            const at::Tensor& t = THPVariable_Unpack(o);
+            const long long elems = t.numel();
+            if (elems < w.low || elems > w.high) return false;
+            if (w.dtype != Py_None && t.scalar_type() != reinterpret_cast<THPDtype*>(w.dtype)->scalar_type) return false;
+            if (!use(i, t)) return false;
         }
     } catch (...) {
-        Py_DECREF(out);
-        Py_RETURN_NONE;
+        return false;
     }
-    return out;
+    return true;
+}
+
+// pointers(tensors[, count, low, high, dtype or None]) -> bytes: the addresses, 8 bytes each; None unless all are
+// contiguous device tensors and, where that is asked, as `sized` wants them.
+PyObject* pointers(PyObject*, PyObject* const* args, Py_ssize_t nargs)
+{
+    Wanted w;
+    if (nargs != 1 && nargs != 5) {
+        PyErr_SetString(PyExc_TypeError, "pointers takes one argument or five");
+        return nullptr;
+    }
+    if (nargs == 5 && !wanted(args + 1, w)) return nullptr;
+    if (!plain_sequence(args[0])) Py_RETURN_NONE;
+    PyObject* out = PyBytes_FromStringAndSize(nullptr, PySequence_Fast_GET_SIZE(args[0]) * (Py_ssize_t)sizeof(void*));
+    if (!out) return nullptr;
+    void** p = reinterpret_cast<void**>(PyBytes_AS_STRING(out));
+    const bool usable = all_as_wanted(args[0], w, [&](Py_ssize_t i, const at::Tensor& t) {
+        if (!t.is_cuda() || !t.is_contiguous()) return false;
+        p[i] = t.data_ptr();
+        return true;
+    });
+    if (usable) return out;
+    Py_DECREF(out);
+    Py_RETURN_NONE;
 }
 
 // sized(tensors, count, low, high, dtype or None) -> bool: whether there are `count` tensors, each of low .. high elements
 // and of that dtype.
 PyObject* sized(PyObject*, PyObject* const* args, Py_ssize_t nargs)
 {
+    Wanted w;
     if (nargs != 5) {
         PyErr_SetString(PyExc_TypeError, "sized takes five arguments");
         return nullptr;
     }
-    PyObject* seq = args[0];
-    const long long count = PyLong_AsLongLong(args[1]), low = PyLong_AsLongLong(args[2]), high = PyLong_AsLongLong(args[3]);
-    if (PyErr_Occurred()) return nullptr;
-    if (!plain_sequence(seq) || PySequence_Fast_GET_SIZE(seq) != count) Py_RETURN_FALSE;
-    if (args[4] != Py_None && !THPDtype_Check(args[4])) Py_RETURN_FALSE;
-    try {
-        for (Py_ssize_t i = 0; i < count; ++i) {
-            PyObject* o = PySequence_Fast_GET_ITEM(seq, i);
-            if (!THPVariable_CheckExact(o)) Py_RETURN_FALSE;
-            const at::Tensor& t = THPVariable_Unpack(o);
-            const long long n = t.numel();
-            if (n < low || n > high) Py_RETURN_FALSE;
-            if (args[4] != Py_None && t.scalar_type() != reinterpret_cast<THPDtype*>(args[4])->scalar_type) Py_RETURN_FALSE;
-        }
-    } catch (...) {
-        Py_RETURN_FALSE;
-    }
-    Py_RETURN_TRUE;
+    if (!wanted(args + 1, w)) return nullptr;
+    if (w.count < 0) Py_RETURN_FALSE;
+    return PyBool_FromLong(all_as_wanted(args[0], w, [](Py_ssize_t, const at::Tensor&) { return true; }));
 }
 
 PyMethodDef methods[] = {
-    {"pointers", pointers, METH_O, nullptr},
+    {"pointers", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(pointers)), METH_FASTCALL, nullptr},
     {"sized", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(sized)), METH_FASTCALL, nullptr},
     {nullptr, nullptr, 0, nullptr}};
 

@@ -67,6 +67,11 @@ def test_pointers_are_left_to_python_off_the_device():
     assert M.pointers([torch.zeros(8, device="meta")]) is None and M.pointers([]) == b""
     with pytest.raises(ValueError, match="g must be a contiguous device tensor"):
         B._ptr_array([torch.zeros(8)], "g")
+    assert M.pointers([], 0, 1, 1, None) == b"" and M.pointers([], 1, 0, BIG, None) is None
+    with pytest.raises(TypeError):
+        M.pointers([], 0)
+    with pytest.raises(TypeError):
+        M.pointers([], "0", 0, 0, None)
 
 
 def test_sizes_are_still_refused():
@@ -85,3 +90,8 @@ def test_pointers_on_the_device():
     a, b = torch.zeros(64, device="cuda"), torch.zeros(8, 8, device="cuda")
     assert M.pointers([a, b]) == b"".join(t.data_ptr().to_bytes(8, "little") for t in (a, b))
     assert M.pointers([a, b.t()]) is None and M.pointers([a, a.cpu()]) is None
+    # with the sizes and the type that are wanted
+    assert M.pointers((a, b), 2, 64, 64, torch.float32) == M.pointers([a, b], 2, 0, BIG, None) == M.pointers([a, b])
+    for wanted in ((1, 64, 64, None), (3, 64, 64, None), (2, 65, BIG, None), (2, 0, 63, None), (2, 64, 64, torch.bfloat16), (2, 64, 64, "f32")):
+        assert M.pointers([a, b], *wanted) is None, wanted
+    assert M.pointers([a, b[:7]], 2, 64, BIG, None) is None

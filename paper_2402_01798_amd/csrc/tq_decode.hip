@@ -537,22 +537,25 @@ bool streams_output(uint64_t d)
 }
 
 // Outputs of more bytes than this go through LDS on their way out, where the call is the plain average of buckets (U workers
-// of tq_decode_fast_kernel); by what both ways measured over 12 M to 930 M elements, in registers against through LDS, per cent:
+// of tq_decode_fast_kernel); by what both ways measured over 12 M to 2 x 10^9 elements, in registers against through LDS, per cent:
 //   b = 2, 16 workers  +3 .. +19 everywhere        8 workers  +2 .. +6 above 64 MiB, -3 .. +2 below
 //   b = 4,  8 workers  +1 .. +5 above 160 MiB, -3 .. -11 below
-//   b = 4, up to 4     -4 .. +1 up to 1.5 GiB, +1 .. +11 above (one worker from 2.3 GiB on)
-//   b = 2, up to 4     -5 .. +4 up to 2.5 GiB; above, one worker -2, two +5 .. +7, four +1 .. +3 (but 4 x 10^9 bf16, one step,
-//                      3952 us in registers, 3964 through LDS)
-//   b = 3, one worker  -5 .. +1 up to 2.5 GiB, +4 .. +8 above;   8 workers  -5 .. -14;   others  -2 .. +1
+//   b = 4, two and four  -4 .. +1 up to 1 GiB, +0 .. +12 above      one  -6 .. -2 up to 2 GiB, +4 .. +16 above
+//   b = 2, one  -5 .. +4 up to 4.25 GiB, +5 .. +16 above            two  -5 .. +2 up to 2 GiB, +2 .. +9 above (-2 once)
+//   b = 3, one  -8 .. +1 up to 2.75 GiB, +7 .. +13 above            8 workers  -5 .. -14   others  -4 .. +1
+//   b = 2, four workers  -2 .. +1 up to 2.5 GiB, +1 .. +4 above by itself; behind a compress the other way round (4 x 10^9
+//          bf16, one step, 3952 us in registers, 3964 through LDS), and it stays in registers
 // The updates and sums lose nothing in registers (16 workers at b = 2 with SGD -5 .. -15), nor do segments (8 x 124 M at
 // b = 2 in 68 layers 124 -> 114 us).
 constexpr uint64_t kNever = ~0ull;
 constexpr uint64_t lds_above(int bits, int U)
 {
+    constexpr uint64_t kMiB = 1ull << 20;
     if (U == 16) return bits == 2 ? 0 : kNever;
-    if (U == 8) return bits == 2 ? 64ull << 20 : (bits == 4 ? 160ull << 20 : kNever);
-    if (bits == 4) return 1536ull << 20;
-    return U == (bits == 2 ? 2 : 1) ? 2560ull << 20 : kNever;
+    if (U == 8) return bits == 2 ? 64 * kMiB : (bits == 4 ? 160 * kMiB : kNever);
+    if (bits == 4) return (U == 1 ? 2048 : 1024) * kMiB;
+    if (U == 1) return (bits == 2 ? 4352 : 2816) * kMiB;
+    return bits == 2 && U == 2 ? 2048 * kMiB : kNever;
 }
 
 // Whether launches of this kind can be above it: kStore is the mode of outputs of 64 to 160 MiB.

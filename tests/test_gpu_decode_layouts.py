@@ -16,7 +16,8 @@ MIB = (1 << 20) // 4                                           # elements
     (8, 2, 64 * MIB), (8, 2, 64 * MIB + 1), (5, 2, 100 * MIB + 4_095), (7, 2, 160 * MIB + 1),
     (8, 4, 160 * MIB), (5, 4, 160 * MIB + 4_097),
     (1, 4, 1536 * MIB + 3), (2, 4, 1536 * MIB + 2_049), (4, 4, 1536 * MIB + 128),
-    (1, 3, 2560 * MIB + 9), (2, 2, 2560 * MIB + 1)])
+    (1, 3, 2560 * MIB + 9), (2, 2, 2560 * MIB + 1),
+    (1, 2, 4352 * MIB + 1), (1, 3, 2816 * MIB + 9), (1, 4, 2048 * MIB + 3), (2, 4, 1024 * MIB + 2_049), (2, 2, 2048 * MIB + 1)])
 @pytest.mark.parametrize("weighted", [False, True])
 def test_same_bytes(N, bits, d, weighted):
     gen = torch.Generator(device="cuda").manual_seed(d)
@@ -34,4 +35,4 @@ def test_same_bytes(N, bits, d, weighted):
     segments = torch.full((d + 64,), 7.0, device="cuda")
     B.tq_decompress_aggregate_segments(payloads, params, B.Segments([0, d]), segments[:d], bits, weights)
     assert torch.equal(buckets, segments)                      # and nothing past the end on either side
-    assert torch.unique(buckets[:4096]).numel() > 4
+    assert torch.unique(buckets[:4096]).numel() >= 1 << bits     # one worker's average takes its 2^b levels, several workers' more

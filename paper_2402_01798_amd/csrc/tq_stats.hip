@@ -442,9 +442,10 @@ __device__ __forceinline__ StatsExtra stats_slice(const void* __restrict__ g, ui
 // Buckets of fewer than 32768 elements: a workgroup takes one and writes its record.  Cut in two, a handful of them
 // needed the second kernel, which costs more than the wider read gives; captured calls, cut / whole, us: 1 x 17,001 fp32 with
 // tail 7.8 / 6.4, 1 x 24,000 6.4 / 5.1, 1 x 32,767 with tail 8.8 / 8.1, 1 x 60,000 in buckets of 16,512 6.5 / 4.5, 4 x 300,000 in
-// buckets of 32,640 8.1 / 5.8; bf16 7.5 / 5.8, 6.3 / 4.6, 8.3 / 7.8, 6.3 / 4.2, 7.9 / 5.4.  Read through the caches at any size: it has no
-// full trips below 16384 elements (fp32) and hardly any above.
-template <int DTYPE, bool TAIL>
+// buckets of 32,640 8.1 / 5.8; bf16 7.5 / 5.8, 6.3 / 4.6, 8.3 / 7.8, 6.3 / 4.2, 7.9 / 5.4.  Read through the caches at any size.
+// A bucket is a few tiles, so what counts is how many workgroups a compute unit holds, and the buffers of long trips cost
+// registers: fp32 with tail takes 176 in trips of four (one workgroup), 103 of two (two), 69 of one (three); see bucket_trip.
+template <int DTYPE, bool TAIL, int TRIP>
 __global__ __launch_bounds__(kStatsBlock) void tq_stats_partial_kernel(
     const PtrTable g_tab, uint64_t d, uint64_t bucket_elems, float g_min, const MutPtrTable stats_tab)
 {
@@ -454,7 +455,7 @@ __global__ __launch_bounds__(kStatsBlock) void tq_stats_partial_kernel(
     const uint64_t hi = lo + bucket_elems < d ? lo + bucket_elems : d;
     __shared__ StatsLds L;
     tq_stats_t* S = static_cast<tq_stats_t*>(stats_tab.p[blockIdx.y]) + bucket;      // blockIdx.y = tensor of the batch
-    const StatsExtra x = stats_slice<DTYPE, TAIL, false, DTYPE == TQ_F32 ? 4 : 2>(g_tab.p[blockIdx.y], lo, hi, 0, g_min, L, S->hist);
+    const StatsExtra x = stats_slice<DTYPE, TAIL, false, TRIP>(g_tab.p[blockIdx.y], lo, hi, 0, g_min, L, S->hist);
     if (threadIdx.x == 0) write_scalars(S, x, hi - lo, g_min);
 }
 
@@ -764,6 +765,17 @@ bool uses_shares(uint64_t d, uint64_t bucket_elems)
     return be >= tq::kBalancedMinBucket;
 }
 
+// Tiles of a trip where a workgroup takes a bucket.  Trips of four (bf16 two) / two / one, us: fp32 with tail 2 x 124 M in
+// buckets of 4096 945 / 479 / 355, 8192 513 / 275 / 233, 16384 316 / 195 / 198, 20480 300 / 183 / 196, 32640 255 / 182 / 186, 1 x 16384
+// 5.9 / 5.3 / 5.6, 1 x 1.2 M in 4096 8.9 / 5.9 / 5.7; without 4096 347 / 255 / 217, 8192 211 / 195 / 201, 12288 183 / 192 / 194, 16384
+// 183 / 199 / 192, 1 x 1.2 M in 4096 4.4 / 4.2 / 4.3; bf16 with tail 4096 432 / - / 306, 16384 156 / - / 125, 32640 121 / - / 107,
+// 1 x 1.2 M in 4096 6.0 / - / 5.8; without 4096 195 / - / 187, 16384 99.8 / - / 102.6.
+int bucket_trip(int dtype, bool tail, uint64_t be)
+{
+    if (dtype == TQ_BF16) return tail ? 1 : 2;
+    return tail ? (be <= 16384 ? 1 : 2) : (be <= 8192 ? 1 : 4);
+}
+
 // Whether a batch in equal shares is read past the caches, and the tiles at the end of every share that are read through them
 // all the same.  A piece's first full trip, the last one where their number is even, and what is left after them are always
 // read through them: of a bucket of 32768 fp32 elements everything, of 65536 two trips of four.  Smaller buckets always are.
@@ -890,12 +902,14 @@ hipError_t tq_launch_stats(const void* const* g, int count, int dtype, uint64_t 
     tq::PtrTable gt{};
     tq::MutPtrTable stt{};
     for (int i = 0; i < count; ++i) { gt.p[i] = g[i]; stt.p[i] = stats[i]; }
-#define TQ_LAUNCH_PARTIAL(DT, TL) \
-    hipLaunchKernelGGL((tq::tq_stats_partial_kernel<DT, TL>), pgrid, dim3(tq::kStatsBlock), 0, st, gt, d, be, g_min, stt)
+    const int trip = bucket_trip(dtype, g_min > 0.0f, be);
+#define TQ_LAUNCH_PARTIAL(DT, TL, TR) \
+    hipLaunchKernelGGL((tq::tq_stats_partial_kernel<DT, TL, TR>), pgrid, dim3(tq::kStatsBlock), 0, st, gt, d, be, g_min, stt)
     if (dtype == TQ_F32) {
-        if (g_min > 0.0f) TQ_LAUNCH_PARTIAL(TQ_F32, true); else TQ_LAUNCH_PARTIAL(TQ_F32, false);
+        if (g_min > 0.0f) { if (trip == 1) TQ_LAUNCH_PARTIAL(TQ_F32, true, 1); else TQ_LAUNCH_PARTIAL(TQ_F32, true, 2); }
+        else { if (trip == 1) TQ_LAUNCH_PARTIAL(TQ_F32, false, 1); else TQ_LAUNCH_PARTIAL(TQ_F32, false, 4); }
     } else {
-        if (g_min > 0.0f) TQ_LAUNCH_PARTIAL(TQ_BF16, true); else TQ_LAUNCH_PARTIAL(TQ_BF16, false);
+        if (g_min > 0.0f) TQ_LAUNCH_PARTIAL(TQ_BF16, true, 1); else TQ_LAUNCH_PARTIAL(TQ_BF16, false, 2);
     }
 #undef TQ_LAUNCH_PARTIAL
     return hipGetLastError();

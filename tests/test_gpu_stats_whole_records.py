@@ -28,3 +28,12 @@ def test_statistics(d, bucket, count, g_min, dtype):
             assert (got[f] == want[f]).all(), (i, f)
         # one fp32 logarithm per 8 elements and 2^-28 fixed point: 1e-6 of the sum, as everywhere
         np.testing.assert_allclose(got["sum_log_tail"], want["sum_log_tail"], rtol=1e-6, atol=4e-7)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("g_min", [0.0, 1e-5])
+@pytest.mark.parametrize("d,bucket", [(100_003, 128), (100_003, 4_096), (50_001, 4_224), (8_192 * 3, 8_192), (50_005, 8_320),
+                                      (16_384 * 3 - 1, 16_384), (70_000, 16_512), (100_000, 24_576), (8_192, 0), (8_193, 0), (16_384, 0)])
+def test_small_buckets(d, bucket, g_min, dtype):
+    """Both sides of the bucket sizes where the trips' length changes (bucket_trip), whole and ragged."""
+    test_statistics(d, bucket, 2, g_min, dtype)

@@ -279,6 +279,23 @@ def _params_batch(stats, params, nb):
     return _ptr_array(stats, "stats"), _ptr_array(params, "params")
 
 
+def _compress_batch(gs, params, payloads, d, dtype, qbytes, pbytes, of):
+    m, n = _tq_marshal, len(gs)
+    if m is not None:
+        gp, qp = m.pointers(gs, n, d, d, dtype), m.pointers(params, n, qbytes, qbytes, None)
+        pp = m.pointers(payloads, n, pbytes, _ANY_SIZE, None)
+        if gp is not None and qp is not None and pp is not None:
+            return gp, qp, pp
+    _one_each(n, params, "params")
+    _one_each(n, payloads, "payload")
+    for g, q, p in zip(gs, params, payloads):
+        if g.numel() != d or g.dtype != dtype:
+            raise ValueError("batched tensors must share shape and dtype")
+        if q.numel() != qbytes or p.numel() < pbytes:
+            raise ValueError("params / payload buffer size does not match " + of)
+    return _ptr_array(gs, "g"), _ptr_array(params, "params"), _ptr_array(payloads, "payload")
+
+
 def tq_stats_multi(gs, stats, workspace, bucket_elems=0, g_min=0.0):
     """Batched tq_stats: lists of same-shaped gradients and their stats buffers."""
     g = gs[0]
@@ -299,19 +316,9 @@ def tq_params_multi(stats, params, bits, grid, alpha_override=0.0):
 
 def tq_compress_multi(gs, params, payloads, bits, seed, first_worker, step, bucket_elems=0, grid=GRID_UNIFORM):
     d, dtype = gs[0].numel(), gs[0].dtype
-    qsize, psize = num_buckets(d, bucket_elems) * PARAMS_BYTES, payload_bytes(d, bits)
-    if not (_sized(gs, len(gs), d, d, dtype) and _sized(params, len(gs), qsize, qsize)
-            and _sized(payloads, len(gs), psize, _ANY_SIZE)):
-        _one_each(len(gs), params, "params")
-        _one_each(len(gs), payloads, "payload")
-        for g, q, p in zip(gs, params, payloads):
-            if g.numel() != d or g.dtype != dtype:
-                raise ValueError("batched tensors must share shape and dtype")
-            if q.numel() != qsize or p.numel() < psize:
-                raise ValueError("params / payload buffer size does not match d")
-    _check(lib().tq_compress_multi(_ptr_array(gs, "g"), len(gs), _dtype_code(gs[0]), d, bucket_elems,
-                                   _ptr_array(params, "params"), bits, grid, seed, first_worker, step,
-                                   _ptr_array(payloads, "payload"), _stream()), "tq_compress_multi")
+    gp, qp, pp = _compress_batch(gs, params, payloads, d, dtype, num_buckets(d, bucket_elems) * PARAMS_BYTES, payload_bytes(d, bits), "d")
+    _check(lib().tq_compress_multi(gp, len(gs), _dtype_code(gs[0]), d, bucket_elems, qp, bits, grid, seed, first_worker, step,
+                                   pp, _stream()), "tq_compress_multi")
     return payloads
 
 
@@ -410,20 +417,10 @@ def tq_stats_segments_multi(gs, seg, stats, workspace, g_min=0.0):
 
 def tq_compress_segments_multi(gs, seg, params, payloads, bits, seed, first_worker, step):
     d, dtype = gs[0].numel(), gs[0].dtype
-    qsize, psize = seg.nseg * PARAMS_BYTES, payload_bytes(d, bits)
-    if not (_sized(gs, len(gs), d, d, dtype) and _sized(params, len(gs), qsize, qsize)
-            and _sized(payloads, len(gs), psize, _ANY_SIZE)):
-        _one_each(len(gs), params, "params")
-        _one_each(len(gs), payloads, "payload")
-        for g, q, p in zip(gs, params, payloads):
-            if g.numel() != d or g.dtype != dtype:
-                raise ValueError("batched tensors must share shape and dtype")
-            if q.numel() != qsize or p.numel() < psize:
-                raise ValueError("params / payload buffer size does not match the segments")
+    gp, qp, pp = _compress_batch(gs, params, payloads, d, dtype, seg.nseg * PARAMS_BYTES, payload_bytes(d, bits), "the segments")
     dev, host, nseg = seg.args()
-    _check(lib().tq_compress_segments_multi(_ptr_array(gs, "g"), len(gs), _dtype_code(gs[0]), d, dev, host, nseg,
-                                            _ptr_array(params, "params"), bits, seed, first_worker, step,
-                                            _ptr_array(payloads, "payload"), _stream()), "tq_compress_segments_multi")
+    _check(lib().tq_compress_segments_multi(gp, len(gs), _dtype_code(gs[0]), d, dev, host, nseg, qp, bits, seed, first_worker,
+                                            step, pp, _stream()), "tq_compress_segments_multi")
     return payloads
 
 

@@ -161,6 +161,13 @@ def alloc_payload(d, bits, device="cuda"):
     return torch.empty(payload_bytes(d, bits), dtype=torch.uint8, device=device)
 
 
+def _records(d, bucket_elems):
+    """num_buckets; a call into the library (0.4 us) only for what it refuses later."""
+    if bucket_elems == 0 and d:
+        return 1
+    return -(-d // bucket_elems) if bucket_elems > 0 else num_buckets(d, bucket_elems)
+
+
 def _stats_bytes(d, bucket_elems):
     """Bytes of the records tq_stats writes, without a call into the library."""
     return -(-d // bucket_elems) * STATS_BYTES if bucket_elems > 0 else STATS_BYTES if d else 0
@@ -202,7 +209,7 @@ def tq_params(stats, params, bits, grid, alpha_override=0.0):
 def tq_compress(g, params, payload, bits, seed, worker, step, bucket_elems=0, grid=GRID_UNIFORM):
     """``grid``: the family ``params`` was designed with; it only shapes the launch (see tq.h)."""
     d = g.numel()
-    if params.numel() != num_buckets(d, bucket_elems) * PARAMS_BYTES:
+    if params.numel() != _records(d, bucket_elems) * PARAMS_BYTES:
         raise ValueError("params buffer does not match the number of buckets")
     if payload.numel() < payload_bytes(d, bits):
         raise ValueError("payload buffer too small")
@@ -214,7 +221,7 @@ def tq_compress(g, params, payload, bits, seed, worker, step, bucket_elems=0, gr
 
 def tq_quantize_dequantize(g, params, out, bits, seed, worker, step, bucket_elems=0, accumulate=False):
     d = g.numel()
-    if params.numel() != num_buckets(d, bucket_elems) * PARAMS_BYTES:
+    if params.numel() != _records(d, bucket_elems) * PARAMS_BYTES:
         raise ValueError("params buffer does not match the number of buckets")
     if out.dtype != torch.float32 or out.numel() != d:
         raise ValueError("out must be float32 of the gradient's size")
@@ -316,7 +323,7 @@ def tq_params_multi(stats, params, bits, grid, alpha_override=0.0):
 
 def tq_compress_multi(gs, params, payloads, bits, seed, first_worker, step, bucket_elems=0, grid=GRID_UNIFORM):
     d, dtype = gs[0].numel(), gs[0].dtype
-    gp, qp, pp = _compress_batch(gs, params, payloads, d, dtype, num_buckets(d, bucket_elems) * PARAMS_BYTES, payload_bytes(d, bits), "d")
+    gp, qp, pp = _compress_batch(gs, params, payloads, d, dtype, _records(d, bucket_elems) * PARAMS_BYTES, payload_bytes(d, bits), "d")
     _check(lib().tq_compress_multi(gp, len(gs), _dtype_code(gs[0]), d, bucket_elems, qp, bits, grid, seed, first_worker, step,
                                    pp, _stream()), "tq_compress_multi")
     return payloads
@@ -326,7 +333,7 @@ def _decode_args(payloads, params, d, bits, bucket_elems, weights):
     N = len(payloads)
     if len(params) != N:
         raise ValueError("one params buffer per payload")
-    psize, qsize = payload_bytes(d, bits), num_buckets(d, bucket_elems) * PARAMS_BYTES
+    psize, qsize = payload_bytes(d, bits), _records(d, bucket_elems) * PARAMS_BYTES
     if not (_sized(payloads, N, psize, _ANY_SIZE) and _sized(params, N, qsize, qsize)):
         for p, q in zip(payloads, params):
             if p.numel() < psize or q.numel() != qsize:

@@ -130,6 +130,12 @@ assert B.stats_workspace_bytes(1000, 2**64 - 1024) > 0
     assert run.returncode == 0, (run.returncode, run.stderr)
 
 
+def test_records_are_the_librarys_buckets():
+    for d in (0, 1, 127, 128, 129, 61_706, (1 << 40) - 1, 1 << 40):
+        for bucket in (0, 1, 128, 16_384, 61_706, 1 << 20, 1 << 40, -1, -128):
+            assert B._records(d, bucket) == B.num_buckets(d, bucket), (d, bucket)
+
+
 @pytest.mark.parametrize("d,bucket,rows", [
     (1, 0, 1), (16_385, 0, 2), (32_767, 0, 2), (32_768, 0, 1025), (61_706, 0, 1025), (128 * 4096, 128, 4096), (20_000, 1 << 20, 64),
     (100_000, 16_384, 7), (100_000, 32_640, 8), (11_200_000, 16_512, 679), (124_000_000, 1 << 20, 1024 + 119)])

@@ -872,10 +872,12 @@ namespace {
 // Then a lane reads its own 32 bytes past the caches and the payload is stored through them, else fp32 lines are read whole
 // (load_groups_wave) and the payload goes past them (store_codes_wave).  Beside that: ranges that are cut and the one-tile
 // segments kernel read a lane's own 32 bytes through the caches at any size; see reads_through too.
-// Level tables at b = 4, fp32, are the one kind whose launch by itself is slower with whole lines, for the exchange's instructions:
-// a lane's own 32 bytes through the caches / whole lines, us: 140 M 113 / 121 (the client's three calls 312 / 315), 8 x 37.5 M
-// 238 / 249 (one step 502 / 492), 8 x 62 M 390 / 402 (768 / 759), 2 x 310 M 494 / 502 (1117 / 1083), 16 x 62 M 793 / 812
-// (1508 / 1516), in layers 8 x 124 M 799 / 797 (1559 / 1531): the steps around it gain more often than they lose.
+// fp32, a lane's own 32 bytes through the caches / whole lines, launches by themselves, us: uniform, one record 8 x 124 M at
+// b = 2 699 / 670, at b = 4 743 / 695, buckets of 4096 2 x 400 M 550 / 524, but of 2^20 8 x 124 M 634 / 660 and 677 / 692, 900 M
+// 574 / 600 (behind the statistics one step of 8 x 124 M at b = 2 1356 / 1338).  Level tables at b = 4 are slower with whole lines,
+// for the exchange's instructions: 140 M 113 / 121 (the client's three calls 312 / 315), 8 x 37.5 M 238 / 249 (one step
+// 502 / 492), 8 x 62 M 390 / 402 (768 / 759), 2 x 310 M 494 / 502 (1117 / 1083), 16 x 62 M 793 / 812 (1508 / 1516), in layers
+// 8 x 124 M 799 / 797 (1559 / 1531).  The steps around the slower launches gain more often than they lose.
 bool compress_cached(int count, uint64_t d, int dtype)
 {
     return (uint64_t)count * d * (dtype == TQ_F32 ? 4u : 2u) <= (512ull << 20);

@@ -440,7 +440,7 @@ __device__ __forceinline__ StatsExtra stats_slice(const void* __restrict__ g, ui
 }
 
 // Buckets of fewer than 32768 elements: a workgroup takes one and writes its record.  Cut in two, a handful of them
-// needed the second kernel, which costs more than the wider read gives; captured calls, cut / whole, us: 1 x 17,001 fp32 with
+// needed the second kernel, which costs more than the wider read gives; captured calls in trips of four, cut / whole, us: 1 x 17,001 fp32 with
 // tail 7.8 / 6.4, 1 x 24,000 6.4 / 5.1, 1 x 32,767 with tail 8.8 / 8.1, 1 x 60,000 in buckets of 16,512 6.5 / 4.5, 4 x 300,000 in
 // buckets of 32,640 8.1 / 5.8; bf16 7.5 / 5.8, 6.3 / 4.6, 8.3 / 7.8, 6.3 / 4.2, 7.9 / 5.4.  Read through the caches at any size.
 // A bucket is a few tiles, so what counts is how many workgroups a compute unit holds, and the buffers of long trips cost

@@ -180,7 +180,7 @@ def _holds(buf, nbytes, what):
 
 def tq_stats(g, stats, workspace, bucket_elems=0, g_min=0.0):
     d = g.numel()
-    if bucket_elems or stats.numel() < STATS_BYTES:        # one record: a look at the size is enough
+    if stats.numel() < (_stats_bytes(d, bucket_elems) if bucket_elems else STATS_BYTES):
         _holds(stats, _stats_bytes(d, bucket_elems), "stats")
     _check(lib().tq_stats(_dev(g, "g"), _dtype_code(g), d, bucket_elems, g_min,
                           _dev(stats, "stats"), _dev(workspace, "workspace"), workspace.numel(),
@@ -190,7 +190,7 @@ def tq_stats(g, stats, workspace, bucket_elems=0, g_min=0.0):
 
 def tq_stats_static(g, stats, bucket_elems=0, g_min=0.0):
     d = g.numel()
-    if bucket_elems or stats.numel() < STATS_BYTES:        # one record: a look at the size is enough
+    if stats.numel() < (_stats_bytes(d, bucket_elems) if bucket_elems else STATS_BYTES):
         _holds(stats, _stats_bytes(d, bucket_elems), "stats")
     _check(lib().tq_stats_static(_dev(g, "g"), _dtype_code(g), d, bucket_elems, g_min,
                                  _dev(stats, "stats"), _stream()), "tq_stats_static")

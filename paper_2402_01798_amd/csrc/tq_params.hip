@@ -29,15 +29,20 @@
 //     then polished by fp64 Newton steps on the logarithmic residual.  When the map does not
 //     contract safely (see kCertifiedSlope), the plain fp64 iteration of the definition runs,
 //     because there the result is where that iteration stops, not a fixed point;
+//   - BiScaled's search, taken a dozen times a record, looks at the 128 edges below the threshold, a lane each, and
+//     at more only if one of those could win;
 //   - a lane per level for the codebook and its reciprocal widths;
 //   - one kernel per codebook family: what a family does not need costs it no LDS and no
 //     instruction fetch.
 // Measured on MI355X, us for one launch, against all-fp64 iteration on lane 0 of one kernel for
 // all families: uniform, 4 records 11.2 -> 4.7, 952 records 30.3 -> 7.2; non-uniform, 1 record
 // 18.7 -> 7.7, 768 records 34.3 -> 10.4, 2736 records 78 -> 25.3; BiScaled, 391 records 128 -> 19.3.
-// Records whose iteration does not converge pay for both ways: BiScaled, 391 records with one such among them 234.
+// The search of BiScaled by one wavefront over the edges that can win instead of four over all of them, with their barriers:
+// 1 record 15.9 -> 13.6, 391 19.0 -> 16.6, 952 25.6 -> 17.4, 2736 168 -> 122.
 // 512 or 1024 threads per record instead of 256 gain 0.4 us on a single non-uniform record and lose
 // 6 and 18 us on 2736 of them.
+#include <type_traits>
+
 #include "tq_device.h"
 
 namespace tq {
@@ -161,7 +166,7 @@ template <> struct BinCounts<true> {
     __device__ __forceinline__ Bin at(int i) const { const double b = cum[i]; return {cum[i + 1] - b, b}; }
 };
 
-template <bool ROOTS, bool WIDE>
+template <bool ROOTS, bool WIDE, bool SEARCH>
 struct ParamsLds {
     BinCounts<WIDE> bins;
     double H[ROOTS ? kNB + 1 : 1];         // H[i] = int_0^{lo_i} p^(1/3), times (2n)^(1/3)
@@ -170,9 +175,7 @@ struct ParamsLds {
     double wave_tail[kParamsWaves];
     double tail_edge_log;                  // ln(1 + m/16) of the tail's first bin
     int tail_bin;
-    float search_q[2][kParamsWaves], search_slope[2][kParamsWaves];   // BiScaled search in fp32, double-buffered; in fp64
-    double best_q[kParamsWaves];
-    int best_j[kParamsWaves];
+    float in13[SEARCH ? kNB : 1];          // BiScaled: (mass below bin i * lo_i^2)^(1/3), in fp32
 };
 
 template <int CTRL, int ROWS>
@@ -217,9 +220,9 @@ __device__ __forceinline__ T bin_scan(T (&v)[kBinsPerLane], T* chunk)
 }
 
 // The density's integrals up to x, in fp64.
-template <bool ROOTS, bool WIDE>
+template <typename Lds>
 struct DensityView {
-    const ParamsLds<ROOTS, WIDE>& L;
+    const Lds& L;
     double inv_n, absmax;
     // part of bin j below x, as a fraction of the bin; rw = 1 / its width
     __device__ __forceinline__ void covered(int j, double x, double& frac, double& rw) const
@@ -295,7 +298,7 @@ __device__ __forceinline__ bool certified_slope(float r) { return fabsf(r) <= kC
 
 // One record.  WIDE: its counts may add up to more than 32 bits hold.
 template <int GRID, bool WIDE>
-__device__ __forceinline__ void design(ParamsLds<GRID != TQ_GRID_UNIFORM, WIDE>& L, const tq_stats_t* __restrict__ S, int bits,
+__device__ __forceinline__ void design(ParamsLds<GRID != TQ_GRID_UNIFORM, WIDE, GRID == TQ_GRID_BISCALED>& L, const tq_stats_t* __restrict__ S, int bits,
                                        float alpha_override, tq_params_t* __restrict__ P)
 {
     constexpr bool kRoots = GRID != TQ_GRID_UNIFORM;       // the integral of p^(1/3) is needed
@@ -366,6 +369,7 @@ __device__ __forceinline__ void design(ParamsLds<GRID != TQ_GRID_UNIFORM, WIDE>&
     else if (tail_bin >= kNB) { g_min = 0.0; }
     else g_min = bin_lo(tail_bin);                         // 0 when the quantile sits in bin 0
     const bool binned_tail = !fixed_gmin && g_min > 0.0;
+    const double inv_n = n > 0.0 ? recip(n) : 0.0;
 
     // density^(1/3) (times (2n)^(1/3), which cancels or is put back where it is used), its integral up
     // to each bin, and the binned log-sum of the tail
@@ -406,6 +410,10 @@ __device__ __forceinline__ void design(ParamsLds<GRID != TQ_GRID_UNIFORM, WIDE>&
                 }
             }
             L.H[i] = c;
+            if constexpr (kBiscaled) {
+                const float inside = (float)L.bins.at(i).below * (float)inv_n;
+                L.in13[i] = inside > 0.0f ? exp2_hw((log2_hw(inside) + 2.0f * log2_hw((float)bin_lo(i))) * (1.0f / 3.0f)) : 0.0f;
+            }
         }
 #pragma unroll
         for (int k = 0; k < kBinsPerLane; ++k) pw[k] = kParamsBlock * k + tid < kNB ? L.H[kParamsBlock * k + tid] : 0.0;
@@ -422,39 +430,43 @@ __device__ __forceinline__ void design(ParamsLds<GRID != TQ_GRID_UNIFORM, WIDE>&
 #pragma unroll
         for (int w = 0; w < kParamsWaves; ++w) sum_log_binned += L.wave_tail[w];
     }
-    // one wavefront goes on, every lane with the same scalars; BiScaled: all of them, in lockstep
-    if (!kBiscaled && wave != 0) return;
+    if (wave != 0) return;                                 // one wavefront goes on, every lane with the same scalars
 
-    const double inv_n = n > 0.0 ? recip(n) : 0.0;
-    const DensityView<kRoots, WIDE> D{L, inv_n, absmax};
+    const DensityView<ParamsLds<kRoots, WIDE, kBiscaled>> D{L, inv_n, absmax};
 
-    // BiScaled search, collective: the edge lo_j < a (j = 0: beta = 0) that minimises Q_B(a, lo_j / a) =
+    // BiScaled search: the edge lo_j < a (j = 0: beta = 0) that minimises Q_B(a, lo_j / a) =
     // v^3, v = ((mass outside beta) (1 - k)^2)^(1/3) + ((mass inside) k^2)^(1/3), the smallest such edge on a tie.
-    // Each lane keeps, for its bins, what does not depend on a.
-    auto below_edge = [&](int k) {                         // the count below the lane's k-th edge
-        if constexpr (WIDE) return L.bins.cum[kParamsBlock * k + tid < kNB ? kParamsBlock * k + tid : kNB];
-        else return cum[k];
+    // One wavefront, a lane per edge, windows of 64 edges (four octaves) from a's bin downwards.  The first summand grows
+    // towards smaller edges: the search ends where it alone is above the best v, nearly always within the two windows
+    // that are looked at at once.
+    constexpr int kAtOnce = 2;
+    struct Edge { float v, s1, mass, rest, lo, in; };
+    struct Threshold { float a, inv_a16, inv_a23, part; int bin; decltype(L.bins.at(0).below) below; };
+    auto edge_of = [&](int window, const Threshold& A) {
+        const int i = A.bin - 64 * window - lane, j = i > 0 ? i : 0;
+        Edge e;
+        e.lo = i > 0 ? __uint_as_float((uint32_t)(i + 1391) << 19) : (i == 0 ? 0.0f : __builtin_inff());
+        // mass between the edge and a, from an exact difference of counts; 1 - k of the formula
+        e.mass = ((float)(A.below - L.bins.at(j).below) + A.part) * (float)inv_n;
+        e.rest = (0.0625f * (A.a - e.lo)) * A.inv_a16;
+        e.in = L.in13[kBiscaled ? j : 0] * A.inv_a23;
+        e.s1 = exp2_hw(log2_hw(e.mass * (e.rest * e.rest)) * (1.0f / 3.0f));
+        e.v = e.lo < A.a ? e.s1 + e.in : __builtin_inff();
+        return e;
     };
-    float lo_f[kBinsPerLane], in13_f[kBinsPerLane];        // the edge, (mass below it * edge^2)^(1/3)
-    int flip = 0;
-    if constexpr (kBiscaled) {
-#pragma unroll
-        for (int k = 0; k < kBinsPerLane; ++k) {
-            const int i = kParamsBlock * k + tid;
-            lo_f[k] = i < kNB ? (float)bin_lo(i) : __builtin_inff();
-            in13_f[k] = below_edge(k) > 0 && i < kNB ? exp2_hw((log2_hw((float)below_edge(k) * (float)inv_n) + 2.0f * log2_hw(lo_f[k])) * (1.0f / 3.0f)) : 0.0f;
-        }
-    }
     // the fp32 search at threshold a: min_k v, and the elasticity of Q_B = v^3 in a with the best edge held
-    // fixed; v_f keeps the lane's candidates
-    float v_f[kBinsPerLane];
-    auto search_f = [&](float a, float& elasticity) {
+    // fixed; v_f keeps the first candidates, `windows` is how many were looked at
+    float v_f[kAtOnce];
+    int windows = 0;
+    Threshold at_a = {};
+    auto search_f = [&](float a, float& elasticity, auto inner) {
+        constexpr bool INNER = decltype(inner)::value;     // a is in bins 1 .. 896
         const uint32_t bits_a = __float_as_uint(a);
         int ja = (int)(bits_a >> 19) - 1391;
         ja = ja < 0 ? 0 : (ja > kNB - 1 ? kNB - 1 : ja);
         // fraction of a's bin below a, and d(fraction)/d(ln a) = a / (bin width)
         float frac, per_ln;
-        if (ja >= 1 && ja < kNB - 1) {
+        if (INNER || (ja >= 1 && ja < kNB - 1)) {
             frac = (float)(bits_a & 0x7FFFFu) * (1.0f / 524288.0f);
             per_ln = __uint_as_float((bits_a & 0x7FFFFFu) | 0x41800000u);
         } else {
@@ -465,82 +477,80 @@ __device__ __forceinline__ void design(ParamsLds<GRID != TQ_GRID_UNIFORM, WIDE>&
         }
         const auto bin = L.bins.at(ja);
         // 16 / a: the hardware's reciprocal has no subnormal results, which 1 / a is from 2^126 on
-        const float inv_nf = (float)inv_n, part = (float)bin.here * frac, inv_a16 = rcp_hw(0.0625f * a);
-        const float inv_a23 = exp2_hw(log2_hw(a) * (-2.0f / 3.0f));
-        float v = __builtin_inff(), b_mass = 0.0f, b_rest = 1.0f, b_lo = 0.0f, b_in = 0.0f;
+        at_a = Threshold{a, rcp_hw(0.0625f * a), exp2_hw(log2_hw(a) * (-2.0f / 3.0f)), (float)bin.here * frac,
+                         __builtin_amdgcn_readfirstlane(ja), bin.below};
+        Edge best = edge_of(0, at_a), e = best;
+        v_f[0] = best.v;
 #pragma unroll
-        for (int k = 0; k < kBinsPerLane; ++k) {
-            v_f[k] = __builtin_inff();
-            if (__builtin_amdgcn_ballot_w64(lo_f[k] < a) == 0ull) continue;
-            // mass between the edge and a, from an exact difference of counts; 1 - k of the formula
-            const float mass = ((float)(bin.below - below_edge(k)) + part) * inv_nf, rest = (0.0625f * (a - lo_f[k])) * inv_a16;
-            const float in = in13_f[k] * inv_a23;
-            const float vk = exp2_hw((log2_hw(mass) + 2.0f * log2_hw(rest)) * (1.0f / 3.0f)) + in;
-            v_f[k] = lo_f[k] < a ? vk : __builtin_inff();
-            if (v_f[k] < v) { v = v_f[k]; b_mass = mass; b_rest = rest; b_lo = lo_f[k]; b_in = in; }
+        for (int w = 1; w < kAtOnce; ++w) {
+            e = edge_of(w, at_a);
+            v_f[w] = e.v;
+            if (e.v <= best.v) best = e;
         }
-        const float m = wave_min(v);
-        const unsigned long long at = __builtin_amdgcn_ballot_w64(v == m);
+        float m = wave_min(best.v);
+        windows = kAtOnce;
+        while (at_a.bin >= 64 * windows && !(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(e.s1), 63)) > m * 1.0002f)) {
+            e = edge_of(windows++, at_a);
+            if (e.v <= best.v) best = e;
+            m = wave_min(best.v);
+        }
         // v = s1 + s2: d ln(s1) = dmass / (3 mass) + 2/3 k / (1 - k), d ln(s2) = -2/3
-        const float s1 = v - b_in;
-        const float d1 = b_mass > 0.0f ? (float)bin.here * per_ln * inv_nf * rcp_hw(b_mass) + 0.125f * b_lo * inv_a16 * rcp_hw(b_rest) : 0.0f;
-        const float slope = (s1 * d1 - 2.0f * b_in) * rcp_hw(v);
-        if (lane == (at ? __builtin_ctzll(at) : 0)) { L.search_q[flip][wave] = m; L.search_slope[flip][wave] = slope; }
-        __syncthreads();
-        float q = L.search_q[flip][0];
-        elasticity = L.search_slope[flip][0];
-#pragma unroll
-        for (int w = 1; w < kParamsWaves; ++w)
-            if (L.search_q[flip][w] < q) { q = L.search_q[flip][w]; elasticity = L.search_slope[flip][w]; }
-        flip ^= 1;                                         // the other buffer next: one barrier per search
-        return q;
+        const float d1 = best.mass > 0.0f ? (float)bin.here * per_ln * (float)inv_n * rcp_hw(best.mass) + 0.125f * best.lo * at_a.inv_a16 * rcp_hw(best.rest) : 0.0f;
+        const float slope = (best.s1 * d1 - 2.0f * best.in) * rcp_hw(best.v);
+        const unsigned long long at = __builtin_amdgcn_ballot_w64(best.v == m);
+        elasticity = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(slope), at ? __builtin_ctzll(at) : 0));
+        return m;
     };
     // the search in fp64, over the edges whose fp32 value is within 1e-4 of the fp32 minimum (its error is
-    // below 1e-5: the masses are differences of exact counts, every other term is good to a few ulp)
+    // below 1e-5: the masses are differences of exact counts, every other term is good to a few ulp).  Nearly always that
+    // is one edge, and where only the edge is asked for the search ends with it.
     int best_bin = 0;
-    auto search_d = [&](double a, double& elasticity) {
+    bool only_one = false;                                 // no other is within 1e-5: it is the best edge at a rounded to fp32, too
+    auto search_d = [&](double a, double& elasticity, bool edge_only = false) {
         float el;
-        const float bound = search_f((float)a, el) * 1.0001f;
+        const float a_f = (float)a, bound = search_f(a_f, el, std::false_type{}) * 1.0001f;
+        auto close_ones = [&](int window, float v32) {     // an edge between a and a rounded to fp32 counts as close
+            const int i = at_a.bin - 64 * window - lane;
+            const double lo = i >= 0 ? bin_lo(i) : __builtin_inf();
+            return (unsigned long long)__builtin_amdgcn_ballot_w64(lo < a && (v32 <= bound || !(lo < (double)a_f)));
+        };
+        if (edge_only && windows == kAtOnce) {
+            const unsigned long long c0 = close_ones(0, v_f[0]), c1 = close_ones(1, v_f[1]);
+            only_one = __builtin_popcountll(c0) + __builtin_popcountll(c1) == 1;
+            if (only_one) {
+                best_bin = at_a.bin - (c0 ? __builtin_ctzll(c0) : 64 + __builtin_ctzll(c1));
+                return 0.0;
+            }
+        }
         const int ja = bin_of(a);
         double frac, rw;
         D.covered(ja, a, frac, rw);
         const auto bin = L.bins.at(ja);
         const double part = (double)bin.here * frac, inv_a = recip(a);
-        double q = 1.0e300;
-        int jbest = kNB;
+        double q = 1.0e300, second = 1.0e300;
+        int jbest = 0;
 #pragma unroll 1
-        for (int k = 0; k < kBinsPerLane; ++k) {
-            float v32 = v_f[0];
-            double lo = (double)lo_f[0];
-            auto below = below_edge(0);
-#pragma unroll
-            for (int m = 1; m < kBinsPerLane; ++m)
-                if (m == k) { v32 = v_f[m]; lo = (double)lo_f[m]; below = below_edge(m); }
-            // an edge between a and a rounded to fp32 counts as close
-            const bool close = lo < a && (v32 <= bound || !(lo < (double)(float)a));
-            unsigned long long left = __builtin_amdgcn_ballot_w64(close);
+        for (int window = 0; window < windows; ++window) {
+            float v32 = window == 0 ? v_f[0] : v_f[1];
+            if (window >= kAtOnce) v32 = edge_of(window, at_a).v;
+            unsigned long long left = close_ones(window, v32);
             if (left == 0ull) continue;
+            const int i = at_a.bin - 64 * window - lane, j = i > 0 ? i : 0;
+            const double lo = bin_lo(j);
+            const auto below = L.bins.at(j).below;
             const double kk = lo * inv_a, rest = (a - lo) * inv_a;
             const double out_mass = ((double)(bin.below - below) + part) * inv_n, in_mass = (double)below * inv_n;
             const double v = cube_root(out_mass * rest * rest) + cube_root(in_mass * kk * kk);
-            while (left) {                                 // a few candidates, in ascending order
+            while (left) {                                 // a few candidates, in descending order
                 const int l = __builtin_ctzll(left);
                 left &= left - 1;
                 const double vl = lane_value(v, l);
-                if (vl < q) { q = vl; jbest = kParamsBlock * k + 64 * wave + l; }
+                second = vl <= q ? q : (vl < second ? vl : second);
+                if (vl <= q) { q = vl; jbest = at_a.bin - 64 * window - l; }
             }
         }
-        if (lane == 0) { L.best_q[wave] = q; L.best_j[wave] = jbest; }   // read before search_f's barrier last time
-        __syncthreads();
-        q = L.best_q[0];
-        jbest = L.best_j[0];
-#pragma unroll
-        for (int w = 1; w < kParamsWaves; ++w) {
-            const double oq = L.best_q[w];
-            const int oj = L.best_j[w];
-            if (oq < q || (oq == q && oj < jbest)) { q = oq; jbest = oj; }
-        }
         best_bin = jbest;
+        only_one = second > q * 1.00001;
         // the elasticity of the edge that won here: near a tie the fp32 search may have taken another one's
         const double lo = bin_lo(jbest), rest = (a - lo) * inv_a;
         const double below = (double)L.bins.at(jbest).below, mass = ((double)bin.below - below + part) * inv_n;
@@ -569,7 +579,7 @@ __device__ __forceinline__ void design(ParamsLds<GRID != TQ_GRID_UNIFORM, WIDE>&
             elasticity = (float)bin.here * mant * rcp_hw(mass);
             return log2_hw(mass * (float)inv_n);
         } else if constexpr (kBiscaled) {
-            return 3.0f * log2_hw(search_f(a, elasticity));
+            return 3.0f * log2_hw(search_f(a, elasticity, std::true_type{}));
         } else {
             const double below = L.H[j];
             const float mine = (float)(L.H[j + 1] - below), half = (float)below + mine * frac;
@@ -661,8 +671,8 @@ __device__ __forceinline__ void design(ParamsLds<GRID != TQ_GRID_UNIFORM, WIDE>&
                     if constexpr (kBiscaled) {
                         // and where the best edge changes Q_B has a kink: it has to be the same at the end of the step
                         const int from = best_bin;
-                        have_split = converged;
-                        if (converged) (void)search_d((double)(float)an, el);
+                        if (converged) (void)search_d(an, el, true);
+                        have_split = converged && only_one;
                         converged = (converged && best_bin == from) || fabs(residual) <= kRelTol;
                     }
                     a = an;
@@ -701,8 +711,7 @@ __device__ __forceinline__ void design(ParamsLds<GRID != TQ_GRID_UNIFORM, WIDE>&
     }
     if constexpr (kBiscaled) {
         double el;
-        if (half > 0.0 && !have_split) (void)search_d(af, el);   // the split belongs to the rounded threshold
-        if (wave != 0) return;
+        if (half > 0.0 && !have_split) (void)search_d(af, el, true);   // the split belongs to the rounded threshold
     }
     const int k = lane;                                    // this lane's level, 0 .. s
     float lv = 0.0f;
@@ -772,8 +781,8 @@ __global__ __launch_bounds__(kParamsBlock) void tq_params_kernel(const PtrTable 
 {
     constexpr bool kRoots = GRID != TQ_GRID_UNIFORM;
     __shared__ union Lds {
-        ParamsLds<kRoots, false> narrow;
-        ParamsLds<kRoots, true> wide;
+        ParamsLds<kRoots, false, GRID == TQ_GRID_BISCALED> narrow;
+        ParamsLds<kRoots, true, GRID == TQ_GRID_BISCALED> wide;
         __device__ Lds() {}
     } L;
     // one workgroup per bucket, blockIdx.y = tensor of the batch

@@ -192,6 +192,21 @@ def test_the_best_split_changes_beside_the_fixed_point():
 
 
 @pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("low", [1, 200, 561, 640, 700])
+def test_best_splits_in_every_window_below_the_threshold(low, bits):
+    """The search looks at 64 edges at a time from the threshold's bin downwards: most of the mass 40, 104, 179, 540 and 739
+    bins below it, thresholds at a bin's lower edge, inside it, and where rounding to binary32 moves them across an edge."""
+    h = np.zeros(898, dtype=np.int64)
+    h[low:low + 20] = 3_000_000
+    h[700:760] = 400
+    h[0] = 5
+    st = np.concatenate([record(h, edge(760))] * 5)
+    for alpha in (edge(759), edge(741) * 1.01, float(np.nextafter(np.float32(edge(750)), np.float32(0)))):
+        got, want = design(st, bits, B.GRID_BISCALED, alpha)
+        assert_params_close(got, want)
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
 @pytest.mark.parametrize("grid", [B.GRID_NONUNIFORM, B.GRID_BISCALED])
 def test_records_whose_iteration_does_not_settle(bits, grid):
     """The records left out above: the tail estimates are the oracle's, alpha lies in its range and is a fixed point

@@ -94,8 +94,31 @@ def lib():
         for f in (L.tq_stats, L.tq_stats_static, L.tq_params, L.tq_compress, L.tq_decompress_aggregate,
                   L.tq_decompress_aggregate_update, L.tq_stats_multi, L.tq_params_multi, L.tq_compress_multi):
             f.restype = i32
+        for name in _NATIVE:
+            f = getattr(L, name)
+            f.address = C.cast(f, C.c_void_p).value
         _lib = L
     return _lib
+
+
+# Calls whose arguments are plain tensors, lists of them and plain numbers are taken whole by the host module, which looks at
+# them as the code below does; it answers None for everything else, errors among it, and the code below takes the call.
+_NATIVE = {"tq_stats": "stats", "tq_stats_multi": "stats_multi", "tq_params": "params", "tq_params_multi": "params_multi",
+           "tq_compress": "compress", "tq_compress_multi": "compress_multi", "tq_decompress_aggregate": "aggregate",
+           "tq_decompress_aggregate_update": "update", "tq_quantize_dequantize": "simulate",
+           "tq_stats_segments": "stats_segments", "tq_stats_segments_multi": "stats_segments_multi",
+           "tq_compress_segments": "compress_segments", "tq_compress_segments_multi": "compress_segments_multi",
+           "tq_decompress_aggregate_segments": "aggregate_segments"}
+
+
+def _native(name, *args):
+    """Whether the host module has made the call; a code other than OK raises."""
+    if _tq_marshal is None:
+        return False
+    rc = getattr(_tq_marshal, _NATIVE[name])(getattr(getattr(lib(), name), "address", 0), *args)
+    if rc:
+        raise TqError(rc, name)
+    return rc is not None
 
 
 def strerror(code):
@@ -179,6 +202,8 @@ def _holds(buf, nbytes, what):
 
 
 def tq_stats(g, stats, workspace, bucket_elems=0, g_min=0.0):
+    if _native("tq_stats", g, stats, workspace, bucket_elems, g_min):
+        return stats
     d = g.numel()
     if stats.numel() < (_stats_bytes(d, bucket_elems) if bucket_elems else STATS_BYTES):
         _holds(stats, _stats_bytes(d, bucket_elems), "stats")
@@ -198,6 +223,8 @@ def tq_stats_static(g, stats, bucket_elems=0, g_min=0.0):
 
 
 def tq_params(stats, params, bits, grid, alpha_override=0.0):
+    if _native("tq_params", stats, params, bits, grid, alpha_override):
+        return params
     nb = stats.numel() // STATS_BYTES
     if params.numel() != nb * PARAMS_BYTES:
         raise ValueError("params buffer does not match the number of buckets")
@@ -208,6 +235,8 @@ def tq_params(stats, params, bits, grid, alpha_override=0.0):
 
 def tq_compress(g, params, payload, bits, seed, worker, step, bucket_elems=0, grid=GRID_UNIFORM):
     """``grid``: the family ``params`` was designed with; it only shapes the launch (see tq.h)."""
+    if _native("tq_compress", g, params, payload, bits, seed, worker, step, bucket_elems, grid):
+        return payload
     d = g.numel()
     if params.numel() != _records(d, bucket_elems) * PARAMS_BYTES:
         raise ValueError("params buffer does not match the number of buckets")
@@ -220,6 +249,8 @@ def tq_compress(g, params, payload, bits, seed, worker, step, bucket_elems=0, gr
 
 
 def tq_quantize_dequantize(g, params, out, bits, seed, worker, step, bucket_elems=0, accumulate=False):
+    if _native("tq_quantize_dequantize", g, params, out, bits, seed, worker, step, bucket_elems, accumulate):
+        return out
     d = g.numel()
     if params.numel() != _records(d, bucket_elems) * PARAMS_BYTES:
         raise ValueError("params buffer does not match the number of buckets")
@@ -305,6 +336,8 @@ def _compress_batch(gs, params, payloads, d, dtype, qbytes, pbytes, of):
 
 def tq_stats_multi(gs, stats, workspace, bucket_elems=0, g_min=0.0):
     """Batched tq_stats: lists of same-shaped gradients and their stats buffers."""
+    if _native("tq_stats_multi", gs, stats, workspace, bucket_elems, g_min):
+        return stats
     g = gs[0]
     d = g.numel()
     gp, sp = _stats_batch(gs, stats, d, g.dtype, _stats_bytes(d, bucket_elems))
@@ -315,6 +348,8 @@ def tq_stats_multi(gs, stats, workspace, bucket_elems=0, g_min=0.0):
 
 
 def tq_params_multi(stats, params, bits, grid, alpha_override=0.0):
+    if _native("tq_params_multi", stats, params, bits, grid, alpha_override):
+        return params
     nb = stats[0].numel() // STATS_BYTES
     sp, qp = _params_batch(stats, params, nb)
     _check(lib().tq_params_multi(sp, len(stats), nb, bits, grid, alpha_override, qp, _stream()), "tq_params_multi")
@@ -322,6 +357,8 @@ def tq_params_multi(stats, params, bits, grid, alpha_override=0.0):
 
 
 def tq_compress_multi(gs, params, payloads, bits, seed, first_worker, step, bucket_elems=0, grid=GRID_UNIFORM):
+    if _native("tq_compress_multi", gs, params, payloads, bits, seed, first_worker, step, bucket_elems, grid):
+        return payloads
     d, dtype = gs[0].numel(), gs[0].dtype
     gp, qp, pp = _compress_batch(gs, params, payloads, d, dtype, _records(d, bucket_elems) * PARAMS_BYTES, payload_bytes(d, bits), "d")
     _check(lib().tq_compress_multi(gp, len(gs), _dtype_code(gs[0]), d, bucket_elems, qp, bits, grid, seed, first_worker, step,
@@ -349,6 +386,8 @@ def _decode_args(payloads, params, d, bits, bucket_elems, weights):
 
 def tq_decompress_aggregate(payloads, params, out, bits, bucket_elems=0, weights=None,
                             accumulate=False):
+    if _native("tq_decompress_aggregate", payloads, params, out, bits, bucket_elems, weights, accumulate):
+        return out
     d = out.numel()
     if out.dtype != torch.float32:
         raise TypeError("out must be float32")
@@ -360,6 +399,9 @@ def tq_decompress_aggregate(payloads, params, out, bits, bucket_elems=0, weights
 
 def tq_decompress_aggregate_update(payloads, params, theta, bits, eta, momentum=0.0, weight_decay=0.0,
                                    velocity=None, bucket_elems=0, weights=None):
+    if _native("tq_decompress_aggregate_update", payloads, params, theta, bits, eta, momentum, weight_decay, velocity, bucket_elems,
+               weights):
+        return theta
     d = theta.numel()
     if theta.dtype != torch.float32 or (velocity is not None and velocity.dtype != torch.float32):
         raise TypeError("theta and velocity must be float32")
@@ -392,6 +434,8 @@ def stats_segments_workspace_bytes(d, nseg):
 
 
 def tq_stats_segments(g, seg, stats, workspace, g_min=0.0):
+    if _native("tq_stats_segments", g, stats, workspace, g_min, *seg.args()):
+        return stats
     _holds(stats, seg.nseg * STATS_BYTES, "stats")
     dev, host, nseg = seg.args()
     _check(lib().tq_stats_segments(_dev(g, "g"), _dtype_code(g), g.numel(), dev, host, nseg, g_min,
@@ -401,6 +445,8 @@ def tq_stats_segments(g, seg, stats, workspace, g_min=0.0):
 
 
 def tq_compress_segments(g, seg, params, payload, bits, seed, worker, step):
+    if _native("tq_compress_segments", g, params, payload, bits, seed, worker, step, *seg.args()):
+        return payload
     d = g.numel()
     if params.numel() != seg.nseg * PARAMS_BYTES or payload.numel() < payload_bytes(d, bits):
         raise ValueError("params / payload buffer size does not match the segments")
@@ -413,6 +459,8 @@ def tq_compress_segments(g, seg, params, payload, bits, seed, worker, step):
 
 def tq_stats_segments_multi(gs, seg, stats, workspace, g_min=0.0):
     """Batched tq_stats_segments: same-shaped gradients that share the segment table."""
+    if _native("tq_stats_segments_multi", gs, stats, workspace, g_min, *seg.args()):
+        return stats
     g = gs[0]
     gp, sp = _stats_batch(gs, stats, g.numel(), g.dtype, seg.nseg * STATS_BYTES)
     dev, host, nseg = seg.args()
@@ -423,6 +471,8 @@ def tq_stats_segments_multi(gs, seg, stats, workspace, g_min=0.0):
 
 
 def tq_compress_segments_multi(gs, seg, params, payloads, bits, seed, first_worker, step):
+    if _native("tq_compress_segments_multi", gs, params, payloads, bits, seed, first_worker, step, *seg.args()):
+        return payloads
     d, dtype = gs[0].numel(), gs[0].dtype
     gp, qp, pp = _compress_batch(gs, params, payloads, d, dtype, seg.nseg * PARAMS_BYTES, payload_bytes(d, bits), "the segments")
     dev, host, nseg = seg.args()
@@ -432,6 +482,8 @@ def tq_compress_segments_multi(gs, seg, params, payloads, bits, seed, first_work
 
 
 def tq_decompress_aggregate_segments(payloads, params, seg, out, bits, weights=None, accumulate=False):
+    if _native("tq_decompress_aggregate_segments", payloads, params, out, bits, weights, accumulate, *seg.args()):
+        return out
     d = out.numel()
     if out.dtype != torch.float32:
         raise TypeError("out must be float32")

@@ -73,15 +73,16 @@ def build_marshal(force: bool = False, verbose: bool = False) -> str:
     from torch.utils import cpp_extension
 
     src = os.path.join(CSRC, "tq_marshal.cpp")
-    if force or _stale(MARSHAL, [src, __file__]):
+    if force or _stale(MARSHAL, [src, os.path.join(ROOT, "include", "tq.h"), __file__]):
         lib_dir = os.path.join(os.path.dirname(torch.__file__), "lib")
         tmp = MARSHAL + ".tmp.%d" % os.getpid()
         cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wno-attributes",
                "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
-               "-I", sysconfig.get_paths()["include"]]
+               "-D__HIP_PLATFORM_AMD__=1", "-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"],
+               "-isystem", "/opt/rocm/include"]
         for inc in cpp_extension.include_paths():
             cmd += ["-isystem", inc]
-        cmd += [src, "-o", tmp, "-L", lib_dir, "-ltorch_python", "-ltorch_cpu", "-lc10"]
+        cmd += [src, "-o", tmp, "-L", lib_dir, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
         if verbose:
             print(" ".join(cmd))
         subprocess.check_call(cmd)

@@ -95,3 +95,20 @@ def test_pointers_on_the_device():
     for wanted in ((1, 64, 64, None), (3, 64, 64, None), (2, 65, BIG, None), (2, 0, 63, None), (2, 64, 64, torch.bfloat16), (2, 64, 64, "f32")):
         assert M.pointers([a, b], *wanted) is None, wanted
     assert M.pointers([a, b[:7]], 2, 64, BIG, None) is None
+
+
+CALLS = {"stats": 6, "stats_multi": 6, "params": 6, "params_multi": 6, "compress": 10, "compress_multi": 10, "aggregate": 8,
+         "update": 11, "simulate": 10, "stats_segments": 8, "stats_segments_multi": 8, "compress_segments": 11,
+         "compress_segments_multi": 11, "aggregate_segments": 10}
+
+
+@pytest.mark.parametrize("name", CALLS)
+def test_whole_calls_leave_what_they_do_not_know(name):
+    """Host tensors, other objects in every place, too few or too many arguments, no entry point: None, and no exception is
+    left behind.  The address is never called: there is no device tensor here."""
+    t, call = torch.zeros(4096), getattr(M, name)
+    assert sorted(B._NATIVE.values()) == sorted(CALLS)
+    for address in (0, 1 << 40, -1, 1 << 70, None):
+        for filler in (t, [t], [], (t, t), 1, -1, 1 << 70, 0.5, True, None, "x"):
+            for count in (0, CALLS[name] - 2, CALLS[name] - 1, CALLS[name]):
+                assert call(address, *[filler] * count) is None

@@ -52,6 +52,7 @@ constexpr uint64_t kWholeTensor = 65536;
 constexpr int share_trip(int dtype, bool past) { return dtype == TQ_F32 && past ? 4 : 2; }
 constexpr int kReduceBlock = 1024;                     // threads of the reduce kernel: 64 bins x 16 slice lanes
 constexpr int kReduceBins = 64;
+constexpr uint32_t kReduceGroups = (TQ_NBINS + kReduceBins - 1) / kReduceBins + 1;   // its workgroups per bucket (16)
 constexpr int kBinBias = 1391;                         // 16 * (biased exponent of 2^-40) - 1
 
 // Per (bucket, slice).  The log-sum of the tail travels as two exact integer sums (ln(a/g_min)
@@ -460,20 +461,29 @@ __global__ __launch_bounds__(kStatsBlock) void tq_stats_partial_kernel(
 }
 
 // Adds `rows` consecutive partial rows (row0 onwards) of one bucket into its record S.  The
-// bucket's workgroups are numbered grp = 0 .. groups_per_bucket - 1: all but the last take 64
+// bucket's workgroups are numbered grp = 0 .. kReduceGroups - 1: all but the last take 64
 // bins each, the last one the scalar fields.  n = elements of the bucket.
 __device__ __forceinline__ void reduce_rows(const uint32_t* __restrict__ ws_hist, const StatsExtra* __restrict__ ws_extra,
-                                            uint64_t row0, uint32_t rows, uint32_t grp, uint32_t groups_per_bucket,
+                                            uint64_t row0, uint32_t rows, uint32_t grp,
                                             tq_stats_t* __restrict__ S, uint64_t n, float g_min, uint32_t* part)
 {
-    if (grp + 1 < groups_per_bucket) {
+    if (grp + 1 < kReduceGroups) {
         // 64 consecutive bins x 16 interleaved row lanes; a wavefront reads 256 contiguous bytes
         const uint32_t bin = grp * kReduceBins + (threadIdx.x & (kReduceBins - 1));
         const uint32_t sl = threadIdx.x / kReduceBins;
         uint32_t total = 0u;
         if (bin < TQ_NBINS) {
+            // eight rows a lane requested at once, those past the last row being that one again, not added: one round of
+            // latency for up to 128 rows (row after row: the statistics of 1.2 M bf16 elements, 75 rows, 10.2 us, this way 9.6)
             const uint32_t* col = ws_hist + row0 * TQ_NBINS + bin;
-            for (uint32_t p = sl; p < rows; p += kReduceBlock / kReduceBins) total += col[(uint64_t)p * TQ_NBINS];
+            constexpr uint32_t kLanes = kReduceBlock / kReduceBins, kAtOnce = 8;
+            for (uint32_t p = sl; p < rows; p += kAtOnce * kLanes) {
+                uint32_t v[kAtOnce];
+#pragma unroll
+                for (uint32_t i = 0; i < kAtOnce; ++i) v[i] = col[(uint64_t)(p + i * kLanes < rows ? p + i * kLanes : rows - 1u) * TQ_NBINS];
+#pragma unroll
+                for (uint32_t i = 0; i < kAtOnce; ++i) total += p + i * kLanes < rows ? v[i] : 0u;
+            }
         }
         part[threadIdx.x] = total;
         __syncthreads();
@@ -527,24 +537,25 @@ constexpr uint64_t kBalancedMinBucket = 32768;
 
 template <int DTYPE, bool TAIL, bool PAST>
 __global__ __launch_bounds__(kStatsBlock) void tq_stats_balanced_kernel(
-    const PtrTable g_tab, uint64_t d, uint64_t be, uint64_t nb, uint64_t tiles_per_tensor, uint64_t total_tiles,
+    const PtrTable g_tab, uint64_t d, const Divisor by_bucket, uint64_t nb, const Divisor by_tensor, uint64_t total_tiles, const Divisor groups,
     uint64_t kept_tiles, float g_min, uint32_t* __restrict__ ws_hist, StatsExtra* __restrict__ ws_extra, const MutPtrTable stats_tab)
 {
     const uint32_t w = blockIdx.x;
-    uint64_t tile = share_start(w, total_tiles, gridDim.x);
-    const uint64_t tile_end = share_start((uint64_t)w + 1, total_tiles, gridDim.x);
+    const uint64_t be = by_bucket.b, tiles_per_tensor = by_tensor.b;
+    uint64_t tile = share_start(w, total_tiles, groups);
+    const uint64_t tile_end = share_start((uint64_t)w + 1, total_tiles, groups);
     const uint64_t past_tile = PAST && tile_end > kept_tiles ? tile_end - kept_tiles : 0;
     __shared__ StatsLds L;
     bool first = true;
     while (tile < tile_end) {                                          // one pass per tensor the share touches
-        const uint64_t t = quotient(tile, tiles_per_tensor), i = tile - t * tiles_per_tensor;
+        const uint64_t t = quotient(tile, by_tensor), i = tile - t * tiles_per_tensor;
         const uint64_t i_end = i + (tile_end - tile) < tiles_per_tensor ? i + (tile_end - tile) : tiles_per_tensor;
         const uint64_t e0 = i * kStatsTile;
         const uint64_t e1 = i_end * kStatsTile < d ? i_end * kStatsTile : d;
         const void* __restrict__ g = g_tab.p[t];
         const uint64_t past_end = past_tile > t * tiles_per_tensor ? (past_tile - t * tiles_per_tensor) * kStatsTile : 0;
         tq_stats_t* __restrict__ stats = static_cast<tq_stats_t*>(stats_tab.p[t]);
-        for (uint64_t b = quotient(e0, be); b * be < e1; ++b) {
+        for (uint64_t b = quotient(e0, by_bucket); b * be < e1; ++b) {
             const uint64_t lo = b * be, hi = lo + be < d ? lo + be : d;
             const uint64_t cs = e0 > lo ? e0 : lo, ce = e1 < hi ? e1 : hi;
             const bool whole = cs == lo && ce == hi;                   // no other share has a piece of this bucket
@@ -562,32 +573,39 @@ __global__ __launch_bounds__(kStatsBlock) void tq_stats_balanced_kernel(
 }
 
 // Adds the rows of the buckets that more than one share has a piece of.  One unit of
-// groups_per_bucket workgroups per bucket (by_boundary = 0), or -- when there are more buckets
+// kReduceGroups workgroups (the narrow kernel: one) per bucket (by_boundary = 0), or -- when there are more buckets
 // than shares -- per boundary between two shares: the unit of boundary k takes the bucket the
 // boundary cuts, if it cuts one and if it is the first boundary inside that bucket.
 // The bucket a unit of the second kernel adds up, if any: tensor t, bucket b, its first row and
 // the number of rows.
 struct SplitBucket { uint64_t t, b, row0, n; uint32_t rows; bool any; };
 
-__device__ __forceinline__ SplitBucket split_bucket(uint64_t unit, uint32_t by_boundary, uint64_t d, uint64_t be, uint64_t nb,
-                                                    uint64_t tiles_per_tensor, uint64_t total_tiles, uint32_t groups)
+struct SplitArgs {
+    uint64_t d, n_units;
+    Divisor be, nb, tiles_per_tensor, total_tiles, groups;
+    uint32_t by_boundary;
+};
+
+__device__ __forceinline__ SplitBucket split_bucket(uint64_t unit, const SplitArgs& a)
 {
+    const uint64_t d = a.d, be = a.be.b, nb = a.nb.b, tiles_per_tensor = a.tiles_per_tensor.b;
+    const uint32_t groups = (uint32_t)a.groups.b;
     SplitBucket k{0, 0, 0, 0, 0, false};
-    if (by_boundary) {
-        const uint64_t tile = share_start(unit + 1, total_tiles, groups);
-        k.t = quotient(tile, tiles_per_tensor);
+    if (a.by_boundary) {
+        const uint64_t tile = share_start(unit + 1, a.total_tiles.b, a.groups);
+        k.t = quotient(tile, a.tiles_per_tensor);
         const uint64_t e = (tile - k.t * tiles_per_tensor) * kStatsTile;
-        k.b = quotient(e, be);
+        k.b = quotient(e, a.be);
         if (e == k.b * be) return k;                                   // the shares meet where a bucket (or tensor) begins
     } else {
-        k.t = quotient(unit, nb);
+        k.t = quotient(unit, a.nb);
         k.b = unit - k.t * nb;
     }
     const uint64_t lo = k.b * be, hi = lo + be < d ? lo + be : d;
-    const uint32_t w0 = share_of_tile(k.t * tiles_per_tensor + lo / kStatsTile, total_tiles, groups);
-    const uint32_t w1 = share_of_tile(k.t * tiles_per_tensor + (hi - 1) / kStatsTile, total_tiles, groups);
+    const uint32_t w0 = share_of_tile(k.t * tiles_per_tensor + lo / kStatsTile, a.total_tiles, groups);
+    const uint32_t w1 = share_of_tile(k.t * tiles_per_tensor + (hi - 1) / kStatsTile, a.total_tiles, groups);
     if (w0 == w1) return k;                                            // written as a finished record already
-    if (by_boundary && w0 != unit) return k;                           // added at the first boundary inside it
+    if (a.by_boundary && w0 != unit) return k;                           // added at the first boundary inside it
     k.row0 = (uint64_t)w0 + k.t * nb + k.b;
     k.rows = w1 - w0 + 1;
     k.n = hi - lo;
@@ -599,13 +617,11 @@ __device__ __forceinline__ SplitBucket split_bucket(uint64_t unit, uint32_t by_b
 constexpr int kNarrowBlock = 512;
 constexpr uint32_t kNarrowRows = 8;
 __global__ __launch_bounds__(kNarrowBlock) void tq_stats_balanced_reduce_narrow_kernel(
-    uint64_t d, uint64_t be, uint64_t nb, uint64_t tiles_per_tensor, uint64_t total_tiles, uint32_t groups,
-    uint32_t by_boundary, uint64_t n_units, float g_min,
-    const uint32_t* __restrict__ ws_hist, const StatsExtra* __restrict__ ws_extra, const MutPtrTable stats_tab)
+    const SplitArgs a, float g_min, const uint32_t* __restrict__ ws_hist, const StatsExtra* __restrict__ ws_extra, const MutPtrTable stats_tab)
 {
     const uint64_t unit = linear_block();
-    if (unit >= n_units) return;                                       // padding of a folded grid
-    const SplitBucket k = split_bucket(unit, by_boundary, d, be, nb, tiles_per_tensor, total_tiles, groups);
+    if (unit >= a.n_units) return;                                     // padding of a folded grid
+    const SplitBucket k = split_bucket(unit, a);
     if (!k.any) return;
     tq_stats_t* __restrict__ S = static_cast<tq_stats_t*>(stats_tab.p[k.t]) + k.b;
     // the rows past the bucket's last are that one again, not added: every load is on its way at once
@@ -643,18 +659,16 @@ __global__ __launch_bounds__(kNarrowBlock) void tq_stats_balanced_reduce_narrow_
 }
 
 __global__ __launch_bounds__(kReduceBlock) void tq_stats_balanced_reduce_kernel(
-    uint64_t d, uint64_t be, uint64_t nb, uint64_t tiles_per_tensor, uint64_t total_tiles, uint32_t groups,
-    uint32_t by_boundary, uint64_t n_units, uint32_t groups_per_bucket, float g_min,
-    const uint32_t* __restrict__ ws_hist, const StatsExtra* __restrict__ ws_extra, const MutPtrTable stats_tab)
+    const SplitArgs a, float g_min, const uint32_t* __restrict__ ws_hist, const StatsExtra* __restrict__ ws_extra, const MutPtrTable stats_tab)
 {
     __shared__ uint32_t part[kReduceBlock];
     const uint32_t blk = linear_block();
-    const uint64_t unit = blk / groups_per_bucket;
-    const uint32_t grp = blk - (uint32_t)unit * groups_per_bucket;
-    if (unit >= n_units) return;                                       // padding of a folded grid
-    const SplitBucket k = split_bucket(unit, by_boundary, d, be, nb, tiles_per_tensor, total_tiles, groups);
+    const uint64_t unit = blk / kReduceGroups;
+    const uint32_t grp = blk % kReduceGroups;
+    if (unit >= a.n_units) return;                                     // padding of a folded grid
+    const SplitBucket k = split_bucket(unit, a);
     if (!k.any) return;
-    reduce_rows(ws_hist, ws_extra, k.row0, k.rows, grp, groups_per_bucket,
+    reduce_rows(ws_hist, ws_extra, k.row0, k.rows, grp,
                 static_cast<tq_stats_t*>(stats_tab.p[k.t]) + k.b, k.n, g_min, part);
 }
 
@@ -672,18 +686,19 @@ __global__ __launch_bounds__(kReduceBlock) void tq_stats_balanced_reduce_kernel(
 
 template <int DTYPE, bool TAIL, bool PAST>
 __global__ __launch_bounds__(kStatsBlock) void tq_stats_segments_partial_kernel(
-    const PtrTable g_tab, uint64_t d, uint64_t tiles_per_tensor, uint64_t total_tiles,
+    const PtrTable g_tab, uint64_t d, const Divisor by_tensor, uint64_t total_tiles, const Divisor groups,
     const uint64_t* __restrict__ seg_off, uint32_t nseg, uint64_t kept_tiles, float g_min,
     uint32_t* __restrict__ ws_hist, StatsExtra* __restrict__ ws_extra)
 {
     const uint32_t w = blockIdx.x;
-    uint64_t tile = share_start(w, total_tiles, gridDim.x);
-    const uint64_t tile_end = share_start((uint64_t)w + 1, total_tiles, gridDim.x);
+    const uint64_t tiles_per_tensor = by_tensor.b;
+    uint64_t tile = share_start(w, total_tiles, groups);
+    const uint64_t tile_end = share_start((uint64_t)w + 1, total_tiles, groups);
     const uint64_t past_tile = PAST && tile_end > kept_tiles ? tile_end - kept_tiles : 0;
     __shared__ StatsLds L;
     bool first = true;
     while (tile < tile_end) {                                          // one pass per tensor the share touches
-        const uint64_t t = quotient(tile, tiles_per_tensor), i = tile - t * tiles_per_tensor;
+        const uint64_t t = quotient(tile, by_tensor), i = tile - t * tiles_per_tensor;
         const uint64_t i_end = i + (tile_end - tile) < tiles_per_tensor ? i + (tile_end - tile) : tiles_per_tensor;
         const uint64_t cstart = i * kStatsTile;
         const uint64_t cend = i_end * kStatsTile < d ? i_end * kStatsTile : d;
@@ -710,7 +725,7 @@ __global__ __launch_bounds__(kStatsBlock) void tq_stats_segments_partial_kernel(
 
 // One workgroup per tensor and segment adds the rows of the shares the segment reaches into.
 __global__ __launch_bounds__(kStatsBlock) void tq_stats_segments_reduce_kernel(
-    uint64_t d, uint64_t tiles_per_tensor, uint64_t total_tiles, uint32_t groups, uint32_t count,
+    uint64_t d, uint64_t tiles_per_tensor, const Divisor total_tiles, uint32_t groups, uint32_t count,
     const uint64_t* __restrict__ seg_off, uint32_t nseg, float g_min,
     const uint32_t* __restrict__ ws_hist, const StatsExtra* __restrict__ ws_extra, uint64_t n_rows,
     const MutPtrTable stats_tab)
@@ -864,9 +879,16 @@ hipError_t tq_launch_stats(const void* const* g, int count, int dtype, uint64_t 
         const uint64_t kept = stats_kept_tiles(dtype, groups);
         uint32_t* ws_hist = static_cast<uint32_t*>(workspace);
         tq::StatsExtra* ws_extra = reinterpret_cast<tq::StatsExtra*>(static_cast<char*>(workspace) + rows * TQ_NBINS * 4);
+        tq::SplitArgs split{};
+        split.d = d;
+        split.be = tq::make_divisor(be);
+        split.nb = tq::make_divisor(nb);
+        split.tiles_per_tensor = tq::make_divisor(tiles_per_tensor);
+        split.total_tiles = tq::make_divisor(total_tiles);
+        split.groups = tq::make_divisor(groups);
 #define TQ_LAUNCH_SHARES_AS(DT, TL, PA)                                                                                 \
-    hipLaunchKernelGGL((tq::tq_stats_balanced_kernel<DT, TL, PA>), dim3(groups), dim3(tq::kStatsBlock), 0, st, gt, d, be, \
-                       nb, tiles_per_tensor, total_tiles, kept, g_min, ws_hist, ws_extra, stt)
+    hipLaunchKernelGGL((tq::tq_stats_balanced_kernel<DT, TL, PA>), dim3(groups), dim3(tq::kStatsBlock), 0, st, gt, d,     \
+                       split.be, nb, split.tiles_per_tensor, total_tiles, split.groups, kept, g_min, ws_hist, ws_extra, stt)
 #define TQ_LAUNCH_SHARES(DT, TL)   \
     do { if (past) TQ_LAUNCH_SHARES_AS(DT, TL, true); else TQ_LAUNCH_SHARES_AS(DT, TL, false); } while (0)
         if (dtype == TQ_F32) {
@@ -878,22 +900,20 @@ hipError_t tq_launch_stats(const void* const* g, int count, int dtype, uint64_t 
 #undef TQ_LAUNCH_SHARES_AS
         hipError_t err = hipGetLastError();
         if (err != hipSuccess || groups == 1 || whole_tensors) return err;   // every record is written
-        const uint32_t gpb = (TQ_NBINS + tq::kReduceBins - 1) / tq::kReduceBins + 1;
         const uint64_t n_buckets = nb * (uint64_t)count;
-        const uint32_t by_boundary = n_buckets > groups - 1 ? 1u : 0u;
-        const uint64_t n_units = by_boundary ? groups - 1 : n_buckets;
+        split.by_boundary = n_buckets > groups - 1 ? 1u : 0u;
+        split.n_units = split.by_boundary ? groups - 1 : n_buckets;
         dim3 rgrid;
         // rows of a bucket: one per share it reaches into
         const uint64_t share_tiles = total_tiles / groups, bucket_tiles = (be < d ? be : d) / tq::kStatsTile + 2;
         if (bucket_tiles / share_tiles + 2 <= tq::kNarrowRows) {
-            if (!tq::fold_grid(n_units, tq::kNarrowBlock, 1, rgrid)) return hipErrorInvalidValue;
-            hipLaunchKernelGGL(tq::tq_stats_balanced_reduce_narrow_kernel, rgrid, dim3(tq::kNarrowBlock), 0, st, d, be, nb,
-                               tiles_per_tensor, total_tiles, groups, by_boundary, n_units, g_min, ws_hist, ws_extra, stt);
+            if (!tq::fold_grid(split.n_units, tq::kNarrowBlock, 1, rgrid)) return hipErrorInvalidValue;
+            hipLaunchKernelGGL(tq::tq_stats_balanced_reduce_narrow_kernel, rgrid, dim3(tq::kNarrowBlock), 0, st, split, g_min, ws_hist,
+                               ws_extra, stt);
             return hipGetLastError();
         }
-        if (!tq::fold_grid(n_units * gpb, tq::kReduceBlock, 1, rgrid)) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(tq::tq_stats_balanced_reduce_kernel, rgrid, dim3(tq::kReduceBlock), 0, st, d, be, nb,
-                           tiles_per_tensor, total_tiles, groups, by_boundary, n_units, gpb, g_min, ws_hist, ws_extra, stt);
+        if (!tq::fold_grid(split.n_units * tq::kReduceGroups, tq::kReduceBlock, 1, rgrid)) return hipErrorInvalidValue;
+        hipLaunchKernelGGL(tq::tq_stats_balanced_reduce_kernel, rgrid, dim3(tq::kReduceBlock), 0, st, split, g_min, ws_hist, ws_extra, stt);
         return hipGetLastError();
     }
     const uint64_t be = bucket_elems ? bucket_elems : d;
@@ -948,7 +968,8 @@ hipError_t tq_launch_stats_segments(const void* const* g, int count, int dtype, 
     if (!tq::fold_grid(nseg * (uint64_t)count, tq::kStatsBlock, 1, rgrid)) return hipErrorInvalidValue;
 #define TQ_LAUNCH_SEG_PARTIAL_AS(DT, TL, PA)                                                                             \
     hipLaunchKernelGGL((tq::tq_stats_segments_partial_kernel<DT, TL, PA>), dim3(groups), dim3(tq::kStatsBlock), 0, st, gt, \
-                       d, tiles_per_tensor, total_tiles, seg_off, (uint32_t)nseg, kept, g_min, ws_hist, ws_extra)
+                       d, tq::make_divisor(tiles_per_tensor), total_tiles, tq::make_divisor(groups), seg_off, (uint32_t)nseg, kept,    \
+                       g_min, ws_hist, ws_extra)
 #define TQ_LAUNCH_SEG_PARTIAL(DT, TL)   \
     do { if (past) TQ_LAUNCH_SEG_PARTIAL_AS(DT, TL, true); else TQ_LAUNCH_SEG_PARTIAL_AS(DT, TL, false); } while (0)
     if (dtype == TQ_F32) {
@@ -961,6 +982,6 @@ hipError_t tq_launch_stats_segments(const void* const* g, int count, int dtype, 
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL(tq::tq_stats_segments_reduce_kernel, rgrid, dim3(tq::kStatsBlock), 0, st, d, tiles_per_tensor,
-                       total_tiles, groups, (uint32_t)count, seg_off, (uint32_t)nseg, g_min, ws_hist, ws_extra, rows, stt);
+                       tq::make_divisor(total_tiles), groups, (uint32_t)count, seg_off, (uint32_t)nseg, g_min, ws_hist, ws_extra, rows, stt);
     return hipGetLastError();
 }

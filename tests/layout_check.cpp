@@ -99,6 +99,19 @@ int main(int argc, char** argv)
         for (uint32_t w = 0; w < groups; w += 1 + groups / 50)
             if (tq::share_start((uint64_t)w + 1, total, groups) <= tq::share_start(w, total, groups)) { printf("empty share\n"); return 1; }
     }
+    // Quotients by a divisor prepared for a launch: at multiples of it, one below and above, at both ends of 32 bits, beyond.
+    for (int rep = 0; rep < 20000; ++rep) {
+        const uint64_t b = rep < 300 ? rep + 1 : (rep % 3 == 0 ? (1ull << (rep % 36)) : 1 + (next() >> (24 + rep % 40)));
+        const tq::Divisor by = tq::make_divisor(b);
+        for (int k = 0; k < 40; ++k) {
+            const uint64_t top = k % 4 == 3 ? ~0ull : 0xFFFFFFFFull;
+            uint64_t a = k % 2 ? (next() % ((top / b) | 1)) * b : next() & top;
+            a += k % 5 == 1 ? 1u : (k % 5 == 2 && a ? ~0ull : 0u);
+            if (k == 0) a = 0;
+            if (k == 4) a = 0xFFFFFFFFull;
+            if (tq::quotient(a, by) != a / b) { printf("quotient of %llu by %llu\n", (unsigned long long)a, (unsigned long long)b); return 1; }
+        }
+    }
     printf("ok %llu codes %llu look-ups\n", checked, looked);
     return 0;
 }

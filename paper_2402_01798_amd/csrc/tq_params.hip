@@ -273,10 +273,18 @@ struct DensityView {
     }
     __device__ __forceinline__ double inv_half_int(double t) const     // smallest x with int_0^x p^(1/3) >= t
     {
-        int lo = 0, hi = kNB;                              // smallest i with H[i+1] >= t
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (L.H[mid + 1] >= t) hi = mid; else lo = mid + 1;
+        // smallest i with H[i+1] >= t = how many of H[1 ..] are below t: three rounds of independent reads, 64, 8 and 1 bins
+        // apart, instead of ten of one read each (1 record 7.0 -> 6.8 us, 400 8.1 -> 7.9)
+        int lo = 0, n = 0;
+#pragma unroll
+        for (int m = 1; m <= 14; ++m) n += L.H[64 * m] < t ? 1 : 0;
+        lo = 64 * n;
+#pragma unroll
+        for (int step = 8; step >= 1; step >>= 3) {
+            n = 0;
+#pragma unroll
+            for (int m = 1; m <= 7; ++m) n += L.H[lo + step * m < kNB ? lo + step * m : kNB] < t ? 1 : 0;
+            lo += step * n;
         }
         if (lo >= kNB) return 65536.0 + last_bin_width(absmax);
         const double w = lo < kNB - 1 ? ldexp(1.0, lo > 0 ? ((lo - 1) >> 4) - 44 : -40) : last_bin_width(absmax);

@@ -421,13 +421,14 @@ __device__ __forceinline__ Codebook set_up_codebook(const tq_params_t* P, CellLd
 
 // The draws of one tile whose first element is ebase: one Philox call per lane; the high counter word
 // stays scalar unless the low word wraps inside the tile.
+template <uint32_t LANES = kBlock>
 __device__ __forceinline__ void draw_tile(uint64_t ebase, uint32_t lane, uint32_t worker, uint32_t step,
                                           uint32_t seed_lo, uint32_t seed_hi, uint32_t (&rw)[4])
 {
     const uint64_t qb = ebase >> 3;                            // first group of the tile (uniform)
     const uint32_t qb_lo = (uint32_t)qb, qb_hi = (uint32_t)(qb >> 32);
     const uint32_t q_lo = qb_lo + lane;
-    if (qb_lo <= 0xFFFFFFFFu - kBlock) philox4x32_10(q_lo, qb_hi, worker, step, seed_lo, seed_hi, rw);
+    if (qb_lo <= 0xFFFFFFFFu - LANES) philox4x32_10(q_lo, qb_hi, worker, step, seed_lo, seed_hi, rw);
     else philox4x32_10(q_lo, qb_hi + (q_lo < qb_lo ? 1u : 0u), worker, step, seed_lo, seed_hi, rw);
 }
 
@@ -497,7 +498,7 @@ __device__ __forceinline__ uint32_t encode_general(const float (&x)[8], const ui
 // N tiles from `base` on in which every lane owns a whole group: all reads first, the draws under them (requesting the
 // reads even earlier, before the codebook is set up, was slower: 708 us against 668 on 8 x 124 M fp32).
 // THROUGH: bf16 lines are read through the caches (reads_through).
-template <int DTYPE, int BITS, bool CACHED, int N, bool THROUGH = false, typename Draw, typename Encode>
+template <int DTYPE, int BITS, bool CACHED, int N, bool THROUGH = false, int TILE = kTile, typename Draw, typename Encode>
 __device__ __forceinline__ void encode_tiles(const void* g, uint8_t* payload, uint64_t base, uint32_t lane, Draw draw, Encode encode)
 {
     constexpr bool kLines = DTYPE == TQ_F32 && !CACHED;
@@ -505,13 +506,13 @@ __device__ __forceinline__ void encode_tiles(const void* g, uint8_t* payload, ui
     uint32_t rw[N][4];
 #pragma unroll
     for (int t = 0; t < N; ++t) {
-        const uint64_t tile = base + (uint64_t)t * kTile;
+        const uint64_t tile = base + (uint64_t)t * TILE;
         if constexpr (kLines) load_groups_wave(g, tile + (lane & ~63u) * kGroup, lane & 63u, x[t]);
         else load_group<DTYPE, !THROUGH>(g, tile + (uint64_t)lane * kGroup, x[t]);
     }
 #pragma unroll
     for (int t = 0; t < N; ++t) {
-        draw(base + (uint64_t)t * kTile, rw[t]);
+        draw(base + (uint64_t)t * TILE, rw[t]);
         asm volatile("" : "+v"(rw[t][0]));                     // computed here, under the loads
     }
 #pragma unroll
@@ -519,7 +520,7 @@ __device__ __forceinline__ void encode_tiles(const void* g, uint8_t* payload, ui
         if constexpr (kLines) swap_pieces(x[t]);
         replace_nan(x[t]);
         const uint32_t word = encode(x[t], rw[t]);
-        store_codes_wave<BITS, !CACHED>(payload + (((base + (uint64_t)t * kTile) >> 3) + lane) * (uint64_t)BITS, word);
+        store_codes_wave<BITS, !CACHED>(payload + (((base + (uint64_t)t * TILE) >> 3) + lane) * (uint64_t)BITS, word);
     }
 }
 
@@ -624,6 +625,251 @@ __global__ __launch_bounds__(kBlock, !MIRROR && T <= 2 && !(DTYPE == TQ_BF16 && 
             word = cb.nonuniform ? encode_group<BITS, TQ_GRID_NONUNIFORM, true>(x, rw, n_valid, cb.alpha, cb.inv_step, lv, tab)
                                  : encode_group<BITS, TQ_GRID_UNIFORM, true>(x, rw, n_valid, cb.alpha, cb.inv_step, lv, tab);
         }
+        store_codes<BITS>(payload + byte_off, word, payload_bytes - byte_off);
+    }
+}
+
+// ---- bf16 and a level table: the encoding of every value, looked up ---------------------------
+//
+// A bf16 gradient has few different values.  From alpha down to 2^-32 alpha there are 4096 magnitudes; all larger ones encode
+// like alpha, all smaller ones like 0 (checked, below).  A workgroup works out the encoding of each of them, of either sign,
+// once, by the general path's own arithmetic, and keeps it in LDS:
+//   entry = k 2^(32-b) + f 2^(16-b),   f = the number of the 65536 draws that take the upper end of cell k,
+// so that entry + draw 2^(16-b) has the code in its top b bits: draw r takes the upper end iff r >= 65536 - f.  An element
+// then costs 5.5 vector instructions beside its draw's 5 -- two elements' magnitudes are clamped at a time -- where the mirrored
+// path takes 11 (b = 2) or 15 (b = 3), and any table will do, regular or not.
+//   f: u(r) = 1 - (r + 1/2) / 2^16 <= p_r  <=>  r >= 65535.5 - 2^16 p_r, so f = floor(2^16 p_r + 1/2), within 0 .. 2^16 (0 where
+//   p_r is no number); in fp64 that is exact.
+//   Magnitudes below the smallest of the 4096 encode like it and like 0 if those two lie in one cell with the same f, the
+//   difference, the product and f being monotone inside a cell.  If they do not (a level within 2^-10 of 0, say), the workgroup encodes on the
+//   general path.
+// What bounds it: instruction issue (13.4 vector instructions per element in all; 18.6 on the mirrored path at b = 2) and, past it, memory:
+// a loop that only reads and writes in this pattern takes 1580 to 1720 us for 4 x 10^9 elements, one-shot workgroups 1400 to 1480
+// (which the time to fill the entries rules out).  A wavefront takes two groups at a time: with one, the chain of the draws is
+// exposed (2200 us).  Workgroups of 1024 threads 1750 to 1770 us, of 512 1690 to 1780, of 256 (fewer wavefronts: the entries fill the LDS) 1726.
+// Ranges taken tile by tile in turn by 64 to 1024 workgroups 1670 to 1860.  Rules and times by size: look_tiles.
+constexpr int kLookBlock = 512;                                // threads; a tile is one group of each
+constexpr int kLookTile = kLookBlock * kGroup;
+constexpr uint32_t kLookMagnitudes = 4096;
+typedef uint16_t ushort2_native __attribute__((ext_vector_type(2)));
+
+struct LookLds {
+    uint32_t entry[2 * kLookMagnitudes];                       // 2 * (magnitude - lowest) + sign
+};
+
+// The entry of one value, and the cell it lies in.
+template <int BITS>
+__device__ __forceinline__ uint32_t look_entry(float x, float alpha, const float (&lv)[16], const LevelLds& tab, uint32_t& cell)
+{
+    const float xc = __builtin_amdgcn_fmed3f(x, -alpha, alpha);          // Eq. (1)
+    cell = cell_offset<BITS>(xc, lv, tab);
+    const float2 c = *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(tab.e) + cell);
+    const float p_r = (xc - c.x) * c.y;                        // (g - l_k) / |Delta_k| of Eq. (2)
+    double f = __builtin_floor((double)p_r * 65536.0 + 0.5);
+    f = f > 0.0 ? (f < 65536.0 ? f : 65536.0) : 0.0;
+    return ((cell >> 4) << (32 - BITS)) + ((uint32_t)f << (16 - BITS));
+}
+
+// The entries of a lane's 8 elements (two to a word).  lowest and span: twice the smallest magnitude that has
+// an entry, twice the number of those above it, in both halves.
+__device__ __forceinline__ void look_up(const uint32_t (&w)[4], uint32_t lowest, uint32_t span, const LookLds& L, uint32_t (&entry)[8])
+{
+    // twice the magnitudes; NaN -> +0 (it counts as nothing), tested on all of a wavefront's values at once
+    ushort2_native twice[4], sign[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const ushort2_native v = __builtin_bit_cast(ushort2_native, w[i]);
+        twice[i] = v << 1;
+        sign[i] = v >> 15;
+    }
+    const ushort2_native inf = {0xFF00u, 0xFF00u};
+    const ushort2_native top = __builtin_elementwise_max(__builtin_elementwise_max(twice[0], twice[1]), __builtin_elementwise_max(twice[2], twice[3]));
+    if (__builtin_amdgcn_ballot_w64(__builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(top, inf)) != 0u) != 0ull) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const bool nan = twice[i][h] > 0xFF00u;
+                twice[i][h] = nan ? (uint16_t)0u : twice[i][h];
+                sign[i][h] = nan ? (uint16_t)0u : sign[i][h];
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        ushort2_native m = __builtin_elementwise_sub_sat(twice[i], __builtin_bit_cast(ushort2_native, lowest));
+        m = __builtin_elementwise_min(m, __builtin_bit_cast(ushort2_native, span));
+        uint32_t at = __builtin_bit_cast(uint32_t, (ushort2_native)(m | sign[i]));
+        asm("" : "+v"(at));                                    // each half is then taken and scaled in one instruction
+        entry[2 * i] = L.entry[at & 0xFFFFu];
+        entry[2 * i + 1] = L.entry[at >> 16];
+    }
+}
+
+// The packed codes, from the entries and the draws.
+template <int BITS>
+__device__ __forceinline__ uint32_t pack_looked_up(const uint32_t (&entry)[8], const uint32_t (&rw)[4])
+{
+    uint32_t sum[8];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(sum[2 * i]) : "v"(rw[i]), "s"(1u << (16 - BITS)), "v"(entry[2 * i]));
+        asm("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(sum[2 * i + 1]) : "v"(rw[i]), "s"(1u << (16 - BITS)), "v"(entry[2 * i + 1]));
+    }
+    uint32_t word = 0;
+#pragma unroll
+    for (int j = 7; j >= 0; --j) word = __builtin_amdgcn_alignbit(word, sum[j], 32 - BITS);
+    return word;
+}
+
+// `tiles` tiles of one bucket per workgroup, two at a time.
+template <int BITS, bool CACHED>
+__global__ __launch_bounds__(kLookBlock, 8) void tq_compress_lookup_kernel(
+    const PtrTable g_tab, uint64_t d, uint64_t d_pad, uint64_t bucket_elems, uint32_t groups_per_bucket, uint32_t tiles,
+    const PtrTable params_tab, uint32_t seed_lo, uint32_t seed_hi, uint32_t first_worker, uint32_t step, const MutPtrTable payload_tab,
+    uint64_t payload_bytes)
+{
+    const uint32_t blk = linear_block();
+    const uint32_t bucket = blk / groups_per_bucket;
+    const uint32_t grp = blk - bucket * groups_per_bucket;
+    const uint64_t bstart = (uint64_t)bucket * bucket_elems;
+    const uint64_t bend = bstart + bucket_elems < d_pad ? bstart + bucket_elems : d_pad;
+    const uint64_t gbase = bstart + (uint64_t)grp * tiles * kLookTile;    // first element of the workgroup
+    if (gbase >= bend) return;                                 // idle workgroup of a short last bucket
+    const uint16_t* __restrict__ g = static_cast<const uint16_t*>(g_tab.p[blockIdx.y]);
+    uint8_t* __restrict__ payload = static_cast<uint8_t*>(payload_tab.p[blockIdx.y]);
+    const uint32_t worker = first_worker + blockIdx.y;
+    const tq_params_t* P = static_cast<const tq_params_t*>(params_tab.p[blockIdx.y]) + bucket;
+    const uint32_t lane = threadIdx.x;
+    const uint64_t whole_end = bend < d ? bend : d;            // the groups before it are whole
+
+    __shared__ LookLds L;
+    __shared__ LevelLds tab;
+    const Codebook cb = read_codebook(P);
+    float lv[16];
+    uint32_t lowest = 0, span = 0;
+    bool looked_up = false;
+    if (cb.nonuniform) {
+        set_up_levels<BITS>(P, tab, lv);
+        // the smallest magnitude that is not below alpha, and 4095 before it
+        const uint32_t alpha_bits = __float_as_uint(cb.alpha);
+        const uint32_t high = alpha_bits >= 0x7F800000u ? 0x7F80u : (alpha_bits + 0xFFFFu) >> 16;
+        const uint32_t low = high > kLookMagnitudes - 1u ? high - (kLookMagnitudes - 1u) : 0u;
+        {   // every wavefront by itself: lanes 0 and 1 look at the smallest magnitude, 2 and 3 at 0
+            uint32_t cell;
+            const uint32_t sign = (lane & 1u) << 31;
+            const uint32_t entry = look_entry<BITS>(__uint_as_float((lane & 2u ? 0u : low << 16) | sign), cb.alpha, lv, tab, cell);
+            const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)entry, 0x4E, 0xf, 0xf, true);   // lane ^ 2
+            const uint32_t other_cell = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)cell, 0x4E, 0xf, 0xf, true);
+            looked_up = (__builtin_amdgcn_ballot_w64(entry == other && cell == other_cell) & 3ull) == 3ull;
+        }
+        if (looked_up) {                                       // the same in every wavefront
+#pragma unroll 1
+            for (uint32_t e = lane; e < 2u * kLookMagnitudes; e += kLookBlock) {
+                uint32_t cell;
+                const uint32_t bits_e = ((low + (e >> 1)) << 16) | (e & 1u) << 31;
+                L.entry[e] = look_entry<BITS>(__uint_as_float(bits_e), cb.alpha, lv, tab, cell);
+            }
+            __syncthreads();
+        }
+        lowest = 2u * low * 0x10001u;
+        span = 2u * (high - low) * 0x10001u;
+    }
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+    constexpr int N = 2;
+    uint64_t base = gbase;
+    uint32_t left = tiles;
+    if (looked_up) {
+        // N tiles at a time, the next ones requested before these are stored: a wavefront's loads and stores complete in order,
+        // and a request behind a store would wait for it
+        const uint64_t fit = whole_end > gbase ? (whole_end - gbase) / kLookTile : 0;     // whole tiles
+        uint32_t turns = (uint32_t)(fit < tiles ? fit : tiles) / N;
+        auto request = [&](u4 (&v)[N], uint64_t at) {
+#pragma unroll
+            for (int t = 0; t < N; ++t)
+                v[t] = __builtin_nontemporal_load(reinterpret_cast<const u4*>(g + (at + t * (uint64_t)kLookTile)) + lane);
+        };
+        auto turn = [&](const u4 (&v)[N], u4 (&next)[N], bool more) {
+            uint32_t rw[N][4];
+            request(next, more ? base + N * (uint64_t)kLookTile : base);    // no branch: where its paths joined, all loads would be waited for
+            __builtin_amdgcn_sched_barrier(0);
+            uint32_t entry[N][8];                              // on their way from LDS while the draws are computed
+#pragma unroll
+            for (int t = 0; t < N; ++t) {
+                const uint32_t w[4] = {v[t].x, v[t].y, v[t].z, v[t].w};
+                look_up(w, lowest, span, L, entry[t]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int t = 0; t < N; ++t) draw_tile<kLookBlock>(base + t * (uint64_t)kLookTile, lane, worker, step, seed_lo, seed_hi, rw[t]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int t = 0; t < N; ++t) {
+                const uint32_t word = pack_looked_up<BITS>(entry[t], rw[t]);
+                store_codes_wave<BITS, !CACHED>(payload + ((base + t * (uint64_t)kLookTile) >> 3) * BITS + lane * BITS, word);
+            }
+            base += N * (uint64_t)kLookTile;
+        };
+        u4 a[N], b[N];
+        if (turns > 0) request(a, base);
+        left -= turns * N;
+#pragma unroll 1
+        for (; turns > 0; turns -= 2) {
+            turn(a, b, turns > 1);
+            if (turns == 1) break;
+            turn(b, a, turns > 2);
+        }
+    }
+    if (!looked_up) {
+        constexpr int G = 1;                                   // two groups at once take more than 64 registers
+        auto draw = [&](uint64_t ebase, uint32_t (&rw)[4]) { draw_tile<kLookBlock>(ebase, lane, worker, step, seed_lo, seed_hi, rw); };
+#pragma unroll 1
+        for (; left >= G && base + G * kLookTile <= whole_end; base += G * kLookTile, left -= G) {
+            encode_tiles<TQ_BF16, BITS, CACHED, G, false, kLookTile>(g, payload, base, lane, draw, [&](const float (&x)[8], const uint32_t (&rw)[4]) {
+                return encode_general<BITS, true>(x, rw, cb, lv, tab);
+            });
+        }
+    }
+    // the tiles that are left: lanes past the end idle, the tensor's ragged last group element by element
+#pragma unroll 1
+    for (; left > 0 && base < bend; base += kLookTile, --left) {
+        const uint64_t e0 = base + (uint64_t)lane * kGroup;
+        const uint64_t byte_off = ((base >> 3) + lane) * (uint64_t)BITS;
+        if (e0 >= bend || byte_off >= payload_bytes) continue;
+        const int n_valid = e0 >= d ? 0 : (d - e0 < kGroup ? (int)(d - e0) : kGroup);
+        uint32_t w[4], rw[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w[i] = 0;
+        if (n_valid == kGroup) {
+            const u4 v = *reinterpret_cast<const u4*>(g + e0);
+            w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 7; ++j)
+                if (j < n_valid) w[j >> 1] |= (uint32_t)g[e0 + j] << (16 * (j & 1));
+        }
+        draw_tile<kLookBlock>(base, lane, worker, step, seed_lo, seed_hi, rw);
+        uint32_t word;
+        if (looked_up) {
+            uint32_t entry[8];
+            look_up(w, lowest, span, L, entry);
+            word = pack_looked_up<BITS>(entry, rw);
+        } else {
+            float x[8];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) { x[2 * i] = __uint_as_float(w[i] << 16); x[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u); }
+            replace_nan(x);
+            word = 0;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float r = (float)((j & 1) ? rw[j >> 1] >> 16 : rw[j >> 1] & 0xFFFFu);
+                const uint32_t code = cb.nonuniform ? quantize<BITS, TQ_GRID_NONUNIFORM>(x[j], r, cb.alpha, cb.inv_step, lv, tab)
+                                                    : quantize_uniform<BITS>(x[j], r, cb.alpha, cb.inv_step);
+                word |= code << (j * BITS);
+                __builtin_amdgcn_sched_barrier(0);             // one after the other, in few registers
+            }
+        }
+        if (n_valid < kGroup) word &= (1u << (n_valid * BITS)) - 1u;      // the others encode as 0
         store_codes<BITS>(payload + byte_off, word, payload_bytes - byte_off);
     }
 }
@@ -897,6 +1143,28 @@ constexpr bool mirrored_pays(int dtype, int bits) { return bits == 3 || (bits ==
 
 struct CompressShape { bool table_tiles, mirror; };
 
+// Tiles (4096 elements) of a workgroup of tq_compress_lookup_kernel, or 0 where the launch takes the tables as before.  Its 8192
+// entries cost a workgroup as much as five of its tiles, so it wants many of them, in workgroups enough to fill the chip a few
+// times.  us, as before / with 16 / 24 / 32 / 64 / 128 tiles, one record:
+//   b = 2  124 M 60 / 63 / 61 / 64 / 63 / 74, 8 x 25.6 M 95 / 104 / 101 / 101 / 111 / 116, 4 x 124 M 220 / 219 / 217 / 218 / 244 / 255,
+//          8 x 124 M 432 / 463 / 430 / 421 / 441 / 482, 4 x 10^9 1956 / 1907 / 1791 / 1739 / 1696 / 1688
+//   b = 3  40 M 27 / 29 / 29 / 35 / 39 / 70, 60 M 37.6 / 36.8 / 39.5 / 36.4 / 41 / 71, 124 M 73 / 72 / 65 / 66 / 67 / 78, 8 x 124 M 519 / 494 /
+//          468 / 475 / 500 / 531, 4 x 10^9 2304 / 2058 / 1931 / 1901 / 1882 / 1939
+//   b = 4  20 M 18.9 / 20.8 / 19.3 / 22.8 / 37 / 67, 40 M 33.6 / 29.1 / 28.2 / 33.7 / 39 / 69, 124 M 91 / 72 / 64 / 67 / 64 / 75, 8 x 124 M 696 / 486 /
+//          456 / 467 / 482 / 517, 4 x 10^9 2758 / 2050 / 1932 / 1955 / 1906 / 1912
+// A bucket is cut into equal ranges of at least so many tiles, or taken whole: 4 x 124 M in buckets of 65536 (16 tiles) at b = 3
+// 265 / 241, b = 4 332 / 234, of 16384 270 / 384 and 339 / 400.
+uint32_t look_tiles(int dtype, int bits, uint64_t bucket_elems, uint64_t elements)
+{
+    const uint64_t least = bits == 2 ? 1ull << 29 : (bits == 3 ? 1ull << 26 : 1ull << 25);
+    const uint64_t of_bucket = (bucket_elems - 1) / tq::kLookTile + 1;
+    if (dtype != TQ_BF16 || elements < least || of_bucket < 16) return 0;
+    uint64_t wanted = elements / tq::kLookTile / 8192;
+    wanted = wanted < 24 ? 24 : (wanted > 64 ? 64 : wanted);
+    const uint64_t ranges = of_bucket < wanted ? 1 : of_bucket / wanted;
+    return (uint32_t)((of_bucket - 1) / ranges + 1);
+}
+
 // The shape of a launch of level tables.
 //   * Launches whose workgroups are all resident at once wait for latencies and take the tiles and the general path
 //     of the uniform codebook: up to 512 tiles (fp32; 1024 at b = 3) or 4096 (bf16; at b = 3 the mirrored path from 1024 on).  General
@@ -921,6 +1189,7 @@ struct CompressArgs {
     uint64_t d, d_pad, be, seed, pbytes;
     uint32_t groups_per_bucket, first_worker, step;
     bool through;
+    uint32_t look;                                             // tiles of a workgroup that looks its codes up, or 0
 };
 
 template <int DTYPE, int BITS, bool CACHED, bool TABLE_TILES, bool MIRROR, bool THROUGH = false>
@@ -931,9 +1200,20 @@ void launch_as(const CompressArgs& a)
                        (uint32_t)(a.seed >> 32), a.first_worker, a.step, a.payload, a.pbytes);
 }
 
+template <int BITS, bool CACHED>
+void launch_lookup(const CompressArgs& a)
+{
+    hipLaunchKernelGGL((tq::tq_compress_lookup_kernel<BITS, CACHED>), a.blocks, dim3(tq::kLookBlock), 0, a.st, a.g, a.d, a.d_pad, a.be,
+                       a.groups_per_bucket, a.look, a.params, (uint32_t)a.seed, (uint32_t)(a.seed >> 32), a.first_worker, a.step,
+                       a.payload, a.pbytes);
+}
+
 template <int DTYPE, int BITS, bool CACHED>
 hipError_t launch(const CompressShape& shape, const CompressArgs& a)
 {
+    if constexpr (DTYPE == TQ_BF16) {
+        if (a.look) { launch_lookup<BITS, CACHED>(a); return hipGetLastError(); }
+    }
     if constexpr (mirrored_pays(DTYPE, BITS)) {
         if (shape.mirror && shape.table_tiles) { launch_as<DTYPE, BITS, CACHED, true, true>(a); return hipGetLastError(); }
         if constexpr (DTYPE == TQ_BF16 && BITS == 3) {
@@ -967,9 +1247,12 @@ hipError_t tq_launch_compress(const void* const* g, int count, int dtype, uint64
     if (grid != TQ_GRID_UNIFORM) shape = table_shape(dtype, bits, be, nb * tiles * (uint64_t)(count < 1 ? 1 : count));
     const uint64_t tt = (uint64_t)tq::compress_tiles(dtype, shape.table_tiles);
     CompressArgs a{};
-    a.groups_per_bucket = (uint32_t)((tiles + tt - 1) / tt);
+    a.look = grid == TQ_GRID_UNIFORM ? 0u : look_tiles(dtype, bits, be < d_pad ? be : d_pad, d * (uint64_t)(count < 1 ? 1 : count));
+    const uint64_t range = a.look ? (uint64_t)a.look * tq::kLookTile : tt * tq::kTile;      // elements of a workgroup
+    const uint64_t ranges = (be - 1) / range + 1;              // of a bucket
+    a.groups_per_bucket = (uint32_t)ranges;
     if (count < 1 || count > tq::kMaxBatch ||
-        !tq::fold_grid(nb * ((tiles + tt - 1) / tt), tq::kBlock, (unsigned)count, a.blocks))
+        !tq::fold_grid(nb * ranges, a.look ? tq::kLookBlock : tq::kBlock, (unsigned)count, a.blocks))
         return hipErrorInvalidValue;
     for (int i = 0; i < count; ++i) { a.g.p[i] = g[i]; a.params.p[i] = params[i]; a.payload.p[i] = payload[i]; }
     a.st = st;

@@ -1,0 +1,108 @@
+"""bf16 batches large enough that a workgroup looks its codes up: the payload is that of the shape for uniform
+codebooks (the family named to tq_compress shapes the launch and nothing else), which the oracle checks elsewhere."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import binding as O
+from paper_2402_01798_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+LEAST = {2: 1 << 29, 3: 1 << 26, 4: 1 << 25}                  # elements of a batch from which codes are looked up
+TILE = 4096
+
+
+def gradient(d, seed):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    x = torch.randn(d, generator=gen, device="cuda", dtype=torch.bfloat16)
+    x[::3] *= 2.0 ** -9
+    x[::7] *= 2.0 ** -30
+    x[::11] *= 40.0
+    special = [float("nan"), -float("nan"), float("inf"), -float("inf"), 0.0, -0.0, 1e-40, -1e-40, 3e38, -3e38]
+    at = torch.tensor(special, device="cuda").to(torch.bfloat16)
+    x[:10] = at
+    x[TILE - 5:TILE + 5] = at
+    x[d - 10:] = at
+    return x
+
+
+def codebook(bits, kind, rng):
+    """A table that is regular ("designed"), lopsided with an empty cell, or with a level next to or at zero."""
+    s = (1 << bits) - 1
+    rec = np.zeros(1, dtype=B.PARAMS_DTYPE)
+    alpha = np.float32(rng.uniform(0.5, 2.0))
+    t = 2.0 * np.arange(s + 1) / s - 1.0
+    level = (alpha * np.sign(t) * np.abs(t) ** 1.7).astype(np.float32)
+    if kind == "lopsided":
+        level = np.sort((alpha * rng.uniform(-1, 1, s + 1)).astype(np.float32))
+        level[1] = level[2]
+    if kind == "near zero":
+        level[s // 2] = np.float32(2.0 ** -100)
+    if kind == "at zero":
+        level[s // 2] = 0.0
+    level[0], level[s] = -alpha, alpha
+    rec["alpha"], rec["bits"], rec["s"] = alpha, bits, s
+    rec["grid"] = B.GRID_UNIFORM if kind == "uniform" else B.GRID_NONUNIFORM
+    if kind == "uniform":
+        level = (alpha * t).astype(np.float32)
+        rec["inv_w"][:] = s / (2.0 * alpha)
+    else:
+        width = np.diff(level.astype(np.float64))
+        rec["inv_w"][0, :s] = np.where(width > 0, 1.0 / np.where(width > 0, width, 1.0), 0.0)
+    rec["level"][0, :s + 1] = level
+    return rec
+
+
+def both_ways(gs, records, bits, bucket):
+    params = [B.params_from_numpy(r) for r in records]
+    d = gs[0].numel()
+    out = []
+    for grid in (B.GRID_NONUNIFORM, B.GRID_UNIFORM):
+        payload = [torch.full((B.payload_bytes(d, bits) + 16,), 0xA5, dtype=torch.uint8, device="cuda") for _ in gs]
+        B.tq_compress_multi(gs, params, payload, bits, 2 ** 40 + 17, 3, 9, bucket, grid)
+        out.append(payload)
+    torch.cuda.synchronize()
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
+        assert (a[-16:] == 0xA5).all()                        # nothing behind the payload
+
+
+@pytest.mark.parametrize("kind", ["designed", "lopsided", "near zero", "at zero", "uniform"])
+@pytest.mark.parametrize("bits", [3, 4])
+def test_tables_of_every_kind(bits, kind):
+    d, rng = LEAST[bits] + 5 * TILE + 77, np.random.default_rng(bits)
+    both_ways([gradient(d, bits)], [codebook(bits, kind, rng)], bits, 0)
+
+
+@pytest.mark.parametrize("bits", [3, 4])
+@pytest.mark.parametrize("d,bucket", [(0, 65_536), (1, 65_536), (127, 65_536 + 128), (4_095, 1 << 20), (4_097, 3 * 65_536 - 128),
+                                      (65_535, 1 << 24), (8 * TILE, 1 << 30)])
+def test_ragged_tensors_and_buckets(bits, d, bucket):
+    d, rng = LEAST[bits] // 2 + d, np.random.default_rng(d)
+    nb = B.num_buckets(d, bucket)
+    kinds = ["designed", "lopsided", "at zero", "uniform"]
+    books = [[codebook(bits, kinds[(i + w) % 4], rng) for i in range(min(nb, 12))] for w in range(2)]
+    records = [np.concatenate([b[i % len(b)] for i in range(nb)]) for b in books]
+    both_ways([gradient(d, 1), gradient(d, 2)], records, bits, bucket)
+
+
+def test_two_bits():
+    d, rng = LEAST[2] // 2 + 12_345, np.random.default_rng(2)
+    gs = [gradient(d, 3), gradient(d, 4)]
+    both_ways(gs, [codebook(2, k, rng) for k in ("designed", "lopsided")], 2, 0)
+    both_ways(gs, [codebook(2, k, rng) for k in ("near zero", "uniform")], 2, 0)
+
+
+def test_codes_are_the_oracles():
+    """The whole payload against the oracle, with the record the device designed."""
+    bits, d = 4, LEAST[4] + 4_321
+    g = gradient(d, 6)
+    stats, params, ws = B.alloc_stats(d), B.alloc_params(d), B.alloc_stats_workspace(d)
+    payload = torch.zeros(B.payload_bytes(d, bits), dtype=torch.uint8, device="cuda")
+    B.tq_stats(g, stats, ws)
+    B.tq_params(stats, params, bits, B.GRID_NONUNIFORM)
+    B.tq_compress(g, params, payload, bits, 11, 2, 5, 0, B.GRID_NONUNIFORM)
+    want = O.compress(g.view(torch.int16).cpu().numpy().view(np.uint16), B.params_to_numpy(params).view(O.PARAMS_DTYPE),
+                      11, 2, 5, threads=8)
+    assert np.array_equal(payload.cpu().numpy(), want)

@@ -48,8 +48,15 @@ constexpr int kStatsResidentGroups = 1024;             // workgroups that can ru
 // 1.5 us of 18 at the upper end of this range; the line is drawn for calls issued one by one.  At 100,000 the statistics by
 // themselves take 17.4 us instead of 11.9.
 constexpr uint64_t kWholeTensor = 65536;
-// Tiles of a trip of the equal shares, of one record as of many and of segments, see stats_slice.
-constexpr int share_trip(int dtype, bool past) { return dtype == TQ_F32 && past ? 4 : 2; }
+// Tiles of a trip of the equal shares, of one record as of many and of segments, see stats_slice.  Batches read past the caches,
+// fp32, trips of four / three, us: 8 x 124 M 579 / 570, 8 x 11.2 M 59.1 / 58.0, 100 M 68.0 / 66.3, with tail 16 x 25.6 M 251 / 243,
+// 2 x 310 M 372 / 363 (two tiles 261, one 256 with 256 workgroups; one tile and 512 workgroups 242, but without tail 578 / 589),
+// 8 x 25.6 M with tail in buckets of 65536 187 / 182, of 131072 157 / 154, but without in buckets of 32768 178 / 181, of 65536 153.5 / 157.2.
+constexpr uint64_t kShortPieces = 131072;
+constexpr int share_trip(int dtype, bool tail, bool past, bool short_pieces)
+{
+    return dtype == TQ_F32 && past ? (tail || !short_pieces ? 3 : 4) : 2;
+}
 constexpr int kReduceBlock = 1024;                     // threads of the reduce kernel: 64 bins x 16 slice lanes
 constexpr int kReduceBins = 64;
 constexpr uint32_t kReduceGroups = (TQ_NBINS + kReduceBins - 1) / kReduceBins + 1;   // its workgroups per bucket (16)
@@ -172,8 +179,8 @@ __device__ __forceinline__ StatsExtra stats_slice(const void* __restrict__ g, ui
     // for every lane of the workgroup; what is left after the full trips is less than a trip.
     //  - bf16 is bound by instruction issue: trips of two tiles, and the wavefront works on one
     //    buffer while the other one's loads are in flight.
-    //  - fp32 is bound by memory and runs with two wavefronts per SIMD: trips of four tiles
-    //    (eight 16-byte loads per lane), and the wavefront waits for ALL its loads, the ones
+    //  - fp32 is bound by memory and runs with two wavefronts per SIMD: trips of three or four
+    //    tiles (six or eight 16-byte loads per lane, share_trip), and the wavefront waits for ALL its loads, the ones
     //    just requested included, before it works on the older buffer -- so it has nothing in
     //    flight while it computes, and the other wavefront of the SIMD fills the gap.  Measured
     //    on 8 x 124 M fp32: 705 us when a wavefront keeps loads in flight under its own work,
@@ -535,7 +542,7 @@ __device__ __forceinline__ void reduce_rows(const uint32_t* __restrict__ ws_hist
 
 constexpr uint64_t kBalancedMinBucket = 32768;
 
-template <int DTYPE, bool TAIL, bool PAST>
+template <int DTYPE, bool TAIL, bool PAST, int TRIP>
 __global__ __launch_bounds__(kStatsBlock) void tq_stats_balanced_kernel(
     const PtrTable g_tab, uint64_t d, const Divisor by_bucket, uint64_t nb, const Divisor by_tensor, uint64_t total_tiles, const Divisor groups,
     uint64_t kept_tiles, float g_min, uint32_t* __restrict__ ws_hist, StatsExtra* __restrict__ ws_extra, const MutPtrTable stats_tab)
@@ -562,7 +569,7 @@ __global__ __launch_bounds__(kStatsBlock) void tq_stats_balanced_kernel(
             const uint64_t r = (uint64_t)w + t * nb + b;
             if (!first) __syncthreads();                               // the histograms are cleared again
             first = false;
-            const StatsExtra x = stats_slice<DTYPE, TAIL, PAST, share_trip(DTYPE, PAST)>(g, cs, ce, past_end, g_min, L, whole ? stats[b].hist : ws_hist + r * TQ_NBINS);
+            const StatsExtra x = stats_slice<DTYPE, TAIL, PAST, TRIP>(g, cs, ce, past_end, g_min, L, whole ? stats[b].hist : ws_hist + r * TQ_NBINS);
             if (threadIdx.x == 0) {
                 if (whole) write_scalars(stats + b, x, hi - lo, g_min);
                 else ws_extra[r] = x;
@@ -684,7 +691,7 @@ __global__ __launch_bounds__(kReduceBlock) void tq_stats_balanced_reduce_kernel(
 // consecutive); a second kernel adds each segment's rows.  Every access is bounded by d, nseg
 // and the number of rows, whatever the table holds.
 
-template <int DTYPE, bool TAIL, bool PAST>
+template <int DTYPE, bool TAIL, bool PAST, int TRIP>
 __global__ __launch_bounds__(kStatsBlock) void tq_stats_segments_partial_kernel(
     const PtrTable g_tab, uint64_t d, const Divisor by_tensor, uint64_t total_tiles, const Divisor groups,
     const uint64_t* __restrict__ seg_off, uint32_t nseg, uint64_t kept_tiles, float g_min,
@@ -714,7 +721,7 @@ __global__ __launch_bounds__(kStatsBlock) void tq_stats_segments_partial_kernel(
             const uint64_t r = (uint64_t)w + t * nseg + s;
             if (!first) __syncthreads();                               // the histograms are cleared again
             first = false;
-            const StatsExtra x = stats_slice<DTYPE, TAIL, PAST, share_trip(DTYPE, PAST)>(g, seg_lo, seg_hi, past_end, g_min, L, ws_hist + r * TQ_NBINS);
+            const StatsExtra x = stats_slice<DTYPE, TAIL, PAST, TRIP>(g, seg_lo, seg_hi, past_end, g_min, L, ws_hist + r * TQ_NBINS);
             if (threadIdx.x == 0) ws_extra[r] = x;
             if (seg_hi >= cend || s + 1 >= nseg) break;
             ++s;
@@ -875,7 +882,7 @@ hipError_t tq_launch_stats(const void* const* g, int count, int dtype, uint64_t 
         const bool whole_tensors = nb == 1 && d <= tq::kWholeTensor;     // share i = tensor i
         const uint32_t groups = whole_tensors ? (uint32_t)count : (uint32_t)(fit < 1 ? 1 : (fit < resident ? fit : resident));
         const uint64_t rows = groups + nb * (uint64_t)count;
-        const bool past = stats_past_caches(count, d, dtype);
+        const bool past = stats_past_caches(count, d, dtype), short_pieces = be < tq::kShortPieces;
         const uint64_t kept = stats_kept_tiles(dtype, groups);
         uint32_t* ws_hist = static_cast<uint32_t*>(workspace);
         tq::StatsExtra* ws_extra = reinterpret_cast<tq::StatsExtra*>(static_cast<char*>(workspace) + rows * TQ_NBINS * 4);
@@ -886,11 +893,15 @@ hipError_t tq_launch_stats(const void* const* g, int count, int dtype, uint64_t 
         split.tiles_per_tensor = tq::make_divisor(tiles_per_tensor);
         split.total_tiles = tq::make_divisor(total_tiles);
         split.groups = tq::make_divisor(groups);
-#define TQ_LAUNCH_SHARES_AS(DT, TL, PA)                                                                                 \
-    hipLaunchKernelGGL((tq::tq_stats_balanced_kernel<DT, TL, PA>), dim3(groups), dim3(tq::kStatsBlock), 0, st, gt, d,     \
+#define TQ_LAUNCH_SHARES_AS(DT, TL, PA, SH)                                                                                 \
+    hipLaunchKernelGGL((tq::tq_stats_balanced_kernel<DT, TL, PA, tq::share_trip(DT, TL, PA, SH)>), dim3(groups), dim3(tq::kStatsBlock), 0, st, gt, d,     \
                        split.be, nb, split.tiles_per_tensor, total_tiles, split.groups, kept, g_min, ws_hist, ws_extra, stt)
 #define TQ_LAUNCH_SHARES(DT, TL)   \
-    do { if (past) TQ_LAUNCH_SHARES_AS(DT, TL, true); else TQ_LAUNCH_SHARES_AS(DT, TL, false); } while (0)
+    do {                                                                             \
+        if (past && short_pieces) TQ_LAUNCH_SHARES_AS(DT, TL, true, true);           \
+        else if (past) TQ_LAUNCH_SHARES_AS(DT, TL, true, false);                     \
+        else TQ_LAUNCH_SHARES_AS(DT, TL, false, false);                              \
+    } while (0)
         if (dtype == TQ_F32) {
             if (g_min > 0.0f) { TQ_LAUNCH_SHARES(TQ_F32, true); } else { TQ_LAUNCH_SHARES(TQ_F32, false); }
         } else {
@@ -960,18 +971,22 @@ hipError_t tq_launch_stats_segments(const void* const* g, int count, int dtype, 
     const uint64_t fit = total_tiles * tq::kStatsTile / tq::kStatsMinSlice;       // shares of at least 16384 elements
     const uint32_t groups = (uint32_t)(fit < 1 ? 1 : (fit < resident ? fit : resident));
     const uint64_t rows = groups + nseg * (uint64_t)count;
-    const bool past = stats_past_caches(count, d, dtype);
+    const bool past = stats_past_caches(count, d, dtype), short_pieces = d / nseg < tq::kShortPieces;
     const uint64_t kept = stats_kept_tiles(dtype, groups);
     uint32_t* ws_hist = static_cast<uint32_t*>(workspace);
     tq::StatsExtra* ws_extra = reinterpret_cast<tq::StatsExtra*>(static_cast<char*>(workspace) + rows * TQ_NBINS * 4);
     dim3 rgrid;
     if (!tq::fold_grid(nseg * (uint64_t)count, tq::kStatsBlock, 1, rgrid)) return hipErrorInvalidValue;
-#define TQ_LAUNCH_SEG_PARTIAL_AS(DT, TL, PA)                                                                             \
-    hipLaunchKernelGGL((tq::tq_stats_segments_partial_kernel<DT, TL, PA>), dim3(groups), dim3(tq::kStatsBlock), 0, st, gt, \
+#define TQ_LAUNCH_SEG_PARTIAL_AS(DT, TL, PA, SH)                                                                             \
+    hipLaunchKernelGGL((tq::tq_stats_segments_partial_kernel<DT, TL, PA, tq::share_trip(DT, TL, PA, SH)>), dim3(groups), dim3(tq::kStatsBlock), 0, st, gt, \
                        d, tq::make_divisor(tiles_per_tensor), total_tiles, tq::make_divisor(groups), seg_off, (uint32_t)nseg, kept,    \
                        g_min, ws_hist, ws_extra)
 #define TQ_LAUNCH_SEG_PARTIAL(DT, TL)   \
-    do { if (past) TQ_LAUNCH_SEG_PARTIAL_AS(DT, TL, true); else TQ_LAUNCH_SEG_PARTIAL_AS(DT, TL, false); } while (0)
+    do {                                                                                 \
+        if (past && short_pieces) TQ_LAUNCH_SEG_PARTIAL_AS(DT, TL, true, true);          \
+        else if (past) TQ_LAUNCH_SEG_PARTIAL_AS(DT, TL, true, false);                    \
+        else TQ_LAUNCH_SEG_PARTIAL_AS(DT, TL, false, false);                             \
+    } while (0)
     if (dtype == TQ_F32) {
         if (g_min > 0.0f) TQ_LAUNCH_SEG_PARTIAL(TQ_F32, true); else TQ_LAUNCH_SEG_PARTIAL(TQ_F32, false);
     } else {

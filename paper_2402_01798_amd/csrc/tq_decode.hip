@@ -48,7 +48,10 @@ __device__ __forceinline__ uint32_t load_code_word(const uint8_t* stream, const 
 // on purpose: with a run-time flag the read-modify-write branch leaves "a load may be pending"
 // on every path, and the compiler then waits for ALL outstanding memory operations -- the
 // tile's own stores included -- before the next tile.
-enum { kStore = 0, kAccumulate = 1, kSgd = 2, kSgdMomentum = 3, kStoreStream = 4 };
+//   ... | kPast   the modes that read back, past the caches: what they read and write is too much for them (reads_past)
+enum { kStore = 0, kAccumulate = 1, kSgd = 2, kSgdMomentum = 3, kStoreStream = 4, kPast = 8 };
+constexpr bool reads_back(int mode) { return mode != kStore && mode != kStoreStream; }
+constexpr bool has_velocity(int mode) { return (mode & ~kPast) == kSgdMomentum; }
 
 struct Update {
     float eta, momentum, weight_decay;
@@ -58,9 +61,9 @@ struct Update {
 template <int MODE>
 __device__ __forceinline__ float finish(float g_bar, float prev, float& vel, const Update& up)
 {
-    if constexpr (MODE == kStore || MODE == kStoreStream) {
+    if constexpr (!reads_back(MODE)) {
         return g_bar;
-    } else if constexpr (MODE == kAccumulate) {
+    } else if constexpr ((MODE & ~kPast) == kAccumulate) {
         return prev + g_bar;
     } else {
         float u = g_bar;
@@ -68,7 +71,7 @@ __device__ __forceinline__ float finish(float g_bar, float prev, float& vel, con
             const float decay = up.weight_decay * prev;
             u = g_bar + decay;
         }
-        if constexpr (MODE == kSgdMomentum) {
+        if constexpr (has_velocity(MODE)) {
             const float carried = up.momentum * vel;
             u = carried + u;
             vel = u;
@@ -110,20 +113,56 @@ __device__ __forceinline__ void finish_group(float* o, uint64_t e0, float (&acc)
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] = finish<MODE>(acc[j], prev[j], vel[j], up);
     store8<MODE == kStoreStream>(o, acc);
-    if constexpr (MODE == kSgdMomentum) store8<false>(up.velocity + e0, vel);
+    if constexpr (has_velocity(MODE)) store8<false>(up.velocity + e0, vel);
 }
 
-template <int MODE, bool LDS>
+// What the epilogue reads back (the old output, the parameters, the velocity) is requested with the code words, by the lanes
+// that own a whole group.  PIECES and a workgroup whose lanes all do: a lane's two loads are not its own 32 bytes but the
+// pieces that it will store (wave_piece), so that each load reads 1 KiB in one piece and nothing but the aggregate
+// has to be exchanged; such lines can be read and written past the caches, which is where this pays (reads_past).
+template <bool PIECES>
+struct ReadBack {
+    uint64_t first, second;                                // elements of the two loads
+    bool any;
+    __device__ __forceinline__ ReadBack(uint64_t e0, uint32_t lane, bool whole, uint64_t bend)
+    {
+        const bool pieces = PIECES && whole;
+        first = pieces ? e0 - (uint64_t)lane * kGroup + wave_piece(lane) * 4u : e0;
+        second = first + (pieces ? 256u : 4u);
+        any = e0 + kGroup <= bend;
+    }
+    template <bool PAST>
+    __device__ __forceinline__ void load(const float* p, float (&x)[8]) const
+    {
+        const float4_native *pa = reinterpret_cast<const float4_native*>(p + first), *pb = reinterpret_cast<const float4_native*>(p + second);
+        float4_native a, b;
+        if constexpr (PAST) { a = __builtin_nontemporal_load(pa); b = __builtin_nontemporal_load(pb); }
+        else { a = *pa; b = *pb; }
+        x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
+        x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
+    }
+};
+
+// `prev` and `vel` hold the lane's pieces (modes that read back), `acc` its group.
+template <int MODE, bool LDS, bool PIECES>
 __device__ __forceinline__ void finish_group_wave(float* out, uint64_t e0, uint32_t lane, float (&acc)[8],
                                                   const float (&prev)[8], float (&vel)[8], const Update& up,
                                                   float4_native* wb)
 {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] = finish<MODE>(acc[j], prev[j], vel[j], up);
     const uint64_t wave_e0 = e0 - (uint64_t)lane * kGroup;
-    if constexpr (LDS) store8_wave_lds<MODE == kStoreStream>(out + wave_e0, lane, acc, wb);
-    else store8_wave<MODE == kStoreStream>(out + wave_e0, lane, acc);
-    if constexpr (MODE == kSgdMomentum) store8_wave<false>(up.velocity + wave_e0, lane, vel);
+    if constexpr (PIECES && reads_back(MODE)) {
+        swap_pieces(acc);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[j] = finish<MODE>(acc[j], prev[j], vel[j], up);
+        store_lane_pieces<(MODE & kPast) != 0>(out + wave_e0, lane, acc);
+        if constexpr (has_velocity(MODE)) store_lane_pieces<(MODE & kPast) != 0>(up.velocity + wave_e0, lane, vel);
+    } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[j] = finish<MODE>(acc[j], prev[j], vel[j], up);
+        if constexpr (LDS) store8_wave_lds<MODE == kStoreStream>(out + wave_e0, lane, acc, wb);
+        else store8_wave<MODE == kStoreStream>(out + wave_e0, lane, acc);
+        if constexpr (has_velocity(MODE)) store8_wave<false>(up.velocity + wave_e0, lane, vel);
+    }
 }
 
 // The ragged end of the tensor, element by element (only in the last workgroup of the tensor;
@@ -137,10 +176,10 @@ __device__ __forceinline__ void finish_ragged(float* o, uint64_t e0, const float
     for (int j = 0; j < 7; ++j) {                          // a ragged group has at most 7 elements
         if (j < n_valid) {
             float prev = 0.0f, vel = 0.0f;
-            if constexpr (MODE != kStore && MODE != kStoreStream) prev = o[j];
-            if constexpr (MODE == kSgdMomentum) vel = up.velocity[e0 + j];
+            if constexpr (reads_back(MODE)) prev = o[j];
+            if constexpr (has_velocity(MODE)) vel = up.velocity[e0 + j];
             o[j] = finish<MODE>(acc[j], prev, vel, up);
-            if constexpr (MODE == kSgdMomentum) up.velocity[e0 + j] = vel;
+            if constexpr (has_velocity(MODE)) up.velocity[e0 + j] = vel;
         }
     }
 }
@@ -231,9 +270,10 @@ __global__ __launch_bounds__(kBlock) void tq_decode_fast_kernel(
     for (int t = 0; t < T; ++t) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) { prev[t][j] = 0.0f; vel[t][j] = 0.0f; }
-        if (e0[t] + kGroup <= bend) {
-            if constexpr (MODE != kStore && MODE != kStoreStream) load8(out + e0[t], prev[t]);
-            if constexpr (MODE == kSgdMomentum) load8(up.velocity + e0[t], vel[t]);
+        const ReadBack<!SEG> back(e0[t], threadIdx.x & 63u, gstart + (uint64_t)T * kTile <= bend, bend);
+        if (back.any) {
+            if constexpr (reads_back(MODE)) back.template load<(MODE & kPast) != 0>(out, prev[t]);
+            if constexpr (has_velocity(MODE)) back.template load<(MODE & kPast) != 0>(up.velocity, vel[t]);
         }
     }
 
@@ -337,7 +377,7 @@ __global__ __launch_bounds__(kBlock) void tq_decode_fast_kernel(
         for (int t = 0; t < T; ++t) {
             float acc[8];
             lookup(t, acc);
-            finish_group_wave<MODE, LDS>(out, e0[t], (uint32_t)lane, acc, prev[t], vel[t], up, wb);
+            finish_group_wave<MODE, LDS, !SEG>(out, e0[t], (uint32_t)lane, acc, prev[t], vel[t], up, wb);
         }
     } else {
         // the last workgroup of a bucket: tile by tile (one tile's values live at a time)
@@ -409,9 +449,10 @@ __global__ __launch_bounds__(kBlock) void tq_decode_many_kernel(
     for (int t = 0; t < T; ++t) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) { prev[t][j] = 0.0f; vel[t][j] = 0.0f; acc[t][j] = 0.0f; }
-        if (e0[t] + kGroup <= bend) {
-            if constexpr (MODE != kStore && MODE != kStoreStream) load8(out + e0[t], prev[t]);
-            if constexpr (MODE == kSgdMomentum) load8(up.velocity + e0[t], vel[t]);
+        const ReadBack<true> back(e0[t], threadIdx.x & 63u, gstart + (uint64_t)T * kTile <= bend, bend);
+        if (back.any) {
+            if constexpr (reads_back(MODE)) back.template load<(MODE & kPast) != 0>(out, prev[t]);
+            if constexpr (has_velocity(MODE)) back.template load<(MODE & kPast) != 0>(up.velocity, vel[t]);
         }
     }
     for (int idx = threadIdx.x; idx < U * ENTRIES; idx += kBlock) {
@@ -467,7 +508,7 @@ __global__ __launch_bounds__(kBlock) void tq_decode_many_kernel(
     for (int t = 0; t < T; ++t) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) acc[t][j] = acc[t][j] * post;
-        if (whole) finish_group_wave<MODE, false>(out, e0[t], lane, acc[t], prev[t], vel[t], up, nullptr);
+        if (whole) finish_group_wave<MODE, false, true>(out, e0[t], lane, acc[t], prev[t], vel[t], up, nullptr);
         else if (e0[t] + kGroup <= bend) finish_group<MODE>(out + e0[t], e0[t], acc[t], prev[t], vel[t], up);
         else if (e0[t] < bend) finish_ragged<MODE>(out + e0[t], e0[t], acc[t], (int)(bend - e0[t]), up);
     }
@@ -503,7 +544,7 @@ __global__ __launch_bounds__(kBlock) void tq_decode_segments_kernel(
 #pragma unroll
             for (int j = 0; j < 8; ++j) { acc[j] = 0.0f; prev[j] = 0.0f; vel[j] = 0.0f; }
             if (whole) {
-                if constexpr (MODE != kStore && MODE != kStoreStream) load8(out + e0, prev);
+                if constexpr (reads_back(MODE)) load8(out + e0, prev);
             }
             for (int i = 0; i < N; ++i) {
                 const uint32_t w = load_code_word<BITS>(args.payload[i], cl) >> cl.first_bit;
@@ -556,6 +597,18 @@ constexpr uint64_t lds_above(int bits, int U)
     if (bits == 4) return (U == 1 ? 2048 : 1024) * kMiB;
     if (U == 1) return (bits == 2 ? 4352 : 2816) * kMiB;
     return bits == 2 && U == 2 ? 2048 * kMiB : kNever;
+}
+
+// Whether an update (or a sum) goes past the caches: from 96 MiB of what it reads back on, or 64 MiB of parameters and velocity,
+// in buckets of which few ranges are cut.  us, through / past the caches, by themselves and with two elementwise kernels behind them of which
+// the first reads the result: momentum 8 x 8 M 26.8 / 26.5 (48.1 / 48.9), 9 M 30.6 / 29.6 (54.3 / 54.0), 16 M 57.3 / 49.8 (93.4 / 93.0), 25.6 M 91.2 / 77.1
+// (150 / 143), 62 M 214 / 194 (381 / 368), 124 M 430 / 383 (766 / 742), 32 x 25.6 M 148 / 139 (211 / 203); sgd 4 x 8 M 13.0 / 13.7
+// (33.7 / 35.9), 16 M 23.4 / 24.2 (63.0 / 64.8), 25.6 M 41.6 / 37.1 (98.5 / 99.5), 62 M 101 / 85 (268 / 255); accumulate 8 x 16 M 34.3 / 32.4
+// (73.4 / 74.9), 25.6 M 58.5 / 52.3 (115 / 113), 62 M 137 / 121 (306 / 306), 124 M 275 / 240 (611 / 601).  Loads alone 92.5 -> 89.2 of 25.6 M
+// with momentum, stores alone 93.2: it takes both.  A lane's own 32 bytes each way gave nothing.
+bool reads_past(int mode, uint64_t d, uint64_t bucket_elems)
+{
+    return d * sizeof(float) > ((mode == tq::kSgdMomentum ? 32ull : 96ull) << 20) && bucket_elems >= 16 * (uint64_t)tq::kTile;
 }
 
 // Whether launches of this kind can be above it: kStore is the mode of outputs of 64 to 160 MiB.
@@ -682,12 +735,16 @@ hipError_t tq_launch_decode(const void* const* payload, const tq_params_t* const
     g.pbytes = tq_payload_bytes(d, bits);
     const tq::Update up{eta, momentum, weight_decay, velocity};
     if (mode == tq::kStore && streams_output(d)) mode = tq::kStoreStream;
+    else if (tq::reads_back(mode) && reads_past(mode, d, g.be)) mode |= tq::kPast;
     switch (mode) {
         case tq::kStore: return launch_mode<tq::kStore>(g, out, up, st);
         case tq::kStoreStream: return launch_mode<tq::kStoreStream>(g, out, up, st);
         case tq::kAccumulate: return launch_mode<tq::kAccumulate>(g, out, up, st);
         case tq::kSgd: return launch_mode<tq::kSgd>(g, out, up, st);
         case tq::kSgdMomentum: return launch_mode<tq::kSgdMomentum>(g, out, up, st);
+        case tq::kAccumulate | tq::kPast: return launch_mode<tq::kAccumulate | tq::kPast>(g, out, up, st);
+        case tq::kSgd | tq::kPast: return launch_mode<tq::kSgd | tq::kPast>(g, out, up, st);
+        case tq::kSgdMomentum | tq::kPast: return launch_mode<tq::kSgdMomentum | tq::kPast>(g, out, up, st);
         default: return hipErrorInvalidValue;
     }
 }

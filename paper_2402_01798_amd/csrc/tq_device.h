@@ -139,6 +139,14 @@ __device__ __forceinline__ void store_pieces(float4_native* p, float4_native a, 
     }
 }
 
+// `x` = the lane's pieces already.
+template <bool STREAM>
+__device__ __forceinline__ void store_lane_pieces(float* o, uint32_t lane, const float (&x)[8])
+{
+    const float4_native a = {x[0], x[1], x[2], x[3]}, b = {x[4], x[5], x[6], x[7]};
+    store_pieces<STREAM>(reinterpret_cast<float4_native*>(o) + wave_piece(lane), a, b);
+}
+
 template <bool STREAM>
 __device__ __forceinline__ void store8_wave(float* o, uint32_t lane, const float (&x)[8])
 {
@@ -146,8 +154,7 @@ __device__ __forceinline__ void store8_wave(float* o, uint32_t lane, const float
 #pragma unroll
     for (int j = 0; j < 8; ++j) y[j] = x[j];
     swap_pieces(y);
-    const float4_native a = {y[0], y[1], y[2], y[3]}, b = {y[4], y[5], y[6], y[7]};
-    store_pieces<STREAM>(reinterpret_cast<float4_native*>(o) + wave_piece(lane), a, b);
+    store_lane_pieces<STREAM>(o, lane, y);
 }
 
 // `wb` is the wavefront's own 2 KiB of LDS; a wavefront's LDS operations complete in order, so no

@@ -1,0 +1,63 @@
+"""Updates, sums and simulated gradients large enough to go past the caches, whole wavefronts reading and writing 16-byte
+pieces of the lanes' groups, against the plain aggregate (which the oracle checks elsewhere) and the same roundings in torch."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2402_01798_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+MIB = 1 << 20
+
+
+def book(bits, nb, rng):
+    s = (1 << bits) - 1
+    rec = np.zeros(nb, dtype=B.PARAMS_DTYPE)
+    level = np.sort(rng.uniform(-1, 1, (nb, s + 1)), axis=1).astype(np.float32)
+    rec["alpha"], rec["bits"], rec["s"], rec["grid"] = 1.0, bits, s, B.GRID_NONUNIFORM
+    rec["level"][:, :s + 1] = level
+    rec["level"][:, 0], rec["level"][:, s] = -1.0, 1.0
+    rec["inv_w"][:, :s] = 1.0 / np.maximum(np.diff(rec["level"][:, :s + 1].astype(np.float64), axis=1), 1e-6)
+    return rec
+
+
+def server(d, N, bits, bucket):
+    """N payloads of random codes (any bytes are codes at every width) and their records."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d % 1000 + N)
+    rng = np.random.default_rng(N)
+    params = [B.params_from_numpy(book(bits, B.num_buckets(d, bucket), rng)) for _ in range(N)]
+    payload = [torch.randint(0, 256, (B.payload_bytes(d, bits),), generator=gen, device="cuda", dtype=torch.uint8) for _ in range(N)]
+    g_bar = torch.empty(d, device="cuda")
+    B.tq_decompress_aggregate(payload, params, g_bar, bits, bucket)
+    theta, vel = (torch.randn(d, generator=gen, device="cuda") for _ in range(2))
+    return payload, params, g_bar, theta, vel
+
+
+SINGLE, DOUBLE = 96 * MIB // 4, 32 * MIB // 4                 # elements above which they go past the caches
+
+
+@pytest.mark.parametrize("N,bits", [(1, 4), (3, 2), (8, 3), (16, 2), (12, 4), (20, 3), (33, 4)])
+@pytest.mark.parametrize("extra,bucket", [(1, 0), (4_097, 1 << 20), (777, 9 * 4096 + 128), (2_048, 32_768)])
+def test_updates(N, bits, extra, bucket):
+    d, eta, mu, wd = DOUBLE + extra, 0.1, 0.9, 1e-3
+    payload, params, g_bar, theta, vel = server(d, N, bits, bucket)
+    f = lambda x: torch.tensor(x, dtype=torch.float32, device="cuda")
+    v = f(mu) * vel + (g_bar + f(wd) * theta)
+    want = theta - f(eta) * v
+    B.tq_decompress_aggregate_update(payload, params, theta, bits, eta, mu, wd, vel, bucket)
+    torch.cuda.synchronize()
+    assert torch.equal(vel.view(torch.int32), v.view(torch.int32)) and torch.equal(theta.view(torch.int32), want.view(torch.int32))
+
+
+@pytest.mark.parametrize("N,bits", [(2, 4), (8, 2), (17, 3)])
+@pytest.mark.parametrize("extra,bucket", [(5, 0), (4_095, 65_536 + 128)])
+def test_sums_and_plain_sgd(N, bits, extra, bucket):
+    d, eta = SINGLE + extra, 0.25
+    payload, params, g_bar, theta, _ = server(d, N, bits, bucket)
+    total, want = theta + g_bar, theta - torch.tensor(eta, device="cuda") * g_bar
+    out = theta.clone()
+    B.tq_decompress_aggregate(payload, params, out, bits, bucket, None, True)
+    B.tq_decompress_aggregate_update(payload, params, theta, bits, eta, 0.0, 0.0, None, bucket)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int32), total.view(torch.int32)) and torch.equal(theta.view(torch.int32), want.view(torch.int32))

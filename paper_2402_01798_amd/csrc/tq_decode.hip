@@ -27,9 +27,11 @@ struct DecodeArgs {
 // The word that holds the 8 codes of a group, as code_load (tq_layout.h) places it.  Nothing
 // here depends on the loaded value, so the load stays in flight until the codes are used; the
 // caller shifts by CodeLoad::first_bit (non-zero only for the last groups of a 3-bit payload).
-template <int BITS>
+// PAST (b = 4, whose loads of a wavefront are whole lines): past the caches, see tq_decode_many_kernel.
+template <int BITS, bool PAST = false>
 __device__ __forceinline__ uint32_t load_code_word(const uint8_t* stream, const CodeLoad& c)
 {
+    if constexpr (PAST) return __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(stream + c.load_off));
     if constexpr (BITS == 2) return *reinterpret_cast<const uint16_t*>(stream + c.load_off);
     uint32_t w;
     __builtin_memcpy(&w, stream + c.load_off, 4);          // b = 3: byte-aligned only
@@ -400,6 +402,9 @@ __global__ __launch_bounds__(kBlock) void tq_decode_fast_kernel(
 // Bound by the rate of LDS reads (one per four clocks and compute unit, 4 bytes wide as well as 8).  11.2 M
 // elements, N = 32, before (a loop over the workers, a load and eight look-ups each) -> now: b = 4 57.2 -> 44.7 us,
 // b = 3 56.1 -> 45.4 (50.6 with pairs), b = 2 46.3 -> 28.7; N = 64 106 -> 79.5, N = 12 at b = 4 21.6 -> 18.9.
+// The payloads at b = 4 are read past the caches, through / past them, us: 32 x 11.2 M 44.8 / 41.8, 16 x 40 M 91 / 81, 32 x 40 M
+// 156 / 142, 16 x 11.2 M and up to 32 x 2 M the same.  (At b = 2 and 3 a wavefront's load is half a line or not in place: 8 x 124 M at b = 2
+// 120 / 133, 16 x 25.6 M at b = 3 53 / 63; and few workers, tq_decode_fast_kernel, lose too: 8 x 11.2 M at b = 4 17.3 / 18.4, 1 x 124 M 83 / 98.)
 // PART: the last eight end after the pair that holds the last worker; without it they are looked up whole.  The branches
 // cost whole batches up to 6 % at b = 2 and 3 with two tiles (11.2 M, N = 24 at b = 3 28.0 -> 29.9 us) and give what the
 // rows past the last worker would take: N = 9 at b = 4 20.6 -> 17.2, N = 17 28.2 -> 25.6; 61,706 elements (one tile),
@@ -439,7 +444,7 @@ __global__ __launch_bounds__(kBlock) void tq_decode_many_kernel(
         for (int u = 0; u < C; ++u) {
             const uint8_t* stream = args.payload[c + u < N ? c + u : N - 1];
 #pragma unroll
-            for (int t = 0; t < T; ++t) w[t][u] = load_code_word<BITS>(stream, cl[t]);
+            for (int t = 0; t < T; ++t) w[t][u] = load_code_word<BITS, BITS == 4>(stream, cl[t]);
         }
     };
     uint32_t w[2][T][C];

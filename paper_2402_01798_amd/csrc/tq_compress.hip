@@ -1017,12 +1017,11 @@ __global__ __launch_bounds__(kBlock, segment_waves(DTYPE, BITS, T)) void tq_comp
 // this worker's message (the level of the code tq_compress_kernel would have written: same
 // draws, same arithmetic), without the round trip through a payload.  T tiles per workgroup, the compress kernel's
 // general path, and the decode kernel's whole-line stores wherever a whole wavefront has whole
-// groups: past the caches if the output is large (PAST_CACHES), except that large sums are stored a lane's 32 bytes at
-// a time, into lines that were just read.  Bound by its memory traffic and, at 25 M elements, by filling and draining the
+// groups.  Large outputs (PAST_CACHES, simulate_past) are written past the caches, and so is read what is read, old sums
+// in the pieces that are stored.  Bound by its memory traffic and, at 25 M elements, by filling and draining the
 // chip.  The mirrored path of the compress kernel, half-line stores / this: 61,706 fp32 at b = 3 3.8 / 3.4 / 2.9 us, 25.6 M
-// bf16 24.4 / 26.1 / 24.5, accumulating 37.5 / 40.1 / 37.3, in buckets of 1024 64 / 31.6 / 31.1, 124 M bf16 104 / 138 / 103.5;
-// 124 M fp32 accumulating 268 with whole lines, 260 without, bf16 220 both, 11.2 M bf16 17.0 / 18.0.  Whole lines laid out
-// through LDS, of which it reads little otherwise; in registers / through LDS, bf16 25.6 M at b = 4 26.7 / 26.0, 60 M
+// bf16 24.4 / 26.1 / 24.5, accumulating 37.5 / 40.1 / 37.3, in buckets of 1024 64 / 31.6 / 31.1, 124 M bf16 104 / 138 / 103.5.
+// Whole lines laid out through LDS, of which it reads little otherwise; in registers / through LDS, bf16 25.6 M at b = 4 26.7 / 26.0, 60 M
 // 57.1 / 55.2, 124 M 117.0 / 112.9 (b = 3 108.9 / 105.0, b = 2 107.0 / 106.5), fp32 the same.
 template <int DTYPE, int BITS, bool ACC, bool PAST_CACHES, int T>
 __global__ __launch_bounds__(kBlock) void tq_simulate_kernel(
@@ -1051,13 +1050,21 @@ __global__ __launch_bounds__(kBlock) void tq_simulate_kernel(
     if (wave_base >= bend) return;                             // and of the others
 
     // all reads first, the draws under them
+    // past the caches a lane's 32 bytes of fp32 are read as whole lines, of which half is not kept for the other half: a lane's
+    // own / whole lines, 62 M in buckets of 2176 126 / 112 us, of 1024 86.2 / 82.5, of 16384 80.1 / 77.8, 124 M 163 / 154.5
+    constexpr bool kLines = DTYPE == TQ_F32 && PAST_CACHES;
     float x[T][8], prev[T][8];
     uint32_t rw[T][4];
+    // the old sum: past the caches a whole wavefront reads the 16-byte pieces that it will store, otherwise each lane its own
     auto load_prev = [&](int t) {
-        const uint64_t e0 = wave_base + (uint64_t)t * kTile + (uint64_t)lane * kGroup;
+        const uint64_t base = wave_base + (uint64_t)t * kTile, e0 = base + (uint64_t)lane * kGroup;
         if (e0 + kGroup <= bend) {
-            const float4* o4 = reinterpret_cast<const float4*>(out + e0);
-            const float4 a = o4[0], b = o4[1];
+            const bool pieces = PAST_CACHES && base + 64 * kGroup <= bend;
+            const float4_native* pa = reinterpret_cast<const float4_native*>(out + (pieces ? base + 4u * lane : e0));
+            const float4_native* pb = pa + (pieces ? 64 : 1);
+            float4_native a, b;
+            if constexpr (PAST_CACHES) { a = __builtin_nontemporal_load(pa); b = __builtin_nontemporal_load(pb); }
+            else { a = *pa; b = *pb; }
             prev[t][0] = a.x; prev[t][1] = a.y; prev[t][2] = a.z; prev[t][3] = a.w;
             prev[t][4] = b.x; prev[t][5] = b.y; prev[t][6] = b.z; prev[t][7] = b.w;
         } else if (e0 < bend) {
@@ -1068,11 +1075,13 @@ __global__ __launch_bounds__(kBlock) void tq_simulate_kernel(
     };
 #pragma unroll
     for (int t = 0; t < T; ++t) {
-        const uint64_t e0 = wave_base + (uint64_t)t * kTile + (uint64_t)lane * kGroup;
+        const uint64_t base = wave_base + (uint64_t)t * kTile, e0 = base + (uint64_t)lane * kGroup;
 #pragma unroll
         for (int j = 0; j < 8; ++j) { x[t][j] = 0.0f; prev[t][j] = 0.0f; }
-        if (e0 + kGroup <= bend) {
-            load_group<DTYPE, false>(g, e0, x[t]);
+        if (kLines && base + 64 * kGroup <= bend) {
+            load_groups_wave(g, base, lane, x[t]);
+        } else if (e0 + kGroup <= bend) {
+            load_group<DTYPE, PAST_CACHES && !kLines>(g, e0, x[t]);
         } else if (e0 < bend) {
 #pragma unroll
             for (int j = 0; j < 7; ++j)                        // a ragged group has at most 7 elements
@@ -1089,15 +1098,23 @@ __global__ __launch_bounds__(kBlock) void tq_simulate_kernel(
     for (int t = 0; t < T; ++t) {
         const uint64_t base = wave_base + (uint64_t)t * kTile, e0 = base + (uint64_t)lane * kGroup;
         if (base >= bend) break;
+        if (kLines && base + 64 * kGroup <= bend) swap_pieces(x[t]);
         replace_nan(x[t]);
         const uint32_t word = encode_general<BITS, true>(x[t], rw[t], cb, lv, tab);
         float y[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             y[j] = tab.e[(word >> (j * BITS)) & S].x;
-            if constexpr (ACC) y[j] = prev[t][j] + y[j];
         }
-        if (!(ACC && PAST_CACHES) && base + 64 * kGroup <= bend) {
+        if (ACC && PAST_CACHES && base + 64 * kGroup <= bend) {
+            store8_wave_lds<PAST_CACHES>(out + base, lane, y, xbuf[wave], prev[t]);
+            continue;
+        }
+        if constexpr (ACC) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) y[j] = prev[t][j] + y[j];
+        }
+        if (base + 64 * kGroup <= bend) {
             store8_wave_lds<PAST_CACHES>(out + base, lane, y, xbuf[wave]);
         } else if (e0 + kGroup <= bend) {
             reinterpret_cast<float4*>(out + e0)[0] = make_float4(y[0], y[1], y[2], y[3]);
@@ -1269,6 +1286,20 @@ hipError_t tq_launch_compress(const void* const* g, int count, int dtype, uint64
 #undef TQ_LAUNCH_COMPRESS
 }
 
+// Whether a simulated gradient goes past the caches: outputs above 96 MiB, sums above 64 MiB.  us in one bucket, through / past
+// them, by themselves and with an elementwise reader of the result behind them: bf16 25.6 M 30.4 / 28.4 (60.7 / 61.5), 40 M
+// 44.4 / 41.4 (96.4 / 98.1), 62 M 62.9 / 60.4 (149 / 146), 124 M 122 / 120 (297 / 283); fp32 36.6 / 33.4 (71.4 / 66.3), 55.5 / 50.8
+// (111 / 107), 83.3 / 77.1 (176 / 162), 165 / 153 (342 / 318); sums, bf16 20 M 34.9 / 32.2 (57.0 / 57.2), 25.6 M 45.5 / 40.4
+// (75.3 / 72.7), 124 M 218 / 196 (381 / 359), fp32 43.5 / 38.4 (66.3 / 63.2), 55.4 / 48.6 (89.2 / 81.6), 258 / 239 (420 / 402); but below,
+// bf16 20 M 24.9 / 22.8 (47.7 / 49.7), 13 M 15.8 / 16.3 (33.5 / 34.7), sums 20.6 / 21.8 (37.9 / 38.4).  (From 62 M on "through" is stores
+// past them, loads and sums through.)  Buckets of less than a wavefront's 512 elements hold no whole line to store: there the
+// reads keep to the caches, sums of 25.6 M fp32 in buckets of 384 66.8 / 69.7.  62 M in buckets of 1024 and 2176: fp32 82.3 / 81.8
+// and 110.5 / 111.7, sums 126 / 112 and 172 / 143, bf16 77.2 / 74.1 and 107.3 / 104.4, sums 105 / 97.8 and 148 / 125.
+bool simulate_past(uint64_t d, uint64_t be, int accumulate)
+{
+    return be >= 512 && d * sizeof(float) > ((accumulate ? 64ull : 96ull) << 20);
+}
+
 // Host side of tq_quantize_dequantize after the argument checks of the C entry point.
 hipError_t tq_launch_simulate(const void* g, int dtype, uint64_t d, uint64_t bucket_elems, const tq_params_t* params,
                               int bits, uint64_t seed, uint32_t worker, uint32_t step, int accumulate, float* out,
@@ -1277,7 +1308,7 @@ hipError_t tq_launch_simulate(const void* g, int dtype, uint64_t d, uint64_t buc
     const uint64_t d_pad = (d + 127) / 128 * 128;
     const uint64_t be = bucket_elems ? bucket_elems : d_pad;
     const uint64_t nb = (d_pad + be - 1) / be;
-    const bool past = tq::output_past_caches(d * sizeof(float));
+    const bool past = simulate_past(d, be, accumulate);
     // one tile per workgroup; two for bf16 whose output leaves the caches, in buckets of at least four: 124 M at b = 3
     // 107 / 103.5 us, but 25.6 M 24.5 / 25.7 and 124 M in buckets of 2048 111 / 174
     const bool two = dtype == TQ_BF16 && past && !accumulate && be >= 4 * (uint64_t)tq::kTile;

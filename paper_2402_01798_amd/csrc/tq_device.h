@@ -169,6 +169,19 @@ __device__ __forceinline__ void store8_wave_lds(float* o, uint32_t lane, const f
     store_pieces<STREAM>(reinterpret_cast<float4_native*>(o) + lane, a, b);
 }
 
+// The same, added to what the lane's pieces held.
+template <bool STREAM>
+__device__ __forceinline__ void store8_wave_lds(float* o, uint32_t lane, const float (&x)[8], float4_native* wb, const float (&held)[8])
+{
+    wb[2 * lane] = float4_native{x[0], x[1], x[2], x[3]};
+    wb[2 * lane + 1] = float4_native{x[4], x[5], x[6], x[7]};
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const float4_native c = wb[lane], d = wb[64 + lane];
+    const float4_native a = {held[0] + c.x, held[1] + c.y, held[2] + c.z, held[3] + c.w};
+    const float4_native b = {held[4] + d.x, held[5] + d.y, held[6] + d.z, held[7] + d.w};
+    store_pieces<STREAM>(reinterpret_cast<float4_native*>(o) + lane, a, b);
+}
+
 // Inclusive prefix sums over a wavefront by moves inside the vector unit: inside rows of 16 lanes, then the
 // rows' totals handed on (lane 15 of a row to the next row, lane 31 to the upper half).  6 steps of a few clocks each,
 // where a shuffle through LDS takes about a hundred.  Lanes without a source see 0.  The whole wavefront is active.

@@ -61,3 +61,25 @@ def test_sums_and_plain_sgd(N, bits, extra, bucket):
     B.tq_decompress_aggregate_update(payload, params, theta, bits, eta, 0.0, 0.0, None, bucket)
     torch.cuda.synchronize()
     assert torch.equal(out.view(torch.int32), total.view(torch.int32)) and torch.equal(theta.view(torch.int32), want.view(torch.int32))
+
+
+@pytest.mark.parametrize("dtype,bits", [(torch.float32, 2), (torch.bfloat16, 3), (torch.float32, 4), (torch.bfloat16, 2)])
+@pytest.mark.parametrize("extra,bucket", [(3, 0), (2_047, 5 * 2048 + 128), (513, 1 << 20)])
+def test_simulated_gradients(dtype, bits, extra, bucket):
+    """Q[T(g)] is what the server decodes from this worker alone; a sum adds it to what was there."""
+    d = SINGLE + extra
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(bits)
+    g = (torch.randn(d, generator=gen, device="cuda") * 0.5).to(dtype)
+    g[:3] = torch.tensor([float("nan"), float("inf"), -float("inf")])
+    params = B.params_from_numpy(book(bits, B.num_buckets(d, bucket), np.random.default_rng(bits)))
+    payload = torch.empty(B.payload_bytes(d, bits), dtype=torch.uint8, device="cuda")
+    B.tq_compress(g, params, payload, bits, 5, 1, 2, bucket, B.GRID_UNIFORM)
+    want, out, old = torch.empty(d, device="cuda"), torch.full((d + 8,), 7.0, device="cuda"), torch.randn(d, generator=gen, device="cuda")
+    B.tq_decompress_aggregate([payload], [params], want, bits, bucket)
+    B.tq_quantize_dequantize(g, params, out[:d], bits, 5, 1, 2, bucket)
+    total = old + want
+    B.tq_quantize_dequantize(g, params, old, bits, 5, 1, 2, bucket, True)
+    torch.cuda.synchronize()
+    assert torch.equal(out[:d].view(torch.int32), want.view(torch.int32)) and (out[d:] == 7.0).all()
+    assert torch.equal(old.view(torch.int32), total.view(torch.int32))

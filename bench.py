@@ -43,7 +43,8 @@ VARIANTS = [("cfg4", 2, 0), ("cfg4", 2, 1), ("cfg2", 2, 0), ("cfg2", 4, 0), ("cf
 # bits, family and the size of the batch), as rocprofv3's SQ_INSTS_VALU counts them (profiles/valu_instructions.txt): they
 # decide which ceiling binds
 COMPRESS_VALU_PER_ELEM = {"cfg4/b2/g0": 17.0, "cfg4/b2/g1": 21.7, "cfg2/b2/g0": 15.5, "cfg2/b4/g0": 20.3, "cfg3/b3/g1": 25.2,
-                          "cfg5/b2/g1": 18.6}
+                          "cfg5/b2/g1": 12.6}
+COMPRESS_KERNEL = {"cfg5/b2/g1": "tq_compress_lookup_kernel"}      # where it is not tq_compress_kernel
 
 
 def parse():
@@ -335,7 +336,8 @@ def compress_roofline(path, res):
     N = path.N
     comp_us = res["stage_us_per_step"]["compress"]
     gbps = N * path.bytes_compress() / comp_us / 1e3
-    kernel = "tq_compress_segments_kernel" if path.seg is not None else "tq_compress_kernel"
+    kernel = "tq_compress_segments_kernel" if path.seg is not None else COMPRESS_KERNEL.get(
+        "%s/b%d/g%d" % (path.wl.name, path.bits, path.grid), "tq_compress_kernel")
     roof = {"kernel": kernel, "bound": "hbm", "achieved": round(gbps, 1), "peak": HBM_PEAK_GBPS,
             "unit": "GB/s", "frac": round(gbps / HBM_PEAK_GBPS, 4),
             "traffic": load_traffic(kernel, path.wl.name, path.bits, path.grid)}
@@ -356,7 +358,7 @@ def compress_roofline(path, res):
 
 
 # vector-ALU lane-operations per element of the statistics kernel (profiles/valu_instructions.txt)
-STATS_VALU_PER_ELEM = {"cfg4": 5.2, "cfg2": 5.6, "cfg3": 11.4, "cfg5": 10.0}
+STATS_VALU_PER_ELEM = {"cfg4": 5.2, "cfg2": 5.6, "cfg3": 10.3, "cfg5": 10.0}
 
 
 def stats_roofline(path, res):

@@ -36,7 +36,7 @@
 //     instruction fetch.
 // Measured on MI355X, us for one launch, against all-fp64 iteration on lane 0 of one kernel for
 // all families: uniform, 4 records 11.2 -> 4.7, 952 records 30.3 -> 7.2; non-uniform, 1 record
-// 18.7 -> 7.7, 768 records 34.3 -> 10.4, 2736 records 78 -> 25.3; BiScaled, 391 records 128 -> 19.3.
+// 18.7 -> 7.7, 768 records 34.3 -> 10.4, 2736 records 78 -> 21.5; BiScaled, 391 records 128 -> 19.3.
 // The search of BiScaled by one wavefront over the edges that can win instead of four over all of them, with their barriers:
 // 1 record 15.9 -> 13.6, 391 19.0 -> 16.6, 952 25.6 -> 17.4, 2736 168 -> 122.
 // 512 or 1024 threads per record instead of 256 gain 0.4 us on a single non-uniform record and lose
@@ -196,16 +196,17 @@ __device__ __forceinline__ float wave_min(float v)
 
 // Exclusive prefix sums over the bins: lane values v[k] of bins kParamsBlock k + tid.  On return v[k] is
 // the sum over all bins below; the grand total is returned.  `chunk` is 16 entries of LDS that
-// nobody else uses; one barrier.
+// nobody else uses; one barrier.  `live`, bit k: some lane's v[k] is not 0.
 template <typename T>
-__device__ __forceinline__ T bin_scan(T (&v)[kBinsPerLane], T* chunk)
+__device__ __forceinline__ T bin_scan(T (&v)[kBinsPerLane], uint32_t live, T* chunk)
 {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     T incl[kBinsPerLane];
 #pragma unroll
     for (int k = 0; k < kBinsPerLane; ++k) {
-        incl[k] = wave_scan(v[k]);
+        incl[k] = v[k];
+        if (live >> k & 1u) incl[k] = wave_scan(v[k]);
         if (lane == 63) chunk[kParamsWaves * k + wave] = incl[k];
     }
     __syncthreads();
@@ -322,6 +323,11 @@ __device__ __forceinline__ void design(ParamsLds<GRID != TQ_GRID_UNIFORM, WIDE, 
             h[k] = i < kNB ? S->hist[i] : 0u;
         }
     }
+    // bit k: some of the wavefront's bins k count something.  A record of 16,384 elements leaves most of the 15 groups of 64 bins
+    // empty, and thousands of records are bound by how many instructions they issue: empty groups are left out of the scans, the
+    // search for the tail's bin and its logarithms (2736 records uniform 10.1 -> 9.4 us, non-uniform 22.7 -> 21.5, BiScaled of 768
+    // 15.9 -> 15.4; 4 records non-uniform 7.4 -> 7.3)
+    uint32_t live = (1u << kBinsPerLane) - 1u;
     const double centre_log = kOctaveLogs.centre[(tid - 1) & 15], edge_log = kOctaveLogs.edge[(tid - 1) & 15];
     const double absmax = (double)S->absmax;
     const float given_g_min = S->g_min;
@@ -356,13 +362,17 @@ __device__ __forceinline__ void design(ParamsLds<GRID != TQ_GRID_UNIFORM, WIDE, 
         }
     } else {
 #pragma unroll
-        for (int k = 0; k < kBinsPerLane; ++k) cum[k] = h[k];
-        const uint32_t n_count = bin_scan(cum, L.chunk_count);
+        for (int k = 0; k < kBinsPerLane; ++k) {
+            cum[k] = h[k];
+            if (__builtin_amdgcn_ballot_w64(h[k] != 0u) == 0ull) live &= ~(1u << k);
+        }
+        const uint32_t n_count = bin_scan(cum, live, L.chunk_count);
         n = (double)n_count;
 #pragma unroll
         for (int k = 0; k < kBinsPerLane; ++k) {
             const int i = kParamsBlock * k + tid;
             if (i < kNB) L.bins.hc[i] = make_uint2(h[k], cum[k]);
+            if (!(live >> k & 1u)) continue;
             const uint64_t mark = 9ull * n_count;
             if (10ull * cum[k] < mark && 10ull * ((uint64_t)cum[k] + h[k]) >= mark) {
                 L.tail_bin = i;
@@ -387,6 +397,7 @@ __device__ __forceinline__ void design(ParamsLds<GRID != TQ_GRID_UNIFORM, WIDE, 
         double local_t = 0.0;
 #pragma unroll
         for (int k = 0; k < kBinsPerLane; ++k) {
+            if (!(live >> k & 1u)) continue;
             const int i = kParamsBlock * k + tid;
             const double from_octave = i < kNB - 1 ? centre_log : 0.0;
             double here = 0.0;
@@ -425,7 +436,7 @@ __device__ __forceinline__ void design(ParamsLds<GRID != TQ_GRID_UNIFORM, WIDE, 
         }
 #pragma unroll
         for (int k = 0; k < kBinsPerLane; ++k) pw[k] = kParamsBlock * k + tid < kNB ? L.H[kParamsBlock * k + tid] : 0.0;
-        const double all = bin_scan(pw, L.chunk_h);
+        const double all = bin_scan(pw, live, L.chunk_h);
 #pragma unroll
         for (int k = 0; k < kBinsPerLane; ++k) {
             const int i = kParamsBlock * k + tid;

@@ -230,3 +230,33 @@ def test_records_whose_iteration_does_not_settle(bits, grid):
         own = OP.tq_params(st[i:i + 1].view(O.STATS_DTYPE), bits, grid, alpha)[0]
         assert np.allclose(g["level"], own["level"], rtol=1e-6, atol=0), i
         assert np.allclose(g["inv_w"], own["inv_w"], rtol=2e-6, atol=0), i
+
+
+@pytest.mark.parametrize("bits", [2, 4])
+@pytest.mark.parametrize("grid", [B.GRID_UNIFORM, B.GRID_NONUNIFORM, B.GRID_BISCALED])
+def test_groups_of_empty_bins(bits, grid):
+    """Groups of 64 bins that count nothing are left out: one group alone, its first or its last bin alone, every other group,
+    all but one group, the tail's bin at a group's edges."""
+    rng = np.random.default_rng(bits)
+    out = []
+    for group in range(14):
+        alone = np.zeros(898, dtype=np.int64)
+        alone[64 * group + (group == 0):64 * group + 64] = rng.integers(1, 1000, 64 - (group == 0))
+        first, last, without = np.zeros(898, dtype=np.int64), np.zeros(898, dtype=np.int64), np.zeros(898, dtype=np.int64)
+        first[max(64 * group, 1)] = 90
+        first[max(64 * group, 1) + 20] = 10                # 90 of 100: the tail starts at the group's first bin
+        last[64 * group + 63] = 95
+        last[min(64 * group + 70, 896)] += 5
+        without[1:897] = np.round(1e6 * 2.0 ** (-np.arange(896) / 16))
+        without[64 * group:64 * group + 64] = 0
+        out += [alone, first, last, without]
+    for odd in (0, 1):
+        every_other = np.zeros(898, dtype=np.int64)
+        for group in range(odd, 14, 2):
+            every_other[64 * group + 1:64 * group + 64] = 5000 >> group // 2
+        out.append(every_other)
+    st = np.concatenate([record(h, edge(int(np.nonzero(h)[0].max())) * 1.01) for h in out])
+    got, want = design(st, bits, grid)
+    steady = (want["flags"] & 4) == 0
+    assert steady.sum() >= st.size // 2 and (got["flags"][steady] == want["flags"][steady]).all()
+    assert_params_close(got[steady], want[steady])

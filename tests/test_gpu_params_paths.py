@@ -260,3 +260,22 @@ def test_groups_of_empty_bins(bits, grid):
     steady = (want["flags"] & 4) == 0
     assert steady.sum() >= st.size // 2 and (got["flags"][steady] == want["flags"][steady]).all()
     assert_params_close(got[steady], want[steady])
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
+def test_the_same_iteration_inside_and_outside_the_regular_bins(bits):
+    """Thresholds that stay below 65536 take their bin from their bits, others the general form.  Scaled by 8 -- three octaves, where
+    cube roots scale by 4 -- the plain iteration does the same arithmetic, so its result scales to the bit."""
+    low, high = [], []
+    # (2.2, 400), (2.5, 400) and (2.9, 300) do not settle in 100 steps at b = 2, 3 and 4
+    for gamma, width in [(g, w) for g in (2.05, 2.2, 2.5, 3.0, 4.0, 6.0, 9.0) for w in (60, 150, 400)] + [(2.9, 300)]:
+        h = np.zeros(898, dtype=np.int64)
+        h[897 - width:897] = np.round(2_000_000 * 2.0 ** (-(gamma - 1) * np.arange(width) / 16)) + 1
+        high.append(record(h, 65536.0))
+        low.append(record(np.concatenate([h[192:897], np.zeros(193, dtype=np.int64)]), 16.0))
+    got, _ = design(np.concatenate(low), bits, B.GRID_NONUNIFORM)
+    up, _ = design(np.concatenate(high), bits, B.GRID_NONUNIFORM)
+    slow = (got["flags"] & 4) != 0                            # never handed to the Newton steps
+    assert slow.any() and (got["flags"] == up["flags"]).all()
+    assert (got["alpha"][slow] * np.float32(4096) == up["alpha"][slow]).all() and (got["level"][slow] * np.float32(4096) == up["level"][slow]).all()
+    assert np.allclose(got["alpha"] * np.float32(4096), up["alpha"], rtol=1e-6, atol=0)

@@ -291,17 +291,19 @@ struct DensityView {
     }
     __device__ __forceinline__ double inv_half_int(double t) const     // smallest x with int_0^x p^(1/3) >= t
     {
-        // smallest i with H[i+1] >= t = how many of H[1 ..] are below t: three rounds of independent reads, 64, 8 and 1 bins
-        // apart, instead of ten of one read each (1 record 7.0 -> 6.8 us, 400 8.1 -> 7.9)
-        int lo = 0, n = 0;
+        // i with H[i] < t <= H[i+1], the smallest of those that are met: three rounds of independent reads, 64, 8 and 1 bins
+        // apart, instead of ten of one read each (1 record 7.0 -> 6.8 us, 400 8.1 -> 7.9).  Each round goes on below the
+        // first of its reads that is not below t, which keeps H[lo] < t <= the next one also where H is not monotone: its
+        // sums are added in an order that depends on the lane, and over empty bins they differ by an ulp.
+        int lo = 0, n = 14;
 #pragma unroll
-        for (int m = 1; m <= 14; ++m) n += L.H[64 * m] < t ? 1 : 0;
+        for (int m = 14; m >= 1; --m) n = L.H[64 * m] < t ? n : m - 1;
         lo = 64 * n;
 #pragma unroll
         for (int step = 8; step >= 1; step >>= 3) {
-            n = 0;
+            n = 7;
 #pragma unroll
-            for (int m = 1; m <= 7; ++m) n += L.H[lo + step * m < kNB ? lo + step * m : kNB] < t ? 1 : 0;
+            for (int m = 7; m >= 1; --m) n = L.H[lo + step * m < kNB ? lo + step * m : kNB] < t ? n : m - 1;
             lo += step * n;
         }
         if (lo >= kNB) return 65536.0 + last_bin_width(absmax);

@@ -279,3 +279,48 @@ def test_the_same_iteration_inside_and_outside_the_regular_bins(bits):
     assert slow.any() and (got["flags"] == up["flags"]).all()
     assert (got["alpha"][slow] * np.float32(4096) == up["alpha"][slow]).all() and (got["level"][slow] * np.float32(4096) == up["level"][slow]).all()
     assert np.allclose(got["alpha"] * np.float32(4096), up["alpha"], rtol=1e-6, atol=0)
+
+
+def levels_at_gaps(s, count):
+    """Records of two blocks of equal bins with empty bins between them, the largest magnitude at the lower edge of its bin:
+    j / s of the integral of density^(1/3) is the first block's, with j odd as the levels have it, so a level lies at the gap."""
+    rng, out = np.random.default_rng(s), []
+    while len(out) < count:
+        j, octave, higher = 2 * int(rng.integers(1, (s + 1) // 2)) - 1, int(rng.integers(0, 40)), int(rng.integers(1, 4))
+        n1, n2 = int(rng.integers(1, 16)), int(rng.integers(1, 17))
+        lo1 = 1 + 16 * octave + int(rng.integers(0, 17 - n1))
+        lo2 = 1 + 16 * (octave + 3 * higher) + int(rng.integers(0, 17 - n2))
+        # three octaves up a bin is 8 times as wide, its share 4 times: c1^(1/3) n1 (s - j) = j 4^higher c2^(1/3) n2
+        a, b = j * 4 ** higher * n2, n1 * (s - j)
+        a, b = a // np.gcd(a, b), b // np.gcd(a, b)
+        if max(a, b) > 1500:
+            continue
+        h = np.zeros(898, dtype=np.int64)
+        h[lo1:lo1 + n1], h[lo2:lo2 + n2], h[lo2 + n2] = a ** 3, b ** 3, 1
+        out.append(record(h, edge(lo2 + n2)))
+    h = np.zeros(898, dtype=np.int64)
+    h[321:331], h[380:385], h[385] = 4, 4, 1
+    return np.concatenate(out + [record(h, edge(385))])
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
+def test_levels_where_the_integral_stands_still(bits):
+    """The sums over the bins differ by an ulp from one empty bin to the next, so a level at a gap can be found at
+    any point of it.  Wherever it is, the integral there is j / s of the whole.  A level's rounding
+    to binary32 moves it by at most 2^-24 of its magnitude, 32 bin widths: by 2^-19 of one bin's share."""
+    s = (1 << bits) - 1
+    st = levels_at_gaps(s, 1500)
+    dev = torch.from_numpy(st.view(np.uint8).reshape(-1).copy()).cuda()
+    pr = torch.full((st.size * B.PARAMS_BYTES,), 0x77, dtype=torch.uint8, device="cuda")
+    B.tq_params(dev, pr, bits, B.GRID_NONUNIFORM, -1.0)       # alpha = max|g|
+    torch.cuda.synchronize()
+    got = B.params_to_numpy(pr)
+    want = np.arange(1, s + 1, 2) / s
+    off = []
+    for r, q in zip(st, got):
+        dens = OP.Density(r["hist"], r["absmax"])
+        assert (q["level"][:s + 1] == -q["level"][s::-1]).all()
+        up = [dens.half_int_p13(float(x)) if np.isfinite(x) else np.inf for x in q["level"][(s + 1) // 2:s + 1]]
+        off.append(np.abs(np.array(up) / dens.half_int_p13(float(q["alpha"])) - want).max())
+    off = np.array(off)
+    assert (off <= 2.0 ** -19).all(), (np.nonzero(off > 2.0 ** -19)[0], off.max())

@@ -14,6 +14,8 @@ import torch
 HERE = os.path.dirname(os.path.abspath(__file__))
 try:
     from . import _tq_marshal
+    if getattr(_tq_marshal, "interface", 0) != 1:
+        raise ImportError("built from other sources than this file's")
 except ImportError as e:                # the loops below do the same, slower
     _tq_marshal = None
     if os.path.exists(os.path.join(HERE, "_tq_marshal.so")):

@@ -522,4 +522,10 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_tq_marshal", nullptr, -1, methods
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__tq_marshal() { return PyModule_Create(&module); }
+// `interface`: what binding.py asks for before it uses the module; it goes up with every change to the functions or their arguments.
+PyMODINIT_FUNC PyInit__tq_marshal()
+{
+    PyObject* m = PyModule_Create(&module);
+    if (m && PyModule_AddIntConstant(m, "interface", 1) != 0) Py_CLEAR(m);
+    return m;
+}

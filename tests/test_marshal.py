@@ -31,6 +31,32 @@ def test_a_module_that_does_not_load_is_told(built, tmp_path):
     assert ("_tq_marshal.so does not load" in run.stderr) == built
 
 
+@pytest.mark.parametrize("functions", ["", "pointers = sized = lambda *a: None", "interface = 2"])
+def test_a_module_of_other_sources_is_not_used(functions, tmp_path):
+    """One that loads but was built before (or after) the functions the binding calls: told, and the calls go the Python way."""
+    pkg = tmp_path / "paper_2402_01798_amd"
+    (pkg / "_tq_marshal").mkdir(parents=True)
+    for name in ("__init__.py", "binding.py"):
+        shutil.copy(os.path.join(B.HERE, name), pkg)
+    (pkg / "_tq_marshal" / "__init__.py").write_text(functions)
+    (pkg / "_tq_marshal.so").write_bytes(b"the package above it is found first")
+    program = """if True:
+        import torch
+        from paper_2402_01798_amd import binding as b
+        t = torch.zeros(4)
+        for call in (lambda: b.tq_stats(t, t, t), lambda: b.tq_params_multi([t], [t], 3, 0), lambda: b.tq_compress(t, t, t, 3, 0, 0, 0)):
+            try:
+                call()
+            except (ValueError, b.TqError):
+                continue
+            raise AssertionError("not refused")
+    """
+    run = subprocess.run([sys.executable, "-c", program], cwd=tmp_path, capture_output=True, text=True, timeout=300,
+                         env={**os.environ, "TQ_LIBRARY_PATH": B.LIB_PATH})
+    assert run.returncode == 0, run.stderr
+    assert "_tq_marshal.so does not load" in run.stderr
+
+
 def test_sized():
     ts = [torch.zeros(8), torch.nn.Parameter(torch.zeros(8)), torch.zeros(2, 4)]
     for seq in (ts, tuple(ts)):

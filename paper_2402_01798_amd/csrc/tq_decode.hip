@@ -27,7 +27,7 @@ struct DecodeArgs {
 // The word that holds the 8 codes of a group, as code_load (tq_layout.h) places it.  Nothing
 // here depends on the loaded value, so the load stays in flight until the codes are used; the
 // caller shifts by CodeLoad::first_bit (non-zero only for the last groups of a 3-bit payload).
-// PAST (b = 4, whose loads of a wavefront are whole lines): past the caches, see tq_decode_many_kernel.
+// PAST (b = 4, whose loads of a wavefront are whole lines): past the caches, see payloads_past.
 template <int BITS, bool PAST = false>
 __device__ __forceinline__ uint32_t load_code_word(const uint8_t* stream, const CodeLoad& c)
 {
@@ -402,14 +402,12 @@ __global__ __launch_bounds__(kBlock) void tq_decode_fast_kernel(
 // Bound by the rate of LDS reads (one per four clocks and compute unit, 4 bytes wide as well as 8).  11.2 M
 // elements, N = 32, before (a loop over the workers, a load and eight look-ups each) -> now: b = 4 57.2 -> 44.7 us,
 // b = 3 56.1 -> 45.4 (50.6 with pairs), b = 2 46.3 -> 28.7; N = 64 106 -> 79.5, N = 12 at b = 4 21.6 -> 18.9.
-// The payloads at b = 4 are read past the caches, through / past them, us: 32 x 11.2 M 44.8 / 41.8, 16 x 40 M 91 / 81, 32 x 40 M
-// 156 / 142, 16 x 11.2 M and up to 32 x 2 M the same.  (At b = 2 and 3 a wavefront's load is half a line or not in place: 8 x 124 M at b = 2
-// 120 / 133, 16 x 25.6 M at b = 3 53 / 63; and few workers, tq_decode_fast_kernel, lose too: 8 x 11.2 M at b = 4 17.3 / 18.4, 1 x 124 M 83 / 98.)
+// PAST: the payloads are read past the caches (payloads_past).
 // PART: the last eight end after the pair that holds the last worker; without it they are looked up whole.  The branches
 // cost whole batches up to 6 % at b = 2 and 3 with two tiles (11.2 M, N = 24 at b = 3 28.0 -> 29.9 us) and give what the
 // rows past the last worker would take: N = 9 at b = 4 20.6 -> 17.2, N = 17 28.2 -> 25.6; 61,706 elements (one tile),
 // N = 17 at b = 3 7.0 -> 4.5.
-template <int BITS, int U, int T, int MODE, bool PART>
+template <int BITS, int U, int T, int MODE, bool PART, bool PAST>
 __global__ __launch_bounds__(kBlock) void tq_decode_many_kernel(
     const DecodeArgs args, int N, int weighted, float scale, uint64_t d, uint64_t d_pad, uint64_t bucket_elems,
     uint32_t groups_per_bucket, uint64_t payload_bytes, float* __restrict__ out, const Update up)
@@ -444,7 +442,7 @@ __global__ __launch_bounds__(kBlock) void tq_decode_many_kernel(
         for (int u = 0; u < C; ++u) {
             const uint8_t* stream = args.payload[c + u < N ? c + u : N - 1];
 #pragma unroll
-            for (int t = 0; t < T; ++t) w[t][u] = load_code_word<BITS, BITS == 4>(stream, cl[t]);
+            for (int t = 0; t < T; ++t) w[t][u] = load_code_word<BITS, PAST>(stream, cl[t]);
         }
     };
     uint32_t w[2][T][C];
@@ -616,6 +614,25 @@ bool reads_past(int mode, uint64_t d, uint64_t bucket_elems)
     return d * sizeof(float) > ((mode == tq::kSgdMomentum ? 32ull : 96ull) << 20) && bucket_elems >= 16 * (uint64_t)tq::kTile;
 }
 
+// Whether the payloads of a launch of tq_decode_many_kernel are read past the caches: up to 16 MiB of them, and from 112 MiB on
+// unless too many loads repeat the last worker's (the kernel requests eight workers' words at a time), which the caches answer.
+// Through / past them at b = 4, us:
+//   d       N = 9          12            16            17            25            32            64
+//   1 M     4.4 / 4.4      4.6 / 4.5     5.1 / 5.0     6.2 / 6.1     7.5 / 7.2     8.2 / 7.8     13.4 / 13.0
+//   4 M     8.2 / 8.2      8.8 / 8.8     10.2 / 10.3   12.1 / 13.0   14.6 / 15.3   16.6 / 17.3   30.2 / 29.2
+//   8 M     13.5 / 15.3    15.7 / 17.1   17.4 / 19.0   20.8 / 23.4   27.5 / 27.2   35.5 / 33.5   62.9 / 59.5
+//   11.2 M  18.1 / 20.9    19.5 / 22.4   25.6 / 25.8   28.5 / 30.7   36.3 / 34.7   43.9 / 41.5   78.0 / 72.9
+//   40 M    70.0 / 68.1    76.9 / 72.8   92.2 / 86.9   96.5 / 101.6  127.6 / 121.3 156.5 / 149.8
+//   80 M    118.0 / 121.2  139.1 / 133.3 168.2 / 158.6
+// With momentum 12 x 5 M 19.3 / 23.4, 16 x 11.2 M 44.7 / 46.9, 32 x 11.2 M 66.3 / 64.5; added to a sum 32 x 11.2 M 58.7 / 51.1.
+// At b = 2 and 3 a wavefront's load is half a line or not in place: 8 x 124 M at b = 2 120 / 133, 16 x 25.6 M at b = 3 53 / 63; and few
+// workers, tq_decode_fast_kernel, lose too: 8 x 11.2 M at b = 4 17.3 / 18.4, 1 x 124 M 83 / 98.
+bool payloads_past(int bits, int N, uint64_t payload_bytes)
+{
+    const uint64_t all = (uint64_t)N * payload_bytes;
+    return bits == 4 && (all <= (16ull << 20) || (all > (112ull << 20) && 3 * ((N + 7) / 8 * 8) <= 4 * N));
+}
+
 // Whether launches of this kind can be above it: kStore is the mode of outputs of 64 to 160 MiB.
 template <int MODE>
 constexpr bool lds_possible(int bits, int U)
@@ -684,18 +701,28 @@ hipError_t launch_mode(const DecodeGeom& g, float* out, const tq::Update& up, hi
     }
 
     // two tiles per workgroup, one where all workgroups are resident at once (eight per compute unit); one / two on
-    // 11.2 M elements, N = 32: b = 4 45.5 / 44.7 us, b = 2 29.6 / 28.7
-    const bool one_tile = g.nb * g.tpb <= 2048, part = g.bits == 4 && N % 8 != 0;
+    // 11.2 M elements, N = 32: b = 4 45.5 / 44.7 us, b = 2 29.6 / 28.7.  So many tiles are at most 16 MiB of output, which some
+    // modes are not for (streams_output, reads_past).
+    constexpr bool kSmall = MODE != tq::kStore && (MODE & tq::kPast) == 0;
+    const bool one_tile = kSmall && g.nb * g.tpb <= 2048, part = g.bits == 4 && N % 8 != 0;
+    const bool past = payloads_past(g.bits, N, g.pbytes);
     const uint64_t gpb = one_tile ? g.tpb : (g.tpb + 1) / 2;
     dim3 blocks;
     if (!tq::fold_grid(g.nb * gpb, tq::kBlock, 1, blocks)) return hipErrorInvalidValue;
 #define TQ_LAUNCH_MANY_AS(B, UU, T, PART)                                                                      \
-    hipLaunchKernelGGL((tq::tq_decode_many_kernel<B, UU, T, MODE, PART>), blocks, threads, 0, st, g.args, N, g.weighted, \
+    do {                                                                                                       \
+        if (past) TQ_LAUNCH_MANY_READ(B, UU, T, PART, (B == 4));                                               \
+        else TQ_LAUNCH_MANY_READ(B, UU, T, PART, false);                                                       \
+    } while (0)
+#define TQ_LAUNCH_MANY_READ(B, UU, T, PART, PAST)                                                              \
+    hipLaunchKernelGGL((tq::tq_decode_many_kernel<B, UU, T, MODE, PART, PAST>), blocks, threads, 0, st, g.args, N, g.weighted, \
                        g.scale, g.d, g.d_pad, g.be, (uint32_t)gpb, g.pbytes, out, up)
 #define TQ_LAUNCH_MANY(B, UU)                                          \
     do {                                                               \
-        if (one_tile) TQ_LAUNCH_MANY_AS(B, UU, 1, true);               \
-        else if (part) TQ_LAUNCH_MANY_AS(B, UU, 2, (B == 4));          \
+        if constexpr (kSmall) {                                        \
+            if (one_tile) { TQ_LAUNCH_MANY_AS(B, UU, 1, true); break; } \
+        }                                                              \
+        if (part) TQ_LAUNCH_MANY_AS(B, UU, 2, (B == 4));               \
         else TQ_LAUNCH_MANY_AS(B, UU, 2, false);                       \
     } while (0)
     switch (g.bits) {
@@ -708,6 +735,7 @@ hipError_t launch_mode(const DecodeGeom& g, float* out, const tq::Update& up, hi
             break;
     }
 #undef TQ_LAUNCH_MANY
+#undef TQ_LAUNCH_MANY_READ
 #undef TQ_LAUNCH_MANY_AS
     return hipGetLastError();
 }

@@ -83,3 +83,26 @@ def test_simulated_gradients(dtype, bits, extra, bucket):
     torch.cuda.synchronize()
     assert torch.equal(out[:d].view(torch.int32), want.view(torch.int32)) and (out[d:] == 7.0).all()
     assert torch.equal(old.view(torch.int32), total.view(torch.int32))
+
+
+# payloads of up to 16 MiB, of 18 to 112 and above, one and two tiles a workgroup, whole and broken batches of eight workers
+@pytest.mark.parametrize("N,d", [(9, 61_707), (33, 1_000_003), (20, 2_000_003), (64, 4_000_001), (12, 4_500_001), (16, 5_000_003),
+                                 (16, 15_000_001), (25, 10_000_001), (17, 15_000_003), (40, 6_000_002)])
+@pytest.mark.parametrize("bucket", [0, 300 * 2048 + 128])
+def test_many_workers_at_four_bits(N, d, bucket):
+    """The levels added in worker order and scaled, the same roundings in torch."""
+    bits, nb = 4, B.num_buckets(d, bucket)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d % 1000 + N)
+    recs = [book(bits, nb, np.random.default_rng(1000 * N + i)) for i in range(N)]
+    payload = [torch.randint(0, 256, (B.payload_bytes(d, bits),), generator=gen, device="cuda", dtype=torch.uint8) for _ in range(N)]
+    out = torch.full((d + 8,), 7.0, device="cuda")
+    B.tq_decompress_aggregate(payload, [B.params_from_numpy(r) for r in recs], out[:d], bits, bucket)
+    first = torch.arange(d, device="cuda") // (bucket or d) * 16
+    want = torch.zeros(d, device="cuda")
+    for r, p in zip(recs, payload):
+        codes = torch.stack([p & 15, p >> 4], 1).view(-1)[:d]
+        want += torch.from_numpy(r["level"].reshape(-1).copy()).cuda()[first + codes]
+    want *= torch.tensor(1.0 / N, dtype=torch.float32, device="cuda")
+    torch.cuda.synchronize()
+    assert torch.equal(out[:d].view(torch.int32), want.view(torch.int32)) and (out[d:] == 7.0).all()

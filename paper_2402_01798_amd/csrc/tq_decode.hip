@@ -602,16 +602,24 @@ constexpr uint64_t lds_above(int bits, int U)
     return bits == 2 && U == 2 ? 2048 * kMiB : kNever;
 }
 
-// Whether an update (or a sum) goes past the caches: from 96 MiB of what it reads back on, or 64 MiB of parameters and velocity,
-// in buckets of which few ranges are cut.  us, through / past the caches, by themselves and with two elementwise kernels behind them of which
-// the first reads the result: momentum 8 x 8 M 26.8 / 26.5 (48.1 / 48.9), 9 M 30.6 / 29.6 (54.3 / 54.0), 16 M 57.3 / 49.8 (93.4 / 93.0), 25.6 M 91.2 / 77.1
-// (150 / 143), 62 M 214 / 194 (381 / 368), 124 M 430 / 383 (766 / 742), 32 x 25.6 M 148 / 139 (211 / 203); sgd 4 x 8 M 13.0 / 13.7
-// (33.7 / 35.9), 16 M 23.4 / 24.2 (63.0 / 64.8), 25.6 M 41.6 / 37.1 (98.5 / 99.5), 62 M 101 / 85 (268 / 255); accumulate 8 x 16 M 34.3 / 32.4
-// (73.4 / 74.9), 25.6 M 58.5 / 52.3 (115 / 113), 62 M 137 / 121 (306 / 306), 124 M 275 / 240 (611 / 601).  Loads alone 92.5 -> 89.2 of 25.6 M
-// with momentum, stores alone 93.2: it takes both.  A lane's own 32 bytes each way gave nothing.
-bool reads_past(int mode, uint64_t d, uint64_t bucket_elems)
+// Whether an update (or a sum) goes past the caches, in buckets of which few ranges are cut: from 96 MiB of parameters (or sum) on,
+// with momentum from 88 MiB of parameters (at least 32), velocity and payloads on.  us, through / past the caches, by themselves, with an elementwise
+// kernel behind them that reads the result, and with another one behind that; the lines lie where the three together gain:
+//   momentum  1 x 8.5 M, b = 3 (68 MiB)    23.0 / 23.9  33.7 / 35.5  45.1 / 46.9      1 x 10 M, b = 3 (80)     26.2 / 27.6  41.2 / 41.6  54.5 / 54.7
+//             8 x 8.5 M, b = 3 (89)        29.2 / 28.1  39.7 / 40.1  51.3 / 51.2      4 x 11.2 M, b = 2 (96)   33.5 / 32.0  47.6 / 47.2  61.9 / 61.0
+//             16 x 8.5 M, b = 2 (97)       37.5 / 33.9  49.0 / 46.2  60.5 / 57.6      8 x 10 M, b = 4 (114)    38.2 / 35.1  51.0 / 50.2  64.5 / 63.6
+//             8 x 16 M, b = 3 (168)        57.2 / 50.7  76.4 / 74.5  93.2 / 93.5      25 x 10 M, b = 3 (166)   60.8 / 57.1  72.7 / 73.2  86.0 / 85.9
+//             8 x 25.6 M, b = 3 (269)      90.4 / 78.9  125 / 116    151 / 144        8 x 124 M, b = 3         430 / 383                 766 / 742
+//   sgd       4 x 22 M, b = 2 (84 MiB)     34.4 / 32.7  59.9 / 61.9  85.5 / 87.5      4 x 25.6 M (98)          41.3 / 37.2  70.8 / 70.8  98.6 / 100.0
+//             4 x 32 M (122)               52.5 / 45.6  93.2 / 89.6  122 / 122        4 x 62 M                 101 / 86.5   182 / 174    268 / 257
+//   sums      8 x 22 M, b = 3 (84)         45.3 / 43.2  70.3 / 72.0  94.6 / 97.2      8 x 25.6 M (98)          53.0 / 49.7  85.7 / 84.0  110 / 112
+//             8 x 32 M (122)               65.0 / 61.4  109 / 109    138 / 136        8 x 62 M                 122 / 115    204 / 201    291 / 286
+// The same buffers again and again with nothing in between stay in the caches up to about 20 M: 8 x 16 M with momentum 45.7 / 48.1, 25.6 M
+// 79.0 / 73.5.  Loads alone 92.5 -> 89.2 of 25.6 M with momentum, stores alone 93.2: it takes both.  A lane's own 32 bytes each way gave nothing.
+bool reads_past(int mode, uint64_t d, uint64_t payloads, uint64_t bucket_elems)
 {
-    return d * sizeof(float) > ((mode == tq::kSgdMomentum ? 32ull : 96ull) << 20) && bucket_elems >= 16 * (uint64_t)tq::kTile;
+    const uint64_t bytes = d * sizeof(float), all = mode == tq::kSgdMomentum ? 2 * bytes + payloads : bytes;
+    return bytes > (32ull << 20) && all > ((mode == tq::kSgdMomentum ? 88ull : 96ull) << 20) && bucket_elems >= 16 * (uint64_t)tq::kTile;
 }
 
 // Whether the payloads of a launch of tq_decode_many_kernel are read past the caches: up to 16 MiB of them, and from 112 MiB on
@@ -768,7 +776,7 @@ hipError_t tq_launch_decode(const void* const* payload, const tq_params_t* const
     g.pbytes = tq_payload_bytes(d, bits);
     const tq::Update up{eta, momentum, weight_decay, velocity};
     if (mode == tq::kStore && streams_output(d)) mode = tq::kStoreStream;
-    else if (tq::reads_back(mode) && reads_past(mode, d, g.be)) mode |= tq::kPast;
+    else if (tq::reads_back(mode) && reads_past(mode, d, (uint64_t)N * g.pbytes, g.be)) mode |= tq::kPast;
     switch (mode) {
         case tq::kStore: return launch_mode<tq::kStore>(g, out, up, st);
         case tq::kStoreStream: return launch_mode<tq::kStoreStream>(g, out, up, st);

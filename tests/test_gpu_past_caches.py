@@ -34,7 +34,7 @@ def server(d, N, bits, bucket):
     return payload, params, g_bar, theta, vel
 
 
-SINGLE, DOUBLE = 96 * MIB // 4, 32 * MIB // 4                 # elements above which they go past the caches
+SINGLE, DOUBLE = 96 * MIB // 4, 48 * MIB // 4                 # elements above which they go past the caches, whatever the payloads
 
 
 @pytest.mark.parametrize("N,bits", [(1, 4), (3, 2), (8, 3), (16, 2), (12, 4), (20, 3), (33, 4)])

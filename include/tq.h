@@ -157,8 +157,10 @@ int tq_params(const tq_stats_t* stats_dev, uint64_t nb, int bits, int grid,
  *                It chooses the shape of the launch and nothing else: the records live on
  *                the device, and the two families run fastest with different numbers of
  *                tiles per workgroup.  Every bucket is encoded as ITS record says, so the
- *                payload is the same whatever is passed here; a wrong value costs about a
- *                tenth of the speed.
+ *                payload is the same whatever is passed here; a wrong value costs speed:
+ *                about a tenth, and bf16 batches of 2^25 elements and more up to a half
+ *                (tables given as uniform at b = 4) or four fifths (uniform records given as
+ *                tables, 2^25 elements at b = 4)
  *   payload_dev  [tq_payload_bytes(d, bits)] written in full, padding included
  */
 int tq_compress(const void* g_dev, int dtype, uint64_t d, uint64_t bucket_elems,

@@ -641,9 +641,13 @@ __global__ __launch_bounds__(kBlock, !MIRROR && T <= 2 && !(DTYPE == TQ_BF16 && 
 //   f: u(r) = 1 - (r + 1/2) / 2^16 <= p_r  <=>  r >= 65535.5 - 2^16 p_r, so f = floor(2^16 p_r + 1/2), within 0 .. 2^16 (0 where
 //   p_r is no number); in fp64 that is exact.
 //   Magnitudes below the smallest of the 4096 encode like it and like 0 if those two lie in one cell with the same f, the
-//   difference, the product and f being monotone inside a cell.  If they do not (a level within 2^-10 of 0, say), the workgroup encodes on the
-//   general path.
-// What bounds it: instruction issue (13.4 vector instructions per element in all; 18.6 on the mirrored path at b = 2) and, past it, memory:
+//   difference, the product and f being monotone inside a cell.  If they do not (always where the cell at 0 is narrower than
+//   2^-17 alpha, seldom where it is wide), the workgroup encodes on the general path, a tile at a time (two take more than 64
+//   registers), which with so few workgroups is slower than tq_compress_kernel, us: 4 x 250 M at b = 2 460 / 531, b = 3 554 / 653,
+//   b = 4 711 / 711, 1 x 70 M at b = 3 43.6 / 67, b = 4 54 / 71, 1 x 34 M 30.5 / 52.9.  So do uniform records that the caller took
+//   for tables: 399 / 445, 425 / 464, 397 / 471, 34.5 / 47.5, 33.4 / 45.6, 18.7 / 33.8.  (The next tile requested ahead: narrow cells
+//   546 -> 537, 1 x 70 M 67 -> 62 and 71 -> 66, but uniform records at b = 4 471 -> 477: not done.)
+// What bounds it: instruction issue (12.6 vector instructions per element in all; 18.6 on the mirrored path at b = 2) and, past it, memory:
 // a loop that only reads and writes in this pattern takes 1580 to 1720 us for 4 x 10^9 elements, one-shot workgroups 1400 to 1480
 // (which the time to fill the entries rules out).  A wavefront takes two groups at a time: with one, the chain of the draws is
 // exposed (2200 us).  Workgroups of 1024 threads 1750 to 1770 us, of 512 1690 to 1780, of 256 (fewer wavefronts: the entries fill the LDS) 1726.
@@ -821,11 +825,10 @@ __global__ __launch_bounds__(kLookBlock, 8) void tq_compress_lookup_kernel(
         }
     }
     if (!looked_up) {
-        constexpr int G = 1;                                   // two groups at once take more than 64 registers
         auto draw = [&](uint64_t ebase, uint32_t (&rw)[4]) { draw_tile<kLookBlock>(ebase, lane, worker, step, seed_lo, seed_hi, rw); };
 #pragma unroll 1
-        for (; left >= G && base + G * kLookTile <= whole_end; base += G * kLookTile, left -= G) {
-            encode_tiles<TQ_BF16, BITS, CACHED, G, false, kLookTile>(g, payload, base, lane, draw, [&](const float (&x)[8], const uint32_t (&rw)[4]) {
+        for (; left > 0 && base + kLookTile <= whole_end; base += kLookTile, --left) {
+            encode_tiles<TQ_BF16, BITS, CACHED, 1, false, kLookTile>(g, payload, base, lane, draw, [&](const float (&x)[8], const uint32_t (&rw)[4]) {
                 return encode_general<BITS, true>(x, rw, cb, lv, tab);
             });
         }
@@ -1170,7 +1173,8 @@ struct CompressShape { bool table_tiles, mirror; };
 //   b = 4  20 M 18.9 / 20.8 / 19.3 / 22.8 / 37 / 67, 40 M 33.6 / 29.1 / 28.2 / 33.7 / 39 / 69, 124 M 91 / 72 / 64 / 67 / 64 / 75, 8 x 124 M 696 / 486 /
 //          456 / 467 / 482 / 517, 4 x 10^9 2758 / 2050 / 1932 / 1955 / 1906 / 1912
 // A bucket is cut into equal ranges of at least so many tiles, or taken whole: 4 x 124 M in buckets of 65536 (16 tiles) at b = 3
-// 265 / 241, b = 4 332 / 234, of 16384 270 / 384 and 339 / 400.
+// 265 / 241, b = 4 332 / 234, of 16384 270 / 384 and 339 / 400; b = 2 4 x 140 M in buckets of 65536 266 / 264, of 98304 256 / 248, 4 x 250 M
+// 460 / 452 and 457 / 430.
 uint32_t look_tiles(int dtype, int bits, uint64_t bucket_elems, uint64_t elements)
 {
     const uint64_t least = bits == 2 ? 1ull << 29 : (bits == 3 ? 1ull << 26 : 1ull << 25);
@@ -1228,7 +1232,7 @@ void launch_lookup(const CompressArgs& a)
 template <int DTYPE, int BITS, bool CACHED>
 hipError_t launch(const CompressShape& shape, const CompressArgs& a)
 {
-    if constexpr (DTYPE == TQ_BF16) {
+    if constexpr (DTYPE == TQ_BF16 && !(BITS == 2 && CACHED)) {    // 2^29 elements are never read through the caches
         if (a.look) { launch_lookup<BITS, CACHED>(a); return hipGetLastError(); }
     }
     if constexpr (mirrored_pays(DTYPE, BITS)) {
@@ -1286,13 +1290,16 @@ hipError_t tq_launch_compress(const void* const* g, int count, int dtype, uint64
 #undef TQ_LAUNCH_COMPRESS
 }
 
-// Whether a simulated gradient goes past the caches: outputs above 96 MiB, sums above 64 MiB.  us in one bucket, through / past
-// them, by themselves and with an elementwise reader of the result behind them: bf16 25.6 M 30.4 / 28.4 (60.7 / 61.5), 40 M
-// 44.4 / 41.4 (96.4 / 98.1), 62 M 62.9 / 60.4 (149 / 146), 124 M 122 / 120 (297 / 283); fp32 36.6 / 33.4 (71.4 / 66.3), 55.5 / 50.8
-// (111 / 107), 83.3 / 77.1 (176 / 162), 165 / 153 (342 / 318); sums, bf16 20 M 34.9 / 32.2 (57.0 / 57.2), 25.6 M 45.5 / 40.4
-// (75.3 / 72.7), 124 M 218 / 196 (381 / 359), fp32 43.5 / 38.4 (66.3 / 63.2), 55.4 / 48.6 (89.2 / 81.6), 258 / 239 (420 / 402); but below,
-// bf16 20 M 24.9 / 22.8 (47.7 / 49.7), 13 M 15.8 / 16.3 (33.5 / 34.7), sums 20.6 / 21.8 (37.9 / 38.4).  (From 62 M on "through" is stores
-// past them, loads and sums through.)  Buckets of less than a wavefront's 512 elements hold no whole line to store: there the
+// Whether a simulated gradient goes past the caches: outputs above 96 MiB, sums above 64 MiB.  us, through / past them, by itself, with an
+// elementwise kernel behind it that reads the result, and with one that subtracts the gradient from it; the lines lie where the
+// three together gain:
+//   bf16 (past: two tiles a workgroup)  20 M 25.1 / 23.7  47.7 / 49.8  102 / 97    25.2 M 29.9 / 28.4  59.3 / 60.0  87.7 / 74.8
+//         25.6 M 30.4 / 29.1  60.3 / 61.0  114 / 94     30 M 34.5 / 32.9  71.2 / 69.4  102 / 91    40 M 44.1 / 41.8  96.7 / 97.4  144 / 138
+//         62 M 67.0 / 62.5  152 / 146  180 / 175
+//   fp32  22 M 31.2 / 29.3  57.7 / 58.8  68.7 / 71.1    25.6 M 35.9 / 33.5  70.9 / 66.7  83.9 / 87.4    40 M 55.0 / 51.1  111 / 107  139 / 135
+//   sums  bf16 16 M 26.1 / 26.2  45.7 / 46.5  87.0 / 91.2    18 M 30.5 / 29.1  51.4 / 52.0  104 / 98    25.6 M 45.4 / 40.8  74.8 / 73.3  130 / 109
+//         fp32 16 M 33.0 / 31.2  52.3 / 51.6  60.6 / 62.7    18 M 38.5 / 34.9  58.9 / 57.4  68.5 / 69.2    25.6 M 54.7 / 48.7  88.7 / 81.7  102 / 104
+// Buckets of less than a wavefront's 512 elements hold no whole line to store: there the
 // reads keep to the caches, sums of 25.6 M fp32 in buckets of 384 66.8 / 69.7.  62 M in buckets of 1024 and 2176: fp32 82.3 / 81.8
 // and 110.5 / 111.7, sums 126 / 112 and 172 / 143, bf16 77.2 / 74.1 and 107.3 / 104.4, sums 105 / 97.8 and 148 / 125.
 bool simulate_past(uint64_t d, uint64_t be, int accumulate)
@@ -1309,8 +1316,9 @@ hipError_t tq_launch_simulate(const void* g, int dtype, uint64_t d, uint64_t buc
     const uint64_t be = bucket_elems ? bucket_elems : d_pad;
     const uint64_t nb = (d_pad + be - 1) / be;
     const bool past = simulate_past(d, be, accumulate);
-    // one tile per workgroup; two for bf16 whose output leaves the caches, in buckets of at least four: 124 M at b = 3
-    // 107 / 103.5 us, but 25.6 M 24.5 / 25.7 and 124 M in buckets of 2048 111 / 174
+    // one tile per workgroup; two for bf16 past the caches, in buckets of at least four.  One / two, at b = 3 by itself and with the two kernels
+    // above behind it: 25.6 M 28.3 / 29.1  61.4 / 61.0  96.5 / 94.4, 40 M 42.0 / 41.8  99.2 / 97.4  138 / 138, 80 M 82.7 / 80.2  188 / 186  238 / 236;
+    // but through the caches 25.6 M 24.5 / 25.7, and 124 M in buckets of 2048 111 / 174
     const bool two = dtype == TQ_BF16 && past && !accumulate && be >= 4 * (uint64_t)tq::kTile;
     const uint64_t tt = two ? 2 : 1;
     const uint64_t tpb = ((be + tq::kTile - 1) / tq::kTile + tt - 1) / tt;    // workgroups per bucket

@@ -800,7 +800,8 @@ int bucket_trip(int dtype, bool tail, uint64_t be)
 
 // Whether a batch in equal shares is read past the caches, and the tiles at the end of every share that are read through them
 // all the same.  A piece's first full trip, the last one where their number is even, and what is left after them are always
-// read through them: of a bucket of 32768 fp32 elements everything, of 65536 two trips of four.  Smaller buckets always are.
+// read through them: of a bucket of 32768 fp32 elements everything, of 65536 two trips of four (with tail, in trips of three
+// tiles, one of five and the last tile).  Smaller buckets always are.
 // A batch larger than the memory-side cache (256 MiB) read through it leaves there what the next call displaces before
 // reaching it, and reads slower: with non-temporal loads, whole lines at a time, a persistent read loop of this shape reaches
 // 7.0 TB/s instead of 6.2.  What compress reads again should stay, so 192 MiB of the batch are read the ordinary

@@ -94,9 +94,11 @@ def test_two_bits():
     both_ways(gs, [codebook(2, k, rng) for k in ("near zero", "uniform")], 2, 0)
 
 
-def test_codes_are_the_oracles():
-    """The whole payload against the oracle, with the record the device designed."""
-    bits, d = 4, LEAST[4] + 4_321
+@pytest.mark.parametrize("bits", [3, 4])
+def test_codes_are_the_oracles(bits):
+    """The whole payload against the oracle, with the record the device designed (at two bits a billion elements, with the
+    configurations at full size)."""
+    d = LEAST[bits] + 4_321
     g = gradient(d, 6)
     stats, params, ws = B.alloc_stats(d), B.alloc_params(d), B.alloc_stats_workspace(d)
     payload = torch.zeros(B.payload_bytes(d, bits), dtype=torch.uint8, device="cuda")

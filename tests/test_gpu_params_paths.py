@@ -264,8 +264,8 @@ def test_groups_of_empty_bins(bits, grid):
 
 @pytest.mark.parametrize("bits", [2, 3, 4])
 def test_the_same_iteration_inside_and_outside_the_regular_bins(bits):
-    """Thresholds that stay below 65536 take their bin from their bits, others the general form.  Scaled by 8 -- three octaves, where
-    cube roots scale by 4 -- the plain iteration does the same arithmetic, so its result scales to the bit."""
+    """Thresholds that stay below 65536 take their bin from their bits, others the general form.  Scaled by 4096 -- twelve octaves, where
+    w^(2/3) scales by 256 -- the plain iteration does the same arithmetic, so its result scales to the bit."""
     low, high = [], []
     # (2.2, 400), (2.5, 400) and (2.9, 300) do not settle in 100 steps at b = 2, 3 and 4
     for gamma, width in [(g, w) for g in (2.05, 2.2, 2.5, 3.0, 4.0, 6.0, 9.0) for w in (60, 150, 400)] + [(2.9, 300)]:

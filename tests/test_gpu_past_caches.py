@@ -34,7 +34,7 @@ def server(d, N, bits, bucket):
     return payload, params, g_bar, theta, vel
 
 
-SINGLE, DOUBLE = 96 * MIB // 4, 48 * MIB // 4                 # elements above which they go past the caches, whatever the payloads
+SINGLE, DOUBLE = 96 * MIB // 4, 32 * MIB // 4                 # elements above which they go past the caches
 
 
 @pytest.mark.parametrize("N,bits", [(1, 4), (3, 2), (8, 3), (16, 2), (12, 4), (20, 3), (33, 4)])
@@ -48,6 +48,13 @@ def test_updates(N, bits, extra, bucket):
     B.tq_decompress_aggregate_update(payload, params, theta, bits, eta, mu, wd, vel, bucket)
     torch.cuda.synchronize()
     assert torch.equal(vel.view(torch.int32), v.view(torch.int32)) and torch.equal(theta.view(torch.int32), want.view(torch.int32))
+
+
+# from 48 MiB of parameters on whatever the payloads are; at 32 MiB it is the payloads of 8 and more workers that decide
+@pytest.mark.parametrize("N,bits", [(1, 4), (3, 2), (8, 3), (16, 2), (12, 4), (20, 3), (33, 4)])
+@pytest.mark.parametrize("extra,bucket", [(1, 0), (4_097, 1 << 20), (777, 9 * 4096 + 128), (2_048, 32_768)])
+def test_updates_of_few_payloads(N, bits, extra, bucket):
+    test_updates(N, bits, 16 * MIB // 4 + extra, bucket)
 
 
 @pytest.mark.parametrize("N,bits", [(2, 4), (8, 2), (17, 3)])

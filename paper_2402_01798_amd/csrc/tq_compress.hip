@@ -1291,8 +1291,8 @@ hipError_t tq_launch_compress(const void* const* g, int count, int dtype, uint64
 }
 
 // Whether a simulated gradient goes past the caches: outputs above 96 MiB, sums above 64 MiB.  us, through / past them, by itself, with an
-// elementwise kernel behind it that reads the result, and with one that subtracts the gradient from it; the lines lie where the
-// three together gain:
+// elementwise kernel behind it that reads the result, and with one that subtracts the gradient from it; above the
+// lines the three together gain (bf16 20 M gains in sum, too, but the plain reader loses more there than the call gains):
 //   bf16 (past: two tiles a workgroup)  20 M 25.1 / 23.7  47.7 / 49.8  102 / 97    25.2 M 29.9 / 28.4  59.3 / 60.0  87.7 / 74.8
 //         25.6 M 30.4 / 29.1  60.3 / 61.0  114 / 94     30 M 34.5 / 32.9  71.2 / 69.4  102 / 91    40 M 44.1 / 41.8  96.7 / 97.4  144 / 138
 //         62 M 67.0 / 62.5  152 / 146  180 / 175

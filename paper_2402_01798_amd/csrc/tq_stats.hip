@@ -52,6 +52,8 @@ constexpr uint64_t kWholeTensor = 65536;
 // fp32, trips of four / three, us: 8 x 124 M 579 / 570, 8 x 11.2 M 59.1 / 58.0, 100 M 68.0 / 66.3, with tail 16 x 25.6 M 251 / 243,
 // 2 x 310 M 372 / 363 (two tiles 261, one 256 with 256 workgroups; one tile and 512 workgroups 242, but without tail 578 / 589),
 // 8 x 25.6 M with tail in buckets of 65536 187 / 182, of 131072 157 / 154, but without in buckets of 32768 178 / 181, of 65536 153.5 / 157.2.
+// On another card 16 x 25.6 M 253.5 / 247.4, 2 x 310 M 376 / 365, 8 x 124 M 580 / 575, 8 x 11.2 M 64.2 / 62.2, but 100 M 73.0 / 73.4 and 8 x 25.6 M
+// without tail in buckets of 131072 137.9 / 139.4.
 constexpr uint64_t kShortPieces = 131072;
 constexpr int share_trip(int dtype, bool tail, bool past, bool short_pieces)
 {
